@@ -309,8 +309,8 @@ def md_run(args):
 
 def foe_run(args):
     """Finite-temperature Chebyshev expansion (the Fermi function of Eq. 7) on the workload's
-    partition: one JSON line with orbitals/s of the whole path and the roofline of the batched
-    product (one launch per Chebyshev term)."""
+    partition: one JSON line with orbitals/s of the whole path and the time of one Chebyshev
+    term (the recurrence on the core rows, one launch per pass)."""
     import torch
     import paper_1603_00937_amd as gb
     from synth import make_model
@@ -338,8 +338,7 @@ def foe_run(args):
         prod_n += st["n_product"]
     torch.cuda.synchronize()
     dt = (time.perf_counter() - t0) / args.steps
-    avg = prod_ms / prod_n / 1e3 if prod_n else None
-    ach = st["product_flops"] / avg / 1e12 if avg else None
+    avg = prod_ms / prod_n if prod_n else None
     print(json.dumps({
         "metric": "orbitals/s of the finite-temperature D (Chebyshev Fermi expansion)",
         "value": N / dt, "unit": "orbitals/s", "n_gpus": 1, "steps": args.steps,
@@ -349,11 +348,9 @@ def foe_run(args):
                    "beta": args.beta, "order": args.order,
                    "mu": "solved for n_occ" if mu is None else mu, "passes": st["passes"],
                    "n_sub": st["n_sub"], "max_sub": st["max_sub"]},
-        "roofline": {"bound": "mfma", "achieved": ach, "peak": PEAK_TFLOPS["fp64"],
-                     "unit": "TFLOP/s", "frac": ach / PEAK_TFLOPS["fp64"] if ach else None,
-                     "traffic": None, "kernel": "k_symm_mm MODE 3 (Ht T_n) + k_cheb_combine",
-                     "flops_per_launch_alg": st["product_flops"],
-                     "avg_launch_ms": avg * 1e3 if avg else None},
+        "recurrence": {"bound": "lds", "kernel": "k_foe_rows",
+                       "dense_block_flops_per_term": st["product_flops"],
+                       "avg_term_ms": avg},
         "result": {"mu": st["mu"], "trace": st["trace"], "coef_tail": st["coef_tail"]},
         "stage_ms": {k[3:]: st[k] for k in st if k.startswith("ms_")},
     }), flush=True)

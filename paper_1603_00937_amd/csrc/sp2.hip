@@ -10,7 +10,6 @@
 #include <cmath>
 #include <cstring>
 #include <cstdlib>
-#include <deque>
 #include <string>
 #include <map>
 #include <mutex>
@@ -154,7 +153,6 @@ __global__ __launch_bounds__(kT) void k_gather(const int32_t* __restrict__ hcol,
 //   MODE 0: out = A*B          MODE 1: out = alpha*(A*B) + beta*E   (E symmetric)
 //   MODE 3: out = A*B for a general (non-symmetric) product with B symmetric: every tile
 //           (bi, bj) is listed and nothing is mirrored (the adjoint's Gbar*X)
-//   MODE 4: as MODE 1, and dacc += cn * out (the Chebyshev recurrence with the running sum)
 // In MODE 0 (A = B = X) the SP2 update is fused into the epilogue: with the branch
 // 2X - X^2 selected (lin, or *lin_flag on the device-driven loop) the kernel writes 2X - X^2,
 // else X^2.  X is symmetric, so the mirrored entry takes the same value.
@@ -169,8 +167,8 @@ __global__ __launch_bounds__(kT, 2) void k_symm_mm(const T* __restrict__ A, cons
                                                    T alpha, T beta, const int4* __restrict__ tiles,
                                                    const int64_t* __restrict__ offs,
                                                    const int32_t* __restrict__ stopped,
-                                                   int lin, const int32_t* __restrict__ lin_flag,
-                                                   T* __restrict__ dacc, T cn) {
+                                                   int lin,
+                                                   const int32_t* __restrict__ lin_flag) {
   if (stopped && *stopped) return;  // device-driven loop: the expansion already stopped
   using M = Mfma<T>;
   using acc_t = typename M::acc_t;
@@ -376,14 +374,10 @@ __global__ __launch_bounds__(kT, 2) void k_symm_mm(const T* __restrict__ A, cons
         if (grow < np && gcol < np) {
           const int64_t q1 = (int64_t)grow * np + gcol, q2 = (int64_t)gcol * np + grow;
           T v = acc[m][n][r];
-          if (MODE == 1 || MODE == 4) v = alpha * v + beta * e[q1];
+          if (MODE == 1) v = alpha * v + beta * e[q1];
           if (do_lin) v = (T)2 * xa[q1] - v;
           o[q1] = v;
-          if (MODE == 4) dacc[off + q1] += cn * v;
-          if (mirror) {
-            o[q2] = v;
-            if (MODE == 4) dacc[off + q2] += cn * v;
-          }
+          if (mirror) o[q2] = v;
         }
       }
 }
@@ -1512,24 +1506,24 @@ template <typename T, int MODE>
 void launch_symm(const T* A, const T* B, const T* E, T* out, T alpha, T beta, const int4* tiles,
                  const Groups& g, const int64_t* offs, hipStream_t s,
                  const int32_t* stopped = nullptr, int lin = 0,
-                 const int32_t* lin_flag = nullptr, T* dacc = nullptr, T cn = (T)0) {
+                 const int32_t* lin_flag = nullptr) {
   if (g.n[4] > 0 || g.n[5] > 0) fail(GB_EHIP, "split-square tiles given to an FP64/FP32 product");
   const int4* t = tiles;
   if (g.n[0] > 0)
     hipLaunchKernelGGL((k_symm_mm<T, MODE, 128, 2>), dim3(g.n[0]), dim3(kT), 0, s, A, B, E, out,
-                       alpha, beta, t, offs, stopped, lin, lin_flag, dacc, cn);
+                       alpha, beta, t, offs, stopped, lin, lin_flag);
   t += g.n[0];
   if (g.n[1] > 0)
     hipLaunchKernelGGL((k_symm_mm<T, MODE, 64, 2>), dim3(g.n[1]), dim3(kT), 0, s, A, B, E, out,
-                       alpha, beta, t, offs, stopped, lin, lin_flag, dacc, cn);
+                       alpha, beta, t, offs, stopped, lin, lin_flag);
   t += g.n[1];
   if (g.n[2] > 0)
     hipLaunchKernelGGL((k_symm_mm<T, MODE, 64, 3>), dim3(g.n[2]), dim3(kT), 0, s, A, B, E, out,
-                       alpha, beta, t, offs, stopped, lin, lin_flag, dacc, cn);
+                       alpha, beta, t, offs, stopped, lin, lin_flag);
   t += g.n[2];
   if (g.n[3] > 0)
     hipLaunchKernelGGL((k_symm_mm<T, MODE, 64, 2, 1>), dim3(g.n[3]), dim3(kT), 0, s, A, B, E,
-                       out, alpha, beta, t, offs, stopped, lin, lin_flag, dacc, cn);
+                       out, alpha, beta, t, offs, stopped, lin, lin_flag);
   GB_LAUNCH_CHECK();
 }
 
@@ -2612,8 +2606,8 @@ void density_vjp(TapeData& t, const gb_ell& G_D, const gb_ell& H, double* G_H, h
     for (int n = end - 1; n >= start; --n) {
       const double* X = xs[n - start];
       hipLaunchKernelGGL((k_symm_mm<double, 3>), dim3(ntf), dim3(kT), 0, s, G.get(), X, X,
-                         Pm.get(), 1.0, 0.0, t.tiles_full.get(), t.offs.get(), nullptr, 0, nullptr,
-                         (double*)nullptr, 0.0);
+                         Pm.get(), 1.0, 0.0, t.tiles_full.get(), t.offs.get(), nullptr, 0,
+                         (const int32_t*)nullptr);
       GB_LAUNCH_CHECK();
       const double c1 = t.branch[n] == 0 ? 1.0 : -1.0, c2 = t.branch[n] == 0 ? 0.0 : 2.0;
       hipLaunchKernelGGL(k_sym_combine, cgrid, dim3(256), 0, s, Pm.get(), G.get(), G2.get(), c1,
@@ -2656,86 +2650,199 @@ void density_vjp(TapeData& t, const gb_ell& G_D, const gb_ell& H, double* G_H, h
 
 namespace {
 
-// Ht = (2h - (e_max + e_min) delta) / (e_max - e_min) on H's ELL pattern (0 on padding)
-__global__ void k_ht_ell(const int32_t* __restrict__ col, const double* __restrict__ val, int n,
-                         int w, double emin, double emax, double* __restrict__ out) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= (int64_t)n * w) return;
-  const int i = (int)(p / w);
-  const int32_t j = col[p];
-  double v = 0.0;
-  if (j >= 0) v = (2.0 * val[p] - (j == i ? emax + emin : 0.0)) / (emax - emin);
-  out[p] = v;
-}
-
-// X[s] <- identity on the n_s x n_s part (the rest of the batch must already be zero)
-__global__ __launch_bounds__(kT) void k_set_identity(double* __restrict__ X,
-                                                     const int64_t* __restrict__ offs,
-                                                     const int32_t* __restrict__ npad,
-                                                     const int32_t* __restrict__ sub_ptr) {
+// The expansion needs only the core rows of T_n(Ht): with V_n = E T_n for the core unit rows E,
+// V_{n+1} = 2 V_n Ht - V_{n-1}, one row never reads another one, and Ht is as sparse as H.  So a
+// workgroup carries R core rows of one subgraph through the whole recurrence with V_n and V_{n-1}
+// in LDS, and the only traffic of a term is Ht's entries on the subgraph.
+//
+// Those entries, per subgraph: slot t of local column a at eoff[s] + t npad + a (a's entries in
+// H's slot order, so a wave of consecutive columns reads consecutive words), the local index of
+// the other end as 16 bits (a subgraph is limited to about 13600 vertices by the gather's LDS)
+// and Ht = (2h - (e_max + e_min) delta) / (e_max - e_min); len counts a column's slots.
+__global__ __launch_bounds__(kT) void k_foe_ell(const int32_t* __restrict__ hcol,
+                                                const double* __restrict__ hval, int w, double emin,
+                                                double emax, const int32_t* __restrict__ core_ptr,
+                                                const int32_t* __restrict__ sub_ptr,
+                                                const int32_t* __restrict__ sub_idx,
+                                                const int64_t* __restrict__ eoff,
+                                                const int32_t* __restrict__ npad,
+                                                uint16_t* __restrict__ idx, double* __restrict__ val,
+                                                int32_t* __restrict__ len) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  int32_t* sub = reinterpret_cast<int32_t*>(smem);
   const int s = blockIdx.x;
-  const int np = npad[s], n = sub_ptr[s + 1] - sub_ptr[s];
-  double* x = X + offs[s];
-  for (int j = threadIdx.x; j < n; j += kT) x[(int64_t)j * np + j] = 1.0;
-}
-
-__global__ void k_axpby(double* __restrict__ out, double a, const double* __restrict__ x, double b,
-                        const double* __restrict__ y, int64_t n) {
-  const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t st = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = i0; i < n; i += st) out[i] = a * x[i] + b * y[i];
-}
-
-// the summed core diagonal (first partial of each subgraph) into *out
-__global__ __launch_bounds__(kT) void k_trace_total(const double* __restrict__ part, int n_sub,
-                                                    double* __restrict__ out) {
-  double t1, t2;
-  sum_partials(part, n_sub, &t1, &t2);
-  if (threadIdx.x == 0) *out = t1;
-}
-
-// Tn = P + P^T - Tp on 32 x 32 tile pairs (P^T through LDS), and with dacc: dacc += cn Tn
-__global__ __launch_bounds__(256) void k_cheb_combine(const double* __restrict__ P,
-                                                      const double* __restrict__ Tp,
-                                                      double* __restrict__ Tn,
-                                                      double* __restrict__ dacc, double cn,
-                                                      const int64_t* __restrict__ offs,
-                                                      const int32_t* __restrict__ npad,
-                                                      int max_nt) {
-  __shared__ double t[32][33];
-  const int s = blockIdx.y;
-  const int np = npad[s], nt = np / 32;
-  const int bx = blockIdx.x % max_nt, by = blockIdx.x / max_nt;
-  if (bx >= nt || by >= nt) return;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  const int64_t off = offs[s];
-  const double* p = P + off;
-  for (int r = ty; r < 32; r += 8) t[r][tx] = p[(int64_t)(bx * 32 + r) * np + by * 32 + tx];
+  const int b = sub_ptr[s], n = sub_ptr[s + 1] - b;
+  if ((int)blockIdx.y * kT >= n) return;  // the whole workgroup leaves together
+  const int k = core_ptr[s + 1] - core_ptr[s];
+  for (int a = threadIdx.x; a < n; a += kT) sub[a] = sub_idx[b + a];
   __syncthreads();
-  for (int r = ty; r < 32; r += 8) {
-    const int64_t q = off + (int64_t)(by * 32 + r) * np + bx * 32 + tx;
-    const double v = (P[q] + t[tx][r]) - Tp[q];
-    Tn[q] = v;
-    if (dacc) dacc[q] += cn * v;
+  const int a = blockIdx.y * kT + threadIdx.x;
+  if (a >= n) return;
+  const int i = sub[a], np = npad[s];
+  int64_t q = eoff[s] + a;
+  int m = 0;
+  for (int t = 0; t < w; ++t) {
+    const int32_t j = hcol[(int64_t)i * w + t];
+    if (j < 0) continue;
+    int lo = 0, hi = k;  // j in the core run [0, k), else in the halo run [k, n)
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (sub[mid] < j) lo = mid + 1;
+      else hi = mid;
+    }
+    if (lo == k || sub[lo] != j) {
+      lo = k;
+      hi = n;
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (sub[mid] < j) lo = mid + 1;
+        else hi = mid;
+      }
+      if (lo == n || sub[lo] != j) continue;
+    }
+    idx[q] = (uint16_t)lo;
+    val[q] = (2.0 * hval[(int64_t)i * w + t] - (j == i ? emax + emin : 0.0)) / (emax - emin);
+    q += np;
+    ++m;
+  }
+  len[b + a] = m;
+}
+
+// The recurrence of R core rows r0 .. r0 + R - 1 of one subgraph up to V_nterm (rows beyond the
+// core are zero rows).  LDS: V_n and V_{n-1}, columns side by side in pairs of rows (one 16-byte
+// read per pair), V_{n+1} overwriting V_{n-1} entry by entry; one barrier per term.  SPILL: a
+// subgraph too large for two LDS arrays keeps V_{n-1} in global memory and swaps after each term.
+//   coef: dacc (core-row slabs at soffs, row stride npad) = sum_n coef[n] V_n.
+//   part: for the first ntr products n -> n + 1, sum V_n V_{n+1} and sum V_{n+1}^2 over the rows:
+//         T_m T_n = (T_{m+n} + T_{|m-n|}) / 2 turns them into the core traces t_{2n+1} and
+//         t_{2n+2}, so the traces of M terms take M / 2 products.
+// What bounds it is LDS: every entry of Ht reads R doubles of V_n at a scattered column (N = 1024,
+// 64 subgraphs of ~900: LDS active 60 % of the time, half of that bank conflicts of the scattered
+// reads).  R = 4 takes 10 bytes of Ht per four products; R = 2 took 20.7 ms where R = 4 takes
+// 14.2 ms (order 160, mu solved, whole call), and sixteen entries in flight per thread 14.0 ms
+// against 14.2 (eight) and 15.0 (four).  42 us per term; as full products of whole blocks (each
+// term 2 n^3 flops and five passes over the batch) a term took 2.2 ms and the call 743 ms.
+// N = 18000 (565 subgraphs of ~1200): 0.94 ms per term against 57.6.
+template <int R, bool SPILL>
+__global__ __launch_bounds__(1024) void k_foe_rows(
+    const int4* __restrict__ items, const uint16_t* __restrict__ idx,
+    const double* __restrict__ val, const int32_t* __restrict__ len,
+    const int64_t* __restrict__ eoff, const int32_t* __restrict__ sub_ptr,
+    const int32_t* __restrict__ core_ptr, const int64_t* __restrict__ soffs, int nterm, int ntr,
+    const double* __restrict__ coef, double* __restrict__ dacc, double* __restrict__ part,
+    double* __restrict__ spill, int spill_ld) {
+  constexpr int E = R >= 2 ? 2 : 1, PL = R / E, U = 16;
+  static_assert(!SPILL || R == 1, "the spilled form carries one row");
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ double red[2][2][16];
+  double* mine = part ? part + (int64_t)blockIdx.x * 2 * ntr : nullptr;
+  const int4 it = items[blockIdx.x];
+  if (it.x < 0) {  // padding entry of an XCD queue
+    for (int q = threadIdx.x; q < 2 * ntr; q += blockDim.x) mine[q] = 0.0;
+    return;
+  }
+  const int s = it.x, r0 = it.y, np = it.w;
+  const int b = sub_ptr[s], n = sub_ptr[s + 1] - b;
+  const int kr = min(R, core_ptr[s + 1] - core_ptr[s] - r0);
+  double* cur = reinterpret_cast<double*>(smem);
+  double* prev = SPILL ? spill + (int64_t)blockIdx.x * spill_ld : cur + R * n;
+  const uint16_t* ix = idx + eoff[s];
+  const double* hv = val + eoff[s];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwave = blockDim.x >> 6;
+  for (int a = threadIdx.x; a < n; a += blockDim.x)
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      cur[((r / E) * n + a) * E + r % E] = r < kr && a == r0 + r ? 1.0 : 0.0;
+      prev[((r / E) * n + a) * E + r % E] = 0.0;
+    }
+  __syncthreads();
+  for (int t = 0; t < nterm; ++t) {
+    double p0 = 0.0, p1 = 0.0;
+    for (int a = threadIdx.x; a < n; a += blockDim.x) {
+      double acc[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) acc[r] = 0.0;
+      const int L = len[b + a];
+      for (int q = 0; q < L; q += U) {
+        double h[U];
+        int c[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {  // past the end: an entry that is there, times zero
+          const bool in = q + u < L;
+          const uint32_t e = (uint32_t)(in ? q + u : 0) * (uint32_t)np + (uint32_t)a;
+          c[u] = ix[e];
+          h[u] = in ? hv[e] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int p = 0; p < PL; ++p) {
+            double v[E];
+            __builtin_memcpy(v, __builtin_assume_aligned(cur + (p * n + c[u]) * E, 8 * E), 8 * E);
+#pragma unroll
+            for (int x = 0; x < E; ++x)
+              acc[p * E + x] = __builtin_fma(v[x], h[u], acc[p * E + x]);
+          }
+      }
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int o = ((r / E) * n + a) * E + r % E;
+        const double v = cur[o];
+        const double nv = t == 0 ? acc[r] : 2.0 * acc[r] - prev[o];
+        prev[o] = nv;
+        p0 += v * nv;
+        p1 += nv * nv;
+        if (coef && r < kr) {
+          double* d = dacc + soffs[s] + (int64_t)(r0 + r) * np + a;
+          *d = t == 0 ? coef[0] * v + coef[1] * nv : *d + coef[t + 1] * nv;
+        }
+      }
+    }
+    if (t < ntr) {
+      for (int o = 32; o > 0; o >>= 1) {
+        p0 += __shfl_xor(p0, o);
+        p1 += __shfl_xor(p1, o);
+      }
+      if (lane == 0) {
+        red[t & 1][0][wave] = p0;
+        red[t & 1][1][wave] = p1;
+      }
+    }
+    __syncthreads();
+    if (t < ntr && threadIdx.x < 2) {
+      double v = 0.0;
+      for (int q = 0; q < nwave; ++q) v += red[t & 1][threadIdx.x][q];
+      mine[2 * t + threadIdx.x] = v;
+    }
+    if (SPILL) {
+      for (int a = threadIdx.x; a < n; a += blockDim.x) {
+        const double v = cur[a];
+        cur[a] = prev[a];
+        prev[a] = v;
+      }
+      __syncthreads();
+    } else {
+      double* x = cur;
+      cur = prev;
+      prev = x;
+    }
   }
 }
 
-// One Chebyshev term, T_next = Ht T_cur + (Ht T_cur)^T - T_prev (= 2 Ht T_cur - T_prev, since
-// T_cur is a polynomial in Ht), with dacc += cn T_next.  The product is formed on every tile
-// and symmetrised explicitly: taking one triangle of Ht T_cur and mirroring it would turn the
-// rounding part of the commutator [Ht, T_cur] into a symmetric error that the recurrence
-// amplifies (the traces run away after about 200 terms).
-void launch_cheb(const double* A, const double* Tc, const double* Tp, double* Tn, double* dacc,
-                 double cn, double* P, const Plan& pl, const int4* tiles_full,
-                 const int64_t* offs, const int32_t* npad, hipStream_t s) {
-  const int ntf = (int)pl.full_launch.size();
-  hipLaunchKernelGGL((k_symm_mm<double, 3>), dim3(ntf), dim3(kT), 0, s, A, Tc, Tc, P, 1.0, 0.0,
-                     tiles_full, offs, nullptr, 0, nullptr, (double*)nullptr, 0.0);
-  GB_LAUNCH_CHECK();
-  const int max_nt = pl.max_npad / 32;
-  hipLaunchKernelGGL(k_cheb_combine, dim3(max_nt * max_nt, pl.n_sub), dim3(256), 0, s, P, Tp, Tn,
-                     dacc, cn, offs, npad, max_nt);
-  GB_LAUNCH_CHECK();
+// out[q] = the sum over the workgroups of k_foe_rows of part[.][q] (one workgroup per q)
+__global__ __launch_bounds__(kT) void k_foe_sums(const double* __restrict__ part, int n_items,
+                                                 int nq, double* __restrict__ out) {
+  __shared__ double red[kT];
+  const int q = blockIdx.x;
+  double v = 0.0;
+  for (int i = threadIdx.x; i < n_items; i += kT) v += part[(int64_t)i * nq + q];
+  red[threadIdx.x] = v;
+  __syncthreads();
+  for (int h = kT / 2; h > 0; h >>= 1) {
+    if (threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) out[q] = red[0];
 }
 
 int quad_nodes(int order, int n_nodes) { return n_nodes > 0 ? n_nodes : std::max(4 * (order + 1), 1024); }
@@ -2797,107 +2904,124 @@ void foe(const gb_ell& H, int32_t n_occ, const gb_foe_opts& o, const Part& P, do
          double emax, gb_ell& D, gb_foe_stats& st, hipStream_t s) {
   Timer t_all, t_stage;
   GB_HIP(hipEventRecord(t_all.a, s));
-  const bool xcd = o.tile_order == 0;
-  Plan pl = make_plan(P, nullptr, xcd);
-  st.product_flops = pl.flops_alg;
-  DBuf<int64_t> offs(pl.n_sub, s);
-  DBuf<int32_t> npad(pl.n_sub, s);
-  GB_HIP(hipMemcpyAsync(offs.get(), pl.off.data(), pl.n_sub * 8, hipMemcpyHostToDevice, s));
-  GB_HIP(hipMemcpyAsync(npad.get(), pl.npad.data(), pl.n_sub * 4, hipMemcpyHostToDevice, s));
-  DBuf<int4> tiles = upload_tiles(pl, s);
-  const int N = H.n;
-  const int M = o.order;
+  const int N = H.n, M = o.order, w = H.width;
+  // padded sizes, offsets of the subgraphs' entries and of their core-row slabs
+  std::vector<int32_t> np(P.n_sub);
+  std::vector<int64_t> eo(P.n_sub), so(P.n_sub);
+  std::vector<int> order(P.n_sub);
+  int64_t te = 0, ts = 0;
+  int max_np = 0;
+  double t0 = 0;  // t_0 = sum of the core sizes
+  for (int q = 0; q < P.n_sub; ++q) {
+    const int n = P.h_sub_ptr[q + 1] - P.h_sub_ptr[q], k = P.h_core_ptr[q + 1] - P.h_core_ptr[q];
+    np[q] = (n + 63) / 64 * 64;
+    max_np = std::max(max_np, np[q]);
+    eo[q] = te;
+    so[q] = ts;
+    te += (int64_t)np[q] * w;
+    ts += (int64_t)np[q] * k;
+    t0 += k;
+    order[q] = q;
+    st.product_flops += 2.0 * (double)n * n * n;
+  }
+  if ((size_t)max_np * 8 + (size_t)P.max_sub * 4 + 64 > 160 * 1024)
+    fail(GB_EUNSUPPORTED, "subgraph of %d vertices too large", P.max_sub);
+  // rows per workgroup: as many as the LDS of one CU holds (see k_foe_rows), at most four; past
+  // ~9900 vertices not even one row's two arrays fit, and V_{n-1} goes to global memory
+  const size_t lds_max = 158 * 1024;
+  auto lds_of = [&](int r) { return (size_t)2 * r * P.max_sub * 8; };
+  const int R = lds_of(4) <= lds_max ? 4 : lds_of(2) <= lds_max ? 2 : 1;
+  const bool spill = lds_of(1) > lds_max;
+  // workgroups per subgraph, largest subgraphs first, each subgraph's on one XCD (its entries of
+  // Ht, ~2 MB at n ~ 1000, are read by all of them every term)
+  std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return np[x] > np[y]; });
+  std::vector<int4> list, ranges, items;
+  for (int q : order) {
+    const int k = P.h_core_ptr[q + 1] - P.h_core_ptr[q], first = (int)list.size();
+    for (int r = 0; r < k; r += R) list.push_back(make_int4(q, r, 0, np[q]));
+    if (k > 0) ranges.push_back(make_int4(first, (int)list.size() - first, 0, q));
+  }
+  if (o.tile_order == 0) xcd_order(items, list, ranges, 0, ranges.size());
+  else items = list;
+  const int n_items = (int)items.size();
+  DBuf<int32_t> npad(P.n_sub, s), len(P.total, s);
+  DBuf<int64_t> eoff(P.n_sub, s), soff(P.n_sub, s);
+  DBuf<int4> ditems(n_items, s);
+  GB_HIP(hipMemcpyAsync(npad.get(), np.data(), P.n_sub * 4, hipMemcpyHostToDevice, s));
+  GB_HIP(hipMemcpyAsync(eoff.get(), eo.data(), P.n_sub * 8, hipMemcpyHostToDevice, s));
+  GB_HIP(hipMemcpyAsync(soff.get(), so.data(), P.n_sub * 8, hipMemcpyHostToDevice, s));
+  GB_HIP(hipMemcpyAsync(ditems.get(), items.data(), n_items * sizeof(int4),
+                        hipMemcpyHostToDevice, s));
 
-  // gather Ht into the batch
   GB_HIP(hipEventRecord(t_stage.a, s));
-  const int64_t slots = (int64_t)H.n * H.width;
-  DBuf<double> ht(slots, s);
-  hipLaunchKernelGGL(k_ht_ell, dim3(grid_for(slots, kT)), dim3(kT), 0, s, H.col, H.val, H.n,
-                     H.width, emin, emax, ht.get());
-  GB_LAUNCH_CHECK();
-  const size_t lds_g = (size_t)pl.max_npad * 8 + (size_t)P.max_sub * 4 + 64;
-  if (lds_g > 160 * 1024) fail(GB_EUNSUPPORTED, "subgraph of %d vertices too large", P.max_sub);
-  const dim3 ggrid(pl.n_sub, (pl.max_npad + kRows - 1) / kRows);
-  WsLease ws;  // cached batch buffers: Ht, three Chebyshev terms, the running sum
-  double* const A = ws->get<double>(0, pl.total, s);
-  double* const B0 = ws->get<double>(1, pl.total, s);
-  double* const B1 = ws->get<double>(2, pl.total, s);
-  double* const B2 = ws->get<double>(3, pl.total, s);
-  double* const Dacc = ws->get<double>(4, pl.total, s);
-  double* const Pm = ws->get<double>(5, pl.total, s);  // the full product Ht T_n
-  hipLaunchKernelGGL(k_gather<double>, ggrid, dim3(kT), lds_g, s, H.col, ht.get(), H.width,
-                     P.core_ptr.get(), P.sub_ptr.get(), P.sub_idx.get(), offs.get(), npad.get(),
-                     A, 1.0);
+  WsLease ws;  // cached buffers: Ht's entries on the subgraphs, the core rows of D
+  double* const val = ws->get<double>(0, te, s);
+  uint16_t* const idx = ws->get<uint16_t>(1, te, s);
+  double* const Dacc = ws->get<double>(2, ts, s);
+  hipLaunchKernelGGL(k_foe_ell, dim3(P.n_sub, (P.max_sub + kT - 1) / kT), dim3(kT),
+                     (size_t)P.max_sub * 4, s, H.col, H.val, w, emin, emax, P.core_ptr.get(),
+                     P.sub_ptr.get(), P.sub_idx.get(), eoff.get(), npad.get(), idx, val,
+                     len.get());
   GB_LAUNCH_CHECK();
   GB_HIP(hipEventRecord(t_stage.b, s));
   GB_HIP(hipStreamSynchronize(s));
   st.ms_gather = elapsed(t_stage.a, t_stage.b);
-  DBuf<int4> tiles_full(pl.full_launch.size(), s);
-  GB_HIP(hipMemcpyAsync(tiles_full.get(), pl.full_launch.data(),
-                        pl.full_launch.size() * sizeof(int4), hipMemcpyHostToDevice, s));
 
-  double t0 = 0;  // t_0 = sum of the core sizes
-  for (int q = 0; q < P.n_sub; ++q) t0 += P.h_core_ptr[q + 1] - P.h_core_ptr[q];
-  std::vector<double> traces(M + 1, 0.0);
-  DBuf<double> part(2 * (size_t)pl.n_sub, s), tdev(M + 1, s);
-  const int gfill = grid_for(pl.total, kT, 65536);
-  std::deque<Timer> marks;
-  auto record_trace = [&](const double* X, int n) {
-    hipLaunchKernelGGL(k_trace_rows<double>, dim3(pl.n_sub), dim3(kT), 0, s, X, offs.get(),
-                       npad.get(), P.core_ptr.get(), part.get(), nullptr, 1.0, 1.0);
-    hipLaunchKernelGGL(k_trace_total, dim3(1), dim3(kT), 0, s, part.get(), pl.n_sub,
-                       tdev.get() + n);
+  // a column per thread where a workgroup holds that many, else as few equal rounds as possible
+  const int waves = (P.max_sub + 63) / 64, rounds = (waves + 15) / 16;
+  const int threads = 64 * ((waves + rounds - 1) / rounds);
+  const int ntr = (M + 1) / 2;  // products that give the traces t_1 .. t_M
+  DBuf<double> part((size_t)n_items * 2 * ntr, s), sums(2 * (size_t)ntr, s), dc(M + 1, s), sp;
+  if (spill) sp = DBuf<double>((size_t)n_items * P.max_sub, s);
+  std::vector<double> traces(M + 1, 0.0), c(M + 1), h(2 * (size_t)ntr);
+  Timer t_pass;
+  auto pass = [&](const double* coef, int nterm, bool want_traces) {
+    const size_t lds = spill ? (size_t)P.max_sub * 8 : lds_of(R);
+    const int nt = want_traces ? ntr : 0;
+    GB_HIP(hipEventRecord(t_pass.a, s));
+    auto launch = [&](auto kern) {
+      hipLaunchKernelGGL(kern, dim3(n_items), dim3(threads), lds, s, ditems.get(), idx, val,
+                         len.get(), eoff.get(), P.sub_ptr.get(), P.core_ptr.get(), soff.get(),
+                         nterm, nt, coef, Dacc, part.get(), sp.get(), P.max_sub);
+    };
+    if (spill) launch(k_foe_rows<1, true>);
+    else if (R == 4) launch(k_foe_rows<4, false>);
+    else if (R == 2) launch(k_foe_rows<2, false>);
+    else launch(k_foe_rows<1, false>);
     GB_LAUNCH_CHECK();
-  };
-  // one pass of the recurrence; with c: the running sum in Dacc
-  auto pass = [&](const double* c) {
-    double* tp = B0;
-    double* tc = B1;
-    double* tn = B2;
-    hipLaunchKernelGGL(k_fill, dim3(gfill), dim3(kT), 0, s, tp, pl.total, 0.0);
-    GB_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_set_identity, dim3(pl.n_sub), dim3(kT), 0, s, tp, offs.get(), npad.get(),
-                       P.sub_ptr.get());
-    GB_LAUNCH_CHECK();
-    GB_HIP(hipMemcpyAsync(tc, A, pl.total * 8, hipMemcpyDeviceToDevice, s));
-    if (c) {
-      hipLaunchKernelGGL(k_axpby, dim3(gfill), dim3(kT), 0, s, Dacc, c[0], tp, c[1], tc,
-                         pl.total);
+    GB_HIP(hipEventRecord(t_pass.b, s));
+    if (want_traces) {
+      hipLaunchKernelGGL(k_foe_sums, dim3(2 * ntr), dim3(kT), 0, s, part.get(), n_items, 2 * ntr,
+                         sums.get());
       GB_LAUNCH_CHECK();
+      GB_HIP(hipMemcpyAsync(h.data(), sums.get(), h.size() * 8, hipMemcpyDeviceToHost, s));
     }
-    record_trace(tc, 1);
-    for (int n = 1; n < M; ++n) {
-      marks.emplace_back();
-      GB_HIP(hipEventRecord(marks.back().a, s));
-      launch_cheb(A, tc, tp, tn, c ? Dacc : nullptr, c ? c[n + 1] : 0.0, Pm, pl,
-                  tiles_full.get(), offs.get(), npad.get(), s);
-      GB_HIP(hipEventRecord(marks.back().b, s));
-      record_trace(tn, n + 1);
-      double* r = tp;
-      tp = tc;
-      tc = tn;
-      tn = r;
-    }
-    GB_HIP(hipMemcpyAsync(traces.data() + 1, tdev.get() + 1, M * 8, hipMemcpyDeviceToHost, s));
     GB_HIP(hipStreamSynchronize(s));
-    traces[0] = t0;
+    st.ms_product += elapsed(t_pass.a, t_pass.b);
+    st.n_product += nterm - 1;
     ++st.passes;
+    if (!want_traces) return;
+    traces[0] = t0;
+    traces[1] = h[0];
+    for (int n = 0; n < ntr; ++n) {
+      if (n > 0) traces[2 * n + 1] = 2.0 * h[2 * n] - traces[1];
+      if (2 * n + 2 <= M) traces[2 * n + 2] = 2.0 * h[2 * n + 1] - t0;
+    }
   };
 
   GB_HIP(hipEventRecord(t_stage.a, s));
-  std::vector<double> c(M + 1);
   double mu = o.mu;
-  if (std::isnan(mu)) {
-    pass(nullptr);
+  const bool solve = std::isnan(mu);
+  if (solve) {
+    pass(nullptr, ntr, true);
     mu = foe_solve_mu(traces.data(), M, emin, emax, o.beta, (double)n_occ, o.n_nodes);
   }
   chebyshev_fermi(emin, emax, o.beta, mu, M, o.n_nodes, c.data());
-  pass(c.data());
+  GB_HIP(hipMemcpyAsync(dc.get(), c.data(), (M + 1) * 8, hipMemcpyHostToDevice, s));
+  pass(dc.get(), M, !solve);
   GB_HIP(hipEventRecord(t_stage.b, s));
   GB_HIP(hipStreamSynchronize(s));
   st.ms_terms = elapsed(t_stage.a, t_stage.b);
-  for (auto& t : marks) st.ms_product += elapsed(t.a, t.b);
-  st.n_product = (int)marks.size();
   st.mu = mu;
   double tr = 0.0;
   for (int n = 0; n <= M; ++n) tr += c[n] * traces[n];
@@ -2906,7 +3030,7 @@ void foe(const gb_ell& H, int32_t n_occ, const gb_foe_opts& o, const Part& P, do
   if (o.traces) std::memcpy(o.traces, traces.data(), (M + 1) * sizeof(double));
 
   GB_HIP(hipEventRecord(t_stage.a, s));
-  hipLaunchKernelGGL(k_scatter<double>, dim3(N), dim3(kT), 0, s, Dacc, offs.get(),
+  hipLaunchKernelGGL(k_scatter<double>, dim3(N), dim3(kT), 0, s, Dacc, soff.get(),
                      npad.get(), P.sub_ptr.get(), P.sub_idx.get(), P.sub_pos.get(),
                      P.col_sub.get(), P.col_loc.get(), D.width, D.col, D.val);
   GB_LAUNCH_CHECK();
