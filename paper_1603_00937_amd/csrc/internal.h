@@ -121,11 +121,12 @@ void exclusive_scan_i64(const int32_t* in, int64_t* out, int n, hipStream_t s);
 double peak_rate(int kind, hipStream_t s, double* clock_mhz);
 
 // ---- vertex sets in LDS (graph.hip) ----
-// The graph and halo kernels keep vertex sets either as n-bit LDS bitmaps (fast while n is
-// small; LDS grows with n) or as LDS hash sets sorted afterwards (work and LDS independent of
-// n).  Hash sets are used above 2^17 vertices; the environment variable GB_VERTEX_SETS=bitmap
-// or =hash forces one kind (both give the same sets, in the same order).
-bool use_hash_sets(int n);
+// The halo kernels and the two-pass X2 kernels keep vertex sets either as n-bit LDS bitmaps (fast
+// while n is small; LDS grows with n) or as LDS hash sets sorted afterwards (work and LDS
+// independent of n).  Hash sets are used above `from` vertices; the environment variable
+// GB_VERTEX_SETS=bitmap or =hash forces one kind (both give the same sets, in the same order), and
+// with it the two-pass X2 kernels.
+bool use_hash_sets(int n, int from);
 
 // ---- graph (graph.hip) ----
 struct Csr {

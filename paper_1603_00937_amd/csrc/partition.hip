@@ -718,7 +718,9 @@ void finish_partition(const Csr& g, Part& P, hipStream_t s) {
   const int n = g.n;
   const int n_sub = P.n_sub;
   const int nw = (n + 31) >> 5;
-  const bool hash = use_hash_sets(n);
+  // block partition, bitmaps against hash sets: 0.9 / 2.6 ms at n = 160002, 2.1 / 4.0 at 262000
+  // (two workgroups per CU); past that the bitmaps leave one
+  const bool hash = use_hash_sets(n, 1 << 18);
   const size_t lds = (size_t)nw * 8 + kT * 4 + 64;
   if (!hash && lds > 160 * 1024)
     fail(GB_EUNSUPPORTED, "partition: n = %d too large for one LDS bitmap", n);
