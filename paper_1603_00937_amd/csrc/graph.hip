@@ -740,12 +740,14 @@ size_t x2_lds_bytes(int n, int w, int cap) {
 }
 
 // ---- row unions through an LDS bitmap (pattern graphs, symmetrisation) --------------------
-// Row i of the result = (row i of up to two CSR inputs) U {i}, sorted and unique.
+// Row i of the result = (row i of up to three CSR inputs) U {i}, sorted and unique.
 template <int PASS>
 __global__ __launch_bounds__(kT) void k_union_rows(int n, const int32_t* __restrict__ rp0,
                                                    const int32_t* __restrict__ c0,
                                                    const int32_t* __restrict__ rp1,
                                                    const int32_t* __restrict__ c1,
+                                                   const int32_t* __restrict__ rp2,
+                                                   const int32_t* __restrict__ c2,
                                                    int32_t* __restrict__ cnt,
                                                    const int32_t* __restrict__ row_ptr,
                                                    int32_t* __restrict__ out_col) {
@@ -764,6 +766,11 @@ __global__ __launch_bounds__(kT) void k_union_rows(int n, const int32_t* __restr
   if (rp1)
     for (int p = rp1[i] + threadIdx.x; p < rp1[i + 1]; p += kT) {
       const int j = c1[p];
+      atomicOr(&bits[j >> 5], 1u << (j & 31));
+    }
+  if (rp2)
+    for (int p = rp2[i] + threadIdx.x; p < rp2[i + 1]; p += kT) {
+      const int j = c2[p];
       atomicOr(&bits[j >> 5], 1u << (j & 31));
     }
   if (threadIdx.x == 0) atomicOr(&bits[i >> 5], 1u << (i & 31));
@@ -832,41 +839,53 @@ __global__ __launch_bounds__(kT) void k_twohop_rows(int n, const int32_t* __rest
   }
 }
 
-// entries of an ELL matrix with |a| >= tau, as (row-list) CSR counts / fill (rows unsorted
-// only if the ELL rows are; ELL rows are ascending so the output rows are ascending)
+// entries of an ELL matrix with |a| >= tau, as (row-list) CSR counts / fill, in slot order (ELL
+// rows are ascending, so the output rows are); a row ends at its first padding entry.  One wave
+// per row, 64 slots at a time: a previous D is some 2000 slots wide and its rows are read twice,
+// so what counts is that the reads are coalesced (a thread per row: 1.34 + 1.03 ms at N = 4096 x
+// 2304, this way 0.024 + 0.016).
 template <int PASS>
-__global__ void k_ell_threshold(const int32_t* __restrict__ col, const double* __restrict__ val,
-                                int n, int w, double tau, int32_t* __restrict__ cnt,
-                                const int32_t* __restrict__ row_ptr, int32_t* __restrict__ out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(kT) void k_ell_threshold(const int32_t* __restrict__ col,
+                                                      const double* __restrict__ val, int n, int w,
+                                                      double tau, int32_t* __restrict__ cnt,
+                                                      const int32_t* __restrict__ row_ptr,
+                                                      int32_t* __restrict__ out) {
+  const int i = blockIdx.x * (kT / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (i >= n) return;
-  int32_t c = 0;
-  int32_t pos = PASS ? row_ptr[i] : 0;
-  for (int t = 0; t < w; ++t) {
-    const int32_t j = col[(int64_t)i * w + t];
-    if (j < 0) break;
-    if ((unsigned)j >= (unsigned)n) continue;
-    if (fabs(val[(int64_t)i * w + t]) >= tau) {
-      if (PASS) out[pos++] = j;
-      ++c;
-    }
+  const int64_t base = (int64_t)i * w;
+  int pos = PASS ? row_ptr[i] : 0;
+  for (int t0 = 0; t0 < w; t0 += 64) {
+    const int t = t0 + lane;
+    const int32_t j = t < w ? col[base + t] : -1;
+    const double a = t < w ? val[base + t] : 0.0;
+    const unsigned long long end = __ballot(j < 0);
+    const bool before = end == 0 || lane < __ffsll((long long)end) - 1;
+    const bool keep = before && (unsigned)j < (unsigned)n && fabs(a) >= tau;
+    const unsigned long long m = __ballot(keep);
+    if (PASS && keep) out[pos + __popcll(m & ((1ull << lane) - 1ull))] = j;
+    pos += __popcll(m);
+    if (end) break;
   }
-  if (!PASS) cnt[i] = c;
+  if (!PASS && lane == 0) cnt[i] = pos;
 }
 
-// transpose of a CSR pattern: count per column, then fill (order within a row arbitrary)
-__global__ void k_tr_count(const int32_t* __restrict__ rp, const int32_t* __restrict__ c, int n,
-                           int32_t* __restrict__ cnt) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+// transpose of a CSR pattern: count per column, then fill (order within a row arbitrary); a wave
+// per row
+__global__ __launch_bounds__(kT) void k_tr_count(const int32_t* __restrict__ rp,
+                                                 const int32_t* __restrict__ c, int n,
+                                                 int32_t* __restrict__ cnt) {
+  const int i = blockIdx.x * (kT / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (i >= n) return;
-  for (int p = rp[i]; p < rp[i + 1]; ++p) atomicAdd(&cnt[c[p]], 1);
+  for (int p = rp[i] + lane; p < rp[i + 1]; p += 64) atomicAdd(&cnt[c[p]], 1);
 }
-__global__ void k_tr_fill(const int32_t* __restrict__ rp, const int32_t* __restrict__ c, int n,
-                          const int32_t* __restrict__ trp, int32_t* __restrict__ fill,
-                          int32_t* __restrict__ tc) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(kT) void k_tr_fill(const int32_t* __restrict__ rp,
+                                                const int32_t* __restrict__ c, int n,
+                                                const int32_t* __restrict__ trp,
+                                                int32_t* __restrict__ fill,
+                                                int32_t* __restrict__ tc) {
+  const int i = blockIdx.x * (kT / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (i >= n) return;
-  for (int p = rp[i]; p < rp[i + 1]; ++p) {
+  for (int p = rp[i] + lane; p < rp[i + 1]; p += 64) {
     const int j = c[p];
     tc[trp[j] + atomicAdd(&fill[j], 1)] = i;
   }
@@ -934,17 +953,18 @@ void check_lds(size_t bytes, const char* what) {
     fail(GB_EUNSUPPORTED, "%s needs %zu bytes of LDS per workgroup (limit 163840)", what, bytes);
 }
 
-// union of one or two CSRs plus self-loops -> out (sorted rows)
+// union of one to three CSRs plus self-loops -> out (sorted rows)
 void union_rows(int n, const int32_t* rp0, const int32_t* c0, const int32_t* rp1,
-                const int32_t* c1, Csr& out, hipStream_t s) {
+                const int32_t* c1, const int32_t* rp2, const int32_t* c2, Csr& out,
+                hipStream_t s) {
   const int nw = (n + 31) >> 5;
   const size_t lds = (size_t)nw * 8 + kT * 4 + 64;
   check_lds(lds, "graph row union");
   DBuf<int32_t> cnt(n, s);
   out.n = n;
   out.row_ptr = DBuf<int32_t>(n + 1, s);
-  hipLaunchKernelGGL(k_union_rows<0>, dim3(n), dim3(kT), lds, s, n, rp0, c0, rp1, c1, cnt.get(),
-                     nullptr, nullptr);
+  hipLaunchKernelGGL(k_union_rows<0>, dim3(n), dim3(kT), lds, s, n, rp0, c0, rp1, c1, rp2, c2,
+                     cnt.get(), nullptr, nullptr);
   GB_LAUNCH_CHECK();
   exclusive_scan_i32(cnt.get(), out.row_ptr.get(), n, s);
   int32_t nnz = 0;
@@ -952,26 +972,26 @@ void union_rows(int n, const int32_t* rp0, const int32_t* c0, const int32_t* rp1
   GB_HIP(hipStreamSynchronize(s));
   out.nnz = nnz;
   out.col = DBuf<int32_t>(nnz, s);
-  hipLaunchKernelGGL(k_union_rows<1>, dim3(n), dim3(kT), lds, s, n, rp0, c0, rp1, c1, nullptr,
-                     out.row_ptr.get(), out.col.get());
+  hipLaunchKernelGGL(k_union_rows<1>, dim3(n), dim3(kT), lds, s, n, rp0, c0, rp1, c1, rp2, c2,
+                     nullptr, out.row_ptr.get(), out.col.get());
   GB_LAUNCH_CHECK();
 }
 
 // CSR of the entries |a| >= tau of an ELL matrix (row-wise, rows ascending)
 void ell_threshold(const gb_ell& A, double tau, DBuf<int32_t>& rp, DBuf<int32_t>& c,
-                   hipStream_t s) {
+                   int32_t& nnz, hipStream_t s) {
   const int n = A.n;
   DBuf<int32_t> cnt(n, s);
   rp = DBuf<int32_t>(n + 1, s);
-  hipLaunchKernelGGL(k_ell_threshold<0>, dim3(blocks_for(n, kT)), dim3(kT), 0, s, A.col, A.val, n,
+  hipLaunchKernelGGL(k_ell_threshold<0>, dim3(blocks_for(n, kT / 64)), dim3(kT), 0, s, A.col, A.val, n,
                      A.width, tau, cnt.get(), nullptr, nullptr);
   GB_LAUNCH_CHECK();
   exclusive_scan_i32(cnt.get(), rp.get(), n, s);
-  int32_t nnz = 0;
+  nnz = 0;
   GB_HIP(hipMemcpyAsync(&nnz, rp.get() + n, 4, hipMemcpyDeviceToHost, s));
   GB_HIP(hipStreamSynchronize(s));
   c = DBuf<int32_t>(nnz > 0 ? nnz : 1, s);
-  hipLaunchKernelGGL(k_ell_threshold<1>, dim3(blocks_for(n, kT)), dim3(kT), 0, s, A.col, A.val, n,
+  hipLaunchKernelGGL(k_ell_threshold<1>, dim3(blocks_for(n, kT / 64)), dim3(kT), 0, s, A.col, A.val, n,
                      A.width, tau, nullptr, rp.get(), c.get());
   GB_LAUNCH_CHECK();
 }
@@ -982,12 +1002,12 @@ void transpose(int n, const int32_t* rp, const int32_t* c, int64_t nnz, DBuf<int
   hipLaunchKernelGGL(k_zero_i32, dim3(blocks_for(n, kT)), dim3(kT), 0, s, cnt.get(), (int64_t)n);
   hipLaunchKernelGGL(k_zero_i32, dim3(blocks_for(n, kT)), dim3(kT), 0, s, fill.get(), (int64_t)n);
   GB_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_tr_count, dim3(blocks_for(n, kT)), dim3(kT), 0, s, rp, c, n, cnt.get());
+  hipLaunchKernelGGL(k_tr_count, dim3(blocks_for(n, kT / 64)), dim3(kT), 0, s, rp, c, n, cnt.get());
   GB_LAUNCH_CHECK();
   trp = DBuf<int32_t>(n + 1, s);
   exclusive_scan_i32(cnt.get(), trp.get(), n, s);
   tc = DBuf<int32_t>(nnz > 0 ? nnz : 1, s);
-  hipLaunchKernelGGL(k_tr_fill, dim3(blocks_for(n, kT)), dim3(kT), 0, s, rp, c, n, trp.get(),
+  hipLaunchKernelGGL(k_tr_fill, dim3(blocks_for(n, kT / 64)), dim3(kT), 0, s, rp, c, n, trp.get(),
                      fill.get(), tc.get());
   GB_LAUNCH_CHECK();
 }
@@ -1222,12 +1242,10 @@ void graph_x2(const gb_ell& H, const double* x0, double tau, Csr& out, hipStream
 
 void graph_pattern(const gb_ell& A, double tau, Csr& out, hipStream_t s) {
   DBuf<int32_t> rp, c, trp, tc;
-  ell_threshold(A, tau, rp, c, s);
   int32_t nnz = 0;
-  GB_HIP(hipMemcpyAsync(&nnz, rp.get() + A.n, 4, hipMemcpyDeviceToHost, s));
-  GB_HIP(hipStreamSynchronize(s));
+  ell_threshold(A, tau, rp, c, nnz, s);
   transpose(A.n, rp.get(), c.get(), nnz, trp, tc, s);
-  union_rows(A.n, rp.get(), c.get(), trp.get(), tc.get(), out, s);
+  union_rows(A.n, rp.get(), c.get(), trp.get(), tc.get(), nullptr, nullptr, out, s);
 }
 
 void graph_rcut(const double* pos, int n_sites, int m, double box, double r_cut, Csr& out,
@@ -1285,14 +1303,11 @@ void graph_union_dprev(const Csr& base, const gb_ell& Dp, double tau_d, Csr& out
   // The union of base (symmetric), that list (row i gets r) and its transpose (row r gets i)
   // is symmetric.
   DBuf<int32_t> rp, c, trp, tc;
-  ell_threshold(Dp, tau_d, rp, c, s);
   int32_t nnz = 0;
-  GB_HIP(hipMemcpyAsync(&nnz, rp.get() + Dp.n, 4, hipMemcpyDeviceToHost, s));
-  GB_HIP(hipStreamSynchronize(s));
+  ell_threshold(Dp, tau_d, rp, c, nnz, s);
   transpose(Dp.n, rp.get(), c.get(), nnz, trp, tc, s);
-  Csr tmp;
-  union_rows(Dp.n, rp.get(), c.get(), trp.get(), tc.get(), tmp, s);
-  union_rows(Dp.n, base.row_ptr.get(), base.col.get(), tmp.row_ptr.get(), tmp.col.get(), out, s);
+  union_rows(Dp.n, base.row_ptr.get(), base.col.get(), rp.get(), c.get(), trp.get(), tc.get(),
+             out, s);
 }
 
 }  // namespace gbi
