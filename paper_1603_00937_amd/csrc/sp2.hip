@@ -1082,36 +1082,38 @@ __global__ __launch_bounds__(kT) void k_idem(const T* __restrict__ X, const T* _
 // core columns, and V q(X) for a slab V needs only products V X.
 
 // W = (scale V) X on the FP64 matrix cores (scale a power of two, applied exactly to V's entries
-// as they are loaded: the stored iterate may be X / scale): a wave computes all KMAX rows of 64
-// columns of W
-// (KMAX/16 x 4 tiles of 16 x 16, v_mfma_f64_16x16x4) and walks the reduction in chunks of 16
-// rows of X.  Within a chunk, lane l (i = l%16, q = l/16) takes the four consecutive rows
+// as they are loaded: the stored iterate may be X / scale).  A workgroup computes all KMAX rows of
+// 64 columns of W, its four waves a quarter of the reduction each (KMAX/16 x 4 tiles of 16 x 16
+// per wave, v_mfma_f64_16x16x4, in chunks of 16 rows of X), added up through LDS in a fixed
+// order.  Within a chunk, lane l (i = l%16, q = l/16) takes the four consecutive rows
 // a + 4q + u, u = the MFMA index: its A operands of a row tile are one 32-byte run of V
 // (V[16m + i][a + 4q .. a + 4q + 3]), and its B operands are 16-byte pairs of columns
 // (X[a + 4q + u][c + 32g + 2i, +1]; tile 2g + h holds the columns of parity h of group g), so a
 // chunk costs a wave 4 + 8 wide loads for 32 MFMAs.  X is read once; V (a few hundred KB per
-// block) comes from L2: the workgroups are numbered so that all column blocks of a subgraph run
-// on one XCD (workgroup i goes to XCD i mod 8), which fetches V into its L2 once.  Rows of V
-// beyond k_s are read in bounds (row k_s - 1) and zeroed by a select, keeping the loop free of
-// branches.  Output register r of lane l holds row 4r + q of its tile.
+// block) comes from L2: items lists a subgraph's column blocks on one XCD.  Rows of V beyond k_s
+// are read in bounds (row k_s - 1) and zeroed by a select, keeping the loop free of branches.
+// Output register r of lane l holds row 4r + q of its tile.
+// Bound by the FP64 matrix cores and the reads of X together (N = 18000, 32 rows, FP32 X: 0.68 ms
+// of products, 0.70 ms of reads at the copy rate), and by the latency of the reads: four waves per
+// SIMD (128 registers) hide it better than the three that 151 registers leave (8 products 9.2
+// against 9.9 ms).  Four waves on 64 columns are four times as many workgroups, a quarter as long,
+// as a wave per 64 columns: no difference at N = 18000 (9.2 against 9.3 ms), but a chip that the
+// small systems fill, N = 2050 2.13 -> 1.57 ms, N = 3000 (16 rows) 2.37 -> 1.7 ms.
 template <int KMAX, typename TX>
-__global__ __launch_bounds__(256) void k_rows_mm(const TX* __restrict__ X,
+__global__ __launch_bounds__(256, 4) void k_rows_mm(const TX* __restrict__ X,
                                                  const int64_t* __restrict__ offs,
-                                                 const int32_t* __restrict__ npad,
                                                  const double* __restrict__ V,
                                                  double* __restrict__ W,
                                                  const int64_t* __restrict__ soffs,
                                                  const int32_t* __restrict__ core_ptr,
-                                                 int n_sub, int colblocks, double scale) {
+                                                 const int4* __restrict__ items, double scale) {
   using M = Mfma<double>;
   constexpr int MT = KMAX / 16, NT = 4, U = 4;
-  const int id = blockIdx.x, q8 = id >> 3;
-  const int s = (id & 7) + 8 * (q8 / colblocks), cb = q8 % colblocks;
-  if (s >= n_sub) return;  // the grid covers n_sub rounded up to 8
-  const int np = npad[s];
+  __shared__ double2 red[2][MT * 2 * 4 * 64];
+  const int4 it = items[blockIdx.x];
+  if (it.x < 0) return;  // padding entry of an XCD queue
+  const int s = it.x, np = it.w, cw = it.y;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int cw = cb * 256 + wave * 64;
-  if (cw >= np) return;  // np is a multiple of 64: a wave is wholly inside or outside
   const int k = core_ptr[s + 1] - core_ptr[s];
   const int i16 = lane & 15, kq = lane >> 4;
   M::acc_t acc[MT][NT];
@@ -1128,7 +1130,8 @@ __global__ __launch_bounds__(256) void k_rows_mm(const TX* __restrict__ X,
   }
   const double* vb = V + soffs[s] + 4 * kq;
   const TX* xb = X + offs[s] + (int64_t)(4 * kq) * np + cw + 2 * i16;
-  for (int a0 = 0; a0 < np; a0 += 16) {  // np is a multiple of 64
+  const int a_end = (wave + 1) * (np >> 2);  // np is a multiple of 64
+  for (int a0 = wave * (np >> 2); a0 < a_end; a0 += 16) {
     double fa[U][MT], fb[U][NT];
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
@@ -1160,9 +1163,45 @@ __global__ __launch_bounds__(256) void k_rows_mm(const TX* __restrict__ X,
 #pragma unroll
         for (int n = 0; n < NT; ++n) acc[m][n] = M::mma(fa[u][m], fb[u][n], acc[m][n]);
   }
-  double* wb = W + soffs[s] + cw + 2 * i16;
+  // the sum over the waves, (w0 + w2) + (w1 + w3): waves 2 and 3 hand theirs to 0 and 1, then
+  // those exchange halves (two row tiles: a tile each; one: wave 0 takes all)
+  auto put = [&](int buf, int m) {
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        red[buf][((m * 2 + g) * 4 + r) * 64 + lane] =
+            double2{acc[m][2 * g][r], acc[m][2 * g + 1][r]};
+  };
+  auto add = [&](int buf, int m) {
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const double2 v = red[buf][((m * 2 + g) * 4 + r) * 64 + lane];
+        acc[m][2 * g][r] += v.x;
+        acc[m][2 * g + 1][r] += v.y;
+      }
+  };
+  if (wave >= 2)
+#pragma unroll
+    for (int m = 0; m < MT; ++m) put(wave - 2, m);
+  __syncthreads();
+  if (wave < 2)
+#pragma unroll
+    for (int m = 0; m < MT; ++m) add(wave, m);
+  __syncthreads();
+  if (wave == 1) put(0, 0);
+  if (MT == 2 && wave == 0) put(1, MT - 1);
+  __syncthreads();
+  if (wave >= MT) return;
 #pragma unroll
   for (int m = 0; m < MT; ++m)
+    if (m == wave) add(m, m);
+  double* wb = W + soffs[s] + cw + 2 * i16;
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    if (m != wave) continue;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int j = m * 16 + M::row(lane, r);
@@ -1173,6 +1212,7 @@ __global__ __launch_bounds__(256) void k_rows_mm(const TX* __restrict__ X,
               double2{acc[m][2 * g][r], acc[m][2 * g + 1][r]};
       }
     }
+  }
 }
 
 // W = the first k_s rows of X (= E X for the core unit rows E), times scale (a power of two)
@@ -2109,10 +2149,11 @@ int sp2_loop_dev(T*& X, T*& S, const Plan& pl, const DBuf<int4>& tiles, const DB
 // square), evaluated nested so every intermediate stays a polynomial bounded on [0, 1].
 struct CoreRows {
   int kmax = 0;
-  int colblocks = 0;
   int64_t total = 0;  // doubles per slab
   std::vector<int64_t> so;  // slab offset of each subgraph (host)
-  DBuf<int64_t> soffs;      // the same on the device
+  std::vector<int4> items;  // (subgraph, first column, -, npad) of every 64 columns of a slab
+  DBuf<int64_t> soffs;      // so and items on the device
+  DBuf<int4> ditems;
 };
 
 // host part: the slab layout (false when a core exceeds 32 rows: whole blocks instead)
@@ -2130,16 +2171,30 @@ bool core_rows_sizes(const Part& P, const Plan& pl, CoreRows& cr) {
     t += (int64_t)(P.h_core_ptr[q + 1] - P.h_core_ptr[q]) * pl.npad[q];
   }
   cr.kmax = kmax <= 16 ? 16 : 32;
-  cr.colblocks = (pl.max_npad + 255) / 256;
   cr.total = std::max<int64_t>(t, 1);
   return true;
 }
 
 bool core_rows_plan(const Part& P, const Plan& pl, CoreRows& cr, hipStream_t s) {
   if (!core_rows_sizes(P, pl, cr)) return false;
+  // 64 columns per workgroup, largest blocks first, a subgraph's on one XCD
+  std::vector<int> order(pl.n_sub);
+  std::iota(order.begin(), order.end(), 0);
+  std::stable_sort(order.begin(), order.end(),
+                   [&](int a, int b) { return pl.npad[a] > pl.npad[b]; });
+  std::vector<int4> list, ranges;
+  for (int q : order) {
+    const int first = (int)list.size();
+    for (int c = 0; c < pl.npad[q]; c += 64) list.push_back(make_int4(q, c, 0, pl.npad[q]));
+    ranges.push_back(make_int4(first, (int)list.size() - first, 0, q));
+  }
+  xcd_order(cr.items, list, ranges, 0, ranges.size());
   cr.soffs = DBuf<int64_t>(pl.n_sub, s);
-  // cr.so lives as long as cr, so the copy needs no wait
+  cr.ditems = DBuf<int4>(cr.items.size(), s);
+  // cr's vectors live as long as cr, so the copies need no wait
   GB_HIP(hipMemcpyAsync(cr.soffs.get(), cr.so.data(), pl.n_sub * 8, hipMemcpyHostToDevice, s));
+  GB_HIP(hipMemcpyAsync(cr.ditems.get(), cr.items.data(), cr.items.size() * sizeof(int4),
+                        hipMemcpyHostToDevice, s));
   return true;
 }
 
@@ -2153,13 +2208,13 @@ struct RowsCtx {
   double xscale;  // the stored iterate is X / xscale
   template <typename TX>
   void mm(const TX* X, const double* V, double* W) const {
-    const dim3 grid(cr.colblocks * ((pl.n_sub + 7) / 8 * 8));
+    const dim3 grid(cr.items.size());
     if (cr.kmax == 16)
-      hipLaunchKernelGGL((k_rows_mm<16, TX>), grid, dim3(256), 0, s, X, offs, npad, V, W,
-                         cr.soffs.get(), P.core_ptr.get(), pl.n_sub, cr.colblocks, xscale);
+      hipLaunchKernelGGL((k_rows_mm<16, TX>), grid, dim3(256), 0, s, X, offs, V, W,
+                         cr.soffs.get(), P.core_ptr.get(), cr.ditems.get(), xscale);
     else
-      hipLaunchKernelGGL((k_rows_mm<32, TX>), grid, dim3(256), 0, s, X, offs, npad, V, W,
-                         cr.soffs.get(), P.core_ptr.get(), pl.n_sub, cr.colblocks, xscale);
+      hipLaunchKernelGGL((k_rows_mm<32, TX>), grid, dim3(256), 0, s, X, offs, V, W,
+                         cr.soffs.get(), P.core_ptr.get(), cr.ditems.get(), xscale);
     GB_LAUNCH_CHECK();
   }
   void lin2(double* out, double a, const double* x, double b, const double* y) const {
@@ -2410,7 +2465,7 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
                *t1 = sl + 4 * cr.total;
         const RowsCtx rc{cr, pl, P, offs.get(), npad.get(), s, xs_scale};
         // E p(X) = 3 E X^2 - 2 E X^3 (E X: the first k rows of X)
-        hipLaunchKernelGGL(k_rows_copy<float>, dim3(cr.colblocks * 4, pl.n_sub), dim3(256), 0, s,
+        hipLaunchKernelGGL(k_rows_copy<float>, dim3((pl.max_npad + 63) / 64, pl.n_sub), dim3(256), 0, s,
                            xs, offs.get(), npad.get(), t0, cr.soffs.get(), P.core_ptr.get(),
                            xs_scale);
         GB_LAUNCH_CHECK();
