@@ -244,8 +244,10 @@ void gb_partition_destroy(gb_partition_t* p);
 
 /* Arithmetic of the squaring loop. */
 /* Low-precision variants square an FP32 iterate, keep the traces and the branch decision in
- * FP64, stop the low-precision loop when |t1 - t2| <= 1e-5 n / 1024 or when it stops
- * decreasing, and finish with FP64 refinement (McWeeny by default). */
+ * FP64 and finish with FP64 refinement.  With the default refinement the low-precision loop ends
+ * as soon as that can finish: at |t1 - t2| <= (idem_tol / 462)^(1/6) (see refine_kind); with the
+ * others, and where the refinement so far did not reach idem_tol, it runs until |t1 - t2| <=
+ * 1e-7 n / 1024 or stops decreasing.  A replayed sequence runs to its end. */
 typedef enum {
   GB_FP64 = 0,          /* every square in FP64 on the matrix cores                         */
   GB_FP32_REFINE = 1,   /* squares on FP32 MFMA (FP32 accumulate), then FP64 refinement      */
@@ -259,14 +261,17 @@ typedef struct {
   int32_t precision;         /* gb_precision; default GB_FP64                                */
   int32_t n_refine;          /* low precision: at most this many FP64 refinement steps       *
                               * (0 = 8 McWeeny steps / 16 SP2 steps)                          */
-  int32_t refine_kind;       /* low precision: 0 = McWeeny X <- 3X^2 - 2X^3 on the core rows  *
-                              * that D keeps (one or two steps, p or p(p), by products of the *
-                              * k core rows with X; 2 n^2 k flops each), accepted if the FP64 *
-                              * stop test holds on them, else as 2;                           *
+  int32_t refine_kind;       /* low precision: 0 = purification on the core rows that D keeps *
+                              * (by products of the k core rows with X; 2 n^2 k flops each):  *
+                              * S_m(X) for m = 3, 4, .. 6, the polynomial of degree 2m - 1    *
+                              * flat to order m at 0 and 1, until the FP64 stop test holds on *
+                              * the rows (S_2 = McWeeny's 3X^2 - 2X^3 alone for n_refine = 1); *
+                              * if it does not, more low-precision steps, then as 2;          *
                               * 1 = FP64 SP2 steps until it holds, the first by the trace     *
                               * rule, then alternating X^2 / 2X - X^2 (replayed from          *
                               * branch_in when that extends past the low-precision loop);     *
-                              * 2 = McWeeny steps on whole blocks until the stop test holds   */
+                              * 2 = McWeeny steps on whole blocks until the stop test holds,  *
+                              * from the iterate at which 0 would start                       */
   int32_t n_fp64_first;      /* low precision: run the first SP2 steps in FP64 (default 0)   */
   int32_t max_iter;          /* default 100 when 0                                           */
   double idem_tol;           /* stop when |Tr X - Tr X^2| <= idem_tol; 0 = 1e-10 * n / 1024   */
@@ -326,7 +331,8 @@ typedef struct {
   float ms_square_lo;        /* the same for the low-precision squaring launches             */
   int32_t n_square_lo;
   int32_t n_tile64;          /* subgraphs squared with 64-edge tiles                         */
-  int32_t n_refine_done;     /* McWeeny steps applied                                        */
+  int32_t n_refine_done;     /* McWeeny steps applied, or those that S_m stands for (2^steps  *
+                              * >= m; 4 for S_6)                                              */
   int32_t planes_db;         /* split loops: 1-3 bf16 planes, 4 = two fp16 planes; 0 otherwise */
   int32_t n_stage3;          /* subgraphs squared with the three-stage 64-edge kernel         */
   int32_t n_regstage;        /* subgraphs squared with the register-staged 64-edge kernel     */

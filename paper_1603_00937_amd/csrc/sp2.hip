@@ -10,6 +10,7 @@
 #include <cmath>
 #include <cstring>
 #include <cstdlib>
+#include <functional>
 #include <string>
 #include <map>
 #include <mutex>
@@ -942,14 +943,14 @@ __global__ __launch_bounds__(kT) void k_decide(const double* __restrict__ part, 
 struct LoopState {
   int32_t it, stopped, max_iter, n_forced;  // n_forced < 0: choose by the trace rule
   int32_t stag, cur_b, it0;  // it0: first step of this loop (stagnation looks back 2 steps)
-  double n_occ, tol;
+  double n_occ, tol, e_hand;  // e_hand: stop once the traces agree to this (0: never)
   uint8_t forced[128];
   StepRec recs[128];
 };
 // The loop's parameters, passed by value to the kernel that sets up LoopState.
 struct LoopInit {
   int32_t it0, max_iter, n_forced, stag;
-  double n_occ, tol;
+  double n_occ, tol, e_hand;
   uint8_t forced[128];
 };
 
@@ -980,6 +981,8 @@ __global__ __launch_bounds__(kT) void k_decide_dev(const double* __restrict__ pa
       q.stop = 1;
     } else if (it >= st->max_iter) {
       q.stop = 2;
+    } else if (e <= st->e_hand) {
+      q.stop = 5;
     } else if (st->stag && it - st->it0 >= 9 && e > st->recs[it - 2].e) {
       q.stop = 4;
     } else {
@@ -1099,6 +1102,13 @@ __global__ __launch_bounds__(kT) void k_idem(const T* __restrict__ X, const T* _
 // against 9.9 ms).  Four waves on 64 columns are four times as many workgroups, a quarter as long,
 // as a wave per 64 columns: no difference at N = 18000 (9.2 against 9.3 ms), but a chip that the
 // small systems fill, N = 2050 2.13 -> 1.57 ms, N = 3000 (16 rows) 2.37 -> 1.7 ms.
+// acc: y[q] (+)= c[q] W beside (or, with W NULL, instead of) W itself: the sums of a polynomial's
+// terms as they appear.  stopped: the launch returns at once if *stopped is not 0.
+struct RowsAcc {
+  double* y[3];
+  double c[3];
+  int n, fresh;  // fresh: bit q set where y[q] starts here
+};
 template <int KMAX, typename TX>
 __global__ __launch_bounds__(256, 4) void k_rows_mm(const TX* __restrict__ X,
                                                  const int64_t* __restrict__ offs,
@@ -1106,7 +1116,10 @@ __global__ __launch_bounds__(256, 4) void k_rows_mm(const TX* __restrict__ X,
                                                  double* __restrict__ W,
                                                  const int64_t* __restrict__ soffs,
                                                  const int32_t* __restrict__ core_ptr,
-                                                 const int4* __restrict__ items, double scale) {
+                                                 const int4* __restrict__ items, double scale,
+                                                 RowsAcc sums,
+                                                 const int32_t* __restrict__ stopped) {
+  if (stopped && *stopped) return;
   using M = Mfma<double>;
   constexpr int MT = KMAX / 16, NT = 4, U = 4;
   __shared__ double2 red[2][MT * 2 * 4 * 64];
@@ -1198,7 +1211,7 @@ __global__ __launch_bounds__(256, 4) void k_rows_mm(const TX* __restrict__ X,
 #pragma unroll
   for (int m = 0; m < MT; ++m)
     if (m == wave) add(m, m);
-  double* wb = W + soffs[s] + cw + 2 * i16;
+  const int64_t w0 = soffs[s] + cw + 2 * i16;
 #pragma unroll
   for (int m = 0; m < MT; ++m) {
     if (m != wave) continue;
@@ -1207,9 +1220,16 @@ __global__ __launch_bounds__(256, 4) void k_rows_mm(const TX* __restrict__ X,
       const int j = m * 16 + M::row(lane, r);
       if (j < k) {
 #pragma unroll
-        for (int g = 0; g < 2; ++g)
-          *reinterpret_cast<double2*>(wb + (int64_t)j * np + 32 * g) =
-              double2{acc[m][2 * g][r], acc[m][2 * g + 1][r]};
+        for (int g = 0; g < 2; ++g) {
+          const int64_t q = w0 + (int64_t)j * np + 32 * g;
+          const double2 v = double2{acc[m][2 * g][r], acc[m][2 * g + 1][r]};
+          if (W) *reinterpret_cast<double2*>(W + q) = v;
+          for (int p = 0; p < sums.n; ++p) {
+            double2* y = reinterpret_cast<double2*>(sums.y[p] + q);
+            const double2 o = (sums.fresh >> p) & 1 ? double2{0.0, 0.0} : *y;
+            *y = double2{o.x + sums.c[p] * v.x, o.y + sums.c[p] * v.y};
+          }
+        }
       }
     }
   }
@@ -1229,14 +1249,6 @@ __global__ __launch_bounds__(256) void k_rows_copy(const TX* __restrict__ X,
   const int64_t n = (int64_t)k * np;
   for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p < n; p += (int64_t)gridDim.x * 256)
     W[soffs[s] + p] = (double)X[offs[s] + p] * scale;
-}
-
-// out = a x + b y over a whole slab (flat)
-__global__ void k_lin2(double* __restrict__ out, double a, const double* __restrict__ x, double b,
-                       const double* __restrict__ y, int64_t n) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += stride)
-    out[p] = a * x[p] + b * y[p];
 }
 
 __global__ void k_max(const double* __restrict__ in, int n, double* __restrict__ out) {
@@ -1935,14 +1947,14 @@ void launch_step(const T* X, T* S, const Plan& pl, const int4* tiles, const int6
 // trip per step), then one squaring launch writes the next iterate.  Used for one launch per
 // subgraph, for the tape of the adjoint and for the alternating FP64 refinement.  Returns the
 // step index at which the stop rule fired, the replay ended, max_iter was reached, or (low
-// precision) the idempotency error stagnated; X then holds the result.
+// precision) the idempotency error stagnated or fell to e_hand; X then holds the result.
 template <typename T>
 int sp2_loop(T*& X, T*& S, const Plan& pl, const DBuf<int4>& tiles, const DBuf<int64_t>& offs,
              const DBuf<int32_t>& npad, const Part& P, double n_occ, double tol, int max_iter,
              const uint8_t* branch_in, int n_branch_in, bool stagnation_stop, int it0,
              gb_sp2_stats& st, DBuf<StepRec>& recs, hipStream_t s, int* stop_kind,
              TapeData* tape = nullptr, int planes = 0, bool per_subgraph = false,
-             bool alternate = false) {
+             bool alternate = false, double e_hand = 0.0) {
   Timer tm;
   PinnedRec pin;
   int it = it0;
@@ -1966,16 +1978,17 @@ int sp2_loop(T*& X, T*& S, const Plan& pl, const DBuf<int4>& tiles, const DBuf<i
     GB_HIP(hipStreamSynchronize(s));
     const StepRec r = *pin.h;
     es.push_back(r.e);
-    const bool stag = !r.stop && stagnation_stop && es.size() >= 10 &&
+    const bool hand = !r.stop && !branch_in && r.e <= e_hand;
+    const bool stag = !r.stop && !hand && stagnation_stop && es.size() >= 10 &&
                       es.back() > es[es.size() - 3];
-    record_step(st, it, r, !r.stop && !stag, branch_in == nullptr && !alternate, n_occ);
+    record_step(st, it, r, !r.stop && !stag && !hand, branch_in == nullptr && !alternate, n_occ);
     if (r.stop) {
       *stop_kind = (r.stop == 1 && (branch_in == nullptr || r.e <= tol)) ? 1 : 2;
       if (branch_in && r.stop == 1) *stop_kind = r.e <= tol ? 1 : 3;
       return it;
     }
-    if (stag) {
-      *stop_kind = 4;
+    if (stag || hand) {
+      *stop_kind = hand ? 5 : 4;
       return it;
     }
     prev_b = r.b;
@@ -2028,6 +2041,7 @@ __global__ void k_loop_init(LoopState* __restrict__ st, LoopInit in) {
   st->cur_b = -1;
   st->n_occ = in.n_occ;
   st->tol = in.tol;
+  st->e_hand = in.e_hand;
   for (int i = 0; i < 128; ++i) st->forced[i] = in.forced[i];
 }
 
@@ -2043,7 +2057,8 @@ template <typename T>
 int sp2_loop_dev(T*& X, T*& S, const Plan& pl, const DBuf<int4>& tiles, const DBuf<int64_t>& offs,
                  const DBuf<int32_t>& npad, const Part& P, double n_occ, double tol, int max_iter,
                  const uint8_t* branch_in, int n_branch_in, bool stagnation_stop, int it0,
-                 gb_sp2_stats& st, hipStream_t s, int* stop_kind, int planes, bool graph) {
+                 gb_sp2_stats& st, hipStream_t s, int* stop_kind, int planes, bool graph,
+                 double e_hand = 0.0) {
   constexpr int kFirst = 32, kMore = 8;
   // index of the last decision the loop can reach: it stops there at the latest
   const int last = branch_in ? std::min(n_branch_in, 127) : std::min(max_iter, 127);
@@ -2056,6 +2071,7 @@ int sp2_loop_dev(T*& X, T*& S, const Plan& pl, const DBuf<int4>& tiles, const DB
   in.stag = stagnation_stop ? 1 : 0;
   in.n_occ = n_occ;
   in.tol = tol;
+  in.e_hand = e_hand;
   if (branch_in) std::memcpy(in.forced, branch_in, std::min(n_branch_in, 128));
   DBuf<LoopState> d(1, s);
   DBuf<double> part(2 * (size_t)pl.n_sub, s);
@@ -2132,7 +2148,7 @@ int sp2_loop_dev(T*& X, T*& S, const Plan& pl, const DBuf<int4>& tiles, const DB
   }
   const StepRec& lr = h.recs[it_stop];
   if (lr.stop == 1) *stop_kind = (branch_in && lr.e > tol) ? 3 : 1;
-  else *stop_kind = lr.stop == 4 ? 4 : 2;
+  else *stop_kind = lr.stop == 4 || lr.stop == 5 ? lr.stop : 2;
   // n_sq squares were applied, each moving the iterate to the other buffer
   if (n_sq % 2 == 1) std::swap(X, S);
   return it_stop;
@@ -2140,13 +2156,63 @@ int sp2_loop_dev(T*& X, T*& S, const Plan& pl, const DBuf<int4>& tiles, const DB
 
 }  // namespace
 
-// Full gb_density pipeline on an already built partition.
-// ---- FP64 McWeeny refinement on the core rows --------------------------------------------
+// ---- FP64 refinement on the core rows -------------------------------------------------------
 // D keeps only the core columns of each block, i.e. (X symmetric) its core rows E q(X) for the
-// core unit rows E.  For p(x) = 3x^2 - 2x^3: E p(X) = 3 E X^2 - 2 E X^3, V p(X) = 3 V X^2 -
-// 2 V X^3 for any slab V, and p(p(X)) = 3 p(X)^2 - 2 p(X)^3, so one or two McWeeny steps on the
-// core rows take 2 or 8 slab products V X (2 n^2 k flops each instead of 2 n^3 for a block
-// square), evaluated nested so every intermediate stays a polynomial bounded on [0, 1].
+// core unit rows E, and E X^j takes one slab product (2 n^2 k flops instead of 2 n^3) from
+// E X^{j-1}.  The refinement evaluates q = S_m, the polynomial of degree 2m - 1 that is flat to
+// order m at 0 and 1 (S_2 = 3x^2 - 2x^3 is McWeeny's), so an eigenvalue off by d ends
+// C(2m-1, m) d^m off: the terms m .. 2m - 1 of S_m are added up as the powers appear, the FP64
+// stop test is taken on each S_m in turn, and the launches after the first that passes return
+// at once.  The order in which S_2 twice (degree 9, 8 products, 27 d^4) does it needs 6 products
+// (S_4: 35 d^4), and 8 give 126 d^5 (S_5).
+constexpr int kSmoothMax = 6;
+
+// coefficient of x^j in S_m, m <= j < 2m: (-1)^i C(m-1+i, i) C(2m-1, m-1-i) with i = j - m
+double smooth_coef(int m, int j) {
+  auto binom = [](int n, int k) {
+    double b = 1.0;
+    for (int i = 1; i <= k; ++i) b = b * (n - k + i) / i;
+    return b;
+  };
+  const int i = j - m;
+  const double c = std::rint(binom(m - 1 + i, i)) * std::rint(binom(2 * m - 1, m - 1 - i));
+  return i % 2 ? -c : c;
+}
+
+// The idempotency measure at which the low-precision loop hands over to S_6: one eigenvalue
+// carrying all of e ends C(11, 6) e^6 = 462 e^6 off, which is the tolerance here.  (Its own squares cost
+// 3.7 ms at N = 18000, two more slab products 2.3 ms, and a square at this stage gains at most one
+// order; beyond this point it also runs into its rounding floor.)
+double handover_measure(double tol) { return std::pow(tol / 462.0, 1.0 / 6.0); }
+
+// Stop flag and last record of the refinement's checks (device-driven, as LoopState): done is 0,
+// or the order m of the S_m that passed (1: the iterate itself).
+struct RefineState {
+  int32_t done, pad;
+  StepRec rec;
+};
+
+__global__ __launch_bounds__(kT) void k_refine_check(const double* __restrict__ part, int n_sub,
+                                                     double n_occ, double thr, int m,
+                                                     RefineState* __restrict__ st) {
+  if (st->done) return;
+  double t1, t2;
+  sum_partials(part, n_sub, &t1, &t2);
+  if (threadIdx.x == 0) {
+    const double e = fabs(t1 - t2);
+    StepRec q;
+    q.t1 = t1;
+    q.t2 = t2;
+    q.e = e;
+    q.margin = fabs(fabs(t2 - n_occ) - fabs(2.0 * t1 - t2 - n_occ));
+    q.b = -1;
+    q.stop = 1;
+    q.pad0 = q.pad1 = 0;
+    st->rec = q;
+    if (e <= thr) st->done = m;
+  }
+}
+
 struct CoreRows {
   int kmax = 0;
   int64_t total = 0;  // doubles per slab
@@ -2207,28 +2273,16 @@ struct RowsCtx {
   hipStream_t s;
   double xscale;  // the stored iterate is X / xscale
   template <typename TX>
-  void mm(const TX* X, const double* V, double* W) const {
+  void mm(const TX* X, const double* V, double* W, const RowsAcc& sums = RowsAcc{},
+          const int32_t* stopped = nullptr) const {
     const dim3 grid(cr.items.size());
     if (cr.kmax == 16)
       hipLaunchKernelGGL((k_rows_mm<16, TX>), grid, dim3(256), 0, s, X, offs, V, W,
-                         cr.soffs.get(), P.core_ptr.get(), cr.ditems.get(), xscale);
+                         cr.soffs.get(), P.core_ptr.get(), cr.ditems.get(), xscale, sums, stopped);
     else
       hipLaunchKernelGGL((k_rows_mm<32, TX>), grid, dim3(256), 0, s, X, offs, V, W,
-                         cr.soffs.get(), P.core_ptr.get(), cr.ditems.get(), xscale);
+                         cr.soffs.get(), P.core_ptr.get(), cr.ditems.get(), xscale, sums, stopped);
     GB_LAUNCH_CHECK();
-  }
-  void lin2(double* out, double a, const double* x, double b, const double* y) const {
-    hipLaunchKernelGGL(k_lin2, dim3(grid_for(cr.total, 256, 65536)), dim3(256), 0, s, out, a, x, b,
-                       y, cr.total);
-    GB_LAUNCH_CHECK();
-  }
-  // out = V p(X) (out may be V); t0, t1 scratch slabs
-  template <typename TX>
-  void apply_p(const TX* X, const double* V, double* out, double* t0, double* t1) const {
-    mm(X, V, t0);
-    mm(X, t0, t1);
-    mm(X, t1, t0);
-    lin2(out, 3.0, t1, -2.0, t0);
   }
 };
 
@@ -2312,6 +2366,7 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
   const float* xs = nullptr;
   double xs_scale = 1.0;
   bool xd_ready = true;
+  std::function<void(double)> run_low;  // the low-precision loop from step it_end on
   if (low) {
     float* xf = ws->get<float>(3, pl.total, s);
     float* sf = ws->get<float>(4, pl.total, s);
@@ -2351,24 +2406,31 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
       choose_tiles<float>(P, pl, xf, sf, tiles, offs.get(), s, o.tile_policy,
                           planes ? 10 + planes : 1, st, xcd, planes);
       st.planes_db = planes;
-      // The low-precision loop runs until its own rounding floor (the stagnation stop) unless
-      // the traces already agree to 1e-7 per 1024 orbitals, so that one FP64 McWeeny step
-      // usually finishes the job.
-      const double tol_lo = 1e-7 * N / 1024.0;
-      if (dev_loop)
-        it_end = sp2_loop_dev<float>(xf, sf, pl, tiles, offs, npad, P, n_occ, tol_lo, max_iter,
-                                     o.branch_in, o.n_branch_in, true, it_end, st, s, &stop_kind,
-                                     planes, o.launch_mode == 2);
-      else
-        it_end = sp2_loop<float>(xf, sf, pl, tiles, offs, npad, P, n_occ, tol_lo, max_iter,
-                                 o.branch_in, o.n_branch_in, true, it_end, st, recs, s, &stop_kind,
-                                 nullptr, planes, o.launch_mode == 1);
-      // the final low-precision square was only the stop test: continue from X made exactly
-      // symmetric, in FP32, in place (every block is padded to a multiple of 64)
-      hipLaunchKernelGGL(k_sym_diag, dim3(pl.max_npad / 64, pl.n_sub), dim3(256), 0, s, xf,
-                         offs.get(), npad.get());
-      GB_LAUNCH_CHECK();
-      xs = xf;
+      // The low-precision loop hands over to the refinement as soon as that finishes the job
+      // (a replayed sequence or a given number of steps runs as asked).  Where the refinement
+      // is by other means, it runs until its own rounding floor (the stagnation stop) unless the
+      // traces already agree to 1e-7 per 1024 orbitals.
+      CoreRows sizes;
+      const bool by_rows = o.refine_kind != 1 && n_refine == 0 && !o.branch_in &&
+                           core_rows_sizes(P, pl, sizes);
+      run_low = [&, xf, sf](double e_hand) mutable {
+        const double tol_lo = 1e-7 * N / 1024.0;
+        if (dev_loop)
+          it_end = sp2_loop_dev<float>(xf, sf, pl, tiles, offs, npad, P, n_occ, tol_lo, max_iter,
+                                       o.branch_in, o.n_branch_in, true, it_end, st, s, &stop_kind,
+                                       planes, o.launch_mode == 2, e_hand);
+        else
+          it_end = sp2_loop<float>(xf, sf, pl, tiles, offs, npad, P, n_occ, tol_lo, max_iter,
+                                   o.branch_in, o.n_branch_in, true, it_end, st, recs, s,
+                                   &stop_kind, nullptr, planes, o.launch_mode == 1, false, e_hand);
+        // continue from X made exactly symmetric, in FP32, in place (every block is padded to a
+        // multiple of 64)
+        hipLaunchKernelGGL(k_sym_diag, dim3(pl.max_npad / 64, pl.n_sub), dim3(256), 0, s, xf,
+                           offs.get(), npad.get());
+        GB_LAUNCH_CHECK();
+        xs = xf;
+      };
+      run_low(by_rows ? handover_measure(tol) : 0.0);
       xs_scale = planes == 4 ? (double)kF16Down : 1.0;
       xd_ready = false;
     }
@@ -2436,82 +2498,96 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
   if (low && done) {
     // converged during the FP64 steps: nothing to refine
   } else if (low && (o.refine_kind == 0 || o.refine_kind == 2)) {
-    // FP64 refinement by McWeeny purification X <- 3X^2 - 2X^3.  It drives every eigenvalue to
-    // 0 or 1 without acting on the trace, so the occupation the low-precision loop reached is
-    // kept.  The stop test takes the traces from X itself, so no square is spent on it.
-    const int at = std::min(it_end, 127);
-    // Core rows (refine_kind 0): two steps, or one when e <- 12 e^2 (how the summed distances of
-    // the eigenvalues from 0 and 1 contract per step, for one block) lands far below the
-    // tolerance, evaluated on the core rows only, then the stop test on them; if it fails,
-    // whole-block steps from the same X.
+    // FP64 refinement by purification, which drives every eigenvalue to 0 or 1 without acting on
+    // the trace, so the occupation the low-precision loop reached is kept.  The stop test takes
+    // the traces from X itself, so no square is spent on it.
+    // Core rows (refine_kind 0): S_3 .. S_6 of X in turn (see smooth_coef; S_2 first where its
+    // 3 e^2 will do, S_2 alone for n_refine = 1) until the stop test holds with two decades to
+    // spare, at the last one holds.  If it never does and an eigenvalue too far from 0 and 1 is the
+    // cause, the low-precision loop goes on to its rounding floor; whole-block steps follow where
+    // that does not help either.
     bool refined = false;
     if (o.refine_kind == 0 && xs && core_rows_plan(P, pl, cr, s)) {
       DBuf<double> part(2 * (size_t)pl.n_sub, s);
-      StepRec r;
-      hipLaunchKernelGGL(k_trace_rows<float>, dim3(pl.n_sub), dim3(kT), 0, s, xs, offs.get(),
-                         npad.get(), P.core_ptr.get(), part.get(), nullptr, xs_scale,
-                         xs_scale * xs_scale);
-      hipLaunchKernelGGL(k_decide, dim3(1), dim3(kT), 0, s, part.get(), pl.n_sub, (double)n_occ,
-                         tol, 2, 0, recs.get());
-      GB_LAUNCH_CHECK();
-      GB_HIP(hipMemcpyAsync(&r, recs.get(), sizeof(r), hipMemcpyDeviceToHost, s));
-      GB_HIP(hipStreamSynchronize(s));
-      if (r.e <= tol) {
-        refined = true;  // nothing to refine; the whole-block check below
-      } else {
-        const int m = (12.0 * r.e * r.e <= 1e-3 * tol || n_refine == 1) ? 1 : 2;
-        double* sl = ws->get<double>(7, 5 * (size_t)cr.total, s);
-        double *y = sl, *s1 = sl + cr.total, *s2 = sl + 2 * cr.total, *t0 = sl + 3 * cr.total,
-               *t1 = sl + 4 * cr.total;
-        const RowsCtx rc{cr, pl, P, offs.get(), npad.get(), s, xs_scale};
-        // E p(X) = 3 E X^2 - 2 E X^3 (E X: the first k rows of X)
-        hipLaunchKernelGGL(k_rows_copy<float>, dim3((pl.max_npad + 63) / 64, pl.n_sub), dim3(256), 0, s,
-                           xs, offs.get(), npad.get(), t0, cr.soffs.get(), P.core_ptr.get(),
+      DBuf<RefineState> rs(1, s);
+      int32_t* const rdone = &rs.get()->done;
+      double* sl = ws->get<double>(7, 5 * (size_t)cr.total, s);
+      const RowsCtx rc{cr, pl, P, offs.get(), npad.get(), s, xs_scale};
+      auto y_of = [&](int m) { return sl + (2 + m % 3) * cr.total; };  // S_6 follows S_3 in place
+      auto check = [&](const double* y, double thr, int m) {
+        hipLaunchKernelGGL(k_trace_rows<double>, dim3(pl.n_sub), dim3(kT), 0, s, y,
+                           cr.soffs.get(), npad.get(), P.core_ptr.get(), part.get(), rdone, 1.0,
+                           1.0);
+        hipLaunchKernelGGL(k_refine_check, dim3(1), dim3(kT), 0, s, part.get(), pl.n_sub,
+                           (double)n_occ, thr, m, rs.get());
+        GB_LAUNCH_CHECK();
+      };
+      // the terms m .. 2m - 1 of S_m, for the orders lo .. hi, in the product that gives V X^j
+      auto terms = [&](int j, int lo, int hi, auto&& slab) {
+        RowsAcc a{};
+        for (int m = lo; m <= hi; ++m)
+          if (m <= j && j < 2 * m) {
+            if (m == j) a.fresh |= 1 << a.n;
+            a.y[a.n] = slab(m);
+            a.c[a.n++] = smooth_coef(m, j);
+          }
+        return a;
+      };
+      RefineState h;
+      for (int attempt = 0; attempt < 2; ++attempt) {
+        const int lo = n_refine == 1 || 3.0 * st.idem * st.idem <= 1e-2 * tol ? 2 : 3;
+        const int hi = n_refine == 1 ? 2 : kSmoothMax;
+        hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(kT), 0, s, rdone, (int64_t)1);
+        double *v = sl, *w = sl + cr.total;
+        hipLaunchKernelGGL(k_rows_copy<float>, dim3((pl.max_npad + 63) / 64, pl.n_sub), dim3(256),
+                           0, s, xs, offs.get(), npad.get(), v, cr.soffs.get(), P.core_ptr.get(),
                            xs_scale);
         GB_LAUNCH_CHECK();
-        rc.mm(xs, t0, t1);
-        rc.mm(xs, t1, t0);
-        rc.lin2(y, 3.0, t1, -2.0, t0);
-        if (m == 2) {  // E p(p(X)) = 3 E p(X)^2 - 2 E p(X)^3
-          rc.apply_p(xs, y, s1, t0, t1);
-          rc.apply_p(xs, s1, s2, t0, t1);
-          rc.lin2(y, 3.0, s1, -2.0, s2);
+        check(v, tol, 1);
+        for (int j = 2; j < 2 * hi; ++j) {
+          rc.mm(xs, v, j + 1 < 2 * hi ? w : nullptr, terms(j, lo, hi, y_of), rdone);
+          std::swap(v, w);
+          const int m = (j + 1) / 2;
+          if (j % 2 && m >= lo) check(y_of(m), m == hi ? tol : 1e-2 * tol, m);
         }
-        hipLaunchKernelGGL(k_trace_rows<double>, dim3(pl.n_sub), dim3(kT), 0, s, y,
-                           cr.soffs.get(), npad.get(), P.core_ptr.get(), part.get(), nullptr, 1.0,
-                           1.0);
-        hipLaunchKernelGGL(k_decide, dim3(1), dim3(kT), 0, s, part.get(), pl.n_sub,
-                           (double)n_occ, tol, 2, 0, recs.get());
-        GB_LAUNCH_CHECK();
-        StepRec r2;
-        GB_HIP(hipMemcpyAsync(&r2, recs.get(), sizeof(r2), hipMemcpyDeviceToHost, s));
+        GB_HIP(hipMemcpyAsync(&h, rs.get(), sizeof(h), hipMemcpyDeviceToHost, s));
         GB_HIP(hipStreamSynchronize(s));
-        if (r2.e <= tol) {
-          // the check's square: Z = Y P(X) (P = p or p o p), the core rows of D^2 (nine more
-          // slab products; only when the max-norm check is asked for)
-          if (o.check_idem) rc.apply_p(xs, y, s1, t0, t1);
-          if (o.check_idem && m == 2) {
-            rc.apply_p(xs, s1, s2, t0, t1);
-            rc.mm(xs, s2, t0);
-            rc.mm(xs, t0, t1);
-            rc.mm(xs, t1, t0);
-            rc.lin2(s1, 3.0, s2, -6.0, t1);  // 3 A2 - 2 (3 A2 X^2 - 2 A2 X^3)
-            rc.lin2(s1, 1.0, s1, 4.0, t0);
-          }
-          rows_final = y;
-          rows_check = s1;
-          st.n_refine_done = m;
-          r = r2;
-          refined = true;
-        }
+        // short of idem_tol by its rounding only (the default tolerance is met): more low-precision
+        // squares would add theirs and resolve nothing
+        if (h.done || stop_kind != 5 || h.rec.e <= 1e-10 * N / 1024.0) break;
+        run_low(0.0);
       }
+      refined = h.done > 0;
       if (refined) {
-        st.idem = r.e;
-        st.t1[at] = r.t1;
-        st.t2[at] = r.t2;
+        const int m = h.done;
+        rows_final = m == 1 ? sl : y_of(m);
+        if (o.check_idem) {
+          // the check's square: Z = Y S_m(X), the core rows of D^2 (2m - 1 more slab products;
+          // only when the max-norm check is asked for)
+          double* z = y_of(m + 1);
+          double *v = sl, *w = sl + cr.total;
+          if (m == 1) {
+            rc.mm(xs, rows_final, z);
+          } else {
+            rc.mm(xs, rows_final, v);
+            for (int j = 2; j < 2 * m; ++j) {
+              rc.mm(xs, v, w, terms(j, m, m, [&](int) { return z; }));
+              std::swap(v, w);
+            }
+          }
+          rows_check = z;
+        }
+        // in McWeeny steps: what 2^steps >= m takes, one more for S_6, which may end at the
+        // tolerance itself
+        st.n_refine_done = m == 1 ? 0 : m == 2 ? 1 : m <= 4 ? 2 : m - 2;
+        const int at = std::min(it_end, 127);
+        st.idem = h.rec.e;
+        st.t1[at] = h.rec.t1;
+        st.t2[at] = h.rec.t2;
         stop_kind = 1;
       }
     }
+    const int at = std::min(it_end, 127);
     if (!refined) {
       // Whole blocks: X^2 = S, then 3S - 2 S X (S and X commute, so S X is computed on upper
       // tiles and mirrored); steps repeat until the FP64 stop test holds (at most n_refine,
