@@ -281,7 +281,8 @@ typedef struct {
   int32_t n_branch_in;       /* at most 127 (the stats record 128 steps)                     */
   double emin, emax;         /* spectral bounds; both 0 = Gershgorin                          */
   int32_t keep_tape;         /* 1: keep SP2 checkpoints for gb_density_vjp (GB_FP64 only)    */
-  int32_t tape_stride;       /* checkpoint every tape_stride-th iterate; 0 = 4               */
+  int32_t tape_stride;       /* checkpoint every tape_stride-th iterate; 0 = every iterate    *
+                              * where 32 of them take at most 32 GiB, else every fourth       */
   int32_t launch_mode;       /* 0 (default): device-driven loop -- one batched squaring     *
                               *    launch per step over every subgraph; the stop flag, step   *
                               *    counter, branch and step records stay on the device, every *

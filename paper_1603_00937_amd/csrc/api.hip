@@ -111,6 +111,66 @@ void Workspace::release_all() {
   }
 }
 
+std::mutex g_cached_mu;
+std::vector<CachedBuf> g_cached;  // idle
+size_t g_cached_bytes = 0;
+
+CachedBuf::CachedBuf(size_t need, hipStream_t s) {
+  GB_HIP(hipGetDevice(&device));
+  {
+    std::lock_guard<std::mutex> lk(g_cached_mu);
+    for (size_t i = 0; i < g_cached.size(); ++i) {
+      CachedBuf& c = g_cached[i];
+      if (c.device != device || c.bytes < need || c.bytes > 2 * need) continue;
+      p = c.p;
+      bytes = c.bytes;
+      a = c.a;
+      c.p = nullptr;  // its destructor has nothing to give back
+      g_cached_bytes -= bytes;
+      g_cached.erase(g_cached.begin() + i);
+      return;
+    }
+  }
+  bytes = need + need / 16;
+  p = dmalloc(bytes, s, &a);
+}
+
+CachedBuf::~CachedBuf() {
+  if (!p) return;
+  try {
+    std::lock_guard<std::mutex> lk(g_cached_mu);
+    if (g_cached_bytes + bytes <= kCachedMost) {
+      CachedBuf idle;
+      idle.p = p;
+      idle.bytes = bytes;
+      idle.device = device;
+      idle.a = a;
+      g_cached.push_back(std::move(idle));
+      g_cached_bytes += bytes;
+      return;
+    }
+  } catch (...) {  // no room in the list: freed below
+  }
+  dfree(p, nullptr, a);
+}
+
+void cached_trim() {
+  std::vector<CachedBuf> idle;
+  {
+    std::lock_guard<std::mutex> lk(g_cached_mu);
+    idle.swap(g_cached);
+    g_cached_bytes = 0;
+  }
+  int cur = 0;
+  (void)hipGetDevice(&cur);
+  for (CachedBuf& c : idle) {
+    (void)hipSetDevice(c.device);
+    dfree(c.p, nullptr, c.a);
+    c.p = nullptr;
+  }
+  (void)hipSetDevice(cur);
+}
+
 std::mutex g_ws_mu;
 std::vector<Workspace*> g_ws_idle;
 
@@ -293,6 +353,7 @@ const char* gb_last_error(void) { return g_err; }
 gb_status gb_trim(void) {
   return guarded([&] {
     ws_trim();
+    cached_trim();
     ml_trim();
   });
 }

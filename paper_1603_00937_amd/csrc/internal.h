@@ -110,6 +110,37 @@ struct WsLease {
   Workspace* operator->() const { return w; }
 };
 
+// ---- cached checkpoint buffers --------------------------------------------------------------
+// A tape holds one buffer per checkpoint (hundreds of MB to GB each) until it is destroyed.  They
+// go back to a process-wide list, from which the next tape takes one of its size (up to twice;
+// sizes drift between systems of one kind, and mapping a fresh GB costs more than the square that
+// fills it).  The list keeps at most kCachedMost idle bytes; gb_trim empties it.  Every call that
+// uses a buffer synchronises its stream before it returns, so the next holder may use it on any
+// stream.
+constexpr size_t kCachedMost = (size_t)48 << 30;
+struct CachedBuf {
+  void* p = nullptr;
+  size_t bytes = 0;
+  int device = 0;
+  Allocator a;
+  CachedBuf() = default;
+  CachedBuf(size_t need, hipStream_t s);
+  CachedBuf(const CachedBuf&) = delete;
+  CachedBuf& operator=(const CachedBuf&) = delete;
+  CachedBuf(CachedBuf&& o) noexcept : p(o.p), bytes(o.bytes), device(o.device), a(o.a) {
+    o.p = nullptr;
+  }
+  CachedBuf& operator=(CachedBuf&& o) noexcept {  // the two trade places
+    std::swap(p, o.p);
+    std::swap(bytes, o.bytes);
+    std::swap(device, o.device);
+    std::swap(a, o.a);
+    return *this;
+  }
+  ~CachedBuf();
+};
+void cached_trim();
+
 // ---- scans (scan.hip) ----
 // out[0..n] = exclusive prefix sums of in[0..n-1]; out[n] = total.
 void exclusive_scan_i32(const int32_t* in, int32_t* out, int n, hipStream_t s);

@@ -152,8 +152,16 @@ __global__ __launch_bounds__(kT) void k_gather(const int32_t* __restrict__ hcol,
 // k slice [g*KC/4, (g+1)*KC/4): the contraction is a sum over k, so any k order shared by
 // both operands is valid, and each lane reads its slice with 16-byte LDS loads.
 //   MODE 0: out = A*B          MODE 1: out = alpha*(A*B) + beta*E   (E symmetric)
-//   MODE 3: out = A*B for a general (non-symmetric) product with B symmetric: every tile
-//           (bi, bj) is listed and nothing is mirrored (the adjoint's Gbar*X)
+//   MODE 2: out = alpha*(A*B + B*A) + beta*E for symmetric A, B, E (the adjoint's step).  Tile (bi,
+//           bj) sums A's row panel bi with B's bj, then B's bi with A's bj: the flops of the
+//           general product A*B, whose transpose would have to be added in a pass of its own, and
+//           the result is written once.  The halves are summed apart (the first waits in out, not
+//           in registers: 131 of them leave three waves per SIMD, 85 five): each rounds as the
+//           general product did, and an entry of a diagonal tile and its transpose get the same
+//           two sums.  klim > 0: A is zero outside its first klim rows and
+//           columns, so a half of the sum whose panel of A lies below them ends after klim.
+//           57 blocks of ~1330 rows: 4.80 ms a step against 5.09 (general product on 128-edge tiles)
+//           + 0.46 (transpose and combine).
 // In MODE 0 (A = B = X) the SP2 update is fused into the epilogue: with the branch
 // 2X - X^2 selected (lin, or *lin_flag on the device-driven loop) the kernel writes 2X - X^2,
 // else X^2.  X is symmetric, so the mirrored entry takes the same value.
@@ -169,8 +177,10 @@ __global__ __launch_bounds__(kT, 2) void k_symm_mm(const T* __restrict__ A, cons
                                                    const int64_t* __restrict__ offs,
                                                    const int32_t* __restrict__ stopped,
                                                    int lin,
-                                                   const int32_t* __restrict__ lin_flag) {
+                                                   const int32_t* __restrict__ lin_flag,
+                                                   int klim) {
   if (stopped && *stopped) return;  // device-driven loop: the expansion already stopped
+  static_assert(MODE != 2 || LOADER == 1, "the two-sided product stages through registers");
   using M = Mfma<T>;
   using acc_t = typename M::acc_t;
   constexpr int KC = M::KC;              // k elements per 128-byte row chunk
@@ -219,12 +229,18 @@ __global__ __launch_bounds__(kT, 2) void k_symm_mm(const T* __restrict__ A, cons
     for (int n = 0; n < MB; ++n) acc[m][n] = acc_t{0, 0, 0, 0};
 
   const int g = lane >> 4, r16 = lane & 15;
-  const int nk = np / KC;
+  // chunks; MODE 2: of A_i B_j, then of B_i A_j
+  int nk = np / KC, nk1 = 0;
+  if constexpr (MODE == 2) {
+    const int few = klim > 0 ? min((klim + KC - 1) / KC, nk) : nk;
+    nk1 = klim > 0 && bi * BT >= klim ? few : nk;
+    nk = nk1 + (klim > 0 && bj * BT >= klim ? few : nk);
+  }
   // a wave whose row or column block lies in the padding beyond np has nothing to compute;
   // on a diagonal tile of a symmetric product the lower-left block is the transpose of the
   // upper-right one, which that wave writes twice
   const bool in_range = bi * BT + wr * WM < np && bj * BT + wc * WM < np;
-  const bool lower_diag = MODE != 3 && bi == bj && wr > wc;
+  const bool lower_diag = bi == bj && wr > wc;
   const bool active = in_range && !lower_diag;
   // byte offsets of this lane's pieces (2g + h) in rows wr*WM + m*16 + r16 (A) and
   // wc*WM + n*16 + r16 (B); (row & 7) = (r16 & 7) for every m
@@ -243,22 +259,33 @@ __global__ __launch_bounds__(kT, 2) void k_symm_mm(const T* __restrict__ A, cons
   } while (0)
   static_assert(LOADER == 0 || STAGES == 2, "register staging uses two LDS buffers");
   u4v stg[2][NLD];  // LOADER = 1: [operand][j], the 16 bytes this lane moves
-#define GB_STAGE(k0)                                                                        \
-  _Pragma("unroll") for (int j = 0; j < NLD; ++j) {                                         \
-    stg[0][j] = *reinterpret_cast<const u4v*>(asrc[j] + (k0));                             \
-    stg[1][j] = *reinterpret_cast<const u4v*>(bsrc[j] + (k0));                             \
-  }
+  auto stage = [&](int c) {  // chunk c into registers
+    if constexpr (MODE == 2) {
+      const bool first = c < nk1;
+      const T* base = first ? A : B;
+      const int k0 = (first ? c : c - nk1) * KC;
+#pragma unroll
+      for (int j = 0; j < NLD; ++j) {
+        stg[0][j] = *reinterpret_cast<const u4v*>(base + (asrc[j] - A) + k0);
+        stg[1][j] = *reinterpret_cast<const u4v*>((first ? B : A) + (bsrc[j] - B) + k0);
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < NLD; ++j) {
+        stg[0][j] = *reinterpret_cast<const u4v*>(asrc[j] + c * KC);
+        stg[1][j] = *reinterpret_cast<const u4v*>(bsrc[j] + c * KC);
+      }
+    }
+  };
 #define GB_PUT(buf)                                                                         \
   _Pragma("unroll") for (int j = 0; j < NLD; ++j) {                                         \
     *reinterpret_cast<u4v*>(&lds[buf][0][(wave * NLD + j) * 1024 + lane * 16]) = stg[0][j]; \
     *reinterpret_cast<u4v*>(&lds[buf][1][(wave * NLD + j) * 1024 + lane * 16]) = stg[1][j]; \
   }
   if (LOADER == 1) {
-    GB_STAGE(0)
+    stage(0);
     GB_PUT(0)
-    if (nk > 1) {
-      GB_STAGE(KC)
-    }
+    if (nk > 1) stage(1);
   } else {
     GB_ISSUE(0, 0)
     if (STAGES == 3 && nk > 1) {
@@ -274,6 +301,21 @@ __global__ __launch_bounds__(kT, 2) void k_symm_mm(const T* __restrict__ A, cons
     const int ahead = kc + STAGES - 1;  // the chunk issued in this iteration
     if (LOADER == 0 && ahead < nk) {
       GB_ISSUE(ahead % STAGES, ahead * KC)
+    }
+    if (MODE == 2 && kc == nk1 && active) {  // A_i B_j is done: aside, where the result will go
+      T* o = out + off;
+#pragma unroll
+      for (int m = 0; m < MB; ++m)
+#pragma unroll
+        for (int n = 0; n < MB; ++n) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int grow = bi * BT + wr * WM + m * 16 + M::row(lane, r);
+            const int gcol = bj * BT + wc * WM + n * 16 + r16;
+            if (grow < np && gcol < np) o[(int64_t)grow * np + gcol] = acc[m][n][r];
+          }
+          acc[m][n] = acc_t{0, 0, 0, 0};
+        }
     }
     if (active) {
       const unsigned char* la = lds[buf][0];
@@ -322,9 +364,7 @@ __global__ __launch_bounds__(kT, 2) void k_symm_mm(const T* __restrict__ A, cons
       if (kc + 1 < nk) {
         GB_PUT(buf ^ 1)
       }
-      if (kc + 2 < nk) {
-        GB_STAGE((kc + 2) * KC)
-      }
+      if (kc + 2 < nk) stage(kc + 2);
     } else if (STAGES == 3 && kc + 2 < nk) {
       // chunk kc + 1 must have landed; with three stages chunk kc + 2 may stay in flight
       GB_WAIT_ALL_BUT_NEWEST();
@@ -334,7 +374,6 @@ __global__ __launch_bounds__(kT, 2) void k_symm_mm(const T* __restrict__ A, cons
     __syncthreads();
   }
 #undef GB_PUT
-#undef GB_STAGE
 #undef GB_WAIT_ALL_BUT_NEWEST
 #undef GB_ISSUE
 
@@ -343,7 +382,7 @@ __global__ __launch_bounds__(kT, 2) void k_symm_mm(const T* __restrict__ A, cons
   const T* e = E + off;
   const T* xa = A + off;
   const bool do_lin = MODE == 0 && (lin_flag ? *lin_flag == 1 : lin != 0);
-  const bool mirror = MODE != 3 && (bi != bj || wr < wc);
+  const bool mirror = bi != bj || wr < wc;
   if constexpr (std::is_same<T, float>::value && MODE == 0) {
     // FP32 layout: lane l holds rows 4(l/16) .. +3 of column l%16, one contiguous run of the
     // transposed row, so the mirrored copy (and the symmetric X read of 2X - X^2) moves as one
@@ -375,7 +414,8 @@ __global__ __launch_bounds__(kT, 2) void k_symm_mm(const T* __restrict__ A, cons
         if (grow < np && gcol < np) {
           const int64_t q1 = (int64_t)grow * np + gcol, q2 = (int64_t)gcol * np + grow;
           T v = acc[m][n][r];
-          if (MODE == 1) v = alpha * v + beta * e[q1];
+          if (MODE == 2) v = o[q1] + v;
+          if (MODE == 1 || MODE == 2) v = alpha * v + beta * e[q1];
           if (do_lin) v = (T)2 * xa[q1] - v;
           o[q1] = v;
           if (mirror) o[q2] = v;
@@ -1301,29 +1341,6 @@ __global__ __launch_bounds__(kT) void k_seed(const double* __restrict__ gval, in
   }
 }
 
-// out = c1 (P + P^T) + c2 G per block, through a 32 x 32 LDS transpose
-__global__ __launch_bounds__(256) void k_sym_combine(const double* __restrict__ P,
-                                                     const double* __restrict__ G,
-                                                     double* __restrict__ out, double c1, double c2,
-                                                     const int64_t* __restrict__ offs,
-                                                     const int32_t* __restrict__ npad, int max_nt) {
-  __shared__ double t[32][33];
-  const int s = blockIdx.y;
-  const int np = npad[s], nt = np / 32;
-  const int bx = blockIdx.x % max_nt, by = blockIdx.x / max_nt;
-  if (bx >= nt || by >= nt) return;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  const double* p = P + offs[s];
-  for (int r = ty; r < 32; r += 8) t[r][tx] = p[(int64_t)(bx * 32 + r) * np + by * 32 + tx];
-  __syncthreads();
-  const double* g = G + offs[s];
-  double* o = out + offs[s];
-  for (int r = ty; r < 32; r += 8) {
-    const int64_t q = (int64_t)(by * 32 + r) * np + bx * 32 + tx;
-    o[q] = c1 * (p[q] + t[tx][r]) + c2 * g[q];
-  }
-}
-
 // vertex -> subgraphs holding it: counts, fill, per-vertex sort by subgraph
 __global__ void k_vs_count(const int32_t* __restrict__ sub_ptr, const int32_t* __restrict__ sub_idx,
                            int32_t* __restrict__ cnt) {
@@ -1342,20 +1359,23 @@ __global__ void k_vs_fill(const int32_t* __restrict__ sub_ptr, const int32_t* __
     vs_loc[q] = p - sub_ptr[s];
   }
 }
-__global__ void k_vs_sort(int n, const int32_t* __restrict__ vs_ptr, int32_t* __restrict__ vs_sub,
-                          int32_t* __restrict__ vs_loc) {
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
+// The lists come in the order of the atomics; each vertex's is put in ascending order of the
+// subgraphs (all different) by rank, a wave per vertex: a lane counts the entries below its own.
+// (Sorted in place by a thread per vertex it took 423 us for 1800 lists of ~42; 12 us this way.)
+__global__ __launch_bounds__(kT) void k_vs_sort(int n, const int32_t* __restrict__ vs_ptr,
+                                                const int32_t* __restrict__ sub,
+                                                const int32_t* __restrict__ loc,
+                                                int32_t* __restrict__ vs_sub,
+                                                int32_t* __restrict__ vs_loc) {
+  const int v = blockIdx.x * (kT / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (v >= n) return;
-  for (int p = vs_ptr[v] + 1; p < vs_ptr[v + 1]; ++p) {
-    const int ks = vs_sub[p], kl = vs_loc[p];
-    int q = p - 1;
-    while (q >= vs_ptr[v] && vs_sub[q] > ks) {
-      vs_sub[q + 1] = vs_sub[q];
-      vs_loc[q + 1] = vs_loc[q];
-      --q;
-    }
-    vs_sub[q + 1] = ks;
-    vs_loc[q + 1] = kl;
+  const int b = vs_ptr[v], e = vs_ptr[v + 1];
+  for (int p = b + lane; p < e; p += 64) {
+    const int key = sub[p];
+    int rank = 0;
+    for (int q = b; q < e; ++q) rank += sub[q] < key;
+    vs_sub[b + rank] = key;
+    vs_loc[b + rank] = loc[p];
   }
 }
 
@@ -1427,8 +1447,6 @@ struct Plan {
   Groups tg;                     //   (subgraph-major; per-subgraph launches use `ranges`)
   std::vector<int4> launch;      // the same tiles as launched in one batch, each variant group
   Groups lg;                     //   in XCD order
-  std::vector<int4> tiles_full;  // every (bi, bj) with edge 128 (general products)
-  std::vector<int4> full_launch; // the same in XCD order (the launch list of general products)
   std::vector<int4> ranges;      // per subgraph: first tile, tile count, variant code, s
   std::vector<int4> idem;        // 128-edge upper tiles covering the core rows (final check)
   double flops_alg = 0, flops_exec = 0;
@@ -1518,37 +1536,28 @@ Plan make_plan(const Part& P, const std::vector<int>* bt = nullptr, bool xcd = t
     pl.launch = pl.tiles;
     pl.lg = pl.tg;
   }
-  std::vector<int4> full_ranges;
   for (int s : order) {
     const int np = pl.npad[s];
     const int nb = (np + kBT - 1) / kBT;
     const int k = P.h_core_ptr[s + 1] - P.h_core_ptr[s];
-    const int first = (int)pl.tiles_full.size();
-    for (int bi = 0; bi < nb; ++bi)
-      for (int bj = 0; bj < nb; ++bj) {
-        pl.tiles_full.push_back(make_int4(s, bi, bj, np));
-        if (bj >= bi && bi * kBT < k) pl.idem.push_back(make_int4(s, bi, bj, np));
-      }
-    full_ranges.push_back(make_int4(first, (int)pl.tiles_full.size() - first, 128, s));
+    for (int bi = 0; bi < nb && bi * kBT < k; ++bi)
+      for (int bj = bi; bj < nb; ++bj) pl.idem.push_back(make_int4(s, bi, bj, np));
   }
-  // the general-product tiles in XCD order (queues padded with empty entries) or as listed
-  if (xcd) xcd_order(pl.full_launch, pl.tiles_full, full_ranges, 0, full_ranges.size());
-  else pl.full_launch = pl.tiles_full;
   return pl;
 }
 
 }  // namespace
 
 struct TapeData {
-  int N = 0, K = 0, stride = 4, max_sub = 0;
+  int N = 0, K = 0, stride = 4, max_sub = 0, max_core = 0;
   double emin = 0, emax = 0;
   std::vector<uint8_t> branch;
   Plan pl;
   DBuf<int64_t> offs;
   DBuf<int32_t> npad;
-  DBuf<int4> tiles, tiles_full;
+  DBuf<int4> tiles;
   DBuf<int32_t> core_ptr, sub_ptr, sub_idx, sub_pos;
-  std::vector<DBuf<double>> ckpt;  // X_0, X_stride, X_2stride, ...
+  std::vector<CachedBuf> ckpt;  // X_0, X_stride, X_2stride, ...
 };
 
 namespace {
@@ -1563,19 +1572,19 @@ void launch_symm(const T* A, const T* B, const T* E, T* out, T alpha, T beta, co
   const int4* t = tiles;
   if (g.n[0] > 0)
     hipLaunchKernelGGL((k_symm_mm<T, MODE, 128, 2>), dim3(g.n[0]), dim3(kT), 0, s, A, B, E, out,
-                       alpha, beta, t, offs, stopped, lin, lin_flag);
+                       alpha, beta, t, offs, stopped, lin, lin_flag, 0);
   t += g.n[0];
   if (g.n[1] > 0)
     hipLaunchKernelGGL((k_symm_mm<T, MODE, 64, 2>), dim3(g.n[1]), dim3(kT), 0, s, A, B, E, out,
-                       alpha, beta, t, offs, stopped, lin, lin_flag);
+                       alpha, beta, t, offs, stopped, lin, lin_flag, 0);
   t += g.n[1];
   if (g.n[2] > 0)
     hipLaunchKernelGGL((k_symm_mm<T, MODE, 64, 3>), dim3(g.n[2]), dim3(kT), 0, s, A, B, E, out,
-                       alpha, beta, t, offs, stopped, lin, lin_flag);
+                       alpha, beta, t, offs, stopped, lin, lin_flag, 0);
   t += g.n[2];
   if (g.n[3] > 0)
     hipLaunchKernelGGL((k_symm_mm<T, MODE, 64, 2, 1>), dim3(g.n[3]), dim3(kT), 0, s, A, B, E,
-                       out, alpha, beta, t, offs, stopped, lin, lin_flag);
+                       out, alpha, beta, t, offs, stopped, lin, lin_flag, 0);
   GB_LAUNCH_CHECK();
 }
 
@@ -1961,6 +1970,7 @@ int sp2_loop(T*& X, T*& S, const Plan& pl, const DBuf<int4>& tiles, const DBuf<i
   // the fp16 loop's iterate is stored as 2^14 X: its traces are scaled back
   const bool scaled = std::is_same<T, float>::value && planes == 4;
   const double ts1 = scaled ? kF16TraceDown1 : 1.0, ts2 = scaled ? kF16TraceDown2 : 1.0;
+  T* const scratch[2] = {X, S};  // checkpoints are written where they stay, never over
   int prev_b = -1;
   std::vector<double> es;
   DBuf<double> part(2 * (size_t)pl.n_sub, s);
@@ -1992,19 +2002,22 @@ int sp2_loop(T*& X, T*& S, const Plan& pl, const DBuf<int4>& tiles, const DBuf<i
       return it;
     }
     prev_b = r.b;
-    GB_HIP(hipEventRecord(tm.a, s));
-    launch_step<T>(X, S, pl, tiles.get(), offs.get(), s, planes, r.b == 1 ? 1 : 0, per_subgraph);
-    GB_HIP(hipEventRecord(tm.b, s));
-    std::swap(X, S);
-    ++it;
-    if (tape) {
-      tape->branch.push_back((uint8_t)r.b);
-      if (it % tape->stride == 0) {
-        DBuf<double> c(pl.total, nullptr);
-        GB_HIP(hipMemcpyAsync(c.get(), X, pl.total * sizeof(T), hipMemcpyDeviceToDevice, s));
-        tape->ckpt.push_back(std::move(c));
+    T* to = S;
+    if constexpr (std::is_same<T, double>::value) {
+      if (tape) {
+        tape->branch.push_back((uint8_t)r.b);
+        if ((it + 1) % tape->stride == 0) {
+          tape->ckpt.emplace_back(pl.total * sizeof(double), s);
+          to = static_cast<double*>(tape->ckpt.back().p);
+        }
       }
     }
+    GB_HIP(hipEventRecord(tm.a, s));
+    launch_step<T>(X, to, pl, tiles.get(), offs.get(), s, planes, r.b == 1 ? 1 : 0, per_subgraph);
+    GB_HIP(hipEventRecord(tm.b, s));
+    X = to;
+    S = X == scratch[0] ? scratch[1] : scratch[0];
+    ++it;
     GB_HIP(hipEventSynchronize(tm.b));
     if (std::is_same<T, float>::value) {
       st.ms_square_lo += elapsed(tm.a, tm.b);
@@ -2436,6 +2449,7 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
     }
     GB_HIP(hipEventRecord(t_sp2.b, s));
   } else {
+    choose_tiles<double>(P, pl, xd, sd, tiles, offs.get(), s, o.tile_policy, 0, st, xcd);
     hipLaunchKernelGGL(k_gather<double>, ggrid, dim3(kT), lds_g, s, H.col, x0, H.width,
                        P.core_ptr.get(), P.sub_ptr.get(), P.sub_idx.get(), offs.get(), npad.get(),
                        X64, 1.0);
@@ -2446,9 +2460,14 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
       t->N = N;
       t->emin = emin;
       t->emax = emax;
-      t->stride = o.tape_stride > 0 ? o.tape_stride : 4;
+      // every iterate where some thirty of them are small change in HBM (the reverse sweep then
+      // recomputes nothing), else every fourth
+      t->stride = o.tape_stride > 0 ? o.tape_stride : 32 * pl.total * 8 <= (int64_t)32 << 30 ? 1 : 4;
       t->max_sub = P.max_sub;
-      t->pl = pl;
+      for (int q = 0; q < P.n_sub; ++q)
+        t->max_core = std::max(t->max_core, P.h_core_ptr[q + 1] - P.h_core_ptr[q]);
+      const std::vector<int> bt(P.n_sub, 62);  // the reverse sweep's tiles, whatever the policy
+      t->pl = make_plan(P, &bt, xcd);
       auto dup_i32 = [&](DBuf<int32_t>& dst, const DBuf<int32_t>& src, size_t n) {
         dst = DBuf<int32_t>(n, nullptr);
         GB_HIP(hipMemcpyAsync(dst.get(), src.get(), n * 4, hipMemcpyDeviceToDevice, s));
@@ -2456,25 +2475,20 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
       t->offs = DBuf<int64_t>(pl.n_sub, nullptr);
       GB_HIP(hipMemcpyAsync(t->offs.get(), pl.off.data(), pl.n_sub * 8, hipMemcpyHostToDevice, s));
       dup_i32(t->npad, npad, pl.n_sub);
-      t->tiles = DBuf<int4>(pl.launch.size(), nullptr);
-      GB_HIP(hipMemcpyAsync(t->tiles.get(), pl.launch.data(), pl.launch.size() * sizeof(int4),
-                            hipMemcpyHostToDevice, s));
-      t->tiles_full = DBuf<int4>(pl.full_launch.size(), nullptr);
-      GB_HIP(hipMemcpyAsync(t->tiles_full.get(), pl.full_launch.data(),
-                            pl.full_launch.size() * sizeof(int4), hipMemcpyHostToDevice, s));
+      t->tiles = DBuf<int4>(t->pl.launch.size(), nullptr);
+      GB_HIP(hipMemcpyAsync(t->tiles.get(), t->pl.launch.data(),
+                            t->pl.launch.size() * sizeof(int4), hipMemcpyHostToDevice, s));
       dup_i32(t->core_ptr, P.core_ptr, P.n_sub + 1);
       dup_i32(t->sub_ptr, P.sub_ptr, P.n_sub + 1);
       dup_i32(t->sub_idx, P.sub_idx, P.total);
       dup_i32(t->sub_pos, P.sub_pos, P.total);
-      DBuf<double> c(pl.total, nullptr);
-      GB_HIP(hipMemcpyAsync(c.get(), X64, pl.total * 8, hipMemcpyDeviceToDevice, s));
-      t->ckpt.push_back(std::move(c));
+      t->ckpt.emplace_back(pl.total * 8, s);
+      GB_HIP(hipMemcpyAsync(t->ckpt[0].p, X64, pl.total * 8, hipMemcpyDeviceToDevice, s));
       GB_HIP(hipStreamSynchronize(s));  // host plan vectors above are copied before return
     }
     GB_HIP(hipEventRecord(t_gather.b, s));
   }
 
-  if (!low && !tape_out) choose_tiles<double>(P, pl, xd, sd, tiles, offs.get(), s, o.tile_policy, 0, st, xcd);
   // (with split-bf16 squares tile_policy picks that kernel's variant; the FP64 refinement tunes
   // its own tile edge)
   // (after split squares the plan holds the split's tile edges; FP64 squares on whole blocks --
@@ -2711,38 +2725,35 @@ void tape_dims(const TapeData* t, int* n, int* max_sub) {
 void density_vjp(TapeData& t, const gb_ell& G_D, const gb_ell& H, double* G_H, hipStream_t s) {
   const Plan& pl = t.pl;
   const int K = t.K, c = t.stride;
-  DBuf<double> G(pl.total, s), G2(pl.total, s), Pm(pl.total, s);
+  WsLease ws;  // the batch buffers of the expansions: Gbar, its successor, a segment's iterates
+  double* G = ws->get<double>(0, pl.total, s);
+  double* G2 = ws->get<double>(1, pl.total, s);
+  double* const seg = c > 1 ? ws->get<double>(5, (c - 1) * (size_t)pl.total, s) : nullptr;
   const int gfill = grid_for(pl.total, kT, 65536);
-  hipLaunchKernelGGL(k_fill, dim3(gfill), dim3(kT), 0, s, G.get(), pl.total, 0.0);
+  hipLaunchKernelGGL(k_fill, dim3(gfill), dim3(kT), 0, s, G, pl.total, 0.0);
   GB_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_seed, dim3(pl.n_sub), dim3(kT), 0, s, G_D.val, G_D.width, t.core_ptr.get(),
                      t.sub_ptr.get(), t.sub_idx.get(), t.sub_pos.get(), t.offs.get(), t.npad.get(),
-                     G.get());
+                     G);
   GB_LAUNCH_CHECK();
-  std::vector<DBuf<double>> seg;
-  for (int q = 1; q < c; ++q) seg.emplace_back(pl.total, s);
-  const int max_nt = pl.max_npad / 32;
-  const dim3 cgrid(max_nt * max_nt, pl.n_sub);
-  const int ntf = (int)pl.full_launch.size();
   for (int m = (K - 1) / c; m >= 0 && K > 0; --m) {
     const int start = m * c, end = std::min(start + c, K);
     std::vector<double*> xs;
-    xs.push_back(t.ckpt[m].get());
+    xs.push_back(static_cast<double*>(t.ckpt[m].p));
     for (int n = start; n + 1 < end; ++n) {
       double* xin = xs.back();
-      double* xout = seg[n - start].get();
+      double* xout = seg + (int64_t)(n - start) * pl.total;
       launch_plan_square_f64(xin, xout, pl, t.tiles.get(), t.offs.get(), s, t.branch[n] == 1);
       xs.push_back(xout);
     }
     for (int n = end - 1; n >= start; --n) {
       const double* X = xs[n - start];
-      hipLaunchKernelGGL((k_symm_mm<double, 3>), dim3(ntf), dim3(kT), 0, s, G.get(), X, X,
-                         Pm.get(), 1.0, 0.0, t.tiles_full.get(), t.offs.get(), nullptr, 0,
-                         (const int32_t*)nullptr);
-      GB_LAUNCH_CHECK();
       const double c1 = t.branch[n] == 0 ? 1.0 : -1.0, c2 = t.branch[n] == 0 ? 0.0 : 2.0;
-      hipLaunchKernelGGL(k_sym_combine, cgrid, dim3(256), 0, s, Pm.get(), G.get(), G2.get(), c1,
-                         c2, t.offs.get(), t.npad.get(), max_nt);
+      // the seed holds core rows and columns only
+      const int klim = n == K - 1 ? t.max_core : 0;
+      hipLaunchKernelGGL((k_symm_mm<double, 2, 64, 2, 1>), dim3(pl.lg.n[variant_index(62)]),
+                         dim3(kT), 0, s, G, X, G, G2, c1, c2, t.tiles.get(),
+                         t.offs.get(), (const int32_t*)nullptr, 0, (const int32_t*)nullptr, klim);
       GB_LAUNCH_CHECK();
       std::swap(G, G2);
     }
@@ -2760,16 +2771,16 @@ void density_vjp(TapeData& t, const gb_ell& G_D, const gb_ell& H, double* G_H, h
   int32_t tot = 0;
   GB_HIP(hipMemcpyAsync(&tot, vs_ptr.get() + n, 4, hipMemcpyDeviceToHost, s));
   GB_HIP(hipStreamSynchronize(s));
-  DBuf<int32_t> vs_sub(tot, s), vs_loc(tot, s);
+  DBuf<int32_t> raw_sub(tot, s), raw_loc(tot, s), vs_sub(tot, s), vs_loc(tot, s);
   hipLaunchKernelGGL(k_vs_fill, dim3(pl.n_sub), dim3(kT), 0, s, t.sub_ptr.get(), t.sub_idx.get(),
-                     vs_ptr.get(), fill.get(), vs_sub.get(), vs_loc.get());
+                     vs_ptr.get(), fill.get(), raw_sub.get(), raw_loc.get());
   GB_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_vs_sort, dim3((n + kT - 1) / kT), dim3(kT), 0, s, n, vs_ptr.get(),
-                     vs_sub.get(), vs_loc.get());
+  hipLaunchKernelGGL(k_vs_sort, dim3((n + kT / 64 - 1) / (kT / 64)), dim3(kT), 0, s, n,
+                     vs_ptr.get(), raw_sub.get(), raw_loc.get(), vs_sub.get(), vs_loc.get());
   GB_LAUNCH_CHECK();
   const int64_t slots = (int64_t)H.n * H.width;
   hipLaunchKernelGGL(k_assemble, dim3(grid_for(slots, kT)), dim3(kT), 0, s, H.col, H.n, H.width,
-                     vs_ptr.get(), vs_sub.get(), vs_loc.get(), t.offs.get(), t.npad.get(), G.get(),
+                     vs_ptr.get(), vs_sub.get(), vs_loc.get(), t.offs.get(), t.npad.get(), G,
                      -1.0 / (t.emax - t.emin), G_H);
   GB_LAUNCH_CHECK();
   GB_HIP(hipStreamSynchronize(s));
