@@ -80,6 +80,18 @@ namespace {
 constexpr int kT = 256;
 constexpr int kBT = 128;  // workgroup tile edge
 
+// LDS slots of the squaring kernels' operand rows.  A fragment read (ds_read_b128) takes lane
+// (g, r) to 16-byte piece g (of 64-byte rows) or 2g + h (of 128-byte rows) of row r, g = lane / 16,
+// r = lane % 16.  LDS serves it at 256 bytes per clock, 16 lanes at a time, but not 16 neighbours:
+// lanes 0-3, 12-15, 20-23, 24-27 go together, then 4-7, 8-11, 16-19, 28-31, and the same of the
+// upper half.  These permutations of a row's pieces keep each such set on 16 different 16-byte
+// banks; permutations made for 16 (or 8) neighbouring lanes put it on eight: 7 clocks per read
+// instead of 4 (measured on the pattern alone).  Conflicts went from a third of the LDS cycles to
+// none; the squares, which the LDS does not bound, gained 1 to 2 % (fp16 N = 18000 3.92 -> 3.88 ms,
+// N = 2050 0.670 -> 0.656, FP32 N = 3000 2.73 -> 2.70).
+__device__ __forceinline__ int swz8(int r) { return (r >> 1) & 5; }
+__device__ __forceinline__ int swz4(int r) { return (0x78 >> ((r >> 1) & 6)) & 3; }
+
 // ---- gather: x0[s] = principal submatrix of X0 on the subgraph, zero padded -------------
 // Block (s, chunk) writes rows [chunk*kRows, +kRows) of block s.  The subgraph list sits in
 // LDS; the local column of an ELL entry is found by binary search in the core run and in
@@ -190,9 +202,8 @@ __global__ __launch_bounds__(kT, 2) void k_symm_mm(const T* __restrict__ A, cons
   constexpr int MB = WM / 16;            // 16 x 16 blocks per wave tile edge
   constexpr int OPB = BT * 128;          // LDS bytes per operand per buffer
   constexpr int NLD = BT / 32;           // 1-KB wave loads per operand per chunk
-  // [buffer][operand][row-major 128-byte rows, the eight 16-byte pieces of row r stored at
-  // slot (piece ^ (r & 7)) so that sixteen lanes reading one piece of sixteen rows hit
-  // different banks]
+  // [buffer][operand][row-major 128-byte rows, the eight 16-byte pieces of row r stored at slot
+  // piece ^ swz8(r)]
   __shared__ __align__(1024) unsigned char lds[STAGES][2][OPB];
 
   const int4 tl = tiles[blockIdx.x];
@@ -211,7 +222,7 @@ __global__ __launch_bounds__(kT, 2) void k_symm_mm(const T* __restrict__ A, cons
 #pragma unroll
   for (int j = 0; j < NLD; ++j) {
     const int slot = (wave * NLD + j) * 64 + lane;
-    const int r = slot >> 3, c = (slot & 7) ^ (r & 7);
+    const int r = slot >> 3, c = (slot & 7) ^ swz8(r);
     const int ar = bi * BT + r, br = bj * BT + r;
     asrc[j] = A + off + (int64_t)(ar < np ? ar : 0) * np + c * V;
     bsrc[j] = B + off + (int64_t)(br < np ? br : 0) * np + c * V;
@@ -243,8 +254,8 @@ __global__ __launch_bounds__(kT, 2) void k_symm_mm(const T* __restrict__ A, cons
   const bool lower_diag = bi == bj && wr > wc;
   const bool active = in_range && !lower_diag;
   // byte offsets of this lane's pieces (2g + h) in rows wr*WM + m*16 + r16 (A) and
-  // wc*WM + n*16 + r16 (B); (row & 7) = (r16 & 7) for every m
-  const int sw = r16 & 7;
+  // wc*WM + n*16 + r16 (B); swz8(row) = swz8(r16) for every m
+  const int sw = swz8(r16);
   const int pa0 = (wr * WM + r16) * 128, pb0 = (wc * WM + r16) * 128;
   const int pc0 = (((2 * g) ^ sw) << 4), pc1 = (((2 * g + 1) ^ sw) << 4);
 
@@ -528,8 +539,7 @@ __device__ __forceinline__ void split_epilogue(const f4v (&big)[BT / 32][BT / 32
 
 // Split squaring: the FP32 iterate itself is read and each lane splits the 16 bytes it loads
 // into the NP planes (bf16, or fp16 of 2^14 x) while staging them into the swizzled LDS layout
-// (eight 16-byte pieces per 64-byte plane row, piece index XORed with bits of the row so that
-// sixteen lanes reading one piece of sixteen rows hit different banks).  X^2 is the sum of the
+// (four 16-byte pieces per 64-byte plane row, piece p of row r at slot p ^ swz4(r)).  X^2 is the sum of the
 // plane products that keep about 8 NP bits (bf16) or 22 bits (two fp16 planes) on the 16 x 16 x
 // 32 matrix cores, the leading product and the corrections in separate FP32 accumulators, added
 // once at the end; the epilogue applies the SP2 update and writes only the FP32 result.  The
@@ -570,7 +580,7 @@ __global__ __launch_bounds__(kT, 2) void k_symm_mm_split(const float* __restrict
     const int ar = bi * BT + r, br = bj * BT + r;
     asrc[q] = X + off + (int64_t)(ar < np ? ar : 0) * np + 4 * c8;
     bsrc[q] = X + off + (int64_t)(br < np ? br : 0) * np + 4 * c8;
-    ldo[q] = r * 64 + (((c8 >> 1) ^ ((r >> 2) & 3)) << 4) + (c8 & 1) * 8;
+    ldo[q] = r * 64 + (((c8 >> 1) ^ swz4(r)) << 4) + (c8 & 1) * 8;
   }
   f4v big[MB][MB], small[MB][MB];
 #pragma unroll
@@ -587,7 +597,7 @@ __global__ __launch_bounds__(kT, 2) void k_symm_mm_split(const float* __restrict
   const bool in_range = bi * BT + wr * WT < np && bj * BT + wc * WT < np;
   const bool active = in_range && !(bi == bj && wr > wc);
   const int pa0 = (wr * WT + r16) * 64, pb0 = (wc * WT + r16) * 64;
-  const int pc = (g ^ ((r16 >> 2) & 3)) << 4;
+  const int pc = (g ^ swz4(r16)) << 4;
   f4v stg[2][NQ];  // [operand][q]
   float neg1 = -1.0f;  // see split_pair
   asm volatile("" : "+v"(neg1));
@@ -689,7 +699,7 @@ __device__ inline void sched_vmr4() { __builtin_amdgcn_sched_group_barrier(0x020
 // planes of chunk kc + 1 are split from registers and written to one buffer while the products
 // of chunk kc read the other, the split's vector instructions and LDS writes interleaved with
 // the matrix-core instructions (the first operand's split under the leading products, the
-// second's under the correction products), one barrier per chunk.  Each operand's next chunk
+// second's under the hi x lo products), one barrier per chunk.  Each operand's next chunk
 // is loaded into registers once its split has consumed them.  The two buffers are separate
 // arrays and the loop is unrolled by two, so reads of one and writes of the other are known
 // not to alias.  Products, their order and the accumulators are those of k_symm_mm_split, so
@@ -727,7 +737,7 @@ __global__ __launch_bounds__(kT, 2) void k_symm_mm_split_il(const float* __restr
     const int ar = bi * BT + r, br = bj * BT + r;
     asrc[q] = (ar < np ? ar : 0) * np + 4 * c8;
     bsrc[q] = (br < np ? br : 0) * np + 4 * c8;
-    ldo[q] = r * 64 + (((c8 >> 1) ^ ((r >> 2) & 3)) << 4) + (c8 & 1) * 8;
+    ldo[q] = r * 64 + (((c8 >> 1) ^ swz4(r)) << 4) + (c8 & 1) * 8;
   }
   f4v big[MB][MB], small[MB][MB];
 #pragma unroll
@@ -742,7 +752,7 @@ __global__ __launch_bounds__(kT, 2) void k_symm_mm_split_il(const float* __restr
   const bool in_range = bi * BT + wr * WT < np && bj * BT + wc * WT < np;
   const bool active = in_range && !(bi == bj && wr > wc);
   const int pa0 = (wr * WT + r16) * 64, pb0 = (wc * WT + r16) * 64;
-  const int pc = (g ^ ((r16 >> 2) & 3)) << 4;
+  const int pc = (g ^ swz4(r16)) << 4;
   f4v stg[2][NQ];  // [operand][q]
   float neg1 = -1.0f;  // see split_pair
   asm volatile("" : "+v"(neg1));
@@ -795,7 +805,8 @@ __global__ __launch_bounds__(kT, 2) void k_symm_mm_split_il(const float* __restr
       }
       load_op(0, k2);
       sched_vmr4();  // the next loads after the split that frees their registers
-      // the second operand's split in two halves, under the hi x lo and the lo x hi products
+      // the second operand's split under the hi x lo products, so that its next chunk's loads, too,
+      // have a third of the step and more ahead of them
 #pragma unroll
       for (int m = 0; m < MB; ++m) {
         bf8v BL;
@@ -803,14 +814,16 @@ __global__ __launch_bounds__(kT, 2) void k_symm_mm_split_il(const float* __restr
 #pragma unroll
         for (int r = 0; r < MB; ++r) small[r][m] = mma_f16(A0[r], BL, small[r][m]);
       }
-      split_op(1, nxt, 0, NQ / 2);
+      split_op(1, nxt, 0, NQ);
 #pragma unroll
       for (int i = 0; i < MB * MB; ++i) {
         if (i % MB == 0) sched_dsr1();
         sched_mfma1();
-        sched_valu2();
-        if (i % (2 * MB * MB / NQ) == 2 * MB * MB / NQ - 1) sched_dsw1();
+        sched_valu4();
+        if (i % (MB * MB / NQ) == MB * MB / NQ - 1) sched_dsw1();
       }
+      load_op(1, k2);
+      sched_vmr4();
 #pragma unroll
       for (int m = 0; m < MB; ++m) {
         bf8v AL;
@@ -818,16 +831,11 @@ __global__ __launch_bounds__(kT, 2) void k_symm_mm_split_il(const float* __restr
 #pragma unroll
         for (int n = 0; n < MB; ++n) small[m][n] = mma_f16(AL, B0[n], small[m][n]);
       }
-      split_op(1, nxt, NQ / 2, NQ / 2);
 #pragma unroll
       for (int i = 0; i < MB * MB; ++i) {
         if (i % MB == 0) sched_dsr1();
         sched_mfma1();
-        sched_valu2();
-        if (i % (2 * MB * MB / NQ) == 2 * MB * MB / NQ - 1) sched_dsw1();
       }
-      load_op(1, k2);
-      sched_vmr4();
     } else {
       split_op(0, nxt, 0, NQ);
       split_op(1, nxt, 0, NQ);
