@@ -536,7 +536,8 @@ __global__ __launch_bounds__(kT) void k_x2_rows_hash(const int32_t* __restrict__
 // pair costs one look-up and one ds_add_f64, and LDS no longer grows with n.  Bound by LDS and the
 // vector work of a pair at two workgroups per CU (the pages take ~50 KB).  Whole graph call, two-
 // pass bitmap -> paged: N = 1024 0.56 -> 0.48 ms, 18000 3.1 -> 2.7, 100000 (clustered) 18.5 ->
-// 10.1, 160002 36.8 -> 15.8 (67 with hash sets, which it took there).  512 threads: 256 take 23.9
+// 10.1, 160002 36.8 -> 15.8 (67 with hash sets, which it took there); rows of consecutive numbers,
+// which share the rows they read, on one XCD: another 5 %.  512 threads: 256 take 23.9
 // and 1024 19.1 ms at 160002.
 struct X2Paged {
   int shift, pcap, cap;
@@ -577,7 +578,8 @@ __global__ __launch_bounds__(kPT) void k_x2_rows_paged(
     int32_t* __restrict__ overflow) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int32_t npages;
-  const int i = blockIdx.x;
+  const int i = xcd_run(blockIdx.x, n);
+  if (i >= n) return;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   constexpr int NW = kPT / 64;
   const int ndir = ((n - 1) >> g.shift) + 1;
@@ -1125,7 +1127,7 @@ bool graph_x2_paged(const gb_ell& H, const double* x0, double tau, Csr& out, hip
   for (int attempt = 0;; ++attempt) {
     rows = DBuf<int32_t>((size_t)n * g.cap, s);
     hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, s, ovf.get(), (int64_t)2);
-    hipLaunchKernelGGL(k_x2_rows_paged, dim3(n), dim3(kPT), x2_paged_lds_bytes(n, w, g), s, H.col,
+    hipLaunchKernelGGL(k_x2_rows_paged, dim3(xcd_grid(n)), dim3(kPT), x2_paged_lds_bytes(n, w, g), s, H.col,
                        x0, rb.get(), rlen.get(), n, w, tau, all_asc, g, cnt.get(), rows.get(),
                        ovf.get());
     GB_LAUNCH_CHECK();

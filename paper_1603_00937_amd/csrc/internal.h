@@ -141,6 +141,13 @@ struct CachedBuf {
 };
 void cached_trim();
 
+// ---- workgroups of consecutive rows on one XCD ----
+// The hardware hands workgroup b to XCD b mod 8, each with an L2 of its own.  Where workgroup b
+// works on vertex b and neighbours share what they read, vertices are dealt to the XCDs in eight
+// runs instead (a grid of xcd_grid(n) workgroups; those past n have nothing to do).
+inline int xcd_grid(int n) { return (n + 7) / 8 * 8; }
+__host__ __device__ inline int xcd_run(int b, int n) { return (b & 7) * ((n + 7) / 8) + (b >> 3); }
+
 // ---- scans (scan.hip) ----
 // out[0..n] = exclusive prefix sums of in[0..n-1]; out[n] = total.
 void exclusive_scan_i32(const int32_t* in, int32_t* out, int n, hipStream_t s);
@@ -210,7 +217,7 @@ struct MlLease {
 };
 void ml_trim();
 // pinned host arrays of the lease for a graph of n vertices and nnz entries (grown on demand):
-// row pointers, columns, edge weights
+// row pointers, columns, edge weights (the latter two only where asked for)
 void ml_stage(MlScratch& sc, int n, int64_t nnz, int32_t** rp, int32_t** col, int32_t** w);
 // host array of the lease for n vertices' candidate lists (n * kMlTop entries)
 int32_t* ml_top_buffer(MlScratch& sc, int n);
@@ -220,7 +227,8 @@ int32_t* ml_top_buffer(MlScratch& sc, int n);
 // (optional) receives the level count, timings and the cost sum (|core| + |halo|)^3, which is
 // only computed when stats is given.  top0 (optional, with ew): per vertex the kMlTop heaviest
 // neighbours by (weight, -index), heaviest first, -1 padded (what the matching would compute).
-constexpr int kMlTop = 8;
+// rows0 (optional, with top0 and dev1): col and ew are NULL, rows come from there.
+constexpr int kMlTop = 12;  // eight: 106 rows of 100000 fetched for the matching, 1 ms more
 // Coarse levels built where the graph lives (the device path, partition.hip): given the
 // matching of level `level` (n vertices, host row pointers frp) -- coarse vertex c is
 // {lead[c], match[lead[c]]}, cmap the fine -> coarse map, cvw the coarse weights -- it builds
@@ -239,6 +247,15 @@ struct MlCoarseDevice {
                      const int32_t** rp, const int32_t** adj, const int32_t** ew,
                      const int32_t** top) = 0;
 };
+// The rows of an input graph that stays on the device: the matching of the input level needs only
+// the few rows whose listed candidates are all taken (about one vertex in a thousand), and the
+// host needs all of them only where it has to build the first coarse level itself or grows the
+// parts on the input.
+struct MlRows {
+  virtual ~MlRows() = default;
+  virtual void row(int v, const int32_t** adj, const int32_t** ew) = 0;
+  virtual void all(const int32_t** adj, const int32_t** ew) = 0;
+};
 // pinned host arrays of the lease for a coarse level built on the device (nc vertices, nnz
 // entries, the candidate lists), grown on demand
 void ml_stage1(MlScratch& sc, int nc, int64_t nnz, int32_t** rp, int32_t** adj, int32_t** ew,
@@ -246,7 +263,8 @@ void ml_stage1(MlScratch& sc, int nc, int64_t nnz, int32_t** rp, int32_t** adj, 
 void partition_multilevel(int n, const int32_t* row_ptr, const int32_t* col, int cap,
                           std::vector<int32_t>& core_ptr, std::vector<int32_t>& core_vtx,
                           MlStats* stats, const int32_t* ew = nullptr, MlScratch* sc = nullptr,
-                          const int32_t* top0 = nullptr, MlCoarseDevice* dev1 = nullptr);
+                          const int32_t* top0 = nullptr, MlCoarseDevice* dev1 = nullptr,
+                          MlRows* rows0 = nullptr);
 // The previous cores carried to a new graph on the same vertices (on-the-fly update between MD
 // steps): the cores renumbered as the partitioner emits them, and (when stats is given) their
 // cost on the new graph.

@@ -137,6 +137,7 @@ struct Level {
   const int32_t* rp = nullptr;
   const int32_t* adj = nullptr;
   const int32_t* ew = nullptr;
+  MlRows* src = nullptr;  // where adj and ew come from while they are NULL
   std::vector<int32_t> rp_v, adj_v, ew_v;  // storage of a coarse level (or of host weights)
   bool sorted = false;                     // rows ascending (a level built on the device)
   std::vector<int32_t> vw;                 // vertex weights
@@ -267,10 +268,18 @@ bool coarsen(Level& f, int cap, int level, Level& c, MlScratch& sc,
     }
     if (best < 0 && !listed_all) {
       int bw = -1, bvw = INT_MAX;
-      for (int e = f.rp[v]; e < f.rp[v + 1]; ++e) {
-        const int u = f.adj[e];
+      const int32_t *adj = nullptr, *ew = nullptr;
+      if (f.adj) {
+        adj = f.adj + f.rp[v];
+        ew = f.ew + f.rp[v];
+      } else {
+        f.src->row(v, &adj, &ew);
+      }
+      const int deg = f.rp[v + 1] - f.rp[v];
+      for (int e = 0; e < deg; ++e) {
+        const int u = adj[e];
         if (u == v || match[u] >= 0 || f.vw[u] + f.vw[v] > cap) continue;
-        const int w = f.ew[e];
+        const int w = ew[e];
         if (w > bw || (w == bw && (f.vw[u] < bvw || (f.vw[u] == bvw && u < best)))) {
           best = u;
           bw = w;
@@ -310,6 +319,7 @@ bool coarsen(Level& f, int cap, int level, Level& c, MlScratch& sc,
   }
   sc.top1 = nullptr;
   c.sorted = false;
+  if (!f.adj) f.src->all(&f.adj, &f.ew);
   // coarse adjacency: summed edge weights, no self loops, neighbours in the order first met
   // (the matching breaks every tie by index, so only the breadth-first order on the coarsest
   // level needs them ascending; sort_rows does that there).  Coarse vertices are independent,
@@ -599,10 +609,10 @@ void ml_trim() {
 
 void ml_stage(MlScratch& sc, int n, int64_t nnz, int32_t** rp, int32_t** col, int32_t** w) {
   pinned_reserve(sc.h_rp, sc.cap_rp, (size_t)n + 1);
-  pinned_reserve(sc.h_col, sc.cap_col, (size_t)std::max<int64_t>(nnz, 1));
+  if (col) pinned_reserve(sc.h_col, sc.cap_col, (size_t)std::max<int64_t>(nnz, 1));
   if (w) pinned_reserve(sc.h_w, sc.cap_w, (size_t)std::max<int64_t>(nnz, 1));
   *rp = sc.h_rp;
-  *col = sc.h_col;
+  if (col) *col = sc.h_col;
   if (w) *w = sc.h_w;
 }
 
@@ -626,7 +636,7 @@ int32_t* ml_top_buffer(MlScratch& sc, int n) {
 void partition_multilevel(int n, const int32_t* row_ptr, const int32_t* col, int cap,
                           std::vector<int32_t>& core_ptr, std::vector<int32_t>& core_vtx,
                           MlStats* stats, const int32_t* ew, MlScratch* scr,
-                          const int32_t* top0, MlCoarseDevice* dev1) {
+                          const int32_t* top0, MlCoarseDevice* dev1, MlRows* rows0) {
   std::unique_ptr<MlLease> own;
   if (!scr) {
     own.reset(new MlLease);
@@ -636,7 +646,8 @@ void partition_multilevel(int n, const int32_t* row_ptr, const int32_t* col, int
   auto t0 = clk::now();
   sc.top1 = nullptr;  // set by this call's dev1 only
   if (sc.lv.empty()) sc.lv.resize(1);  // levels are addressed by index: lv may grow below
-  input_level(n, row_ptr, col, ew, sc.lv[0]);
+  input_level(n, row_ptr, col, ew, sc.lv[0], rows0 == nullptr);
+  sc.lv[0].src = rows0;
   const double ms_weights = ms_since(t0);
   t0 = clk::now();
   const int ccap = std::max(1, cap / 4);
@@ -653,6 +664,7 @@ void partition_multilevel(int n, const int32_t* row_ptr, const int32_t* col, int
   if (nl > 1 && !sc.lv[nl - 1].sorted) sort_rows(sc.lv[nl - 1]);
   const double ms_coarsen = ms_since(t0);
   t0 = clk::now();
+  if (!sc.lv[nl - 1].adj) rows0->all(&sc.lv[nl - 1].adj, &sc.lv[nl - 1].ew);
   std::vector<int32_t> part = grow_parts(sc.lv[nl - 1], cap);
   const double ms_grow = ms_since(t0);
   t0 = clk::now();
@@ -664,6 +676,7 @@ void partition_multilevel(int n, const int32_t* row_ptr, const int32_t* col, int
     part.swap(fine);
   }
   // the cost is a statistic (the device path gets the subgraph sizes from its halos anyway)
+  if (stats && !sc.lv[0].adj) rows0->all(&sc.lv[0].adj, &sc.lv[0].ew);
   const int64_t cost = stats ? subgraph_cost(sc.lv[0], part, np) : 0;
   const double ms_cost = ms_since(t0);
   emit_cores(n, part, np, core_ptr, core_vtx);

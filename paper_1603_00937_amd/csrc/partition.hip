@@ -7,8 +7,6 @@
 #include "lds_scan.h"
 
 #include <climits>
-#include <map>
-#include <mutex>
 
 namespace gbi {
 namespace {
@@ -285,53 +283,124 @@ __global__ void k_sort_cores(const int32_t* __restrict__ order, const int32_t* _
   }
 }
 
-// Common closed neighbours of the ends of every edge: w[e] = |row u ∩ row col[e]| for the rows
+// Rows of an ascending CSR graph as words: the entries of row v that share bits 5.. of their index
+// become one (index, mask, entries of the row before it), listed from rp[v] on, wcnt[v] of them.
+// Vertices close in space are close in number, so ~500 entries make ~75 words.  A wave per row.
+struct RowWord {
+  int32_t idx;
+  uint32_t mask;
+  int32_t before;
+};
+__global__ __launch_bounds__(kT) void k_row_words(int n, const int32_t* __restrict__ rp,
+                                                  const int32_t* __restrict__ col,
+                                                  RowWord* __restrict__ words,
+                                                  int32_t* __restrict__ wcnt) {
+  const int v = blockIdx.x * (kT / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (v >= n) return;
+  const int b = rp[v], end = rp[v + 1];
+  int m = 0;
+  for (int e0 = b; e0 < end; e0 += 64) {
+    const int e = e0 + lane;
+    const int q = e < end ? col[e] >> 5 : -1;
+    const bool head = e < end && (e == b || (col[e - 1] >> 5) != q);
+    const unsigned long long heads = __ballot(head);
+    if (head) {
+      uint32_t mask = 0u;
+      for (int f = e; f < end && (col[f] >> 5) == q; ++f) mask |= 1u << (col[f] & 31);
+      words[b + m + __popcll(heads & ((1ull << lane) - 1ull))] = RowWord{q, mask, e - b};
+    }
+    m += __popcll(heads);
+  }
+  if (lane == 0) wcnt[v] = m;
+}
+
+// Common closed neighbours of the ends of every edge: w[e] = |row u and row col[e]| for the rows
 // of a symmetric CSR graph that holds its self loops (so each row is the closed neighbourhood).
-// One workgroup per vertex u: row u as a bitmap in LDS, then one wave per neighbour v >= u
-// counting the entries of row v found in it; the count is symmetric, so the wave also writes
-// it at the entry of u in row v, which it meets while scanning row v (each entry has one
-// writer).  *missing receives the smallest u whose row lacks u (it is left as it was when
-// every row holds its self loop).
+// One workgroup per vertex u, neighbours in number on one XCD: row u as a bitmap in LDS, then 16 lanes per neighbour
+// v >= u count row v's words against it; the count is symmetric, so they also write it at the
+// entry of u in row v, whose place they meet among the words (each entry has one writer).  *missing receives the smallest u whose row lacks u
+// (it is left as it was when every row holds its self loop).
+// Row v entry by entry against the bitmap, a wave per neighbour, took 1.84 ms at N = 18000 (535
+// entries a row) and 6.8 ms at N = 100000; words take 0.17 + 0.30 and 0.69 + 1.02 ms.
+constexpr int kNbBatch = 512;
+template <bool BIG>
 __global__ __launch_bounds__(kT) void k_common_nb(int n, const int32_t* __restrict__ rp,
                                                   const int32_t* __restrict__ col,
+                                                  const RowWord* __restrict__ words,
+                                                  const int32_t* __restrict__ wcnt,
                                                   int32_t* __restrict__ w,
                                                   int32_t* __restrict__ missing) {
-  extern __shared__ uint32_t bits[];
-  const int u = blockIdx.x;
+  extern __shared__ __align__(16) unsigned char smem[];
   const int nw = (n + 31) >> 5;
+  uint32_t* bits = reinterpret_cast<uint32_t*>(smem);
+  int4* nb = reinterpret_cast<int4*>(smem + (((size_t)nw * 4 + 15) & ~(size_t)15));
+  int32_t* listed = reinterpret_cast<int32_t*>(nb + kNbBatch);
+  const int u = xcd_run(blockIdx.x, n);
+  if (u >= n) return;
   for (int i = threadIdx.x; i < nw; i += kT) bits[i] = 0u;
   __syncthreads();
   const int b = rp[u], e_end = rp[u + 1];
-  for (int e = b + threadIdx.x; e < e_end; e += kT) {
-    const int x = col[e];
-    atomicOr(&bits[x >> 5], 1u << (x & 31));
-  }
+  for (int i = threadIdx.x; i < wcnt[u]; i += kT) bits[words[b + i].idx] = words[b + i].mask;
   __syncthreads();
   if (threadIdx.x == 0 && !((bits[u >> 5] >> (u & 31)) & 1u)) atomicMin(missing, u);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int e = b + wave; e < e_end; e += kT / 64) {
-    const int v = col[e];
-    if (v < u) continue;  // wave-uniform: workgroup v writes this entry
-    int c = 0, pos = -1;
-    const int f1 = rp[v + 1];
-    for (int f = rp[v] + lane; f < f1; f += 4 * 64) {  // four loads in flight per lane
-      int x[4];
+  // the neighbours v >= u with where their words lie, a batch at a time (workgroup v writes the
+  // entries of the others), so that the counting below waits for one load per neighbour and not
+  // for a chain of three.  BIG: the bitmap leaves no LDS for the list.
+  const int l16 = threadIdx.x & 15, team = threadIdx.x >> 4;
+  const int uq = u >> 5;
+  const uint32_t below = (1u << (u & 31)) - 1u, ubit = 1u << (u & 31);
+  constexpr int TEAMS = kT / 16;
+  for (int e0 = b; e0 < e_end; e0 += kNbBatch) {
+    int count = min(kNbBatch, e_end - e0);
+    if (!BIG) {
+      __syncthreads();
+      if (threadIdx.x == 0) *listed = 0;
+      __syncthreads();
+      for (int e = e0 + threadIdx.x; e < e0 + count; e += kT) {
+        const int v = col[e];
+        if (v >= u) nb[atomicAdd(listed, 1)] = make_int4(v, rp[v], wcnt[v], e);
+      }
+      __syncthreads();
+      count = *listed;
+    }
+    auto neighbour = [&](int t) {
+      if (t >= count) return make_int4(-1, 0, 0, 0);
+      if (!BIG) return nb[t];
+      const int v = col[e0 + t];
+      return v >= u ? make_int4(v, rp[v], wcnt[v], e0 + t) : make_int4(-1, 0, 0, 0);
+    };
+    for (int t = team; t < count; t += 2 * TEAMS) {  // two neighbours per 16 lanes
+      const int4 q[2] = {neighbour(t), neighbour(t + TEAMS)};
+      int c[2] = {0, 0}, pos[2] = {-1, -1};
+      for (int i0 = 0; i0 < max(q[0].z, q[1].z); i0 += 64) {
+        RowWord x[2][4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) x[i] = f + 64 * i < f1 ? col[f + 64 * i] : -1;
+        for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (x[i] >= 0) {
-          c += (bits[x[i] >> 5] >> (x[i] & 31)) & 1u;
-          if (x[i] == u) pos = f + 64 * i;
+          for (int k = 0; k < 4; ++k) {
+            const int i = i0 + 16 * k + l16;
+            x[h][k] = i < q[h].z ? words[q[h].y + i] : RowWord{0, 0u, 0};
+          }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            c[h] += __popc(x[h][k].mask & bits[x[h][k].idx]);
+            if (x[h][k].idx == uq && (x[h][k].mask & ubit))
+              pos[h] = q[h].y + x[h][k].before + __popc(x[h][k].mask & below);
+          }
+      }
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        for (int o = 8; o > 0; o >>= 1) {
+          c[h] += __shfl_xor(c[h], o, 16);
+          pos[h] = max(pos[h], __shfl_xor(pos[h], o, 16));
         }
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-      c += __shfl_down(c, off, 64);
-      pos = max(pos, __shfl_down(pos, off, 64));
-    }
-    if (lane == 0) {
-      w[e] = c;
-      if (v != u && pos >= 0) w[pos] = c;  // pos >= 0 in a symmetric graph
+        if (l16 == 0 && q[h].x >= u) {
+          w[q[h].w] = c[h];
+          if (q[h].x != u && pos[h] >= 0) w[pos[h]] = c[h];  // pos >= 0 in a symmetric graph
+        }
+      }
     }
   }
 }
@@ -552,34 +621,38 @@ void partition_from_cores(const Csr& g, const std::vector<int32_t>& core_ptr,
   finish_partition(g, P, s);
 }
 
-// A second stream per device for the copies that overlap the weights kernel (created on first
-// use with the default priority and kept for the life of the process).
-static hipStream_t side_stream() {
-  static std::mutex mu;
-  static std::map<int, hipStream_t> streams;
-  int dev = 0;
-  GB_HIP(hipGetDevice(&dev));
-  std::lock_guard<std::mutex> lk(mu);
-  auto it = streams.find(dev);
-  if (it != streams.end()) return it->second;
-  hipStream_t st = nullptr;
-  GB_HIP(hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
-  streams[dev] = st;
-  return st;
-}
+// The input graph's rows on demand (one row is two small copies and a wait, ~15 us; the whole
+// graph with its weights would be 290 MB at N = 100000, 6 ms over PCIe).
+class DevRows : public MlRows {
+ public:
+  DevRows(const Csr& g, const int32_t* dw, const int32_t* rp, MlScratch& sc, hipStream_t s)
+      : g_(g), dw_(dw), rp_(rp), sc_(sc), s_(s) {}
+  void row(int v, const int32_t** adj, const int32_t** ew) override {
+    const size_t b = rp_[v], m = rp_[v + 1] - rp_[v];
+    if (buf_.size() < 2 * m) buf_.resize(2 * m);
+    fetch(buf_.data(), buf_.data() + m, b, m);
+    *adj = buf_.data();
+    *ew = buf_.data() + m;
+  }
+  void all(const int32_t** adj, const int32_t** ew) override {
+    int32_t *rp, *col, *w;
+    ml_stage(sc_, g_.n, g_.nnz, &rp, &col, &w);
+    fetch(col, w, 0, (size_t)g_.nnz);
+    *adj = col;
+    *ew = w;
+  }
 
-struct SideCopy {  // an event that orders the side stream after the caller's stream
-  hipEvent_t ev = nullptr;
-  hipStream_t cs = nullptr;
-  SideCopy(hipStream_t s) : cs(side_stream()) {
-    GB_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
-    GB_HIP(hipEventRecord(ev, s));
-    GB_HIP(hipStreamWaitEvent(cs, ev, 0));
+ private:
+  void fetch(int32_t* col, int32_t* w, size_t b, size_t m) {
+    GB_HIP(hipMemcpyAsync(col, g_.col.get() + b, m * 4, hipMemcpyDeviceToHost, s_));
+    GB_HIP(hipMemcpyAsync(w, dw_ + b, m * 4, hipMemcpyDeviceToHost, s_));
+    GB_HIP(hipStreamSynchronize(s_));
   }
-  ~SideCopy() {
-    (void)hipStreamSynchronize(cs);  // nothing of the copies outlives the call
-    (void)hipEventDestroy(ev);
-  }
+  const Csr& g_;
+  const int32_t *dw_, *rp_;
+  MlScratch& sc_;
+  hipStream_t s_;
+  std::vector<int32_t> buf_;
 };
 
 // Coarse levels on the device (k_coarse_rows, k_top_coarse): the first from the input graph and
@@ -666,7 +739,7 @@ void partition_multilevel_dev(const Csr& g, int32_t core_size, Part& P, hipStrea
   const int n = g.n;
   std::vector<int32_t> cp, cv;
   MlLease lease;  // pinned staging and coarse levels kept from earlier calls
-  int32_t *rp, *col, *w;
+  int32_t *rp, *col;
   if (prev) {
     // on-the-fly update: the previous cores carried to this graph (no weights needed)
     if (prev->n != n) fail(GB_ESHAPE, "previous partition has %d vertices, graph %d", prev->n, n);
@@ -681,34 +754,40 @@ void partition_multilevel_dev(const Csr& g, int32_t core_size, Part& P, hipStrea
     partition_from_cores(g, cp, cv, P, s);
     return;
   }
-  // edge weights on the device (the graphs built here hold every self loop), the rest on the
-  // host
-  ml_stage(*lease.p, n, g.nnz, &rp, &col, &w);
+  // edge weights and candidate lists on the device (the graphs built here hold every self loop),
+  // the matching on the host, which needs little more than the lists
+  ml_stage(*lease.p, n, g.nnz, &rp, nullptr, nullptr);
   const size_t lds = (size_t)((n + 31) >> 5) * 4;
   if (lds > 160 * 1024) fail(GB_EUNSUPPORTED, "multilevel: n = %d too large for one LDS bitmap", n);
-  DBuf<int32_t> dw(std::max<int64_t>(g.nnz, 1), s), dmiss(1, s);
-  // the graph itself goes to the host on the side stream while the weights are computed
-  SideCopy side(s);
-  GB_HIP(hipMemcpyAsync(rp, g.row_ptr.get(), (n + 1) * 4, hipMemcpyDeviceToHost, side.cs));
-  GB_HIP(hipMemcpyAsync(col, g.col.get(), g.nnz * 4, hipMemcpyDeviceToHost, side.cs));
+  DBuf<int32_t> dw(std::max<int64_t>(g.nnz, 1), s), dmiss(1, s), dwc(n, s);
+  DBuf<RowWord> dwords(std::max<int64_t>(g.nnz, 1), s);
   int32_t miss = n;  // no vertex lacks its self loop
   GB_HIP(hipMemcpyAsync(dmiss.get(), &miss, 4, hipMemcpyHostToDevice, s));
-  hipLaunchKernelGGL(k_common_nb, dim3(n), dim3(kT), lds, s, n, g.row_ptr.get(), g.col.get(),
-                     dw.get(), dmiss.get());
+  GB_HIP(hipMemcpyAsync(rp, g.row_ptr.get(), (n + 1) * 4, hipMemcpyDeviceToHost, s));
+  hipLaunchKernelGGL(k_row_words, dim3((n + kT / 64 - 1) / (kT / 64)), dim3(kT), 0, s, n,
+                     g.row_ptr.get(), g.col.get(), dwords.get(), dwc.get());
+  GB_LAUNCH_CHECK();
+  const size_t lds_list = lds + 16 + kNbBatch * sizeof(int4) + 16;
+  auto count = [&](auto kern, size_t bytes) {
+    hipLaunchKernelGGL(kern, dim3(xcd_grid(n)), dim3(kT), bytes, s, n, g.row_ptr.get(),
+                       g.col.get(), dwords.get(), dwc.get(), dw.get(), dmiss.get());
+  };
+  if (lds_list <= 160 * 1024) count(k_common_nb<false>, lds_list);
+  else count(k_common_nb<true>, lds);
   GB_LAUNCH_CHECK();
   DBuf<int32_t> dtop((size_t)n * kMlTop, s);
   hipLaunchKernelGGL(k_top_nb, dim3((n + kT / 64 - 1) / (kT / 64)), dim3(kT), 0, s, n,
                      g.row_ptr.get(), g.col.get(), dw.get(), dtop.get());
   GB_LAUNCH_CHECK();
   int32_t* top = ml_top_buffer(*lease.p, n);  // read by the matching of the input level
-  GB_HIP(hipMemcpyAsync(w, dw.get(), g.nnz * 4, hipMemcpyDeviceToHost, s));
   GB_HIP(hipMemcpyAsync(top, dtop.get(), (size_t)n * kMlTop * 4, hipMemcpyDeviceToHost, s));
   GB_HIP(hipMemcpyAsync(&miss, dmiss.get(), 4, hipMemcpyDeviceToHost, s));
-  GB_HIP(hipStreamSynchronize(side.cs));
   GB_HIP(hipStreamSynchronize(s));
   if (miss < n) fail(GB_EINVAL, "multilevel: vertex %d has no self loop", miss);
   DevCoarse dev1(g, dw.get(), *lease.p, s);
-  partition_multilevel(n, rp, col, core_size, cp, cv, stats, w, lease.p, top, &dev1);
+  DevRows rows(g, dw.get(), rp, *lease.p, s);
+  partition_multilevel(n, rp, nullptr, core_size, cp, cv, stats, nullptr, lease.p, top, &dev1,
+                       &rows);
   partition_from_cores(g, cp, cv, P, s);
 }
 
