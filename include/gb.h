@@ -287,8 +287,8 @@ typedef struct {
                               *    launch per step over every subgraph; the stop flag, step   *
                               *    counter, branch and step records stay on the device, every *
                               *    launch reads the branch there and returns at once after    *
-                              *    the stop, so the host enqueues 32 steps (then 8 at a time) *
-                              *    without waiting for any decision;                          *
+                              *    the stop, so the host keeps four steps queued beyond the   *
+                              *    last decision it has seen and waits for none;              *
                               * 1: one launch per subgraph per step, decided on the host     *
                               *    (the baseline);                                            *
                               * 2: as 0 with two steps captured in a hipGraph and replayed;   *

@@ -7,6 +7,7 @@
 // refinement) such buffers ping-pong.  Core vertices are the first k_s rows of each block.
 #include "internal.h"
 
+#include <chrono>
 #include <cmath>
 #include <cstring>
 #include <cstdlib>
@@ -15,6 +16,7 @@
 #include <map>
 #include <mutex>
 #include <numeric>
+#include <thread>
 #include <type_traits>
 
 #pragma clang fp contract(off)
@@ -873,17 +875,18 @@ __global__ __launch_bounds__(kT, 2) void k_symm_mm_split_il(const float* __restr
 struct StepRec {
   double t1, t2, e, margin;
   int32_t b, stop, pad0, pad1;
+  // device-driven loop: the wall clock (wall_clock64) when the step's trace kernel began and
+  // when its decision was made; the square in between ran from `out` to the next step's `in`
+  long long in, out;
 };
 
+// the two partial sums of subgraph blockIdx.x (valid in thread 0)
 template <typename T>
-__global__ __launch_bounds__(kT) void k_trace_rows(const T* __restrict__ X,
-                                                   const int64_t* __restrict__ offs,
-                                                   const int32_t* __restrict__ npad,
-                                                   const int32_t* __restrict__ core_ptr,
-                                                   double* __restrict__ part,
-                                                   const int32_t* __restrict__ stopped,
-                                                   double s1, double s2) {
-  if (stopped && *stopped) return;
+__device__ __forceinline__ void trace_block(const T* __restrict__ X,
+                                            const int64_t* __restrict__ offs,
+                                            const int32_t* __restrict__ npad,
+                                            const int32_t* __restrict__ core_ptr, double* sum1,
+                                            double* sum2) {
   constexpr int V = 16 / sizeof(T);  // values per 16-byte load
   typedef T vec __attribute__((ext_vector_type(V)));
   __shared__ double r1[kT], r2[kT];
@@ -927,18 +930,40 @@ __global__ __launch_bounds__(kT) void k_trace_rows(const T* __restrict__ X,
     }
     __syncthreads();
   }
+  *sum1 = r1[0];
+  *sum2 = r2[0];
+}
+
+template <typename T>
+__global__ __launch_bounds__(kT) void k_trace_rows(const T* __restrict__ X,
+                                                   const int64_t* __restrict__ offs,
+                                                   const int32_t* __restrict__ npad,
+                                                   const int32_t* __restrict__ core_ptr,
+                                                   double* __restrict__ part,
+                                                   const int32_t* __restrict__ stopped,
+                                                   double s1, double s2) {
+  if (stopped && *stopped) return;
+  double p1, p2;
+  trace_block(X, offs, npad, core_ptr, &p1, &p2);
   if (threadIdx.x == 0) {
-    part[2 * s] = r1[0] * s1;
-    part[2 * s + 1] = r2[0] * s2;
+    part[2 * blockIdx.x] = p1 * s1;
+    part[2 * blockIdx.x + 1] = p2 * s2;
   }
 }
 
+// FRESH: the partials were written by other workgroups of this launch (read past the XCD's L2)
+template <bool FRESH = false>
 __device__ void sum_partials(const double* __restrict__ part, int n_sub, double* t1, double* t2) {
   __shared__ double r1[kT], r2[kT];
   double p1 = 0.0, p2 = 0.0;
   for (int s = threadIdx.x; s < n_sub; s += kT) {
-    p1 += part[2 * s];
-    p2 += part[2 * s + 1];
+    if (FRESH) {
+      p1 += __hip_atomic_load(&part[2 * s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      p2 += __hip_atomic_load(&part[2 * s + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+      p1 += part[2 * s];
+      p2 += part[2 * s + 1];
+    }
   }
   r1[threadIdx.x] = p1;
   r2[threadIdx.x] = p2;
@@ -991,9 +1016,14 @@ __global__ __launch_bounds__(kT) void k_decide(const double* __restrict__ part, 
 struct LoopState {
   int32_t it, stopped, max_iter, n_forced;  // n_forced < 0: choose by the trace rule
   int32_t stag, cur_b, it0;  // it0: first step of this loop (stagnation looks back 2 steps)
+  int32_t ticket;  // workgroups of the step's trace kernel that are done
   double n_occ, tol, e_hand;  // e_hand: stop once the traces agree to this (0: never)
   uint8_t forced[128];
   StepRec recs[128];
+};
+// What the host sees of it while it runs (pinned memory): decisions made, and the stop.
+struct LoopProgress {
+  int32_t it, stopped;
 };
 // The loop's parameters, passed by value to the kernel that sets up LoopState.
 struct LoopInit {
@@ -1002,11 +1032,37 @@ struct LoopInit {
   uint8_t forced[128];
 };
 
-__global__ __launch_bounds__(kT) void k_decide_dev(const double* __restrict__ part, int n_sub,
-                                                   LoopState* __restrict__ st) {
+// One launch per decision: every workgroup leaves its subgraph's two partial sums, and the last
+// one to do so adds them up (in the fixed order of the kernels above) and decides.  (A launch of
+// its own for the decision cost 4 us a step and its gap.)
+template <typename T>
+__global__ __launch_bounds__(kT) void k_trace_step(const T* __restrict__ X,
+                                                   const int64_t* __restrict__ offs,
+                                                   const int32_t* __restrict__ npad,
+                                                   const int32_t* __restrict__ core_ptr,
+                                                   double* __restrict__ part, double s1, double s2,
+                                                   LoopState* __restrict__ st,
+                                                   LoopProgress* __restrict__ seen) {
+  __shared__ int last;
+  // read by every workgroup before its ticket, written after the last one's
   if (st->stopped) return;
+  const long long began = wall_clock64();
+  double p1, p2;
+  trace_block(X, offs, npad, core_ptr, &p1, &p2);
+  if (threadIdx.x == 0) {
+    __hip_atomic_store(&part[2 * blockIdx.x], p1 * s1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&part[2 * blockIdx.x + 1], p2 * s2, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+    if (blockIdx.x == 0)
+      __hip_atomic_store(&st->recs[st->it].in, began, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int t = __hip_atomic_fetch_add(&st->ticket, 1, __ATOMIC_ACQ_REL,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+    last = t == (int)gridDim.x - 1;
+  }
+  __syncthreads();
+  if (!last) return;
   double t1, t2;
-  sum_partials(part, n_sub, &t1, &t2);
+  sum_partials<true>(part, gridDim.x, &t1, &t2);
   if (threadIdx.x == 0) {
     const int it = st->it;
     const double n_occ = st->n_occ;
@@ -1036,10 +1092,19 @@ __global__ __launch_bounds__(kT) void k_decide_dev(const double* __restrict__ pa
     } else {
       q.b = dsq < dlin ? 0 : 1;
     }
+    q.in = __hip_atomic_load(&st->recs[it].in, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    q.out = wall_clock64();
     st->recs[it] = q;
     st->cur_b = q.b;
+    st->ticket = 0;
     if (q.stop) st->stopped = 1;
     else st->it = it + 1;
+    if (seen) {
+      if (q.stop)
+        __hip_atomic_store(&seen->stopped, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      else
+        __hip_atomic_store(&seen->it, it + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
   }
 }
 
@@ -1369,7 +1434,7 @@ __global__ void k_vs_fill(const int32_t* __restrict__ sub_ptr, const int32_t* __
 }
 // The lists come in the order of the atomics; each vertex's is put in ascending order of the
 // subgraphs (all different) by rank, a wave per vertex: a lane counts the entries below its own.
-// (Sorted in place by a thread per vertex it took 423 us for 1800 lists of ~42; 12 us this way.)
+// (Sorted in place by a thread per vertex it took 423 us for 1800 lists of ~42; 6 us this way.)
 __global__ __launch_bounds__(kT) void k_vs_sort(int n, const int32_t* __restrict__ vs_ptr,
                                                 const int32_t* __restrict__ sub,
                                                 const int32_t* __restrict__ loc,
@@ -1668,17 +1733,48 @@ void launch_plan_square_f64(const double* X, double* S, const Plan& pl, const in
   launch_square<double>(X, S, tiles, pl.lg, offs, s, lin);
 }
 
+// Idle objects of a device, shared by the process's threads: no more than were ever in use at
+// once.  (Creating and destroying the events of a call cost 20 us.)
+template <typename H>
+class IdlePool {
+ public:
+  bool take(int dev, H* h) {
+    std::lock_guard<std::mutex> g(m_);
+    auto& v = idle_[dev];
+    if (v.empty()) return false;
+    *h = v.back();
+    v.pop_back();
+    return true;
+  }
+  void give(int dev, H h) {
+    std::lock_guard<std::mutex> g(m_);
+    idle_[dev].push_back(h);
+  }
+
+ private:
+  std::mutex m_;
+  std::map<int, std::vector<H>> idle_;
+};
+
 struct Timer {
   hipEvent_t a = nullptr, b = nullptr;
-  explicit Timer() {
-    GB_HIP(hipEventCreate(&a));
-    GB_HIP(hipEventCreate(&b));
+  int dev = 0;
+  Timer() {
+    GB_HIP(hipGetDevice(&dev));
+    for (hipEvent_t* e : {&a, &b})
+      if (!pool().take(dev, e)) GB_HIP(hipEventCreate(e));
   }
   Timer(const Timer&) = delete;
   Timer& operator=(const Timer&) = delete;
   ~Timer() {
-    if (a) (void)hipEventDestroy(a);
-    if (b) (void)hipEventDestroy(b);
+    for (hipEvent_t e : {a, b})
+      if (e) pool().give(dev, e);
+  }
+
+ private:
+  static IdlePool<hipEvent_t>& pool() {
+    static auto* p = new IdlePool<hipEvent_t>;  // outlives the runtime's own teardown
+    return *p;
   }
 };
 
@@ -2037,19 +2133,33 @@ int sp2_loop(T*& X, T*& S, const Plan& pl, const DBuf<int4>& tiles, const DBuf<i
   }
 }
 
-// Events of the device-driven loop (one pair per enqueued step), kept per thread and device for
-// the life of the process.
-std::vector<hipEvent_t>& step_events(size_t need) {
-  thread_local std::map<int, std::vector<hipEvent_t>> pool;
+// The progress words of one device-driven loop.
+struct ProgressLease {
+  LoopProgress* p = nullptr;
+  int dev = 0;
+  ProgressLease() {
+    GB_HIP(hipGetDevice(&dev));
+    if (!pool().take(dev, &p))
+      GB_HIP(hipHostMalloc((void**)&p, sizeof(LoopProgress), hipHostMallocDefault));
+  }
+  ProgressLease(const ProgressLease&) = delete;
+  ProgressLease& operator=(const ProgressLease&) = delete;
+  ~ProgressLease() { pool().give(dev, p); }
+
+ private:
+  static IdlePool<LoopProgress*>& pool() {
+    static auto* q = new IdlePool<LoopProgress*>;
+    return *q;
+  }
+};
+
+double wall_clock_khz() {
+  thread_local std::map<int, int> rate;
   int dev = 0;
   GB_HIP(hipGetDevice(&dev));
-  auto& v = pool[dev];
-  while (v.size() < need) {
-    hipEvent_t e;
-    GB_HIP(hipEventCreate(&e));
-    v.push_back(e);
-  }
-  return v;
+  int& r = rate[dev];
+  if (!r) GB_HIP(hipDeviceGetAttribute(&r, hipDeviceAttributeWallClockRate, dev));
+  return r;
 }
 
 __global__ void k_loop_init(LoopState* __restrict__ st, LoopInit in) {
@@ -2063,24 +2173,25 @@ __global__ void k_loop_init(LoopState* __restrict__ st, LoopInit in) {
   st->n_occ = in.n_occ;
   st->tol = in.tol;
   st->e_hand = in.e_hand;
+  st->ticket = 0;
   for (int i = 0; i < 128; ++i) st->forced[i] = in.forced[i];
 }
 
 // Device-driven SP2 loop (launch modes 0 and 2): the stop flag, the step counter, the branch
 // and the step records live on the device, each squaring launch reads the branch there, and
 // every kernel of a step returns at once after the stop, so steps are enqueued without waiting
-// for any decision.  The host enqueues the first kFirst steps (or every step the loop can still
-// take, if fewer), then reads the loop state once; only an expansion longer than that costs one
-// more read per kMore further steps.  Mode 0 enqueues the kernels on the stream (a pair of
-// events around every square gives its duration); mode 2 captures two steps, one per buffer
-// parity, in a hipGraph and replays it.
+// for any decision.  Mode 0 keeps kAhead steps in the queue beyond the last decision, which the
+// kernels post to pinned memory (32 steps enqueued at once left 15 empty ones behind the stop, 20
+// us each at N = 2050, and an event before and after every square: 45 us a step at 256 orbitals,
+// where the square takes 11).  Mode 2 captures two steps, one per buffer parity, in a hipGraph and
+// replays it, 32 steps and then 8 at a time, reading the loop state in between.
 template <typename T>
 int sp2_loop_dev(T*& X, T*& S, const Plan& pl, const DBuf<int4>& tiles, const DBuf<int64_t>& offs,
                  const DBuf<int32_t>& npad, const Part& P, double n_occ, double tol, int max_iter,
                  const uint8_t* branch_in, int n_branch_in, bool stagnation_stop, int it0,
                  gb_sp2_stats& st, hipStream_t s, int* stop_kind, int planes, bool graph,
                  double e_hand = 0.0) {
-  constexpr int kFirst = 32, kMore = 8;
+  constexpr int kFirst = 32, kMore = 8, kAhead = 4;
   // index of the last decision the loop can reach: it stops there at the latest
   const int last = branch_in ? std::min(n_branch_in, 127) : std::min(max_iter, 127);
   if (last < it0) fail(GB_EINVAL, "no SP2 step left (first step %d, last %d)", it0, last);
@@ -2103,17 +2214,15 @@ int sp2_loop_dev(T*& X, T*& S, const Plan& pl, const DBuf<int4>& tiles, const DB
   GB_LAUNCH_CHECK();
   const int32_t* stopped = &d.get()->stopped;
   const int32_t* cur_b = &d.get()->cur_b;
-  auto& ev = step_events(2 * (size_t)max_dec);
-  auto enqueue = [&](hipStream_t q, int k, bool timed) {  // step k of the loop (0-based)
+  std::unique_ptr<ProgressLease> progress(graph ? nullptr : new ProgressLease);
+  LoopProgress* const seen = graph ? nullptr : progress->p;
+  auto enqueue = [&](hipStream_t q, int k) {  // step k of the loop (0-based)
     T* A = (k & 1) ? S : X;
     T* B = (k & 1) ? X : S;
-    hipLaunchKernelGGL(k_trace_rows<T>, dim3(pl.n_sub), dim3(kT), 0, q, A, offs.get(),
-                       npad.get(), P.core_ptr.get(), part.get(), stopped, ts1, ts2);
-    hipLaunchKernelGGL(k_decide_dev, dim3(1), dim3(kT), 0, q, part.get(), pl.n_sub, d.get());
+    hipLaunchKernelGGL(k_trace_step<T>, dim3(pl.n_sub), dim3(kT), 0, q, A, offs.get(), npad.get(),
+                       P.core_ptr.get(), part.get(), ts1, ts2, d.get(), seen);
     GB_LAUNCH_CHECK();
-    if (timed) GB_HIP(hipEventRecord(ev[2 * k], q));
     launch_step<T>(A, B, pl, tiles.get(), offs.get(), q, planes, 0, false, stopped, cur_b);
-    if (timed) GB_HIP(hipEventRecord(ev[2 * k + 1], q));
   };
   hipStream_t cs = nullptr;
   hipGraph_t gr = nullptr;
@@ -2131,35 +2240,57 @@ int sp2_loop_dev(T*& X, T*& S, const Plan& pl, const DBuf<int4>& tiles, const DB
   if (graph) {
     GB_HIP(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
     GB_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-    enqueue(cs, 0, false);
-    enqueue(cs, 1, false);
+    enqueue(cs, 0);
+    enqueue(cs, 1);
     GB_HIP(hipStreamEndCapture(cs, &gr));
     GB_HIP(hipGraphInstantiate(&exec, gr, nullptr, nullptr, 0));
   }
   LoopState h;
   int queued = 0;
+  if (seen) {
+    auto word = [](int32_t& w) { return __atomic_load_n(&w, __ATOMIC_RELAXED); };
+    __atomic_store_n(&seen->it, it0, __ATOMIC_RELAXED);
+    __atomic_store_n(&seen->stopped, 0, __ATOMIC_RELAXED);
+    int idle = 0;  // looks since the last step was enqueued
+    while (queued < max_dec && !word(seen->stopped)) {
+      if (queued < word(seen->it) - it0 + kAhead) {
+        enqueue(s, queued++);
+        idle = 0;
+        continue;
+      }
+      // a step of 0.1 ms or less is waited for awake; longer ones leave time to sleep, since the
+      // queue holds several (and now and then the stream is asked whether it still runs)
+      if (++idle <= (1 << 15)) continue;
+      std::this_thread::sleep_for(std::chrono::microseconds(20));
+      if (idle % 64 == 0) {
+        const hipError_t e = hipStreamQuery(s);
+        if (e == hipSuccess) break;  // nothing is left in the queue: the state tells
+        if (e != hipErrorNotReady) GB_HIP(e);
+      }
+    }
+  }
   for (;;) {
-    const int batch = std::min(queued == 0 ? kFirst : kMore, max_dec - queued);
     if (graph) {
+      const int batch = std::min(queued == 0 ? kFirst : kMore, max_dec - queued);
       const int pairs = (batch + 1) / 2;  // the graph holds two steps
       for (int r = 0; r < pairs; ++r) GB_HIP(hipGraphLaunch(exec, s));
       queued += 2 * pairs;
-    } else {
-      for (int k = queued; k < queued + batch; ++k) enqueue(s, k, true);
-      queued += batch;
     }
     GB_HIP(hipMemcpyAsync(&h, d.get(), sizeof(h), hipMemcpyDeviceToHost, s));
     GB_HIP(hipStreamSynchronize(s));
     if (h.stopped) break;
     if (queued >= max_dec) fail(GB_EHIP, "device-driven SP2 loop did not stop");
+    if (!graph)
+      for (int k = 0; k < kMore && queued < max_dec; ++k) enqueue(s, queued++);
   }
   const int it_stop = h.it;
   for (int it = it0; it <= it_stop && it < 128; ++it)
     record_step(st, it, h.recs[it], it < it_stop, branch_in == nullptr, n_occ);
   const int n_sq = it_stop - it0;
-  float ms = 0.f;
-  if (!graph)
-    for (int k = 0; k < n_sq; ++k) ms += elapsed(ev[2 * k], ev[2 * k + 1]);
+  double ticks = 0.0;
+  for (int it = it0; it < it_stop && it + 1 < 128; ++it)
+    ticks += (double)std::max(0ll, h.recs[it + 1].in - h.recs[it].out);
+  const float ms = graph ? 0.f : (float)(ticks / wall_clock_khz());
   if (std::is_same<T, float>::value) {
     st.n_square_lo += n_sq;
     st.ms_square_lo += ms;
