@@ -1,0 +1,46 @@
+"""Blocks whose rows end anywhere in a chunk of the contraction, a wave's block or a tile: the
+squares multiply no padding, and write it as zeros, for every kernel variant.  One block holds
+the whole matrix, so D is the projector of the dense eigenproblem: the stop test leaves
+sum lambda (1 - lambda) <= 1e-10 N / 1024 over the core, which bounds the FP64 error of an entry by
+twice that and the rounding of some twenty squares.  The low precisions keep the rounding of up to 25
+squares of values of 22 bits or more, which adds up as sqrt(n) 2^-22 each (a lost chunk of the
+contraction changes entries by 1e-2), and the tilings of a split square agree bit for bit."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _dense(n):
+    rng = np.random.default_rng(n)
+    q, _ = np.linalg.qr(rng.standard_normal((n, n)))
+    occ = n // 3
+    e = np.concatenate([-1 + 0.5 * rng.random(occ), 0.5 + 0.5 * rng.random(n - occ)])
+    h = (q * e) @ q.T
+    return 0.5 * (h + h.T), q[:, :occ] @ q[:, :occ].T, occ
+
+
+@pytest.mark.parametrize("n", [3, 31, 33, 64, 79, 81, 96, 97, 129, 191, 300])
+@pytest.mark.parametrize("precision,policies", [("fp64", (0, 1, 2, 4, 5)), ("fp32", (0, 1, 2, 4, 5)),
+                                                ("fp16x3", (1, 2, 6, 7)), ("bf16x6", (1, 2))])
+def test_rows_end_anywhere(n, precision, policies):
+    import torch
+    import paper_1603_00937_amd as gb
+    h, d, occ = _dense(n)
+    hc = torch.arange(n, dtype=torch.int32).repeat(n, 1).cuda()
+    hv = torch.from_numpy(h).cuda()
+    bar = 2e-10 * n / 1024 + 1e-13 * n if precision == "fp64" else 25 * n ** 0.5 * 2.0 ** -22
+    first = None
+    for policy in policies:
+        cols, got, st = gb.density(hc, hv, occ, 1e-9, core_size=n, precision=precision,
+                                   tile_policy=policy)
+        assert st["converged"]
+        full = np.zeros((n, n))
+        c, v = cols.cpu().numpy(), got.cpu().numpy().astype(np.float64)
+        for i in range(n):
+            ok = (c[i] >= 0) & (c[i] < n)
+            full[i, c[i][ok]] = v[i][ok]
+        assert np.abs(full - d).max() <= bar, (policy, np.abs(full - d).max())
+        first = full if first is None else first
+        if precision in ("fp16x3", "bf16x6"):
+            assert np.array_equal(full, first)
