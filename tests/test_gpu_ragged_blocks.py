@@ -44,3 +44,29 @@ def test_rows_end_anywhere(n, precision, policies):
         if policy in (6, 7):
             assert np.array_equal(full, last)
         last = full
+
+
+@pytest.mark.parametrize("sizes", [(300,), (40, 300), (200, 130, 70), (64,) * 9, (500, 20, 20)])
+def test_few_blocks_over_all_queues(sizes):
+    """Launch orders that cut blocks across XCDs give the bits of the plain order."""
+    import torch
+    import paper_1603_00937_amd as gb
+    n, w = sum(sizes), max(sizes)
+    hc = torch.full((n, w), -1, dtype=torch.int32)
+    hv = torch.zeros((n, w), dtype=torch.float64)
+    occ, at = 0, 0
+    for b in sizes:
+        h, _, k = _dense(b)
+        hc[at:at + b, :b] = torch.arange(at, at + b, dtype=torch.int32)
+        hv[at:at + b, :b] = torch.from_numpy(h)
+        occ, at = occ + k, at + b
+    hc, hv = hc.cuda(), hv.cuda()
+    part = gb.partition(gb.build_graph(hc, hv, 1e-9), 20)
+    got = []
+    for order in ("plain", "xcd"):
+        for policy in ("64r", 2, 1):
+            _, d, st = gb.density(hc, hv, occ, 1e-9, partition=part, tile_order=order,
+                                  tile_policy=policy)
+            assert st["converged"]
+            got.append(torch.nan_to_num(d).cpu())
+    assert all(torch.equal(got[i], got[i + 3]) for i in range(3))
