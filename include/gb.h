@@ -297,14 +297,16 @@ typedef struct {
   int32_t tile_policy;       /* kernel variant of the squares: 0 = split squares autotuned   *
                               * per 256-wide size bucket (timed once per process or read from *
                               * the tuning table), FP64 / FP32 squares on policy 5 (the       *
-                              * fastest measured in every bucket); 1 = 128-edge tiles, 2 =    *
+                              * fastest measured in every bucket) or, in small batches, its   *
+                              * 32-edge form (the same bits); 1 = 128-edge tiles, 2 =    *
                               * 64-edge; FP64 / FP32 squares                                   *
                               * also 4 = 64-edge with three LDS stages, 5 = 64-edge with      *
                               * register-staged loads; GB_FP16X3_REFINE also 6 / 7 = 128- /   *
                               * 64-edge tiles with the split under the products (two LDS      *
                               * buffers; bit-identical to 1 / 2).  Values a precision has no   *
                               * kernel for are taken as 0, as 3 is by all.                    */
-  int32_t tile_order;        /* 0: each subgraph's tiles on one XCD (L2 reuse); 1: as listed */
+  int32_t tile_order;        /* 0: each subgraph's tiles on one XCD (L2 reuse; few subgraphs  *
+                              * are cut over all); 1: as listed                                */
   int32_t check_idem;        /* 1: also compute stats.idem_max, max |X^2 - X| over the core   *
                               *    columns (one more square of the core tiles, or nine slab  *
                               *    products after the core-row refinement); 0 (default): the  *
@@ -331,12 +333,13 @@ typedef struct {
   int32_t n_square;          /* number of FP64 SP2 steps, one fused square+update launch each */
   float ms_square_lo;        /* the same for the low-precision squaring launches             */
   int32_t n_square_lo;
-  int32_t n_tile64;          /* subgraphs squared with 64-edge tiles                         */
+  int32_t n_tile64;          /* subgraphs squared with 64-edge tiles (or 32-edge)            */
   int32_t n_refine_done;     /* McWeeny steps applied, or those that S_m stands for (2^steps  *
                               * >= m; 4 for S_6)                                              */
   int32_t planes_db;         /* split loops: 1-3 bf16 planes, 4 = two fp16 planes; 0 otherwise */
   int32_t n_stage3;          /* subgraphs squared with the three-stage 64-edge kernel         */
-  int32_t n_regstage;        /* subgraphs squared with the register-staged 64-edge kernel     */
+  int32_t n_regstage;        /* subgraphs squared with the register-staged 64-edge kernel (or  *
+                              * its 32-edge form)                                              */
   double square_flops;       /* algorithmic flops of one square launch: sum_s 2 n_s^3        */
   double square_flops_exec;  /* matrix-core flops one launch executes: every active wave's    *
                               * block, k up to the next multiple of 32 of the block's rows    *

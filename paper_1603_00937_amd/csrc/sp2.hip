@@ -445,6 +445,99 @@ __global__ __launch_bounds__(kT, 2) void k_symm_mm(const T* __restrict__ A, cons
 }
 
 
+// The squares (MODE 0 of k_symm_mm) of a small batch on 32 x 32 tiles, one 16 x 16 block a wave
+// (small_batch below says which batches).  What bounds such a launch is the chain of one tile,
+// not any rate: a 64-edge tile of a 256-row block is 16 chunks, each a wait for memory, a
+// barrier and 16 products per wave, on fewer compute units than there are.  Here a wave has four
+// products per chunk, and the loads of two chunks go out under the products of the two before
+// (one chunk: 3 % slower at 512 rows, four: 8 % at 704).  Every output is the same sum in the same
+// order.  FP64, against k_symm_mm on 64-edge tiles: one block of 704 rows 41.9 -> 20.3 us, 16 of
+// 256 20.7 -> 15.5, 32 of 512 118 -> 91; large batches lose the reuse: 64 of ~900 rows 568 -> 639.
+template <typename T>
+__global__ __launch_bounds__(kT) void k_square_small(const T* __restrict__ X, T* __restrict__ S,
+                                                     const int4* __restrict__ tiles,
+                                                     const int64_t* __restrict__ offs,
+                                                     const int32_t* __restrict__ stopped, int lin,
+                                                     const int32_t* __restrict__ lin_flag) {
+  if (stopped && *stopped) return;
+  using M = Mfma<T>;
+  using acc_t = typename M::acc_t;
+  constexpr int KC = M::KC, V = 16 / sizeof(T);
+  constexpr int NCH = 2;  // chunks per stage
+  __shared__ __align__(1024) unsigned char lds[2][NCH][32 * 128];  // rows as in k_symm_mm
+  const int4 tl = tiles[blockIdx.x];
+  if (tl.x < 0) return;
+  const int s = tl.x, bi = tl.y, bj = tl.z, n_row = tl.w, np = padded(n_row);
+  const int64_t off = offs[s];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wr = wave >> 1, wc = wave & 1, g = lane >> 4, r16 = lane & 15;
+  // np is a multiple of the tile: every row of the tile exists
+  const int sr = tid >> 3, sc = ((tid & 7) ^ swz8(sr)) * V;
+  const T* asrc = X + off + (int64_t)(bi * 32 + sr) * np + sc;
+  const T* bsrc = X + off + (int64_t)(bj * 32 + sr) * np + sc;
+  const int nk = (n_row + KC - 1) / KC;
+  const bool stores = !(bi == bj && wr > wc);
+  const bool active = stores && bi * 32 + wr * 16 < n_row && bj * 32 + wc * 16 < n_row;
+  u4v stg[2][NCH];
+  auto load = [&](int c0) {  // chunks c0 .. c0 + NCH - 1; past the last one: that one again
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+      const int k = min(c0 + c, nk - 1) * KC;
+      stg[0][c] = *reinterpret_cast<const u4v*>(asrc + k);
+      stg[1][c] = *reinterpret_cast<const u4v*>(bsrc + k);
+    }
+  };
+  const int sw = swz8(r16);
+  const int pa = (wr * 16 + r16) * 128, pb = (wc * 16 + r16) * 128;
+  const int pc[2] = {((2 * g) ^ sw) << 4, ((2 * g + 1) ^ sw) << 4};
+  acc_t acc = {0, 0, 0, 0};
+  load(0);
+  for (int c0 = 0; c0 < nk; c0 += NCH) {
+    __syncthreads();  // the previous chunks' reads are done
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+      *reinterpret_cast<u4v*>(&lds[0][c][tid * 16]) = stg[0][c];
+      *reinterpret_cast<u4v*>(&lds[1][c][tid * 16]) = stg[1][c];
+    }
+    __syncthreads();
+    if (c0 + NCH < nk) load(c0 + NCH);
+    if (active) {
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) {
+        if (c0 + c >= nk) break;
+        constexpr bool kBlocked = std::is_same<T, float>::value;  // as in k_symm_mm
+        acc_t part = {0, 0, 0, 0};
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          T fa[V], fb[V];
+          __builtin_memcpy(fa, &lds[0][c][pa + pc[h]], 16);
+          __builtin_memcpy(fb, &lds[1][c][pb + pc[h]], 16);
+#pragma unroll
+          for (int e = 0; e < V; ++e) {
+            if constexpr (kBlocked) part = M::mma(fa[e], fb[e], part);
+            else acc = M::mma(fa[e], fb[e], acc);
+          }
+        }
+        if constexpr (kBlocked) acc += part;
+      }
+    }
+  }
+  if (!stores) return;
+  T* o = S + off;
+  const bool do_lin = lin_flag ? *lin_flag == 1 : lin != 0;
+  const bool mirror = bi != bj || wr < wc;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int grow = bi * 32 + wr * 16 + M::row(lane, r), gcol = bj * 32 + wc * 16 + r16;
+    const int64_t q1 = (int64_t)grow * np + gcol, q2 = (int64_t)gcol * np + grow;
+    T v = acc[r];
+    if (do_lin) v = (T)2 * X[off + q1] - v;
+    o[q1] = v;
+    if (mirror) o[q2] = v;
+  }
+}
+
+
 // ---- split squaring ---------------------------------------------------------------------
 // An FP32 iterate x is split into planes: bf16 ones hi = bf16(x), mid = bf16(x - hi),
 // lo = bf16(x - hi - mid) (each remainder is exact in FP32, and hi + mid + lo = x whenever x
@@ -1502,11 +1595,12 @@ int grid_for(int64_t n, int t, int cap = 1 << 20) {
 // largest blocks come first (most k work per tile).
 // Kernel variants of the batched products, one code per subgraph: 128 (128-edge tiles, two LDS
 // stages), 64 (64-edge, two stages), 63 (64-edge, three stages), 62 (64-edge, two stages,
-// register-staged loads); split squares: 128 and 64, and for fp16 planes 129 and 65 (128- and
-// 64-edge tiles with the split under the products, k_symm_mm_split_il).
-constexpr int kNVar = 6;
-constexpr int kVariants[kNVar] = {128, 64, 63, 62, 129, 65};
-inline int variant_edge(int code) { return code >= 128 ? 128 : 64; }
+// register-staged loads), 32 (32-edge, k_square_small); split squares: 128 and 64, and for fp16
+// planes 129 and 65 (128- and 64-edge tiles with the split under the products,
+// k_symm_mm_split_il).
+constexpr int kNVar = 7;
+constexpr int kVariants[kNVar] = {128, 64, 63, 62, 129, 65, 32};
+inline int variant_edge(int code) { return code >= 128 ? 128 : code == 32 ? 32 : 64; }
 inline bool split_il_code(int code) { return code == 129 || code == 65; }
 inline int variant_index(int code) {
   for (int v = 0; v < kNVar; ++v)
@@ -1680,6 +1774,14 @@ void launch_symm(const T* A, const T* B, const T* E, T* out, T alpha, T beta, co
   if (g.n[3] > 0)
     hipLaunchKernelGGL((k_symm_mm<T, MODE, 64, 2, 1>), dim3(g.n[3]), dim3(kT), 0, s, A, B, E,
                        out, alpha, beta, t, offs, stopped, lin, lin_flag, 0);
+  t += g.n[3];
+  if (g.n[6] > 0) {
+    if constexpr (MODE == 0)
+      hipLaunchKernelGGL(k_square_small<T>, dim3(g.n[6]), dim3(kT), 0, s, A, out, t, offs, stopped,
+                         lin, lin_flag);
+    else
+      fail(GB_EHIP, "32-edge tiles take squares only");
+  }
   GB_LAUNCH_CHECK();
 }
 
@@ -1705,7 +1807,8 @@ template <int NP, bool F16>
 void launch_split_np(const float* X, float* S, const int4* tiles, const Groups& g,
                      const int64_t* offs, hipStream_t s, int lin, const int32_t* stopped,
                      const int32_t* lin_flag) {
-  if (g.n[2] > 0 || g.n[3] > 0) fail(GB_EHIP, "split squares take 128- or 64-edge tiles only");
+  if (g.n[2] > 0 || g.n[3] > 0 || g.n[6] > 0)
+    fail(GB_EHIP, "split squares take 128- or 64-edge tiles only");
   const int4* t = tiles;
   if (g.n[0] > 0)
     hipLaunchKernelGGL((k_symm_mm_split<NP, F16, 128>), dim3(g.n[0]), dim3(kT), 0, s, X, S, t,
@@ -1904,7 +2007,8 @@ int tune_read(const char* path, std::string* why) {
     }
     // kinds: 0 FP64, 1 FP32, 10 + planes split squares; the interleaved split (129, 65)
     // exists for the fp16 planes (kind 14) only
-    const bool known = variant_index(variant) >= 0;
+    // (32 is chosen by the batch's size, never from a table)
+    const bool known = variant_index(variant) >= 0 && variant != 32;
     const bool split = kind >= 11 && kind <= 14;
     const bool split_ok = variant == 128 || variant == 64 || (kind == 14 && split_il_code(variant));
     if (!known || bucket < 1 || !(kind == 0 || kind == 1 || split) || (split && !split_ok) ||
@@ -1958,7 +2062,7 @@ std::vector<int> tune_tiles(const Part& P, const Plan& pl, T* X, T* S, const int
       for (int code : kVariants) {
         if (planes > 0 && code != 128 && code != 64 && !(planes == 4 && split_il_code(code)))
           continue;
-        if (planes == 0 && split_il_code(code)) continue;
+        if (planes == 0 && (split_il_code(code) || code == 32)) continue;
         std::vector<int> e(pl.n_sub, 0);
         for (int i : kv.second) e[i] = code;
         const Plan sub = make_plan(P, &e, xcd);
@@ -1997,6 +2101,19 @@ std::vector<int> tune_tiles(const Part& P, const Plan& pl, T* X, T* S, const int
   return bt;
 }
 
+// Squares on 32-edge tiles (k_square_small)?  FP64 while at most five 64-edge tiles fall to each of
+// the 256 compute units, which is what one holds at a time: the launch then lasts as long as a
+// tile does (1280 tiles, 128 blocks of 256 rows: 71.2 -> 54.6 us; 1088, 8 of 1024: 191 -> 166;
+// 3600, 32 of ~900: 568 -> 639).  FP32, whose products take half the time, up to one and a half
+// (325 tiles, one block of 1600: 72.0 -> 53.6; 396, 6 of 704: 35.3 -> 30.8; 448, 16 of 400:
+// 23.2 -> 23.7; 640, 64 of 256: 21.7 -> 22.9).
+template <typename T>
+bool small_batch(const Plan& pl) {
+  int64_t t64 = 0;
+  for (const int32_t np : pl.npad) t64 += (int64_t)(np / 64) * (np / 64 + 1) / 2;
+  return t64 <= (std::is_same<T, double>::value ? 1280 : 400);
+}
+
 template <typename T>
 void choose_tiles(const Part& P, Plan& pl, T* X, T* S, DBuf<int4>& tiles, const int64_t* offs,
                   hipStream_t s, int policy, int kind, gb_sp2_stats& st, bool xcd,
@@ -2008,9 +2125,9 @@ void choose_tiles(const Part& P, Plan& pl, T* X, T* S, DBuf<int4>& tiles, const 
   else if (policy == 6 && planes == 4) bt.assign(pl.n_sub, 129);
   else if (policy == 7 && planes == 4) bt.assign(pl.n_sub, 65);
   // FP64 / FP32 squares: the register-staged 64-edge variant, the fastest measured in every
-  // size bucket of the N = 1024, 18000 and 100000 systems (the others stay selectable); split
-  // squares: timed per bucket
-  else if (policy != 1 && planes == 0) bt.assign(pl.n_sub, 62);
+  // size bucket of the N = 1024, 18000 and 100000 systems (the others stay selectable), but for
+  // small batches; split squares: timed per bucket
+  else if (policy != 1 && planes == 0) bt.assign(pl.n_sub, small_batch<T>(pl) ? 32 : 62);
   else if (policy != 1) bt = tune_tiles<T>(P, pl, X, S, offs, s, kind, xcd, planes);
   if (policy == 1) return;
   pl = make_plan(P, &bt, xcd);
@@ -2022,9 +2139,9 @@ void choose_tiles(const Part& P, Plan& pl, T* X, T* S, DBuf<int4>& tiles, const 
   st.n_split_il = 0;
   for (int e : bt) {
     st.n_split_il += split_il_code(e);
-    st.n_tile64 += variant_edge(e) == 64;
+    st.n_tile64 += variant_edge(e) <= 64;
     st.n_stage3 += e == 63;
-    st.n_regstage += e == 62;
+    st.n_regstage += e == 62 || e == 32;
   }
   st.square_flops_exec = pl.flops_exec;
 }
@@ -2661,9 +2778,9 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
     GB_LAUNCH_CHECK();
     xd_ready = true;
   };
-  auto fp64_tiles_for_blocks = [&] {
-    if (low && planes > 0)
-      choose_tiles<double>(P, pl, xd, sd, tiles, offs.get(), s, 0, 0, st, xcd, 0, false);
+  auto fp64_tiles_for_blocks = [&] {  // (32-edge tiles take squares only)
+    if (low && (planes > 0 || pl.lg.n[variant_index(32)] > 0))
+      choose_tiles<double>(P, pl, xd, sd, tiles, offs.get(), s, 5, 0, st, xcd, 0, false);
   };
   CoreRows cr;
   const double* rows_final = nullptr;  // core-row refinement: the core rows of D and of D^2

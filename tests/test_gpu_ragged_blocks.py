@@ -44,6 +44,9 @@ def test_rows_end_anywhere(n, precision, policies):
         if policy in (6, 7):
             assert np.array_equal(full, last)
         last = full
+        if precision == "fp64":  # one sum per entry, whatever the tile
+            first = full if policy == 0 else first
+            assert np.array_equal(full, first)
 
 
 @pytest.mark.parametrize("sizes", [(300,), (40, 300), (200, 130, 70), (64,) * 9, (500, 20, 20)])
@@ -70,3 +73,23 @@ def test_few_blocks_over_all_queues(sizes):
             assert st["converged"]
             got.append(torch.nan_to_num(d).cpu())
     assert all(torch.equal(got[i], got[i + 3]) for i in range(3))
+
+
+@pytest.mark.parametrize("precision,blocks,n", [("fp64", 128, 256), ("fp64", 129, 256),
+                                                ("fp32", 40, 256), ("fp32", 41, 256)])
+def test_small_batches_change_no_bit(precision, blocks, n):
+    """The last batch on 32-edge tiles and the first on 64-edge ones, against the 64-edge kernel.
+    (FP32 results are compared through the loop's traces: the FP64 steps after it use the tiles
+    of their own policy.)"""
+    import torch
+    import paper_1603_00937_amd as gb
+    h, _, occ = _dense(n)
+    rows = torch.arange(blocks * n, dtype=torch.int32)[:, None] // n * n
+    hc = (rows + torch.arange(n, dtype=torch.int32)[None]).contiguous().cuda()
+    hv = torch.from_numpy(np.tile(h, (blocks, 1))).cuda()
+    part = gb.partition(gb.build_graph(hc, hv, 1e-9), n)
+    out = [gb.density(hc, hv, blocks * occ, 1e-9, partition=part, precision=precision,
+                      tile_policy=p) for p in ("auto", "64r")]
+    assert out[0][2]["t2"] == out[1][2]["t2"] and out[0][2]["converged"]
+    if precision == "fp64":
+        assert torch.equal(out[0][1], out[1][1])
