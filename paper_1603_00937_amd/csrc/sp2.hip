@@ -2405,6 +2405,7 @@ int sp2_loop_dev(T*& X, T*& S, const Plan& pl, const DBuf<int4>& tiles, const DB
         const hipError_t e = hipStreamQuery(s);
         if (e == hipSuccess) break;  // nothing is left in the queue: the state tells
         if (e != hipErrorNotReady) GB_HIP(e);
+        (void)hipGetLastError();  // "not ready" is no error of the launches that follow
       }
     }
   }
