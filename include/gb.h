@@ -43,8 +43,8 @@ typedef int32_t gb_status;
 /* The dense batch buffers of gb_density / gb_foe_density are cached between calls (per device
  * and per concurrent call, grown when a call needs more), so a loop of calls does not
  * reallocate them; so are the host buffers of the multilevel partitioner (its coarse graphs
- * and the pinned copy of the graph it reads).  gb_trim frees the cached buffers of every call
- * that has returned. */
+ * and the pinned copy of the graph it reads), and up to 256 MiB of the smaller device buffers that
+ * calls have freed.  gb_trim frees the cached buffers of every call that has returned. */
 gb_status gb_trim(void);
 
 /* Kernel-variant table of the autotuner (the tile edge, and for FP64 / FP32 the LDS staging,

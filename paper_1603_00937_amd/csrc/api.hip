@@ -5,6 +5,7 @@
 #include <cmath>
 #include <cstdarg>
 #include <cstring>
+#include <map>
 #include <mutex>
 
 namespace gbi {
@@ -31,6 +32,114 @@ void fail(gb_status code, const char* fmt, ...) {
 
 Allocator g_alloc;  // the registered hook (all null: the device pool)
 
+// ---- the buffers of a call ----
+// A call makes and frees some forty buffers, and a stream-ordered free costs the host 8 us: a third
+// of a step at 256 orbitals.  Buffers of up to 32 MiB that a call frees are put aside
+// until it ends, and where the work of their streams is then known to be done (every call waits
+// for it; the query below makes sure) they go to a process-wide list of idle ones, from which any
+// later call of the device, on any thread and stream, takes one of its power of two.  What a failed
+// call freed, what is freed outside of a call and what the list has no room for goes back to the
+// device pool as before.
+namespace {
+constexpr int kMinClass = 8, kMaxClass = 25;
+constexpr size_t kIdleMost = (size_t)256 << 20;
+struct IdleBuffers {
+  std::mutex m;
+  std::map<std::pair<int, int>, std::vector<void*>> list;  // by device and class
+  size_t bytes = 0;
+};
+IdleBuffers& idle_buffers() {
+  static auto* p = new IdleBuffers;  // outlives the runtime's own teardown
+  return *p;
+}
+}  // namespace
+
+struct CallScope {
+  struct Freed {
+    void* p;
+    hipStream_t s;
+    int cls;
+  };
+  static thread_local CallScope* top;
+  bool outer;
+  int dev = -1;
+  std::vector<Freed> freed;
+  size_t bytes = 0;
+  CallScope() : outer(top == nullptr) {
+    if (outer) top = this;
+  }
+  ~CallScope() {
+    if (!outer) return;
+    top = nullptr;
+    for (const Freed& f : freed) (void)hipFreeAsync(f.p, f.s);
+  }
+  CallScope(const CallScope&) = delete;
+  CallScope& operator=(const CallScope&) = delete;
+  void* take(int cls) {
+    if (dev < 0) GB_HIP(hipGetDevice(&dev));
+    IdleBuffers& b = idle_buffers();
+    std::lock_guard<std::mutex> lk(b.m);
+    auto it = b.list.find({dev, cls});
+    if (it == b.list.end() || it->second.empty()) return nullptr;
+    void* p = it->second.back();
+    it->second.pop_back();
+    b.bytes -= (size_t)1 << cls;
+    return p;
+  }
+  bool put(void* p, hipStream_t s, int cls) {
+    if (bytes + ((size_t)1 << cls) > kIdleMost) return false;
+    try {
+      freed.push_back({p, s, cls});
+    } catch (...) {
+      return false;
+    }
+    bytes += (size_t)1 << cls;
+    return true;
+  }
+  void done() {  // the call succeeded
+    if (!outer || freed.empty()) return;
+    std::vector<Freed> back;
+    back.reserve(freed.size());
+    IdleBuffers& b = idle_buffers();
+    hipStream_t last = freed[0].s;
+    bool idle = hipStreamQuery(last) == hipSuccess;
+    for (const Freed& f : freed) {
+      if (f.s != last) {
+        last = f.s;
+        idle = hipStreamQuery(last) == hipSuccess;
+      }
+      const size_t n = (size_t)1 << f.cls;
+      std::lock_guard<std::mutex> lk(b.m);
+      if (idle && b.bytes + n <= kIdleMost) {
+        b.list[{dev, f.cls}].push_back(f.p);
+        b.bytes += n;
+      } else {
+        back.push_back(f);
+      }
+    }
+    (void)hipGetLastError();
+    freed.swap(back);  // the destructor's
+  }
+};
+thread_local CallScope* CallScope::top = nullptr;
+
+void small_trim() {
+  IdleBuffers& b = idle_buffers();
+  std::map<std::pair<int, int>, std::vector<void*>> idle;
+  {
+    std::lock_guard<std::mutex> lk(b.m);
+    idle.swap(b.list);
+    b.bytes = 0;
+  }
+  int cur = 0;
+  (void)hipGetDevice(&cur);
+  for (auto& kv : idle) {
+    (void)hipSetDevice(kv.first.first);
+    for (void* p : kv.second) (void)hipFreeAsync(p, nullptr);
+  }
+  (void)hipSetDevice(cur);
+}
+
 void* dmalloc(size_t bytes, hipStream_t s, Allocator* used) {
   *used = g_alloc;
   void* p = nullptr;
@@ -38,6 +147,15 @@ void* dmalloc(size_t bytes, hipStream_t s, Allocator* used) {
     p = used->alloc(bytes ? bytes : 1, (void*)s, used->ctx);
     if (!p) fail(GB_ENOMEM, "registered allocator returned NULL for %zu bytes", bytes);
     return p;
+  }
+  size_t want = bytes ? bytes : 1;
+  if (CallScope::top && want <= ((size_t)1 << kMaxClass)) {
+    int cls = kMinClass;
+    while (((size_t)1 << cls) < want) ++cls;
+    want = (size_t)1 << cls;
+    used->cls = cls;
+    p = CallScope::top->take(cls);
+    if (p) return p;
   }
   // keep freed pool memory cached instead of returning it at every synchronisation
   std::call_once(g_pool_once, [] {
@@ -48,7 +166,7 @@ void* dmalloc(size_t bytes, hipStream_t s, Allocator* used) {
       (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &thr);
     }
   });
-  const hipError_t e = hipMallocAsync(&p, bytes ? bytes : 1, s);
+  const hipError_t e = hipMallocAsync(&p, want, s);
   if (e != hipSuccess || !p) {
     (void)hipGetLastError();
     fail(GB_ENOMEM, "device allocation of %zu bytes failed: %s", bytes, hipGetErrorString(e));
@@ -58,8 +176,13 @@ void* dmalloc(size_t bytes, hipStream_t s, Allocator* used) {
 
 void dfree(void* p, hipStream_t s, const Allocator& a) {
   if (!p) return;
-  if (a.free) a.free(p, (void*)s, a.ctx);
-  else (void)hipFreeAsync(p, s);
+  if (a.free) {
+    a.free(p, (void*)s, a.ctx);
+    return;
+  }
+  CallScope* c = CallScope::top;
+  if (a.cls >= 0 && c && c->dev >= 0 && c->put(p, s, a.cls)) return;
+  (void)hipFreeAsync(p, s);
 }
 
 size_t workspace_total(const size_t slot[Workspace::kSlots]) {
@@ -238,7 +361,9 @@ namespace {
 template <typename F>
 gb_status guarded(F&& f) {
   try {
+    CallScope call;
     f();
+    call.done();
     g_err[0] = '\0';
     return GB_OK;
   } catch (const Error& e) {
@@ -355,6 +480,7 @@ gb_status gb_trim(void) {
     ws_trim();
     cached_trim();
     ml_trim();
+    small_trim();
   });
 }
 

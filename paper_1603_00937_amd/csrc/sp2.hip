@@ -1843,13 +1843,14 @@ void launch_split(const float* X, float* S, const int4* tiles, const Groups& g,
   else launch_split_np<3, false>(X, S, tiles, g, offs, s, lin, stopped, lin_flag);
 }
 
-// device tile table: the launch list, then the subgraph-major list
-DBuf<int4> upload_tiles(const Plan& pl, hipStream_t s) {
-  DBuf<int4> t(pl.launch.size() + pl.tiles.size(), s);
+// device tile table: the launch list, then (for launches per subgraph) the subgraph-major list
+DBuf<int4> upload_tiles(const Plan& pl, hipStream_t s, bool per_subgraph) {
+  DBuf<int4> t(pl.launch.size() + (per_subgraph ? pl.tiles.size() : 0), s);
   GB_HIP(hipMemcpyAsync(t.get(), pl.launch.data(), pl.launch.size() * sizeof(int4),
                         hipMemcpyHostToDevice, s));
-  GB_HIP(hipMemcpyAsync(t.get() + pl.launch.size(), pl.tiles.data(), pl.tiles.size() * sizeof(int4),
-                        hipMemcpyHostToDevice, s));
+  if (per_subgraph)
+    GB_HIP(hipMemcpyAsync(t.get() + pl.launch.size(), pl.tiles.data(),
+                          pl.tiles.size() * sizeof(int4), hipMemcpyHostToDevice, s));
   return t;
 }
 
@@ -2066,7 +2067,7 @@ std::vector<int> tune_tiles(const Part& P, const Plan& pl, T* X, T* S, const int
         std::vector<int> e(pl.n_sub, 0);
         for (int i : kv.second) e[i] = code;
         const Plan sub = make_plan(P, &e, xcd);
-        DBuf<int4> tl = upload_tiles(sub, s);
+        DBuf<int4> tl = upload_tiles(sub, s, false);
         auto run = [&] {
           if constexpr (std::is_same<T, float>::value) {
             if (planes > 0) {
@@ -2108,31 +2109,44 @@ std::vector<int> tune_tiles(const Part& P, const Plan& pl, T* X, T* S, const int
 // (325 tiles, one block of 1600: 72.0 -> 53.6; 396, 6 of 704: 35.3 -> 30.8; 448, 16 of 400:
 // 23.2 -> 23.7; 640, 64 of 256: 21.7 -> 22.9).
 template <typename T>
-bool small_batch(const Plan& pl) {
+bool small_batch(const Part& P) {
   int64_t t64 = 0;
-  for (const int32_t np : pl.npad) t64 += (int64_t)(np / 64) * (np / 64 + 1) / 2;
+  for (int q = 0; q < P.n_sub; ++q) {
+    const int64_t nb = padded(P.h_sub_ptr[q + 1] - P.h_sub_ptr[q]) / 64;
+    t64 += nb * (nb + 1) / 2;
+  }
   return t64 <= (std::is_same<T, double>::value ? 1280 : 400);
 }
 
+// The variant of every subgraph where a policy says it (0: split squares, timed per bucket).
+template <typename T>
+int fixed_tiles(const Part& P, int policy, int planes) {
+  if (policy == 1) return kBT;
+  if (policy == 2) return 64;
+  if (policy == 4 && planes == 0) return 63;
+  if (policy == 5 && planes == 0) return 62;
+  if (policy == 6 && planes == 4) return 129;
+  if (policy == 7 && planes == 4) return 65;
+  // FP64 / FP32 squares: the register-staged 64-edge variant, the fastest measured in every
+  // size bucket of the N = 1024, 18000 and 100000 systems (the others stay selectable), but for
+  // small batches
+  if (planes == 0) return small_batch<T>(P) ? 32 : 62;
+  return 0;
+}
+
+// The tiles of a loop: pl and its device copy are made again where they are not of the variant
+// asked for (tiles empty: not uploaded yet).
 template <typename T>
 void choose_tiles(const Part& P, Plan& pl, T* X, T* S, DBuf<int4>& tiles, const int64_t* offs,
                   hipStream_t s, int policy, int kind, gb_sp2_stats& st, bool xcd,
-                  int planes = 0, bool record = true) {
-  std::vector<int> bt(pl.n_sub, kBT);
-  if (policy == 2) bt.assign(pl.n_sub, 64);
-  else if (policy == 4 && planes == 0) bt.assign(pl.n_sub, 63);
-  else if (policy == 5 && planes == 0) bt.assign(pl.n_sub, 62);
-  else if (policy == 6 && planes == 4) bt.assign(pl.n_sub, 129);
-  else if (policy == 7 && planes == 4) bt.assign(pl.n_sub, 65);
-  // FP64 / FP32 squares: the register-staged 64-edge variant, the fastest measured in every
-  // size bucket of the N = 1024, 18000 and 100000 systems (the others stay selectable), but for
-  // small batches; split squares: timed per bucket
-  else if (policy != 1 && planes == 0) bt.assign(pl.n_sub, small_batch<T>(pl) ? 32 : 62);
-  else if (policy != 1) bt = tune_tiles<T>(P, pl, X, S, offs, s, kind, xcd, planes);
-  if (policy == 1) return;
-  pl = make_plan(P, &bt, xcd);
-  tiles = upload_tiles(pl, s);
-  if (!record) return;  // the refinement's squares: the stats describe the loop's
+                  bool per_subgraph, int planes = 0, bool record = true) {
+  const int code = fixed_tiles<T>(P, policy, planes);
+  const std::vector<int> bt = code ? std::vector<int>(pl.n_sub, code)
+                                   : tune_tiles<T>(P, pl, X, S, offs, s, kind, xcd, planes);
+  const bool changed = bt != pl.bt;
+  if (changed) pl = make_plan(P, &bt, xcd);
+  if (changed || !tiles.get()) tiles = upload_tiles(pl, s, per_subgraph);
+  if (!record || policy == 1) return;  // the refinement's squares: the stats describe the loop's
   st.n_tile64 = 0;
   st.n_stage3 = 0;
   st.n_regstage = 0;
@@ -2201,8 +2215,8 @@ void launch_step(const T* X, T* S, const Plan& pl, const int4* tiles, const int6
 // step index at which the stop rule fired, the replay ended, max_iter was reached, or (low
 // precision) the idempotency error stagnated or fell to e_hand; X then holds the result.
 template <typename T>
-int sp2_loop(T*& X, T*& S, const Plan& pl, const DBuf<int4>& tiles, const DBuf<int64_t>& offs,
-             const DBuf<int32_t>& npad, const Part& P, double n_occ, double tol, int max_iter,
+int sp2_loop(T*& X, T*& S, const Plan& pl, const DBuf<int4>& tiles, const int64_t* offs,
+             const int32_t* npad, const Part& P, double n_occ, double tol, int max_iter,
              const uint8_t* branch_in, int n_branch_in, bool stagnation_stop, int it0,
              gb_sp2_stats& st, DBuf<StepRec>& recs, hipStream_t s, int* stop_kind,
              TapeData* tape = nullptr, int planes = 0, bool per_subgraph = false,
@@ -2218,7 +2232,7 @@ int sp2_loop(T*& X, T*& S, const Plan& pl, const DBuf<int4>& tiles, const DBuf<i
   std::vector<double> es;
   DBuf<double> part(2 * (size_t)pl.n_sub, s);
   for (;;) {
-    hipLaunchKernelGGL(k_trace_rows<T>, dim3(pl.n_sub), dim3(kT), 0, s, X, offs.get(), npad.get(),
+    hipLaunchKernelGGL(k_trace_rows<T>, dim3(pl.n_sub), dim3(kT), 0, s, X, offs, npad,
                        P.core_ptr.get(), part.get(), nullptr, ts1, ts2);
     int forced = -1;
     if (branch_in) forced = it < n_branch_in ? (int)branch_in[it] : 2;
@@ -2256,7 +2270,7 @@ int sp2_loop(T*& X, T*& S, const Plan& pl, const DBuf<int4>& tiles, const DBuf<i
       }
     }
     GB_HIP(hipEventRecord(tm.a, s));
-    launch_step<T>(X, to, pl, tiles.get(), offs.get(), s, planes, r.b == 1 ? 1 : 0, per_subgraph);
+    launch_step<T>(X, to, pl, tiles.get(), offs, s, planes, r.b == 1 ? 1 : 0, per_subgraph);
     GB_HIP(hipEventRecord(tm.b, s));
     X = to;
     S = X == scratch[0] ? scratch[1] : scratch[0];
@@ -2325,8 +2339,8 @@ __global__ void k_loop_init(LoopState* __restrict__ st, LoopInit in) {
 // where the square takes 11).  Mode 2 captures two steps, one per buffer parity, in a hipGraph and
 // replays it, 32 steps and then 8 at a time, reading the loop state in between.
 template <typename T>
-int sp2_loop_dev(T*& X, T*& S, const Plan& pl, const DBuf<int4>& tiles, const DBuf<int64_t>& offs,
-                 const DBuf<int32_t>& npad, const Part& P, double n_occ, double tol, int max_iter,
+int sp2_loop_dev(T*& X, T*& S, const Plan& pl, const DBuf<int4>& tiles, const int64_t* offs,
+                 const int32_t* npad, const Part& P, double n_occ, double tol, int max_iter,
                  const uint8_t* branch_in, int n_branch_in, bool stagnation_stop, int it0,
                  gb_sp2_stats& st, hipStream_t s, int* stop_kind, int planes, bool graph,
                  double e_hand = 0.0) {
@@ -2358,10 +2372,10 @@ int sp2_loop_dev(T*& X, T*& S, const Plan& pl, const DBuf<int4>& tiles, const DB
   auto enqueue = [&](hipStream_t q, int k) {  // step k of the loop (0-based)
     T* A = (k & 1) ? S : X;
     T* B = (k & 1) ? X : S;
-    hipLaunchKernelGGL(k_trace_step<T>, dim3(pl.n_sub), dim3(kT), 0, q, A, offs.get(), npad.get(),
+    hipLaunchKernelGGL(k_trace_step<T>, dim3(pl.n_sub), dim3(kT), 0, q, A, offs, npad,
                        P.core_ptr.get(), part.get(), ts1, ts2, d.get(), seen);
     GB_LAUNCH_CHECK();
-    launch_step<T>(A, B, pl, tiles.get(), offs.get(), q, planes, 0, false, stopped, cur_b);
+    launch_step<T>(A, B, pl, tiles.get(), offs, q, planes, 0, false, stopped, cur_b);
   };
   hipStream_t cs = nullptr;
   hipGraph_t gr = nullptr;
@@ -2612,14 +2626,6 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
   Timer t_all;
   GB_HIP(hipEventRecord(t_all.a, s));
   const bool xcd = o.tile_order == 0;
-  Plan pl = make_plan(P, nullptr, xcd);
-  st.square_flops = pl.flops_alg;
-  st.square_flops_exec = pl.flops_exec;
-  DBuf<int64_t> offs(pl.n_sub, s);
-  DBuf<int32_t> npad(pl.n_sub, s);
-  DBuf<int4> tiles = upload_tiles(pl, s);
-  GB_HIP(hipMemcpyAsync(offs.get(), pl.off.data(), pl.n_sub * 8, hipMemcpyHostToDevice, s));
-  GB_HIP(hipMemcpyAsync(npad.get(), pl.npad.data(), pl.n_sub * 4, hipMemcpyHostToDevice, s));
   DBuf<StepRec> recs(2, s);
   const int N = H.n;
   const double tol = o.idem_tol > 0 ? o.idem_tol : 1e-10 * N / 1024.0;
@@ -2631,7 +2637,26 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
   const int planes = o.precision == GB_BF16_REFINE ? 1 : o.precision == GB_BF16X3_REFINE ? 2
                    : o.precision == GB_BF16X6_REFINE ? 3 : o.precision == GB_FP16X3_REFINE ? 4
                    : 0;
+  const int nhi = low ? std::min(std::max(0, o.n_fp64_first), max_iter) : 0;
+  // the plan of the first loop, where its tiles are known (FP64 steps before a low-precision loop:
+  // 128-edge tiles); offsets and padded sizes go up in one copy, the tiles when a loop takes them
+  const int code0 = nhi > 0 ? kBT
+                    : low   ? fixed_tiles<float>(P, o.tile_policy, planes)
+                            : fixed_tiles<double>(P, o.tile_policy, 0);
+  const std::vector<int> bt0(P.n_sub, code0 ? code0 : kBT);
+  Plan pl = make_plan(P, &bt0, xcd);
+  st.square_flops = pl.flops_alg;
+  st.square_flops_exec = pl.flops_exec;
+  std::vector<int64_t> sizes(pl.off);
+  sizes.resize(pl.n_sub + ((size_t)pl.n_sub + 1) / 2);
+  std::memcpy(sizes.data() + pl.n_sub, pl.npad.data(), pl.n_sub * sizeof(int32_t));
+  DBuf<int64_t> dsizes(sizes.size(), s);
+  GB_HIP(hipMemcpyAsync(dsizes.get(), sizes.data(), sizes.size() * 8, hipMemcpyHostToDevice, s));
+  const int64_t* const offs = dsizes.get();
+  const int32_t* const npad = reinterpret_cast<const int32_t*>(dsizes.get() + pl.n_sub);
+  DBuf<int4> tiles;
   const int n_refine = o.n_refine;
+  const bool per_sub = o.launch_mode == 1;
   // launch modes 0 (default) and 2 run the loop on the device; 1 (one launch per subgraph) and
   // 3 read every decision back on the host
   const bool dev_loop = o.launch_mode == 0 || o.launch_mode == 2;
@@ -2662,20 +2687,20 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
   if (low) {
     float* xf = ws->get<float>(3, pl.total, s);
     float* sf = ws->get<float>(4, pl.total, s);
-    const int nhi = std::min(std::max(0, o.n_fp64_first), max_iter);
     if (nhi > 0) {
       hipLaunchKernelGGL(k_gather<double>, ggrid, dim3(kT), lds_g, s, H.col, x0, H.width,
-                         P.core_ptr.get(), P.sub_ptr.get(), P.sub_idx.get(), offs.get(),
-                         npad.get(), xd, 1.0);
+                         P.core_ptr.get(), P.sub_ptr.get(), P.sub_idx.get(), offs,
+                         npad, xd, 1.0);
     } else {
       hipLaunchKernelGGL(k_gather<float>, ggrid, dim3(kT), lds_g, s, H.col, x0, H.width,
-                         P.core_ptr.get(), P.sub_ptr.get(), P.sub_idx.get(), offs.get(),
-                         npad.get(), xf, planes == 4 ? kF16Scale : 1.0f);
+                         P.core_ptr.get(), P.sub_ptr.get(), P.sub_idx.get(), offs,
+                         npad, xf, planes == 4 ? kF16Scale : 1.0f);
     }
     GB_LAUNCH_CHECK();
     GB_HIP(hipEventRecord(t_gather.b, s));
     GB_HIP(hipEventRecord(t_sp2.a, s));
     if (nhi > 0) {
+      tiles = upload_tiles(pl, s, per_sub);
       // the first steps, where the spectral gap of X is smallest and rounding errors are
       // amplified most, in FP64
       if (dev_loop)
@@ -2685,7 +2710,7 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
       else
         it_end = sp2_loop<double>(xd, sd, pl, tiles, offs, npad, P, n_occ, tol, nhi, o.branch_in,
                                   o.n_branch_in, false, 0, st, recs, s, &stop_kind, nullptr, 0,
-                                  o.launch_mode == 1);
+                                  per_sub);
       done = stop_kind == 1 || stop_kind == 3;
       if (!done) {
         hipLaunchKernelGGL((k_convert<double, float>), dim3(grid_for(pl.total, kT, 65536)),
@@ -2695,8 +2720,8 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
     }
     if (!done) {
       // FP32 squares: kind 1; split squares: kind 10 + planes (128- or 64-edge tiles)
-      choose_tiles<float>(P, pl, xf, sf, tiles, offs.get(), s, o.tile_policy,
-                          planes ? 10 + planes : 1, st, xcd, planes);
+      choose_tiles<float>(P, pl, xf, sf, tiles, offs, s, o.tile_policy,
+                          planes ? 10 + planes : 1, st, xcd, per_sub, planes);
       st.planes_db = planes;
       // The low-precision loop hands over to the refinement as soon as that finishes the job
       // (a replayed sequence or a given number of steps runs as asked).  Where the refinement
@@ -2714,11 +2739,11 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
         else
           it_end = sp2_loop<float>(xf, sf, pl, tiles, offs, npad, P, n_occ, tol_lo, max_iter,
                                    o.branch_in, o.n_branch_in, true, it_end, st, recs, s,
-                                   &stop_kind, nullptr, planes, o.launch_mode == 1, false, e_hand);
+                                   &stop_kind, nullptr, planes, per_sub, false, e_hand);
         // continue from X made exactly symmetric, in FP32, in place (every block is padded to a
         // multiple of 64)
         hipLaunchKernelGGL(k_sym_diag, dim3(pl.max_npad / 64, pl.n_sub), dim3(256), 0, s, xf,
-                           offs.get(), npad.get());
+                           offs, npad);
         GB_LAUNCH_CHECK();
         xs = xf;
       };
@@ -2728,9 +2753,10 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
     }
     GB_HIP(hipEventRecord(t_sp2.b, s));
   } else {
-    choose_tiles<double>(P, pl, xd, sd, tiles, offs.get(), s, o.tile_policy, 0, st, xcd);
+    choose_tiles<double>(P, pl, xd, sd, tiles, offs, s, o.tile_policy, 0, st, xcd,
+                         per_sub);
     hipLaunchKernelGGL(k_gather<double>, ggrid, dim3(kT), lds_g, s, H.col, x0, H.width,
-                       P.core_ptr.get(), P.sub_ptr.get(), P.sub_idx.get(), offs.get(), npad.get(),
+                       P.core_ptr.get(), P.sub_ptr.get(), P.sub_idx.get(), offs, npad,
                        X64, 1.0);
     GB_LAUNCH_CHECK();
     if (tape_out) {
@@ -2753,7 +2779,8 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
       };
       t->offs = DBuf<int64_t>(pl.n_sub, nullptr);
       GB_HIP(hipMemcpyAsync(t->offs.get(), pl.off.data(), pl.n_sub * 8, hipMemcpyHostToDevice, s));
-      dup_i32(t->npad, npad, pl.n_sub);
+      t->npad = DBuf<int32_t>(pl.n_sub, nullptr);
+      GB_HIP(hipMemcpyAsync(t->npad.get(), npad, pl.n_sub * 4, hipMemcpyDeviceToDevice, s));
       t->tiles = DBuf<int4>(t->pl.launch.size(), nullptr);
       GB_HIP(hipMemcpyAsync(t->tiles.get(), t->pl.launch.data(),
                             t->pl.launch.size() * sizeof(int4), hipMemcpyHostToDevice, s));
@@ -2781,7 +2808,7 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
   };
   auto fp64_tiles_for_blocks = [&] {  // (32-edge tiles take squares only)
     if (low && (planes > 0 || pl.lg.n[variant_index(32)] > 0))
-      choose_tiles<double>(P, pl, xd, sd, tiles, offs.get(), s, 5, 0, st, xcd, 0, false);
+      choose_tiles<double>(P, pl, xd, sd, tiles, offs, s, 5, 0, st, xcd, per_sub, 0, false);
   };
   CoreRows cr;
   const double* rows_final = nullptr;  // core-row refinement: the core rows of D and of D^2
@@ -2805,11 +2832,11 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
       DBuf<RefineState> rs(1, s);
       int32_t* const rdone = &rs.get()->done;
       double* sl = ws->get<double>(7, 5 * (size_t)cr.total, s);
-      const RowsCtx rc{cr, pl, P, offs.get(), npad.get(), s, xs_scale};
+      const RowsCtx rc{cr, pl, P, offs, npad, s, xs_scale};
       auto y_of = [&](int m) { return sl + (2 + m % 3) * cr.total; };  // S_6 follows S_3 in place
       auto check = [&](const double* y, double thr, int m) {
         hipLaunchKernelGGL(k_trace_rows<double>, dim3(pl.n_sub), dim3(kT), 0, s, y,
-                           cr.soffs.get(), npad.get(), P.core_ptr.get(), part.get(), rdone, 1.0,
+                           cr.soffs.get(), npad, P.core_ptr.get(), part.get(), rdone, 1.0,
                            1.0);
         hipLaunchKernelGGL(k_refine_check, dim3(1), dim3(kT), 0, s, part.get(), pl.n_sub,
                            (double)n_occ, thr, m, rs.get());
@@ -2833,7 +2860,7 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
         hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(kT), 0, s, rdone, (int64_t)1);
         double *v = sl, *w = sl + cr.total;
         hipLaunchKernelGGL(k_rows_copy<float>, dim3((pl.max_npad + 63) / 64, pl.n_sub), dim3(256),
-                           0, s, xs, offs.get(), npad.get(), v, cr.soffs.get(), P.core_ptr.get(),
+                           0, s, xs, offs, npad, v, cr.soffs.get(), P.core_ptr.get(),
                            xs_scale);
         GB_LAUNCH_CHECK();
         check(v, tol, 1);
@@ -2892,16 +2919,16 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
       const int max_steps = n_refine > 0 ? n_refine : 8;
       StepRec r;
       for (int step = 0;; ++step) {
-        hipLaunchKernelGGL(k_trace_rows<double>, dim3(pl.n_sub), dim3(kT), 0, s, xd, offs.get(),
-                           npad.get(), P.core_ptr.get(), part.get(), nullptr, 1.0, 1.0);
+        hipLaunchKernelGGL(k_trace_rows<double>, dim3(pl.n_sub), dim3(kT), 0, s, xd, offs,
+                           npad, P.core_ptr.get(), part.get(), nullptr, 1.0, 1.0);
         hipLaunchKernelGGL(k_decide, dim3(1), dim3(kT), 0, s, part.get(), pl.n_sub,
                            (double)n_occ, tol, 2, 0, recs.get());
         GB_LAUNCH_CHECK();
         GB_HIP(hipMemcpyAsync(&r, recs.get(), sizeof(r), hipMemcpyDeviceToHost, s));
         GB_HIP(hipStreamSynchronize(s));
         if (r.e <= tol || step == max_steps) break;
-        launch_square<double>(xd, sd, tiles.get(), pl.lg, offs.get(), s);
-        launch_symm<double, 1>(sd, xd, sd, td, -2.0, 3.0, tiles.get(), pl.lg, offs.get(), s);
+        launch_square<double>(xd, sd, tiles.get(), pl.lg, offs, s);
+        launch_symm<double, 1>(sd, xd, sd, td, -2.0, 3.0, tiles.get(), pl.lg, offs, s);
         std::swap(xd, td);
         ++st.n_refine_done;
       }
@@ -2927,7 +2954,7 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
     // with idempotent blocks, and cycles.
     const int cap = std::min(it_end + (n_refine > 0 ? n_refine : 16), 127);
     it_end = sp2_loop<double>(xd, sd, pl, tiles, offs, npad, P, n_occ, tol, cap, bin, nbin, false,
-                              it_end, st, recs, s, &stop_kind, nullptr, 0, o.launch_mode == 1,
+                              it_end, st, recs, s, &stop_kind, nullptr, 0, per_sub,
                               bin == nullptr);
   } else {
     if (dev_loop && !tape_out)
@@ -2937,7 +2964,7 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
     else
       it_end = sp2_loop<double>(xd, sd, pl, tiles, offs, npad, P, n_occ, tol, max_iter,
                                 o.branch_in, o.n_branch_in, false, 0, st, recs, s, &stop_kind,
-                                tape_out ? *tape_out : nullptr, 0, o.launch_mode == 1);
+                                tape_out ? *tape_out : nullptr, 0, per_sub);
     if (tape_out) (*tape_out)->K = it_end;
   }
   GB_HIP(hipEventRecord(t_loop.b, s));
@@ -2950,7 +2977,7 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
   // (only with check_idem: the trace-based FP64 stop test above is the default check)
   if (!rows_final) ensure_xd();
   const double* xfin = rows_final ? rows_final : xd;
-  const int64_t* foffs = rows_final ? cr.soffs.get() : offs.get();
+  const int64_t* foffs = rows_final ? cr.soffs.get() : offs;
   DBuf<int4> idem_tiles;
   DBuf<double> per, mx;
   if (o.check_idem) {
@@ -2959,20 +2986,20 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
       GB_HIP(hipMemcpyAsync(idem_tiles.get(), pl.idem.data(), pl.idem.size() * sizeof(int4),
                             hipMemcpyHostToDevice, s));
       launch_square<double>(xd, sd, idem_tiles.get(), one_group(128, (int)pl.idem.size()),
-                            offs.get(), s);
+                            offs, s);
     }
     const double* sfin = rows_final ? rows_check : sd;
     per = DBuf<double>(pl.n_sub, s);
     mx = DBuf<double>(1, s);
     hipLaunchKernelGGL(k_idem<double>, dim3(pl.n_sub), dim3(kT), 0, s, xfin, sfin, foffs,
-                       npad.get(), P.core_ptr.get(), P.sub_ptr.get(), per.get());
+                       npad, P.core_ptr.get(), P.sub_ptr.get(), per.get());
     GB_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_max, dim3(1), dim3(kT), 0, s, per.get(), pl.n_sub, mx.get());
     GB_LAUNCH_CHECK();
   }
   // scatter
   GB_HIP(hipEventRecord(t_scat.a, s));
-  hipLaunchKernelGGL(k_scatter<double>, dim3(N), dim3(kT), 0, s, xfin, foffs, npad.get(),
+  hipLaunchKernelGGL(k_scatter<double>, dim3(N), dim3(kT), 0, s, xfin, foffs, npad,
                      P.sub_ptr.get(), P.sub_idx.get(), P.sub_pos.get(), P.col_sub.get(),
                      P.col_loc.get(), D.width, D.col, D.val);
   GB_LAUNCH_CHECK();
