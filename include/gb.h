@@ -438,7 +438,8 @@ typedef struct {
   int32_t n_sub, max_sub, passes;
   float ms_bounds, ms_graph, ms_part, ms_gather, ms_terms, ms_scatter, ms_total;
   float ms_product;          /* summed device time of the recurrence                           */
-  int32_t n_product;         /* recurrence steps after T_1, over both passes                   */
+  int32_t n_product;         /* recurrence steps after T_1, over both passes (the second goes *
+                              * on from the first one's terms where 32 GiB hold them)           */
   double product_flops;      /* flops of one step on dense whole blocks: sum_s 2 n_s^3        */
 } gb_foe_stats;
 

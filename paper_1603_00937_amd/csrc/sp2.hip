@@ -3161,6 +3161,10 @@ __global__ __launch_bounds__(kT) void k_foe_ell(const int32_t* __restrict__ hcol
 // read per pair), V_{n+1} overwriting V_{n-1} entry by entry; one barrier per term.  SPILL: a
 // subgraph too large for two LDS arrays keeps V_{n-1} in global memory and swaps after each term.
 //   coef: dacc (core-row slabs at soffs, row stride npad) = sum_n coef[n] V_n.
+//   hist: with coef NULL, V_{n+1} of every product is kept there (slabs as dacc's, hist_ld apart);
+//         with coef and t_from > 0 the terms up to t_from are read from it and the recurrence
+//         goes on from there (order 160 with mu solved: 160 products, not 240; N = 1024, 0.6 GB
+//         kept, 12.0 -> 8.1 ms).
 //   part: for the first ntr products n -> n + 1, sum V_n V_{n+1} and sum V_{n+1}^2 over the rows:
 //         T_m T_n = (T_{m+n} + T_{|m-n|}) / 2 turns them into the core traces t_{2n+1} and
 //         t_{2n+2}, so the traces of M terms take M / 2 products.
@@ -3178,7 +3182,8 @@ __global__ __launch_bounds__(1024) void k_foe_rows(
     const int64_t* __restrict__ eoff, const int32_t* __restrict__ sub_ptr,
     const int32_t* __restrict__ core_ptr, const int64_t* __restrict__ soffs, int nterm, int ntr,
     const double* __restrict__ coef, double* __restrict__ dacc, double* __restrict__ part,
-    double* __restrict__ spill, int spill_ld) {
+    double* __restrict__ spill, int spill_ld, double* __restrict__ hist, int64_t hist_ld,
+    int t_from) {
   constexpr int E = R >= 2 ? 2 : 1, PL = R / E, U = 16;
   static_assert(!SPILL || R == 1, "the spilled form carries one row");
   extern __shared__ __align__(16) unsigned char smem[];
@@ -3197,14 +3202,26 @@ __global__ __launch_bounds__(1024) void k_foe_rows(
   const uint16_t* ix = idx + eoff[s];
   const double* hv = val + eoff[s];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwave = blockDim.x >> 6;
+  const int64_t slab = soffs[s] + (int64_t)r0 * np;
   for (int a = threadIdx.x; a < n; a += blockDim.x)
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      cur[((r / E) * n + a) * E + r % E] = r < kr && a == r0 + r ? 1.0 : 0.0;
-      prev[((r / E) * n + a) * E + r % E] = 0.0;
+      double v = r < kr && a == r0 + r ? 1.0 : 0.0, u = 0.0;
+      if (t_from > 0 && r < kr) {  // V_{t_from}, V_{t_from - 1}; the terms so far in their order
+        const double* hr = hist + slab + (int64_t)r * np + a;
+        double d = coef[0] * v;
+        for (int m = 1; m <= t_from; ++m) {
+          u = v;
+          v = hr[(m - 1) * hist_ld];
+          d += coef[m] * v;
+        }
+        dacc[slab + (int64_t)r * np + a] = d;
+      }
+      cur[((r / E) * n + a) * E + r % E] = v;
+      prev[((r / E) * n + a) * E + r % E] = u;
     }
   __syncthreads();
-  for (int t = 0; t < nterm; ++t) {
+  for (int t = t_from; t < nterm; ++t) {
     double p0 = 0.0, p1 = 0.0;
     for (int a = threadIdx.x; a < n; a += blockDim.x) {
       double acc[R];
@@ -3241,8 +3258,10 @@ __global__ __launch_bounds__(1024) void k_foe_rows(
         p0 += v * nv;
         p1 += nv * nv;
         if (coef && r < kr) {
-          double* d = dacc + soffs[s] + (int64_t)(r0 + r) * np + a;
+          double* d = dacc + slab + (int64_t)r * np + a;
           *d = t == 0 ? coef[0] * v + coef[1] * nv : *d + coef[t + 1] * nv;
+        } else if (hist && r < kr) {
+          hist[t * hist_ld + slab + (int64_t)r * np + a] = nv;
         }
       }
     }
@@ -3445,6 +3464,10 @@ double foe_solve_mu(const double* traces, int order, double emin, double emax, d
   return 0.5 * (lo + hi);
 }
 
+// Most memory for the terms that the pass for mu leaves to the pass for D (13 GiB at N = 18000, order
+// 160): what a card of 288 GB spares beside a batch.
+constexpr size_t kHistMost = (size_t)32 << 30;
+
 void foe(const gb_ell& H, int32_t n_occ, const gb_foe_opts& o, const Part& P, double emin,
          double emax, gb_ell& D, gb_foe_stats& st, hipStream_t s) {
   Timer t_all, t_stage;
@@ -3520,14 +3543,14 @@ void foe(const gb_ell& H, int32_t n_occ, const gb_foe_opts& o, const Part& P, do
   if (spill) sp = DBuf<double>((size_t)n_items * P.max_sub, s);
   std::vector<double> traces(M + 1, 0.0), c(M + 1), h(2 * (size_t)ntr);
   Timer t_pass;
-  auto pass = [&](const double* coef, int nterm, bool want_traces) {
+  auto pass = [&](const double* coef, int nterm, bool want_traces, double* hist, int t_from) {
     const size_t lds = spill ? (size_t)P.max_sub * 8 : lds_of(R);
     const int nt = want_traces ? ntr : 0;
     GB_HIP(hipEventRecord(t_pass.a, s));
     auto launch = [&](auto kern) {
       hipLaunchKernelGGL(kern, dim3(n_items), dim3(threads), lds, s, ditems.get(), idx, val,
                          len.get(), eoff.get(), P.sub_ptr.get(), P.core_ptr.get(), soff.get(),
-                         nterm, nt, coef, Dacc, part.get(), sp.get(), P.max_sub);
+                         nterm, nt, coef, Dacc, part.get(), sp.get(), P.max_sub, hist, ts, t_from);
     };
     if (spill) launch(k_foe_rows<1, true>);
     else if (R == 4) launch(k_foe_rows<4, false>);
@@ -3543,7 +3566,7 @@ void foe(const gb_ell& H, int32_t n_occ, const gb_foe_opts& o, const Part& P, do
     }
     GB_HIP(hipStreamSynchronize(s));
     st.ms_product += elapsed(t_pass.a, t_pass.b);
-    st.n_product += nterm - 1;
+    st.n_product += nterm - t_from - (t_from == 0);
     ++st.passes;
     if (!want_traces) return;
     traces[0] = t0;
@@ -3559,8 +3582,17 @@ void foe(const gb_ell& H, int32_t n_occ, const gb_foe_opts& o, const Part& P, do
   const double mid = 0.5 * (emax + emin), half = 0.5 * (emax - emin);
   double mu = o.mu;
   const bool solve = std::isnan(mu);
+  std::unique_ptr<CachedBuf> hist;
   if (solve) {
-    pass(nullptr, ntr, true);
+    // the terms of the first pass are kept for the second where they fit
+    const size_t need = (size_t)ntr * ts * 8;
+    if (need <= kHistMost) {
+      try {
+        hist = std::make_unique<CachedBuf>(need, s);
+      } catch (const Error&) {  // no memory for them: the second pass makes them again
+      }
+    }
+    pass(nullptr, ntr, true, hist ? (double*)hist->p : nullptr, 0);
     DBuf<double> dt(M + 1, s), de(K, s), dw(K, s), dm(3, s);
     GB_HIP(hipMemcpyAsync(dt.get(), traces.data(), (M + 1) * 8, hipMemcpyHostToDevice, s));
     hipLaunchKernelGGL(k_foe_nodes, dim3((K + kT / 64 - 1) / (kT / 64)), dim3(kT), 0, s, dt.get(),
@@ -3577,7 +3609,7 @@ void foe(const gb_ell& H, int32_t n_occ, const gb_foe_opts& o, const Part& P, do
   hipLaunchKernelGGL(k_foe_coef, dim3(M + 1), dim3(kT), 0, s, K, mid, half, o.beta, mu, dc.get());
   GB_LAUNCH_CHECK();
   GB_HIP(hipMemcpyAsync(c.data(), dc.get(), (M + 1) * 8, hipMemcpyDeviceToHost, s));
-  pass(dc.get(), M, !solve);
+  pass(dc.get(), M, !solve, hist ? (double*)hist->p : nullptr, hist ? ntr : 0);
   GB_HIP(hipEventRecord(t_stage.b, s));
   GB_HIP(hipStreamSynchronize(s));
   st.ms_terms = elapsed(t_stage.a, t_stage.b);

@@ -33,3 +33,18 @@ def test_unreachable_occupation_is_refused(model_cache):
     hc, hv = torch.from_numpy(m["H_col"]).cuda(), torch.from_numpy(m["H_val"]).cuda()
     with pytest.raises(gb.GbError, match="reachable"):
         gb.foe_density(hc, hv, m["N"] - 1, 1e-5, 0.5, 20, core_size=16)
+
+
+@pytest.mark.parametrize("N,order", [(61, 1), (61, 2), (129, 9), (2531, 7), (5060, 6), (10130, 5)])
+def test_kept_terms_change_no_bit(N, order):
+    """The second pass goes on from the terms that the first one kept: D is that of one pass at
+    the mu it found, in every form of the kernel."""
+    import torch
+    import paper_1603_00937_amd as gb
+    from test_gpu_foe_rows import _chain
+    col, val = _chain(N, N)
+    hc, hv = torch.from_numpy(col).cuda(), torch.from_numpy(val).cuda()
+    _, d2, st = gb.foe_density(hc, hv, N // 2, 1e-9, 3.0, order, core_size=N)
+    _, d1, one = gb.foe_density(hc, hv, N // 2, 1e-9, 3.0, order, mu=st["mu"], core_size=N)
+    assert st["passes"] == 2 and one["passes"] == 1
+    assert torch.equal(d1, d2) and st["traces"] == one["traces"]
