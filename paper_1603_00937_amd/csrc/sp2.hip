@@ -3103,57 +3103,95 @@ namespace {
 // workgroup carries R core rows of one subgraph through the whole recurrence with V_n and V_{n-1}
 // in LDS, and the only traffic of a term is Ht's entries on the subgraph.
 //
-// Those entries, per subgraph: slot t of local column a at eoff[s] + t npad + a (a's entries in
-// H's slot order, so a wave of consecutive columns reads consecutive words), the local index of
-// the other end as 16 bits (a subgraph is limited to about 13600 vertices by the gather's LDS)
-// and Ht = (2h - (e_max + e_min) delta) / (e_max - e_min); len counts a column's slots.
+// Those entries, per subgraph, for pairs of neighbouring columns 2p and 2p + 1 (two orbitals of a
+// site, as a rule, which couple to the same others): slot t of pair p at eoff[s] + t npad / 2 + p
+// (a wave of consecutive pairs reads consecutive words) holds the local index of the other end as
+// 16 bits (a subgraph is limited to about 13600 vertices by the gather's LDS) and both values of
+// Ht = (2h - (e_max + e_min) delta) / (e_max - e_min), zero where a column has no such entry;
+// len counts a pair's slots: those of column 2p in H's slot order, then what only 2p + 1 has.
+// A wave per pair, lanes side by side in a row of H; pos tells column 2p + 1 which slot its entry
+// has, where that slot confirms it (so it needs no initial value).  N = 1024: 0.39 ms with
+// a thread per column, 0.16 ms.
+constexpr int kPairsPerBlock = 16;
+constexpr int kFoePad = 8;  // slots come in groups of this many, the last one filled with zeros
 __global__ __launch_bounds__(kT) void k_foe_ell(const int32_t* __restrict__ hcol,
                                                 const double* __restrict__ hval, int w, double emin,
                                                 double emax, const int32_t* __restrict__ core_ptr,
                                                 const int32_t* __restrict__ sub_ptr,
                                                 const int32_t* __restrict__ sub_idx,
                                                 const int64_t* __restrict__ eoff,
-                                                const int32_t* __restrict__ npad,
-                                                uint16_t* __restrict__ idx, double* __restrict__ val,
-                                                int32_t* __restrict__ len) {
+                                                const int32_t* __restrict__ npad, uint16_t* idx,
+                                                double* val, int32_t* __restrict__ len) {
   extern __shared__ __align__(16) unsigned char smem[];
   int32_t* sub = reinterpret_cast<int32_t*>(smem);
   const int s = blockIdx.x;
-  const int b = sub_ptr[s], n = sub_ptr[s + 1] - b;
-  if ((int)blockIdx.y * kT >= n) return;  // the whole workgroup leaves together
-  const int k = core_ptr[s + 1] - core_ptr[s];
-  for (int a = threadIdx.x; a < n; a += kT) sub[a] = sub_idx[b + a];
+  const int b = sub_ptr[s], n = sub_ptr[s + 1] - b, n2 = (n + 1) / 2;
+  if ((int)blockIdx.y * kPairsPerBlock >= n2) return;  // the whole workgroup leaves together
+  const int k = core_ptr[s + 1] - core_ptr[s], hp = npad[s] / 2;
+  for (int a = threadIdx.x; a < n; a += blockDim.x) sub[a] = sub_idx[b + a];
   __syncthreads();
-  const int a = blockIdx.y * kT + threadIdx.x;
-  if (a >= n) return;
-  const int i = sub[a], np = npad[s];
-  int64_t q = eoff[s] + a;
-  int m = 0;
-  for (int t = 0; t < w; ++t) {
-    const int32_t j = hcol[(int64_t)i * w + t];
-    if (j < 0) continue;
-    int lo = 0, hi = k;  // j in the core run [0, k), else in the halo run [k, n)
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, waves = blockDim.x >> 6;
+  uint16_t* pos = reinterpret_cast<uint16_t*>(sub + n) + (int64_t)wave * n;
+  // local index of vertex j: in the core run [0, k) or the halo run [k, n), both ascending; or -1
+  auto local = [&](int32_t j) {
+    int lo = 0, hi = k;
     while (lo < hi) {
       const int mid = (lo + hi) >> 1;
       if (sub[mid] < j) lo = mid + 1;
       else hi = mid;
     }
-    if (lo == k || sub[lo] != j) {
-      lo = k;
-      hi = n;
-      while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (sub[mid] < j) lo = mid + 1;
-        else hi = mid;
-      }
-      if (lo == n || sub[lo] != j) continue;
+    if (lo < k && sub[lo] == j) return lo;
+    lo = k;
+    hi = n;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (sub[mid] < j) lo = mid + 1;
+      else hi = mid;
     }
-    idx[q] = (uint16_t)lo;
-    val[q] = (2.0 * hval[(int64_t)i * w + t] - (j == i ? emax + emin : 0.0)) / (emax - emin);
-    q += np;
-    ++m;
+    return lo < n && sub[lo] == j ? lo : -1;
+  };
+  const int end = min(n2, ((int)blockIdx.y + 1) * kPairsPerBlock);
+  for (int p = blockIdx.y * kPairsPerBlock + wave; p < end; p += waves) {
+    uint16_t* ip = idx + eoff[s] + p;
+    double* vp = val + 2 * (eoff[s] + p);
+    int m = 0, m0 = 0;
+    for (int x = 0; x < 2 && 2 * p + x < n; ++x) {
+      const int i = sub[2 * p + x];
+      for (int t0 = 0; t0 < w; t0 += 64) {
+        const int t = t0 + lane;
+        const int32_t j = t < w ? hcol[(int64_t)i * w + t] : -1;
+        const int loc = j < 0 ? -1 : local(j);
+        double h = 0.0;
+        int at = -1;  // the slot that column 2p gave this entry
+        if (loc >= 0) {
+          h = (2.0 * hval[(int64_t)i * w + t] - (j == i ? emax + emin : 0.0)) / (emax - emin);
+          if (x == 1) {
+            const int q = pos[loc];
+            if (q < m0 && ip[(int64_t)q * hp] == loc) at = q;
+          }
+        }
+        const uint64_t fresh = __ballot(loc >= 0 && at < 0);
+        if (loc >= 0 && at < 0) {
+          const int q = m + __popcll(fresh & ((1ull << lane) - 1));
+          ip[(int64_t)q * hp] = (uint16_t)loc;
+          vp[2 * (int64_t)q * hp + x] = h;
+          vp[2 * (int64_t)q * hp + 1 - x] = 0.0;
+          if (x == 0) pos[loc] = (uint16_t)q;
+        } else if (loc >= 0) {
+          vp[2 * (int64_t)at * hp + 1] = h;
+        }
+        m += __popcll(fresh);
+      }
+      if (x == 0) m0 = m;
+      __threadfence_block();  // column 2p + 1 reads pos and the slots, and overwrites their zeros
+    }
+    const int full = (m + kFoePad - 1) / kFoePad * kFoePad;
+    if (m + lane < full) {
+      ip[(int64_t)(m + lane) * hp] = 0;
+      vp[2 * (int64_t)(m + lane) * hp] = vp[2 * (int64_t)(m + lane) * hp + 1] = 0.0;
+    }
+    if (lane == 0) len[b + p] = full;
   }
-  len[b + a] = m;
 }
 
 // The recurrence of R core rows r0 .. r0 + R - 1 of one subgraph up to V_nterm (rows beyond the
@@ -3168,13 +3206,16 @@ __global__ __launch_bounds__(kT) void k_foe_ell(const int32_t* __restrict__ hcol
 //   part: for the first ntr products n -> n + 1, sum V_n V_{n+1} and sum V_{n+1}^2 over the rows:
 //         T_m T_n = (T_{m+n} + T_{|m-n|}) / 2 turns them into the core traces t_{2n+1} and
 //         t_{2n+2}, so the traces of M terms take M / 2 products.
-// What bounds it is LDS: every entry of Ht reads R doubles of V_n at a scattered column (N = 1024,
-// 64 subgraphs of ~900: LDS active 60 % of the time, half of that bank conflicts of the scattered
-// reads).  R = 4 takes 10 bytes of Ht per four products; R = 2 took 20.7 ms where R = 4 takes
-// 14.2 ms (order 160, mu solved, whole call), and sixteen entries in flight per thread 14.0 ms
-// against 14.2 (eight) and 15.0 (four).  42 us per term; as full products of whole blocks (each
-// term 2 n^3 flops and five passes over the batch) a term took 2.2 ms and the call 743 ms.
-// N = 18000 (565 subgraphs of ~1200): 0.94 ms per term against 57.6.
+// What bounds it is LDS: an entry of Ht reads R doubles of V_n at a scattered column (N = 1024,
+// 64 subgraphs of ~900: LDS active 72 % of the time, 61 % of that bank conflicts of the scattered
+// reads).  So a thread takes two columns that couple to the same others, which halves the reads,
+// and R = 4 rows: eight products for two reads and 18 bytes of Ht.  The lists are filled up with
+// zeros to groups of U slots: a slot's address is then the wave's plus the lane's pair, where a
+// test per slot cost more instructions than the products (4.77 against 5.35 ms).  Order 160 at
+// N = 1024 (whole call) 8.1 -> 5.0 ms against a column per thread, 28 us per term (as full
+// products of whole blocks, each term 2 n^3 flops and five passes over the batch, 2.2 ms); N = 18000
+// (565 subgraphs of ~1200) 140 -> 86 ms, 0.52 ms per term (57.6); U = 4 5.3 and 88 ms, U = 16 5.1
+// and 87; workgroups of at most 512 threads 108 ms at N = 18000.
 template <int R, bool SPILL>
 __global__ __launch_bounds__(1024) void k_foe_rows(
     const int4* __restrict__ items, const uint16_t* __restrict__ idx,
@@ -3184,7 +3225,7 @@ __global__ __launch_bounds__(1024) void k_foe_rows(
     const double* __restrict__ coef, double* __restrict__ dacc, double* __restrict__ part,
     double* __restrict__ spill, int spill_ld, double* __restrict__ hist, int64_t hist_ld,
     int t_from) {
-  constexpr int E = R >= 2 ? 2 : 1, PL = R / E, U = 16;
+  constexpr int E = R >= 2 ? 2 : 1, PL = R / E, U = kFoePad;
   static_assert(!SPILL || R == 1, "the spilled form carries one row");
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ double red[2][2][16];
@@ -3200,7 +3241,8 @@ __global__ __launch_bounds__(1024) void k_foe_rows(
   double* cur = reinterpret_cast<double*>(smem);
   double* prev = SPILL ? spill + (int64_t)blockIdx.x * spill_ld : cur + R * n;
   const uint16_t* ix = idx + eoff[s];
-  const double* hv = val + eoff[s];
+  const double* hv = val + 2 * eoff[s];
+  const int hp = np / 2;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwave = blockDim.x >> 6;
   const int64_t slab = soffs[s] + (int64_t)r0 * np;
   for (int a = threadIdx.x; a < n; a += blockDim.x)
@@ -3223,20 +3265,19 @@ __global__ __launch_bounds__(1024) void k_foe_rows(
   __syncthreads();
   for (int t = t_from; t < nterm; ++t) {
     double p0 = 0.0, p1 = 0.0;
-    for (int a = threadIdx.x; a < n; a += blockDim.x) {
-      double acc[R];
+    for (int p2 = threadIdx.x; 2 * p2 < n; p2 += blockDim.x) {
+      double acc[2][R];
 #pragma unroll
-      for (int r = 0; r < R; ++r) acc[r] = 0.0;
-      const int L = len[b + a];
+      for (int r = 0; r < R; ++r) acc[0][r] = acc[1][r] = 0.0;
+      const int L = len[b + p2];
       for (int q = 0; q < L; q += U) {
-        double h[U];
+        double h[U][2];
         int c[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {  // past the end: an entry that is there, times zero
-          const bool in = q + u < L;
-          const uint32_t e = (uint32_t)(in ? q + u : 0) * (uint32_t)np + (uint32_t)a;
-          c[u] = ix[e];
-          h[u] = in ? hv[e] : 0.0;
+        for (int u = 0; u < U; ++u) {  // the slot's row is the wave's, the pair the lane's
+          const int64_t row = (int64_t)(q + u) * hp;
+          c[u] = (ix + row)[p2];
+          __builtin_memcpy(h[u], __builtin_assume_aligned(hv + 2 * row + 2 * p2, 16), 16);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u)
@@ -3245,23 +3286,30 @@ __global__ __launch_bounds__(1024) void k_foe_rows(
             double v[E];
             __builtin_memcpy(v, __builtin_assume_aligned(cur + (p * n + c[u]) * E, 8 * E), 8 * E);
 #pragma unroll
-            for (int x = 0; x < E; ++x)
-              acc[p * E + x] = __builtin_fma(v[x], h[u], acc[p * E + x]);
+            for (int x = 0; x < E; ++x) {
+              acc[0][p * E + x] = __builtin_fma(v[x], h[u][0], acc[0][p * E + x]);
+              acc[1][p * E + x] = __builtin_fma(v[x], h[u][1], acc[1][p * E + x]);
+            }
           }
       }
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int o = ((r / E) * n + a) * E + r % E;
-        const double v = cur[o];
-        const double nv = t == 0 ? acc[r] : 2.0 * acc[r] - prev[o];
-        prev[o] = nv;
-        p0 += v * nv;
-        p1 += nv * nv;
-        if (coef && r < kr) {
-          double* d = dacc + slab + (int64_t)r * np + a;
-          *d = t == 0 ? coef[0] * v + coef[1] * nv : *d + coef[t + 1] * nv;
-        } else if (hist && r < kr) {
-          hist[t * hist_ld + slab + (int64_t)r * np + a] = nv;
+      for (int y = 0; y < 2; ++y) {
+        const int a = 2 * p2 + y;
+        if (a >= n) break;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const int o = ((r / E) * n + a) * E + r % E;
+          const double v = cur[o];
+          const double nv = t == 0 ? acc[y][r] : 2.0 * acc[y][r] - prev[o];
+          prev[o] = nv;
+          p0 += v * nv;
+          p1 += nv * nv;
+          if (coef && r < kr) {
+            double* d = dacc + slab + (int64_t)r * np + a;
+            *d = t == 0 ? coef[0] * v + coef[1] * nv : *d + coef[t + 1] * nv;
+          } else if (hist && r < kr) {
+            hist[t * hist_ld + slab + (int64_t)r * np + a] = nv;
+          }
         }
       }
     }
@@ -3477,6 +3525,7 @@ void foe(const gb_ell& H, int32_t n_occ, const gb_foe_opts& o, const Part& P, do
   std::vector<int32_t> np(P.n_sub);
   std::vector<int64_t> eo(P.n_sub), so(P.n_sub);
   std::vector<int> order(P.n_sub);
+  const int slots = (2 * w + kFoePad - 1) / kFoePad * kFoePad;  // of a pair, at most
   int64_t te = 0, ts = 0;
   int max_np = 0;
   double t0 = 0;  // t_0 = sum of the core sizes
@@ -3486,7 +3535,7 @@ void foe(const gb_ell& H, int32_t n_occ, const gb_foe_opts& o, const Part& P, do
     max_np = std::max(max_np, np[q]);
     eo[q] = te;
     so[q] = ts;
-    te += (int64_t)np[q] * w;
+    te += (int64_t)(np[q] / 2) * slots;
     ts += (int64_t)np[q] * k;
     t0 += k;
     order[q] = q;
@@ -3523,11 +3572,15 @@ void foe(const gb_ell& H, int32_t n_occ, const gb_foe_opts& o, const Part& P, do
 
   GB_HIP(hipEventRecord(t_stage.a, s));
   WsLease ws;  // cached buffers: Ht's entries on the subgraphs, the core rows of D
-  double* const val = ws->get<double>(0, te, s);
+  double* const val = ws->get<double>(0, 2 * te, s);
   uint16_t* const idx = ws->get<uint16_t>(1, te, s);
   double* const Dacc = ws->get<double>(2, ts, s);
-  hipLaunchKernelGGL(k_foe_ell, dim3(P.n_sub, (P.max_sub + kT - 1) / kT), dim3(kT),
-                     (size_t)P.max_sub * 4, s, H.col, H.val, w, emin, emax, P.core_ptr.get(),
+  const size_t lds_ell = (size_t)P.max_sub * 4;
+  const int ell_waves = lds_ell + 4 * (size_t)P.max_sub * 2 <= lds_max ? 4 : 2;
+  hipLaunchKernelGGL(k_foe_ell,
+                     dim3(P.n_sub, ((P.max_sub + 1) / 2 + kPairsPerBlock - 1) / kPairsPerBlock),
+                     dim3(64 * ell_waves), lds_ell + ell_waves * (size_t)P.max_sub * 2, s,
+                     H.col, H.val, w, emin, emax, P.core_ptr.get(),
                      P.sub_ptr.get(), P.sub_idx.get(), eoff.get(), npad.get(), idx, val,
                      len.get());
   GB_LAUNCH_CHECK();
@@ -3535,8 +3588,10 @@ void foe(const gb_ell& H, int32_t n_occ, const gb_foe_opts& o, const Part& P, do
   GB_HIP(hipStreamSynchronize(s));
   st.ms_gather = elapsed(t_stage.a, t_stage.b);
 
-  // a column per thread where a workgroup holds that many, else as few equal rounds as possible
-  const int waves = (P.max_sub + 63) / 64, rounds = (waves + 15) / 16;
+  // a pair of columns per thread where a workgroup holds that many, else as few equal rounds as
+  // possible
+  const int waves = ((P.max_sub + 1) / 2 + 63) / 64, most = 16;
+  const int rounds = (waves + most - 1) / most;
   const int threads = 64 * ((waves + rounds - 1) / rounds);
   const int ntr = (M + 1) / 2;  // products that give the traces t_1 .. t_M
   DBuf<double> part((size_t)n_items * 2 * ntr, s), sums(2 * (size_t)ntr, s), dc(M + 1, s), sp;
