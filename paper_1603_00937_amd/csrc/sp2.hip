@@ -3108,20 +3108,32 @@ namespace {
 // (a wave of consecutive pairs reads consecutive words) holds the local index of the other end as
 // 16 bits (a subgraph is limited to about 13600 vertices by the gather's LDS) and both values of
 // Ht = (2h - (e_max + e_min) delta) / (e_max - e_min), zero where a column has no such entry;
-// len counts a pair's slots: those of column 2p in H's slot order, then what only 2p + 1 has.
-// A wave per pair, lanes side by side in a row of H; pos tells column 2p + 1 which slot its entry
-// has, where that slot confirms it (so it needs no initial value).  N = 1024: 0.39 ms with
-// a thread per column, 0.16 ms.
+// len counts a pair's slots, in whole groups of kFoePad, the last one filled with zeros.
+//
+// Which slot an entry takes decides the bank conflicts of the recurrence: LDS serves a 16-byte
+// read sixteen lanes at a time from sixteen banks, and slot q of sixteen pairs names sixteen
+// scattered columns, 2.6 clocks' worth where one would do.  So the r-th entry of each residue c mod
+// 16 takes slot 16 r + (c - g) mod 16, g being the pair's rank among the sixteen: slot q then reads
+// bank q + g.  Entries past the end fill the holes that short residues leave (conflicts down by
+// three quarters; N = 1024 4.51 -> 4.11 ms of recurrence for 0.13 ms of sorting).
+// A wave per pair, lanes side by side in a row of H (a thread per column took 0.39 ms; now 0.29 with
+// the order, 0.16 without).
+constexpr int kFoePad = 8;
+__device__ inline int lane_value(int v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
+// Rank of a lane among the sixteen that a 16-byte LDS read serves together (lanes 0-3, 12-15, 20-23,
+// 24-27, then 4-7, 8-11, 16-19, 28-31, and the same of the upper half).
+__device__ __forceinline__ int lds_rank(int lane) { return (lane & 31) / 8 * 4 + (lane & 3); }
 constexpr int kPairsPerBlock = 16;
-constexpr int kFoePad = 8;  // slots come in groups of this many, the last one filled with zeros
 __global__ __launch_bounds__(kT) void k_foe_ell(const int32_t* __restrict__ hcol,
                                                 const double* __restrict__ hval, int w, double emin,
                                                 double emax, const int32_t* __restrict__ core_ptr,
                                                 const int32_t* __restrict__ sub_ptr,
                                                 const int32_t* __restrict__ sub_idx,
                                                 const int64_t* __restrict__ eoff,
-                                                const int32_t* __restrict__ npad, uint16_t* idx,
-                                                double* val, int32_t* __restrict__ len) {
+                                                const int32_t* __restrict__ npad,
+                                                uint16_t* __restrict__ idx,
+                                                double* __restrict__ val,
+                                                int32_t* __restrict__ len, int ordered) {
   extern __shared__ __align__(16) unsigned char smem[];
   int32_t* sub = reinterpret_cast<int32_t*>(smem);
   const int s = blockIdx.x;
@@ -3131,7 +3143,12 @@ __global__ __launch_bounds__(kT) void k_foe_ell(const int32_t* __restrict__ hcol
   for (int a = threadIdx.x; a < n; a += blockDim.x) sub[a] = sub_idx[b + a];
   __syncthreads();
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, waves = blockDim.x >> 6;
-  uint16_t* pos = reinterpret_cast<uint16_t*>(sub + n) + (int64_t)wave * n;
+  // per wave: pos[n]; where the order is chosen, cl[2w] (local indices, then slots), hl[2w], ul[2w]
+  const int cap = ordered ? 2 * w : 0;
+  uint16_t* pos = reinterpret_cast<uint16_t*>(sub + n) + (int64_t)wave * (n + 2 * cap + (cap + 1) / 2);
+  uint16_t *cl = pos + n, *hl = cl + cap;
+  uint8_t* ul = reinterpret_cast<uint8_t*>(hl + cap);
+  const uint64_t below = (1ull << lane) - 1;
   // local index of vertex j: in the core run [0, k) or the halo run [k, n), both ascending; or -1
   auto local = [&](int32_t j) {
     int lo = 0, hi = k;
@@ -3154,43 +3171,88 @@ __global__ __launch_bounds__(kT) void k_foe_ell(const int32_t* __restrict__ hcol
   for (int p = blockIdx.y * kPairsPerBlock + wave; p < end; p += waves) {
     uint16_t* ip = idx + eoff[s] + p;
     double* vp = val + 2 * (eoff[s] + p);
-    int m = 0, m0 = 0;
+    for (int a = lane; a < n; a += 64) pos[a] = 0xffff;
+    __threadfence_block();
+    // the pair's list: what column 2p couples to, then what only 2p + 1 does
+    int m = 0;
     for (int x = 0; x < 2 && 2 * p + x < n; ++x) {
       const int i = sub[2 * p + x];
       for (int t0 = 0; t0 < w; t0 += 64) {
         const int t = t0 + lane;
         const int32_t j = t < w ? hcol[(int64_t)i * w + t] : -1;
         const int loc = j < 0 ? -1 : local(j);
-        double h = 0.0;
-        int at = -1;  // the slot that column 2p gave this entry
-        if (loc >= 0) {
-          h = (2.0 * hval[(int64_t)i * w + t] - (j == i ? emax + emin : 0.0)) / (emax - emin);
-          if (x == 1) {
-            const int q = pos[loc];
-            if (q < m0 && ip[(int64_t)q * hp] == loc) at = q;
-          }
+        const bool fresh = loc >= 0 && (x == 0 || pos[loc] == 0xffff);
+        const uint64_t mask = __ballot(fresh);
+        if (fresh) {
+          const int q = m + __popcll(mask & below);
+          pos[loc] = (uint16_t)q;
+          if (ordered) cl[q] = (uint16_t)loc;
         }
-        const uint64_t fresh = __ballot(loc >= 0 && at < 0);
-        if (loc >= 0 && at < 0) {
-          const int q = m + __popcll(fresh & ((1ull << lane) - 1));
-          ip[(int64_t)q * hp] = (uint16_t)loc;
-          vp[2 * (int64_t)q * hp + x] = h;
-          vp[2 * (int64_t)q * hp + 1 - x] = 0.0;
-          if (x == 0) pos[loc] = (uint16_t)q;
-        } else if (loc >= 0) {
-          vp[2 * (int64_t)at * hp + 1] = h;
-        }
-        m += __popcll(fresh);
+        m += __popcll(mask);
       }
-      if (x == 0) m0 = m;
-      __threadfence_block();  // column 2p + 1 reads pos and the slots, and overwrites their zeros
+      __threadfence_block();
     }
+    if (ordered) {
+      // slot 16 r + (c - g) mod 16 for the r-th entry of residue c mod 16, where that is below m;
+      // the others fill the holes
+      const int g = lds_rank(p & 63);
+      int count = 0;  // of residue `lane`
+      for (int q0 = 0; q0 < m; q0 += 64) {
+        const int q = q0 + lane, c = q < m ? cl[q] & 15 : -1;
+        int r = 0;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const uint64_t mask = __ballot(c == e);
+          const int had = lane_value(count, e);
+          if (c == e) r = had + __popcll(mask & below);
+          if (lane == e) count += __popcll(mask);
+        }
+        if (q < m) cl[q] = (uint16_t)(16 * r + ((c - g) & 15));
+      }
+      for (int t = lane; t < m; t += 64) ul[t] = 0;
+      __threadfence_block();
+      for (int q = lane; q < m; q += 64)
+        if (cl[q] < m) ul[cl[q]] = 1;
+      __threadfence_block();
+      int holes = 0;
+      for (int t0 = 0; t0 < m; t0 += 64) {
+        const bool hole = t0 + lane < m && !ul[t0 + lane];
+        const uint64_t mask = __ballot(hole);
+        if (hole) hl[holes + __popcll(mask & below)] = (uint16_t)(t0 + lane);
+        holes += __popcll(mask);
+      }
+      __threadfence_block();
+      int out = 0;
+      for (int q0 = 0; q0 < m; q0 += 64) {
+        const bool late = q0 + lane < m && cl[q0 + lane] >= m;
+        const uint64_t mask = __ballot(late);
+        if (late) cl[q0 + lane] = hl[out + __popcll(mask & below)];
+        out += __popcll(mask);
+      }
+      __threadfence_block();
+    }
+    // both columns' values over zeros, which also fill the last group
     const int full = (m + kFoePad - 1) / kFoePad * kFoePad;
-    if (m + lane < full) {
-      ip[(int64_t)(m + lane) * hp] = 0;
-      vp[2 * (int64_t)(m + lane) * hp] = vp[2 * (int64_t)(m + lane) * hp + 1] = 0.0;
+    for (int t = lane; t < full; t += 64) {
+      ip[(int64_t)t * hp] = 0;
+      vp[2 * (int64_t)t * hp] = vp[2 * (int64_t)t * hp + 1] = 0.0;
     }
     if (lane == 0) len[b + p] = full;
+    __threadfence_block();
+    for (int x = 0; x < 2 && 2 * p + x < n; ++x) {
+      const int i = sub[2 * p + x];
+      for (int t0 = 0; t0 < w; t0 += 64) {
+        const int t = t0 + lane;
+        const int32_t j = t < w ? hcol[(int64_t)i * w + t] : -1;
+        const int loc = j < 0 ? -1 : local(j);
+        if (loc < 0) continue;
+        const int q = ordered ? cl[pos[loc]] : pos[loc];
+        const double h =
+            (2.0 * hval[(int64_t)i * w + t] - (j == i ? emax + emin : 0.0)) / (emax - emin);
+        ip[(int64_t)q * hp] = (uint16_t)loc;
+        vp[2 * (int64_t)q * hp + x] = h;
+      }
+    }
   }
 }
 
@@ -3206,16 +3268,17 @@ __global__ __launch_bounds__(kT) void k_foe_ell(const int32_t* __restrict__ hcol
 //   part: for the first ntr products n -> n + 1, sum V_n V_{n+1} and sum V_{n+1}^2 over the rows:
 //         T_m T_n = (T_{m+n} + T_{|m-n|}) / 2 turns them into the core traces t_{2n+1} and
 //         t_{2n+2}, so the traces of M terms take M / 2 products.
-// What bounds it is LDS: an entry of Ht reads R doubles of V_n at a scattered column (N = 1024,
-// 64 subgraphs of ~900: LDS active 72 % of the time, 61 % of that bank conflicts of the scattered
-// reads).  So a thread takes two columns that couple to the same others, which halves the reads,
-// and R = 4 rows: eight products for two reads and 18 bytes of Ht.  The lists are filled up with
-// zeros to groups of U slots: a slot's address is then the wave's plus the lane's pair, where a
-// test per slot cost more instructions than the products (4.77 against 5.35 ms).  Order 160 at
-// N = 1024 (whole call) 8.1 -> 5.0 ms against a column per thread, 28 us per term (as full
-// products of whole blocks, each term 2 n^3 flops and five passes over the batch, 2.2 ms); N = 18000
-// (565 subgraphs of ~1200) 140 -> 86 ms, 0.52 ms per term (57.6); U = 4 5.3 and 88 ms, U = 16 5.1
-// and 87; workgroups of at most 512 threads 108 ms at N = 18000.
+// An entry of Ht reads R doubles of V_n in LDS at a scattered column, which bounded the recurrence
+// with a thread per column (LDS active 72 % of the time, mostly bank conflicts).  So a thread takes two
+// columns that couple to the same others, which halves the reads, the lists are ordered by bank
+// (above), and R = 4 rows share an entry: eight products for two reads and 18 bytes of Ht.  What
+// bounds it now is those bytes out of L2: with half the rows per workgroup, twice the bytes, the
+// recurrence takes 6.45 ms for 4.11.  Lists are whole groups of U slots, a slot's address the
+// wave's plus the lane's pair: a test per slot cost more instructions than the products (5.35 against
+// 4.77 ms).  Order 160 at N = 1024 (64 subgraphs of ~900; whole call) 8.1 -> 4.8 ms against a column
+// per thread, 26 us per term (as full products of whole blocks, each term 2 n^3 flops and five
+// passes over the batch, 2.2 ms); N = 18000 (565 subgraphs of ~1200) 140 -> 84 ms, 0.50 ms per term
+// (57.6).  U = 4 5.0, U = 16 4.9 ms; workgroups of at most 512 threads: N = 18000 105 ms.
 template <int R, bool SPILL>
 __global__ __launch_bounds__(1024) void k_foe_rows(
     const int4* __restrict__ items, const uint16_t* __restrict__ idx,
@@ -3544,10 +3607,18 @@ void foe(const gb_ell& H, int32_t n_occ, const gb_foe_opts& o, const Part& P, do
   if ((size_t)max_np * 8 + (size_t)P.max_sub * 4 + 64 > 160 * 1024)
     fail(GB_EUNSUPPORTED, "subgraph of %d vertices too large", P.max_sub);
   // rows per workgroup: as many as the LDS of one CU holds (see k_foe_rows), at most four; past
-  // ~9900 vertices not even one row's two arrays fit, and V_{n-1} goes to global memory
+  // ~9900 vertices not even one row's two arrays fit, and V_{n-1} goes to global memory.  Fewer
+  // rows while that leaves at most a workgroup per compute unit (N = 512, 128 groups of four rows:
+  // 2.99 -> 2.53 ms with two; N = 1024, 256 groups of four: 4.75 ms, with two 7.1)
   const size_t lds_max = 158 * 1024;
   auto lds_of = [&](int r) { return (size_t)2 * r * P.max_sub * 8; };
-  const int R = lds_of(4) <= lds_max ? 4 : lds_of(2) <= lds_max ? 2 : 1;
+  int R = lds_of(4) <= lds_max ? 4 : lds_of(2) <= lds_max ? 2 : 1;
+  auto groups = [&](int r) {
+    int64_t g = 0;
+    for (int q = 0; q < P.n_sub; ++q) g += (P.h_core_ptr[q + 1] - P.h_core_ptr[q] + r - 1) / r;
+    return g;
+  };
+  while (R > 1 && groups(R / 2) <= 256) R /= 2;
   const bool spill = lds_of(1) > lds_max;
   // workgroups per subgraph, largest subgraphs first, each subgraph's on one XCD (its entries of
   // Ht, ~2 MB at n ~ 1000, are read by all of them every term)
@@ -3575,14 +3646,28 @@ void foe(const gb_ell& H, int32_t n_occ, const gb_foe_opts& o, const Part& P, do
   double* const val = ws->get<double>(0, 2 * te, s);
   uint16_t* const idx = ws->get<uint16_t>(1, te, s);
   double* const Dacc = ws->get<double>(2, ts, s);
-  const size_t lds_ell = (size_t)P.max_sub * 4;
-  const int ell_waves = lds_ell + 4 * (size_t)P.max_sub * 2 <= lds_max ? 4 : 2;
+  // the kernel's LDS: the subgraph, and per wave the slots of its vertices and, where there is
+  // room for them, the lists that choose the order
+  auto lds_ell = [&](int waves, bool ordered) {
+    const size_t cap = ordered ? 2 * (size_t)w : 0;
+    return (size_t)P.max_sub * 4 + waves * 2 * (P.max_sub + 2 * cap + (cap + 1) / 2);
+  };
+  bool ordered = true;
+  int ell_waves = 4;
+  while (lds_ell(ell_waves, ordered) > lds_max) {
+    if (ell_waves > 1) {
+      ell_waves /= 2;
+    } else {
+      ell_waves = 4;
+      ordered = false;
+    }
+  }
   hipLaunchKernelGGL(k_foe_ell,
                      dim3(P.n_sub, ((P.max_sub + 1) / 2 + kPairsPerBlock - 1) / kPairsPerBlock),
-                     dim3(64 * ell_waves), lds_ell + ell_waves * (size_t)P.max_sub * 2, s,
+                     dim3(64 * ell_waves), lds_ell(ell_waves, ordered), s,
                      H.col, H.val, w, emin, emax, P.core_ptr.get(),
                      P.sub_ptr.get(), P.sub_idx.get(), eoff.get(), npad.get(), idx, val,
-                     len.get());
+                     len.get(), ordered ? 1 : 0);
   GB_LAUNCH_CHECK();
   GB_HIP(hipEventRecord(t_stage.b, s));
   GB_HIP(hipStreamSynchronize(s));
