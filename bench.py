@@ -160,7 +160,7 @@ def run_step(gb, Hc, Hv, n_occ, tau, core, D, args, times=None):
 def rocpd_summary(path):
     """Per-kernel summary of a rocprofv3 database (--kernel-trace): calls, total and average
     duration; for each kernel also its largest-grid working launches (the SP2 loop's batched
-    launches, not the autotuner's single-bucket ones nor the device-driven loop's launches past
+    launches, not the autotuner's nor the device-driven loop's launches past
     the stop, which return at once)."""
     import sqlite3
     c = sqlite3.connect(path)

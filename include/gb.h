@@ -47,8 +47,8 @@ typedef int32_t gb_status;
  * calls have freed.  gb_trim frees the cached buffers of every call that has returned. */
 gb_status gb_trim(void);
 
-/* Kernel-variant table of the autotuner (the tile edge, and for FP64 / FP32 the LDS staging,
- * chosen per 256-wide size bucket of padded subgraph sizes by timing each variant once; see
+/* Kernel-variant table of the autotuner (the split squares' kernel, chosen per size class of batches,
+ * powers of two of their tiles, by timing each variant once on the whole batch; see
  * gb_sp2_opts.tile_policy).  gb_tune_save writes the table of this process as JSON to `path`
  * (tagged with the library's source hash and the device: "libgb-tune-1" format); gb_tune_load
  * merges such a file into it, so a later process skips the timing runs.  A file written by
@@ -295,9 +295,9 @@ typedef struct {
                               * 3: batched launches, every decision read back by the host.    *
                               * keep_tape and refine_kind 1 run their steps as in 3.          */
   int32_t tile_policy;       /* kernel variant of the squares: 0 = split squares autotuned   *
-                              * per 256-wide size bucket (timed once per process or read from *
-                              * the tuning table), FP64 / FP32 squares on policy 5 (the       *
-                              * fastest measured in every bucket) or, in small batches, its   *
+                              * per size class of batches (timed once per process or read     *
+                              * from the tuning table), FP64 / FP32 squares on policy 5 (the   *
+                              * fastest measured at every size) or, in small batches, its   *
                               * 32-edge form (the same bits); 1 = 128-edge tiles, 2 =    *
                               * 64-edge; FP64 / FP32 squares                                   *
                               * also 4 = 64-edge with three LDS stages, 5 = 64-edge with      *

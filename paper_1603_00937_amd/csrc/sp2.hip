@@ -1918,10 +1918,10 @@ struct PinnedRec {
   }
 };
 
-// ---- autotuner: tile edge per size bucket ----------------------------------------------------
-// Subgraphs are bucketed by padded size (256-wide buckets).  The first time a bucket is seen
-// for a kind of square (0 FP64, 1 FP32, 10 + planes for the split squares), one squaring
-// launch of that bucket's blocks is timed with each kernel variant (one warm-up, two timed
+// ---- autotuner: kernel variant of the split squares ------------------------------------------
+// The first time a size class of batches is seen (tune_class; "bucket" in the table) for a kind of
+// square (10 + planes; 0 FP64 and 1 FP32 take fixed variants), one squaring launch of the whole
+// batch is timed with each kernel variant (one warm-up, two timed
 // launches each) and the fastest is kept.  The table lives for the process and can be kept in
 // a JSON file (gb_tune_save / gb_tune_load, or the GB_TUNE_FILE environment variable: read at
 // the first tuning, rewritten after every new entry), tagged with the library's source hash and
@@ -2038,68 +2038,57 @@ void tune_env_write() {
   if (path && *path) (void)tune_write(path);
 }
 
-// planes = 0: launch_square<T>; planes > 0 (T = float): the split squares, 128- or 64-edge tiles
-template <typename T>
-std::vector<int> tune_tiles(const Part& P, const Plan& pl, T* X, T* S, const int64_t* offs,
-                            hipStream_t s, int kind, bool xcd, int planes = 0) {
-  std::vector<int> bt(pl.n_sub, kBT);
-  std::map<int, std::vector<int>> buckets;
-  for (int i = 0; i < pl.n_sub; ++i) buckets[(pl.npad[i] + 255) / 256].push_back(i);
+// The size class of a batch in the tuning table: powers of two of its 128-edge tiles.
+int tune_class(const Part& P) {
+  int64_t t = 0;
+  for (int q = 0; q < P.n_sub; ++q) {
+    const int64_t nb = (padded(P.h_sub_ptr[q + 1] - P.h_sub_ptr[q]) + kBT - 1) / kBT;
+    t += nb * (nb + 1) / 2;
+  }
+  int c = 1;
+  while (((int64_t)1 << c) <= t) ++c;
+  return c;
+}
+
+// The split squares' kernel for a batch: each variant timed on the whole batch, once per process and
+// size class.  (One variant for all: a choice per size of block, each size timed by itself,
+// paid for every variant's own launch and for small groups that cannot fill the device, which
+// flattered small tiles: bf16 x 3 planes N = 2050 1.118 -> 1.032 ms a square, N = 6014 2.22 -> 2.11, fp16
+// N = 1400 0.341 -> 0.303, N = 2050 0.644 -> 0.633, N = 18000 3.88 -> 3.84.)
+int tune_tiles(const Part& P, const float* X, float* S, const int64_t* offs, hipStream_t s, int kind,
+               bool xcd, int planes) {
+  const std::pair<int, int> key{kind, tune_class(P)};
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     tune_env_read();
+    auto it = g_tune.find(key);
+    if (it != g_tune.end()) return it->second;
   }
   Timer tm;
-  bool added = false;
-  for (auto& kv : buckets) {
-    int choice = 0;
-    {
-      std::lock_guard<std::mutex> lk(g_tune_mu);
-      auto it = g_tune.find({kind, kv.first});
-      if (it != g_tune.end()) choice = it->second;
+  int choice = 0;
+  float best = INFINITY;
+  for (int code : kVariants) {
+    if (code != 128 && code != 64 && !(planes == 4 && split_il_code(code))) continue;
+    const std::vector<int> bt(P.n_sub, code);
+    const Plan pl = make_plan(P, &bt, xcd);
+    DBuf<int4> tl = upload_tiles(pl, s, false);
+    auto run = [&] { launch_split(X, S, tl.get(), pl.lg, offs, s, planes, 0); };
+    run();
+    GB_HIP(hipEventRecord(tm.a, s));
+    run();
+    run();
+    GB_HIP(hipEventRecord(tm.b, s));
+    GB_HIP(hipStreamSynchronize(s));
+    const float ms = elapsed(tm.a, tm.b);
+    if (ms < best) {
+      best = ms;
+      choice = code;
     }
-    if (!choice) {
-      float best = INFINITY;
-      for (int code : kVariants) {
-        if (planes > 0 && code != 128 && code != 64 && !(planes == 4 && split_il_code(code)))
-          continue;
-        if (planes == 0 && (split_il_code(code) || code == 32)) continue;
-        std::vector<int> e(pl.n_sub, 0);
-        for (int i : kv.second) e[i] = code;
-        const Plan sub = make_plan(P, &e, xcd);
-        DBuf<int4> tl = upload_tiles(sub, s, false);
-        auto run = [&] {
-          if constexpr (std::is_same<T, float>::value) {
-            if (planes > 0) {
-              launch_split(X, S, tl.get(), sub.lg, offs, s, planes, 0);
-              return;
-            }
-          }
-          launch_square<T>(X, S, tl.get(), sub.lg, offs, s);
-        };
-        run();
-        GB_HIP(hipEventRecord(tm.a, s));
-        run();
-        run();
-        GB_HIP(hipEventRecord(tm.b, s));
-        GB_HIP(hipStreamSynchronize(s));
-        const float ms = elapsed(tm.a, tm.b);
-        if (ms < best) {
-          best = ms;
-          choice = code;
-        }
-      }
-      std::lock_guard<std::mutex> lk(g_tune_mu);
-      g_tune[{kind, kv.first}] = choice;
-      added = true;
-    }
-    for (int i : kv.second) bt[i] = choice;
   }
-  if (added) {
-    std::lock_guard<std::mutex> lk(g_tune_mu);
-    tune_env_write();
-  }
-  return bt;
+  std::lock_guard<std::mutex> lk(g_tune_mu);
+  g_tune[key] = choice;
+  tune_env_write();
+  return choice;
 }
 
 // Squares on 32-edge tiles (k_square_small)?  FP64 while at most five 64-edge tiles fall to each of
@@ -2118,7 +2107,7 @@ bool small_batch(const Part& P) {
   return t64 <= (std::is_same<T, double>::value ? 1280 : 400);
 }
 
-// The variant of every subgraph where a policy says it (0: split squares, timed per bucket).
+// The variant of every subgraph where a policy says it (0: split squares, timed).
 template <typename T>
 int fixed_tiles(const Part& P, int policy, int planes) {
   if (policy == 1) return kBT;
@@ -2140,9 +2129,11 @@ template <typename T>
 void choose_tiles(const Part& P, Plan& pl, T* X, T* S, DBuf<int4>& tiles, const int64_t* offs,
                   hipStream_t s, int policy, int kind, gb_sp2_stats& st, bool xcd,
                   bool per_subgraph, int planes = 0, bool record = true) {
-  const int code = fixed_tiles<T>(P, policy, planes);
-  const std::vector<int> bt = code ? std::vector<int>(pl.n_sub, code)
-                                   : tune_tiles<T>(P, pl, X, S, offs, s, kind, xcd, planes);
+  int code = fixed_tiles<T>(P, policy, planes);
+  if constexpr (std::is_same<T, float>::value) {
+    if (!code) code = tune_tiles(P, X, S, offs, s, kind, xcd, planes);
+  }
+  const std::vector<int> bt(pl.n_sub, code);
   const bool changed = bt != pl.bt;
   if (changed) pl = make_plan(P, &bt, xcd);
   if (changed || !tiles.get()) tiles = upload_tiles(pl, s, per_subgraph);
