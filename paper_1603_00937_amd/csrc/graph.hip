@@ -534,7 +534,10 @@ __global__ __launch_bounds__(kT) void k_x2_rows_hash(const int32_t* __restrict__
 // left to the kernels below.
 // The two-pass kernels visit every pair twice with an LDS atomic and two LDS look-ups; here a
 // pair costs one look-up and one ds_add_f64, and LDS no longer grows with n.  Bound by LDS and the
-// vector work of a pair at two workgroups per CU (the pages take ~50 KB).  Whole graph call, two-
+// vector work of a pair at two workgroups per CU (the pages take ~50 KB), and, 40 % of it, by the chains
+// of waits around the pairs: so eight look-ups go out at once, the scans shift lanes instead of
+// taking 18 barriers, and a wave reads four groups of sums before it decides (13.8 -> 12.6 ms at
+// 160002; the atomics alone cost 0.4).  Whole graph call, two-
 // pass bitmap -> paged: N = 1024 0.56 -> 0.48 ms, 18000 3.1 -> 2.7, 100000 (clustered) 18.5 ->
 // 10.1, 160002 36.8 -> 15.8 (67 with hash sets, which it took there); rows of consecutive numbers,
 // which share the rows they read, on one XCD: another 5 %.  512 threads: 256 take 23.9
@@ -628,11 +631,18 @@ __global__ __launch_bounds__(kPT) void k_x2_rows_paged(
         j[q] = in ? hcol[((q & 1) ? b1 : b0) + u] : -1;
         v[q] = in ? x0[((q & 1) ? b1 : b0) + u] : 0.0;
       }
+      // every page's slot first, too: one wait for eight LDS reads; only a page not there yet (or
+      // taken by another wave meanwhile) asks again
+      int slot[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        slot[q] = (unsigned)j[q] < (unsigned)n ? *(volatile int32_t*)&dir[j[q] >> g.shift] : 0;
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
         const bool ok = (unsigned)j[q] < (unsigned)n;
         if (__ballot(ok) == 0) continue;  // the same for the whole wave
-        const int sl = x2_page(dir, &npages, spare, ok ? j[q] >> g.shift : 0, ok);
+        int sl = slot[q];
+        if (__ballot(sl < 0)) sl = x2_page(dir, &npages, spare, ok ? j[q] >> g.shift : 0, ok);
         if (ok && sl < g.pcap)
           atomicAdd(&acc[(sl << g.shift) | (j[q] & low)], ((q & 1) ? a1 : a0) * v[q]);
       }
@@ -651,48 +661,49 @@ __global__ __launch_bounds__(kPT) void k_x2_rows_paged(
   const int d0 = min((int)threadIdx.x * seg, ndir), d1 = min(d0 + seg, ndir);
   int mine = 0;
   for (int q = d0; q < d1; ++q) mine += dir[q] >= 0;
-  __syncthreads();  // kw has been read from red
-  red[threadIdx.x] = mine;
-  __syncthreads();
-  for (int d = 1; d < kPT; d <<= 1) {
-    const int32_t y = threadIdx.x >= d ? red[threadIdx.x - d] : 0;
-    __syncthreads();
-    red[threadIdx.x] += y;
-    __syncthreads();
-  }
-  const int used = red[kPT - 1];
-  int at = red[threadIdx.x] - mine;
+  int32_t used;
+  int at = block_inclusive_scan<kPT>(mine, red, &used) - mine;
+  // page and slot in a word: LDS holds neither 2^10 slots of 256 bytes nor a directory of 2^16 pages
   for (int q = d0; q < d1; ++q)
-    if (dir[q] >= 0) plist[at++] = q;
+    if (dir[q] >= 0) plist[at++] = q << 10 | dir[q];
   __syncthreads();
   // decisions, 64 entries of the pages in ascending order per wave
   const double margin = x2_margin(kw, rbound[i], tau);
   const int total = used << g.shift, groups = (total + 63) >> 6;
-  for (int q = wave; q < groups; q += NW) {
-    const int f = (q << 6) | lane;
-    bool keep = false, band = false;
-    int j = -1;
-    if (f < total) {
-      const int pg = plist[f >> g.shift];
-      j = (pg << g.shift) | (f & low);
-      const double a = fabs(acc[(dir[pg] << g.shift) | (f & low)]);
-      if (j == i) keep = true;
-      else if (j < n) {
+  auto page_of = [&](int f) { return plist[f >> g.shift] >> 10; };
+  constexpr int B = 4;  // groups whose sums a wave reads at once
+  for (int qb = wave; qb < groups; qb += B * NW) {
+    double sums[B];
+    int cols[B];
+#pragma unroll
+    for (int e = 0; e < B; ++e) {
+      const int f = ((qb + e * NW) << 6) | lane;
+      const int pl = f < total ? plist[f >> g.shift] : 0;
+      cols[e] = f < total ? (pl >> 10) << g.shift | (f & low) : n;
+      sums[e] = f < total ? fabs(acc[(pl & 1023) << g.shift | (f & low)]) : 0.0;
+    }
+#pragma unroll
+    for (int e = 0; e < B; ++e) {
+      const int q = qb + e * NW, j = cols[e];
+      if (q >= groups) break;
+      const double a = sums[e];
+      bool keep = j == i, band = false;
+      if (j != i && j < n) {
         band = all_ascending || fabs(a - tau) <= margin;
         keep = !band && a >= tau;
       }
-    }
-    unsigned long long again = __ballot(band);
-    while (again) {  // summed in ascending order, the whole wave on one entry
-      const int l = __ffsll((long long)again) - 1;
-      const double a = fabs(x2_sum_ascending(hcol, x0, ci, xi, kw, w, __shfl(j, l)));
-      if (lane == l) keep = a >= tau;
-      again &= again - 1;
-    }
-    const unsigned long long m = __ballot(keep);
-    if (lane == 0) {
-      kept[q] = m;
-      pre[q] = __popcll(m);
+      unsigned long long again = __ballot(band);
+      while (again) {  // summed in ascending order, the whole wave on one entry
+        const int l = __ffsll((long long)again) - 1;
+        const double x = fabs(x2_sum_ascending(hcol, x0, ci, xi, kw, w, __shfl(j, l)));
+        if (lane == l) keep = x >= tau;
+        again &= again - 1;
+      }
+      const unsigned long long m = __ballot(keep);
+      if (lane == 0) {
+        kept[q] = m;
+        pre[q] = __popcll(m);
+      }
     }
   }
   __syncthreads();
@@ -708,7 +719,7 @@ __global__ __launch_bounds__(kPT) void k_x2_rows_paged(
     const int f = (q << 6) | lane;
     if ((m >> lane) & 1ull)
       dst[pre[q] + __popcll(m & ((1ull << lane) - 1ull))] =
-          (plist[f >> g.shift] << g.shift) | (f & low);
+          (page_of(f) << g.shift) | (f & low);
   }
 }
 
