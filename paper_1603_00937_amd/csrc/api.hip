@@ -155,6 +155,7 @@ void* dmalloc(size_t bytes, hipStream_t s, Allocator* used) {
     want = (size_t)1 << cls;
     used->cls = cls;
     p = CallScope::top->take(cls);
+    used->dev = CallScope::top->dev;
     if (p) return p;
   }
   // keep freed pool memory cached instead of returning it at every synchronisation
@@ -181,7 +182,7 @@ void dfree(void* p, hipStream_t s, const Allocator& a) {
     return;
   }
   CallScope* c = CallScope::top;
-  if (a.cls >= 0 && c && c->dev >= 0 && c->put(p, s, a.cls)) return;
+  if (a.cls >= 0 && c && c->dev == a.dev && c->put(p, s, a.cls)) return;
   (void)hipFreeAsync(p, s);
 }
 

@@ -36,7 +36,7 @@ struct Allocator {
   gb_alloc_fn alloc = nullptr;  // nullptr: the device pool
   gb_free_fn free = nullptr;
   void* ctx = nullptr;
-  int cls = -1;  // buffers of a call (see CallScope): 2^cls bytes
+  int cls = -1, dev = -1;  // buffers of a call (see CallScope): 2^cls bytes on device dev
 };
 void* dmalloc(size_t bytes, hipStream_t s, Allocator* used);
 void dfree(void* p, hipStream_t s, const Allocator& a);
