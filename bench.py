@@ -348,7 +348,7 @@ def foe_run(args):
                    "beta": args.beta, "order": args.order,
                    "mu": "solved for n_occ" if mu is None else mu, "passes": st["passes"],
                    "n_sub": st["n_sub"], "max_sub": st["max_sub"]},
-        "recurrence": {"bound": "lds", "kernel": "k_foe_rows",
+        "recurrence": {"bound": "l2", "kernel": "k_foe_rows",
                        "dense_block_flops_per_term": st["product_flops"],
                        "avg_term_ms": avg},
         "result": {"mu": st["mu"], "trace": st["trace"], "coef_tail": st["coef_tail"]},
@@ -680,7 +680,8 @@ def measure(gb, torch, args, precision, model, cfg, Hc, Hv, D, golden, sizes):
     flops_exec = stats["square_flops_exec"] * planes
     flops_dense = stats["square_flops"]
     peak = PEAK_TFLOPS[precision]
-    # per-launch HIP events around every square (host and device-driven loops; the hipGraph
+    # times around every square (events on the host loops, the device's clock on the device-driven
+    # one; the hipGraph
     # replay has none)
     avg_launch_s = (sq_ms / sq_n / 1e3) if (sq_n and sq_ms > 0) else None
     achieved = flops_alg / avg_launch_s / 1e12 if avg_launch_s else None
