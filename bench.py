@@ -681,8 +681,7 @@ def measure(gb, torch, args, precision, model, cfg, Hc, Hv, D, golden, sizes):
     flops_dense = stats["square_flops"]
     peak = PEAK_TFLOPS[precision]
     # times around every square (events on the host loops, the device's clock on the device-driven
-    # one; the hipGraph
-    # replay has none)
+    # one; the hipGraph replay has none)
     avg_launch_s = (sq_ms / sq_n / 1e3) if (sq_n and sq_ms > 0) else None
     achieved = flops_alg / avg_launch_s / 1e12 if avg_launch_s else None
     # the matrix-core rate this device sustains on register operands in the kernel's input

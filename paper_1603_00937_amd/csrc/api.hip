@@ -167,7 +167,20 @@ void* dmalloc(size_t bytes, hipStream_t s, Allocator* used) {
       (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &thr);
     }
   });
-  const hipError_t e = hipMallocAsync(&p, want, s);
+  hipError_t e = hipMallocAsync(&p, want, s);
+  if (e != hipSuccess || !p) {
+    // what earlier calls left idle goes back to the device before the call is refused
+    (void)hipGetLastError();
+    ws_trim();
+    cached_trim();
+    small_trim();
+    int dev = 0;
+    hipMemPool_t pool;
+    if (hipDeviceSynchronize() == hipSuccess && hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess)
+      (void)hipMemPoolTrimTo(pool, 0);
+    e = hipMallocAsync(&p, want, s);
+  }
   if (e != hipSuccess || !p) {
     (void)hipGetLastError();
     fail(GB_ENOMEM, "device allocation of %zu bytes failed: %s", bytes, hipGetErrorString(e));
@@ -302,7 +315,8 @@ Workspace* ws_acquire() {
   int dev = 0;
   GB_HIP(hipGetDevice(&dev));
   std::lock_guard<std::mutex> lk(g_ws_mu);
-  for (size_t i = 0; i < g_ws_idle.size(); ++i)
+  // the one given back last: calls in sequence grow one workspace, whatever threads left behind
+  for (size_t i = g_ws_idle.size(); i-- > 0;)
     if (g_ws_idle[i]->device == dev) {
       Workspace* w = g_ws_idle[i];
       g_ws_idle.erase(g_ws_idle.begin() + i);
