@@ -47,6 +47,18 @@ struct IdleBuffers {
   std::mutex m;
   std::map<std::pair<int, int>, std::vector<void*>> list;  // by device and class
   size_t bytes = 0;
+  bool add(int dev, int cls, void* p) noexcept {  // false: full, or no memory for the entry
+    const size_t n = (size_t)1 << cls;
+    try {
+      std::lock_guard<std::mutex> lk(m);
+      if (bytes + n > kIdleMost) return false;
+      list[{dev, cls}].push_back(p);
+      bytes += n;
+      return true;
+    } catch (...) {
+      return false;
+    }
+  }
 };
 IdleBuffers& idle_buffers() {
   static auto* p = new IdleBuffers;  // outlives the runtime's own teardown
@@ -96,29 +108,22 @@ struct CallScope {
     bytes += (size_t)1 << cls;
     return true;
   }
-  void done() {  // the call succeeded
+  void done() noexcept {  // the call succeeded
     if (!outer || freed.empty()) return;
-    std::vector<Freed> back;
-    back.reserve(freed.size());
     IdleBuffers& b = idle_buffers();
     hipStream_t last = freed[0].s;
     bool idle = hipStreamQuery(last) == hipSuccess;
-    for (const Freed& f : freed) {
+    size_t kept = 0;  // entries that stay for the destructor, moved to the front
+    for (size_t i = 0; i < freed.size(); ++i) {
+      const Freed f = freed[i];
       if (f.s != last) {
         last = f.s;
         idle = hipStreamQuery(last) == hipSuccess;
       }
-      const size_t n = (size_t)1 << f.cls;
-      std::lock_guard<std::mutex> lk(b.m);
-      if (idle && b.bytes + n <= kIdleMost) {
-        b.list[{dev, f.cls}].push_back(f.p);
-        b.bytes += n;
-      } else {
-        back.push_back(f);
-      }
+      if (!idle || !b.add(dev, f.cls, f.p)) freed[kept++] = f;
     }
     (void)hipGetLastError();
-    freed.swap(back);  // the destructor's
+    freed.resize(kept);
   }
 };
 thread_local CallScope* CallScope::top = nullptr;

@@ -1872,9 +1872,14 @@ class IdlePool {
     v.pop_back();
     return true;
   }
-  void give(int dev, H h) {
-    std::lock_guard<std::mutex> g(m_);
-    idle_[dev].push_back(h);
+  bool give(int dev, H h) noexcept {  // false: no room to keep it
+    try {
+      std::lock_guard<std::mutex> g(m_);
+      idle_[dev].push_back(h);
+      return true;
+    } catch (...) {
+      return false;
+    }
   }
 
  private:
@@ -1894,7 +1899,7 @@ struct Timer {
   Timer& operator=(const Timer&) = delete;
   ~Timer() {
     for (hipEvent_t e : {a, b})
-      if (e) pool().give(dev, e);
+      if (e && !pool().give(dev, e)) (void)hipEventDestroy(e);
   }
 
  private:
@@ -2288,7 +2293,7 @@ struct ProgressLease {
   }
   ProgressLease(const ProgressLease&) = delete;
   ProgressLease& operator=(const ProgressLease&) = delete;
-  ~ProgressLease() { pool().give(dev, p); }
+  ~ProgressLease() { (void)pool().give(dev, p); }  // never freed: a failed loop's kernels may write it
 
  private:
   static IdlePool<LoopProgress*>& pool() {
