@@ -137,7 +137,12 @@ struct Level {
   const int32_t* rp = nullptr;
   const int32_t* adj = nullptr;
   const int32_t* ew = nullptr;
-  MlRows* src = nullptr;  // where adj and ew come from while they are NULL
+  // the input level's rows while adj and ew are not there yet (a coarse level without edges has
+  // NULL arrays, too, and nowhere to fetch them from)
+  MlRows* src = nullptr;
+  void fetch() {
+    if (src && !adj) src->all(&adj, &ew);
+  }
   std::vector<int32_t> rp_v, adj_v, ew_v;  // storage of a coarse level (or of host weights)
   bool sorted = false;                     // rows ascending (a level built on the device)
   std::vector<int32_t> vw;                 // vertex weights
@@ -269,11 +274,11 @@ bool coarsen(Level& f, int cap, int level, Level& c, MlScratch& sc,
     if (best < 0 && !listed_all) {
       int bw = -1, bvw = INT_MAX;
       const int32_t *adj = nullptr, *ew = nullptr;
-      if (f.adj) {
+      if (f.src && !f.adj) {
+        f.src->row(v, &adj, &ew);
+      } else {
         adj = f.adj + f.rp[v];
         ew = f.ew + f.rp[v];
-      } else {
-        f.src->row(v, &adj, &ew);
       }
       const int deg = f.rp[v + 1] - f.rp[v];
       for (int e = 0; e < deg; ++e) {
@@ -319,7 +324,7 @@ bool coarsen(Level& f, int cap, int level, Level& c, MlScratch& sc,
   }
   sc.top1 = nullptr;
   c.sorted = false;
-  if (!f.adj) f.src->all(&f.adj, &f.ew);
+  f.fetch();
   // coarse adjacency: summed edge weights, no self loops, neighbours in the order first met
   // (the matching breaks every tie by index, so only the breadth-first order on the coarsest
   // level needs them ascending; sort_rows does that there).  Coarse vertices are independent,
@@ -664,7 +669,7 @@ void partition_multilevel(int n, const int32_t* row_ptr, const int32_t* col, int
   if (nl > 1 && !sc.lv[nl - 1].sorted) sort_rows(sc.lv[nl - 1]);
   const double ms_coarsen = ms_since(t0);
   t0 = clk::now();
-  if (!sc.lv[nl - 1].adj) rows0->all(&sc.lv[nl - 1].adj, &sc.lv[nl - 1].ew);
+  sc.lv[nl - 1].fetch();
   std::vector<int32_t> part = grow_parts(sc.lv[nl - 1], cap);
   const double ms_grow = ms_since(t0);
   t0 = clk::now();
@@ -676,7 +681,7 @@ void partition_multilevel(int n, const int32_t* row_ptr, const int32_t* col, int
     part.swap(fine);
   }
   // the cost is a statistic (the device path gets the subgraph sizes from its halos anyway)
-  if (stats && !sc.lv[0].adj) rows0->all(&sc.lv[0].adj, &sc.lv[0].ew);
+  if (stats) sc.lv[0].fetch();
   const int64_t cost = stats ? subgraph_cost(sc.lv[0], part, np) : 0;
   const double ms_cost = ms_since(t0);
   emit_cores(n, part, np, core_ptr, core_vtx);
