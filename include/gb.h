@@ -265,7 +265,8 @@ typedef struct {
                               * (by products of the k core rows with X; 2 n^2 k flops each):  *
                               * S_m(X) for m = 3, 4, .. 6, the polynomial of degree 2m - 1    *
                               * flat to order m at 0 and 1, until the FP64 stop test holds on *
-                              * the rows (S_2 = McWeeny's 3X^2 - 2X^3 alone for n_refine = 1); *
+                              * the rows (S_2 = McWeeny's 3X^2 - 2X^3 alone for n_refine = 1, *
+                              * at most S_4 for 2 and S_5 for 3: see n_refine_done);          *
                               * if it does not, more low-precision steps, then as 2;          *
                               * 1 = FP64 SP2 steps until it holds, the first by the trace     *
                               * rule, then alternating X^2 / 2X - X^2 (replayed from          *

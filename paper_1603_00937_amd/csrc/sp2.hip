@@ -2852,7 +2852,8 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
       RefineState h;
       for (int attempt = 0; attempt < 2; ++attempt) {
         const int lo = n_refine == 1 || 3.0 * st.idem * st.idem <= 1e-2 * tol ? 2 : 3;
-        const int hi = n_refine == 1 ? 2 : kSmoothMax;
+        // the highest order whose equivalent in McWeeny steps (below) is within the limit given
+        const int hi = n_refine == 1 ? 2 : n_refine == 2 ? 4 : n_refine == 3 ? 5 : kSmoothMax;
         hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(kT), 0, s, rdone, (int64_t)1);
         double *v = sl, *w = sl + cr.total;
         hipLaunchKernelGGL(k_rows_copy<float>, dim3((pl.max_npad + 63) / 64, pl.n_sub), dim3(256),
