@@ -272,7 +272,8 @@ typedef struct {
                               * rule, then alternating X^2 / 2X - X^2 (replayed from          *
                               * branch_in when that extends past the low-precision loop);     *
                               * 2 = McWeeny steps on whole blocks until the stop test holds,  *
-                              * from the iterate at which 0 would start                       */
+                              * from the iterate at which 0 would start; if it does not, more *
+                              * low-precision steps and again                                 */
   int32_t n_fp64_first;      /* low precision: run the first SP2 steps in FP64 (default 0)   */
   int32_t max_iter;          /* default 100 when 0                                           */
   double idem_tol;           /* stop when |Tr X - Tr X^2| <= idem_tol; 0 = 1e-10 * n / 1024   */

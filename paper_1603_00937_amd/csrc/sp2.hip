@@ -1117,7 +1117,7 @@ __global__ __launch_bounds__(kT) void k_decide(const double* __restrict__ part, 
 // simply alternate.
 struct LoopState {
   int32_t it, stopped, max_iter, n_forced;  // n_forced < 0: choose by the trace rule
-  int32_t stag, cur_b, it0;  // it0: first step of this loop (stagnation looks back 2 steps)
+  int32_t stag, cur_b, first;  // first: step at which the loop began (stagnation waits nine steps)
   int32_t ticket;  // workgroups of the step's trace kernel that are done
   double n_occ, tol, e_hand;  // e_hand: stop once the traces agree to this (0: never)
   uint8_t forced[128];
@@ -1129,8 +1129,9 @@ struct LoopProgress {
 };
 // The loop's parameters, passed by value to the kernel that sets up LoopState.
 struct LoopInit {
-  int32_t it0, max_iter, n_forced, stag;
+  int32_t it0, first, max_iter, n_forced, stag;
   double n_occ, tol, e_hand;
+  double e_back[2];  // of the two steps before it0, where first < it0
   uint8_t forced[128];
 };
 
@@ -1189,7 +1190,7 @@ __global__ __launch_bounds__(kT) void k_trace_step(const T* __restrict__ X,
       q.stop = 2;
     } else if (e <= st->e_hand) {
       q.stop = 5;
-    } else if (st->stag && it - st->it0 >= 9 && e > st->recs[it - 2].e) {
+    } else if (st->stag && it - st->first >= 9 && e > st->recs[it - 2].e) {
       q.stop = 4;
     } else {
       q.b = dsq < dlin ? 0 : 1;
@@ -2209,14 +2210,15 @@ void launch_step(const T* X, T* S, const Plan& pl, const int4* tiles, const int6
 // trip per step), then one squaring launch writes the next iterate.  Used for one launch per
 // subgraph, for the tape of the adjoint and for the alternating FP64 refinement.  Returns the
 // step index at which the stop rule fired, the replay ended, max_iter was reached, or (low
-// precision) the idempotency error stagnated or fell to e_hand; X then holds the result.
+// precision) the idempotency error stagnated or fell to e_hand; X then holds the result.  first: the
+// step at which a loop that goes on at it0 began (stagnation is judged over all of its steps).
 template <typename T>
 int sp2_loop(T*& X, T*& S, const Plan& pl, const DBuf<int4>& tiles, const int64_t* offs,
              const int32_t* npad, const Part& P, double n_occ, double tol, int max_iter,
              const uint8_t* branch_in, int n_branch_in, bool stagnation_stop, int it0,
              gb_sp2_stats& st, DBuf<StepRec>& recs, hipStream_t s, int* stop_kind,
              TapeData* tape = nullptr, int planes = 0, bool per_subgraph = false,
-             bool alternate = false, double e_hand = 0.0) {
+             bool alternate = false, double e_hand = 0.0, int first = -1) {
   Timer tm;
   PinnedRec pin;
   int it = it0;
@@ -2226,6 +2228,7 @@ int sp2_loop(T*& X, T*& S, const Plan& pl, const DBuf<int4>& tiles, const int64_
   T* const scratch[2] = {X, S};  // checkpoints are written where they stay, never over
   int prev_b = -1;
   std::vector<double> es;
+  for (int q = first < 0 ? it0 : first; q < it0; ++q) es.push_back(fabs(st.t1[q] - st.t2[q]));
   DBuf<double> part(2 * (size_t)pl.n_sub, s);
   for (;;) {
     hipLaunchKernelGGL(k_trace_rows<T>, dim3(pl.n_sub), dim3(kT), 0, s, X, offs, npad,
@@ -2313,7 +2316,9 @@ double wall_clock_khz() {
 
 __global__ void k_loop_init(LoopState* __restrict__ st, LoopInit in) {
   st->it = in.it0;
-  st->it0 = in.it0;
+  st->first = in.first;
+  for (int i = 1; i <= 2; ++i)
+    if (in.it0 - i >= in.first) st->recs[in.it0 - i].e = in.e_back[i - 1];
   st->stopped = 0;
   st->max_iter = in.max_iter;
   st->n_forced = in.n_forced;
@@ -2339,7 +2344,7 @@ int sp2_loop_dev(T*& X, T*& S, const Plan& pl, const DBuf<int4>& tiles, const in
                  const int32_t* npad, const Part& P, double n_occ, double tol, int max_iter,
                  const uint8_t* branch_in, int n_branch_in, bool stagnation_stop, int it0,
                  gb_sp2_stats& st, hipStream_t s, int* stop_kind, int planes, bool graph,
-                 double e_hand = 0.0) {
+                 double e_hand = 0.0, int first = -1) {
   constexpr int kFirst = 32, kMore = 8, kAhead = 4;
   // index of the last decision the loop can reach: it stops there at the latest
   const int last = branch_in ? std::min(n_branch_in, 127) : std::min(max_iter, 127);
@@ -2347,6 +2352,9 @@ int sp2_loop_dev(T*& X, T*& S, const Plan& pl, const DBuf<int4>& tiles, const in
   const int max_dec = last - it0 + 1;
   LoopInit in{};
   in.it0 = it0;
+  in.first = first < 0 ? it0 : first;
+  for (int i = 1; i <= 2; ++i)
+    in.e_back[i - 1] = it0 - i >= in.first ? fabs(st.t1[it0 - i] - st.t2[it0 - i]) : 0.0;
   in.max_iter = max_iter;
   in.n_forced = branch_in ? std::min(n_branch_in, 127) : -1;
   in.stag = stagnation_stop ? 1 : 0;
@@ -2715,37 +2723,38 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
       }
     }
     if (!done) {
-      // FP32 squares: kind 1; split squares: kind 10 + planes (128- or 64-edge tiles)
-      choose_tiles<float>(P, pl, xf, sf, tiles, offs, s, o.tile_policy,
-                          planes ? 10 + planes : 1, st, xcd, per_sub, planes);
       st.planes_db = planes;
       // The low-precision loop hands over to the refinement as soon as that finishes the job
       // (a replayed sequence or a given number of steps runs as asked).  Where the refinement
-      // is by other means, it runs until its own rounding floor (the stagnation stop) unless the
-      // traces already agree to 1e-7 per 1024 orbitals.
+      // is by other means, and where it did not finish the job, the loop runs until its own
+      // rounding floor (the stagnation stop) unless the traces already agree to 1e-7 per 1024
+      // orbitals.
       CoreRows sizes;
       const bool by_rows = o.refine_kind != 1 && n_refine == 0 && !o.branch_in &&
                            core_rows_sizes(P, pl, sizes);
-      run_low = [&, xf, sf](double e_hand) mutable {
+      run_low = [&, xf, sf, first = it_end](double e_hand) mutable {
         const double tol_lo = 1e-7 * N / 1024.0;
+        // FP32 squares: kind 1; split squares: kind 10 + planes (128- or 64-edge tiles)
+        choose_tiles<float>(P, pl, xf, sf, tiles, offs, s, o.tile_policy,
+                            planes ? 10 + planes : 1, st, xcd, per_sub, planes);
         if (dev_loop)
           it_end = sp2_loop_dev<float>(xf, sf, pl, tiles, offs, npad, P, n_occ, tol_lo, max_iter,
                                        o.branch_in, o.n_branch_in, true, it_end, st, s, &stop_kind,
-                                       planes, o.launch_mode == 2, e_hand);
+                                       planes, o.launch_mode == 2, e_hand, first);
         else
           it_end = sp2_loop<float>(xf, sf, pl, tiles, offs, npad, P, n_occ, tol_lo, max_iter,
                                    o.branch_in, o.n_branch_in, true, it_end, st, recs, s,
-                                   &stop_kind, nullptr, planes, per_sub, false, e_hand);
+                                   &stop_kind, nullptr, planes, per_sub, false, e_hand, first);
         // continue from X made exactly symmetric, in FP32, in place (every block is padded to a
         // multiple of 64)
         hipLaunchKernelGGL(k_sym_diag, dim3(pl.max_npad / 64, pl.n_sub), dim3(256), 0, s, xf,
                            offs, npad);
         GB_LAUNCH_CHECK();
         xs = xf;
+        xd_ready = false;
       };
       run_low(by_rows ? handover_measure(tol) : 0.0);
       xs_scale = planes == 4 ? (double)kF16Down : 1.0;
-      xd_ready = false;
     }
     GB_HIP(hipEventRecord(t_sp2.b, s));
   } else {
@@ -2823,6 +2832,10 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
     // cause, the low-precision loop goes on to its rounding floor; whole-block steps follow where
     // that does not help either.
     bool refined = false;
+    // Does the low-precision loop go on after a refinement that ended at e?  Not where e is short
+    // of idem_tol by rounding only (the default tolerance is met): more low-precision squares would
+    // add theirs and resolve nothing.
+    auto resumes = [&](double e) { return stop_kind == 5 && e > 1e-10 * N / 1024.0; };
     if (o.refine_kind == 0 && xs && core_rows_plan(P, pl, cr, s)) {
       DBuf<double> part(2 * (size_t)pl.n_sub, s);
       DBuf<RefineState> rs(1, s);
@@ -2869,9 +2882,7 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
         }
         GB_HIP(hipMemcpyAsync(&h, rs.get(), sizeof(h), hipMemcpyDeviceToHost, s));
         GB_HIP(hipStreamSynchronize(s));
-        // short of idem_tol by its rounding only (the default tolerance is met): more low-precision
-        // squares would add theirs and resolve nothing
-        if (h.done || stop_kind != 5 || h.rec.e <= 1e-10 * N / 1024.0) break;
+        if (h.done || !resumes(h.rec.e)) break;
         run_low(0.0);
       }
       refined = h.done > 0;
@@ -2904,31 +2915,38 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
         stop_kind = 1;
       }
     }
-    const int at = std::min(it_end, 127);
     if (!refined) {
       // Whole blocks: X^2 = S, then 3S - 2 S X (S and X commute, so S X is computed on upper
       // tiles and mirrored); steps repeat until the FP64 stop test holds (at most n_refine,
-      // default 8).
-      ensure_xd();
-      fp64_tiles_for_blocks();
+      // default 8).  Eight steps do not take an eigenvalue within a tenth of 1/2 to an end (two
+      // pairs of sites, of which one reaches a single site of the other): if the loop before them
+      // was cut short, it goes on and they start again.
       DBuf<double> part(2 * (size_t)pl.n_sub, s);
       double* td = ws->get<double>(2, pl.total, s);
       const int max_steps = n_refine > 0 ? n_refine : 8;
       StepRec r;
-      for (int step = 0;; ++step) {
-        hipLaunchKernelGGL(k_trace_rows<double>, dim3(pl.n_sub), dim3(kT), 0, s, xd, offs,
-                           npad, P.core_ptr.get(), part.get(), nullptr, 1.0, 1.0);
-        hipLaunchKernelGGL(k_decide, dim3(1), dim3(kT), 0, s, part.get(), pl.n_sub,
-                           (double)n_occ, tol, 2, 0, recs.get());
-        GB_LAUNCH_CHECK();
-        GB_HIP(hipMemcpyAsync(&r, recs.get(), sizeof(r), hipMemcpyDeviceToHost, s));
-        GB_HIP(hipStreamSynchronize(s));
-        if (r.e <= tol || step == max_steps) break;
-        launch_square<double>(xd, sd, tiles.get(), pl.lg, offs, s);
-        launch_symm<double, 1>(sd, xd, sd, td, -2.0, 3.0, tiles.get(), pl.lg, offs, s);
-        std::swap(xd, td);
-        ++st.n_refine_done;
+      for (;;) {
+        ensure_xd();
+        fp64_tiles_for_blocks();
+        st.n_refine_done = 0;
+        for (int step = 0;; ++step) {
+          hipLaunchKernelGGL(k_trace_rows<double>, dim3(pl.n_sub), dim3(kT), 0, s, xd, offs,
+                             npad, P.core_ptr.get(), part.get(), nullptr, 1.0, 1.0);
+          hipLaunchKernelGGL(k_decide, dim3(1), dim3(kT), 0, s, part.get(), pl.n_sub,
+                             (double)n_occ, tol, 2, 0, recs.get());
+          GB_LAUNCH_CHECK();
+          GB_HIP(hipMemcpyAsync(&r, recs.get(), sizeof(r), hipMemcpyDeviceToHost, s));
+          GB_HIP(hipStreamSynchronize(s));
+          if (r.e <= tol || step == max_steps) break;
+          launch_square<double>(xd, sd, tiles.get(), pl.lg, offs, s);
+          launch_symm<double, 1>(sd, xd, sd, td, -2.0, 3.0, tiles.get(), pl.lg, offs, s);
+          std::swap(xd, td);
+          ++st.n_refine_done;
+        }
+        if (r.e <= tol || !resumes(r.e)) break;
+        run_low(0.0);
       }
+      const int at = std::min(it_end, 127);
       st.idem = r.e;
       st.t1[at] = r.t1;
       st.t2[at] = r.t2;
