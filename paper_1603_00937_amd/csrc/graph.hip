@@ -1165,7 +1165,6 @@ bool graph_x2_paged(const gb_ell& H, const double* x0, double tau, Csr& out, hip
 // per CU), raised to the largest count a row reports and run again (at most twice).
 void graph_x2_hash(const gb_ell& H, const double* x0, double tau, Csr& out, hipStream_t s) {
   const int n = H.n, w = H.width;
-  if (w > kX2Q * kT) fail(GB_EUNSUPPORTED, "X2 graph: ELL width %d above %d", w, kX2Q * kT);
   int cap = (int)std::min<int64_t>(std::min<int64_t>((int64_t)w * w, n) + 1, 2048);
   cap = std::max(cap, kT);
   DBuf<int32_t> cnt(n, s), ovf(1, s), rows, rlen;
@@ -1204,6 +1203,8 @@ void graph_x2_hash(const gb_ell& H, const double* x0, double tau, Csr& out, hipS
 
 void graph_x2(const gb_ell& H, const double* x0, double tau, Csr& out, hipStream_t s) {
   const int n = H.n, w = H.width;
+  // what the two-pass kernels' rows hold, whichever kernels would take these
+  if (w > kX2Q * kT) fail(GB_EUNSUPPORTED, "X2 graph: ELL width %d above %d", w, kX2Q * kT);
   // tau = 0 keeps candidates whose sum is 0, which only the candidate sets know
   if (tau > 0.0 && !vertex_sets_forced() && graph_x2_paged(H, x0, tau, out, s)) return;
   // two passes: bitmaps 37 against 67 ms at n = 160002, 125 against 112 at n = 262000
@@ -1214,7 +1215,6 @@ void graph_x2(const gb_ell& H, const double* x0, double tau, Csr& out, hipStream
   // candidate capacity: small enough for six or more workgroups per CU at n up to ~2e4 (the
   // accumulators are most of the LDS); a row with more two-hop candidates makes the launch
   // report its count, and the launch reruns with it
-  if (w > kX2Q * kT) fail(GB_EUNSUPPORTED, "X2 graph: ELL width %d above %d", w, kX2Q * kT);
   const size_t fixed = x2_lds_bytes(n, w, 0);
   if (fixed > 150 * 1024) fail(GB_EUNSUPPORTED, "X2 graph: n = %d too large for one LDS bitmap", n);
   const int64_t cap_lds = (int64_t)((160 * 1024 - fixed) / 8);

@@ -1,0 +1,79 @@
+"""Which kernels build the X2 graph: the same graph on every route, the widths that are refused are
+refused on all of them, and a call is never much slower than on the kernels that it could have
+taken instead (vertices numbered at random, narrow matrices, thresholds near rounding)."""
+import time
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _lattice(L, reach=1):
+    """One orbital per site of an L^3 periodic lattice, all sites within `reach` per axis."""
+    x = np.indices((L, L, L)).reshape(3, -1).T
+    off = np.indices((2 * reach + 1,) * 3).reshape(3, -1).T - reach
+    col = np.empty((L ** 3, len(off)), dtype=np.int64)
+    for q, o in enumerate(off):
+        y = (x + o) % L
+        col[:, q] = (y[:, 0] * L + y[:, 1]) * L + y[:, 2]
+    col.sort(axis=1)
+    rows = np.arange(L ** 3)[:, None]
+    val = np.where(col == rows, np.where(rows % 2 == 0, -1.5, 1.5), -0.05)
+    return col.astype(np.int32), val
+
+
+def _renumbered(col, val, seed):
+    """The same matrix with its vertices numbered at random."""
+    n = len(col)
+    p = np.random.default_rng(seed).permutation(n)
+    c = np.where(col >= 0, p[np.maximum(col, 0)], n)
+    s = np.argsort(c, axis=1, kind="stable")
+    c, v = np.take_along_axis(c, s, 1), np.take_along_axis(val, s, 1)
+    out_c, out_v = np.empty_like(col), np.empty_like(val)
+    out_c[p], out_v[p] = np.where(c == n, -1, c), v
+    return out_c, out_v
+
+
+def _build(gb, Hc, Hv, tau, monkeypatch, sets, reps=5):
+    """The graph and the fastest of a few builds, in seconds."""
+    import torch
+    if sets:
+        monkeypatch.setenv("GB_VERTEX_SETS", sets)
+    else:
+        monkeypatch.delenv("GB_VERTEX_SETS", raising=False)
+    best = np.inf
+    for _ in range(reps):
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        g = gb.build_graph(Hc, Hv, tau)
+        best = min(best, time.perf_counter() - t0)
+    return [t.cpu().numpy() for t in g.arrays()], best
+
+
+def _same_and_not_slower(col, val, tau, monkeypatch, factor, sets="bitmap"):
+    import torch
+    import paper_1603_00937_amd as gb
+    Hc, Hv = torch.from_numpy(col).cuda(), torch.from_numpy(val).cuda()
+    want, other = _build(gb, Hc, Hv, tau, monkeypatch, sets)
+    got, own = _build(gb, Hc, Hv, tau, monkeypatch, None)
+    assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+    assert own <= factor * other, (own, other)
+
+
+@pytest.mark.parametrize("n,width,sets", [(1100, 1025, None), (1100, 1025, "bitmap"),
+                                          (1100, 1025, "hash"), (140000, 1030, None)])
+def test_wide_rows_are_refused_on_every_route(n, width, sets, monkeypatch):
+    import torch
+    import paper_1603_00937_amd as gb
+    if sets:
+        monkeypatch.setenv("GB_VERTEX_SETS", sets)
+    col = torch.full((n, width), -1, dtype=torch.int32, device="cuda")
+    val = torch.zeros((n, width), dtype=torch.float64, device="cuda")
+    i = torch.arange(n, device="cuda")
+    col[:, 0], val[:, 0] = i.int(), torch.where(i % 2 == 0, 1.0, -1.0).double()
+    for tau in (1e-5, 0.0):
+        with pytest.raises(gb.GbError, match="width"):
+            gb.build_graph(col, val, tau)
+    narrow = gb.build_graph(col[:, :1024].contiguous(), val[:, :1024].contiguous(), 1e-5)
+    assert narrow.nnz == n
