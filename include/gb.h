@@ -80,8 +80,9 @@ const char* gb_last_error(void);
  * scratch) comes from the device's stream-ordered pool (hipMallocAsync / hipFreeAsync, with
  * the pool's release threshold raised so freed memory stays cached).  gb_set_allocator
  * replaces that for every later allocation in the process: alloc(bytes, stream, ctx) returns
- * device memory usable in stream order on `stream` (NULL on failure: the call then fails with
- * GB_ENOMEM), free(ptr, stream, ctx) returns it.  Each buffer is freed through the allocator
+ * device memory usable in stream order on `stream` (NULL on failure: the library frees what no
+ * call holds and asks once more, then the call fails with GB_ENOMEM), free(ptr, stream, ctx)
+ * returns it.  Each buffer is freed through the allocator
  * that made it, so the hook may be changed while handles are alive; it must stay valid (and
  * ctx alive) until every buffer it made is freed.  gb_set_allocator(NULL, NULL, NULL)
  * restores the default; exactly one of alloc/free NULL is GB_EINVAL.  Not thread-safe with

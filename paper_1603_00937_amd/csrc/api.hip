@@ -83,7 +83,12 @@ struct CallScope {
   ~CallScope() {
     if (!outer) return;
     top = nullptr;
+    flush();
+  }
+  void flush() {  // back to the device pool
     for (const Freed& f : freed) (void)hipFreeAsync(f.p, f.s);
+    freed.clear();
+    bytes = 0;
   }
   CallScope(const CallScope&) = delete;
   CallScope& operator=(const CallScope&) = delete;
@@ -145,15 +150,34 @@ void small_trim() {
   (void)hipSetDevice(cur);
 }
 
+// What no call holds goes back to the device (or to the allocator that made it): the idle lists, and
+// what the running call has put aside, which takes the small buffers of the former on their way.
+static void give_back_idle() {
+  ws_trim();
+  cached_trim();
+  small_trim();
+  if (CallScope::top) CallScope::top->flush();
+  int dev = 0;
+  hipMemPool_t pool;
+  if (hipDeviceSynchronize() == hipSuccess && hipGetDevice(&dev) == hipSuccess &&
+      hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess)
+    (void)hipMemPoolTrimTo(pool, 0);
+  (void)hipGetLastError();
+}
+
 void* dmalloc(size_t bytes, hipStream_t s, Allocator* used) {
   *used = g_alloc;
   void* p = nullptr;
+  size_t want = bytes ? bytes : 1;
   if (used->alloc) {
-    p = used->alloc(bytes ? bytes : 1, (void*)s, used->ctx);
+    p = used->alloc(want, (void*)s, used->ctx);
+    if (!p) {
+      give_back_idle();
+      p = used->alloc(want, (void*)s, used->ctx);
+    }
     if (!p) fail(GB_ENOMEM, "registered allocator returned NULL for %zu bytes", bytes);
     return p;
   }
-  size_t want = bytes ? bytes : 1;
   if (CallScope::top && want <= ((size_t)1 << kMaxClass)) {
     int cls = kMinClass;
     while (((size_t)1 << cls) < want) ++cls;
@@ -174,16 +198,8 @@ void* dmalloc(size_t bytes, hipStream_t s, Allocator* used) {
   });
   hipError_t e = hipMallocAsync(&p, want, s);
   if (e != hipSuccess || !p) {
-    // what earlier calls left idle goes back to the device before the call is refused
     (void)hipGetLastError();
-    ws_trim();
-    cached_trim();
-    small_trim();
-    int dev = 0;
-    hipMemPool_t pool;
-    if (hipDeviceSynchronize() == hipSuccess && hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess)
-      (void)hipMemPoolTrimTo(pool, 0);
+    give_back_idle();
     e = hipMallocAsync(&p, want, s);
   }
   if (e != hipSuccess || !p) {

@@ -1,0 +1,139 @@
+// The library's device memory (buffers of a call, cached checkpoints, workspaces, the refusal of an
+// allocation) on a device that exists only here: a counted heap behind the few runtime calls that
+// this code makes.  api.hip is compiled as host C++ and the rest of the library is left out (its
+// symbols stay unresolved and are never called).  argv[1] names the check; prints "ok".
+#include "../../paper_1603_00937_amd/csrc/api.hip"
+
+#include <cstdio>
+#include <cstdlib>
+#include <new>
+#include <set>
+
+namespace {
+size_t g_capacity = (size_t)1 << 40, g_used = 0, g_pooled = 0;
+int g_mallocs = 0, g_frees = 0;
+bool g_no_host_memory = false;
+std::map<void*, size_t> g_live;
+
+#define CHECK(c)                                                              \
+  do {                                                                        \
+    if (!(c)) {                                                               \
+      std::fprintf(stderr, "check failed: %s (line %d)\n", #c, __LINE__);     \
+      std::exit(1);                                                           \
+    }                                                                         \
+  } while (0)
+}  // namespace
+
+// host allocations fail on demand
+void* operator new(std::size_t n) {
+  if (g_no_host_memory) throw std::bad_alloc();
+  void* p = std::malloc(n ? n : 1);
+  if (!p) throw std::bad_alloc();
+  return p;
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, std::size_t) noexcept { std::free(p); }
+
+extern "C" {
+hipError_t hipMallocAsync(void** p, size_t n, hipStream_t) {
+  *p = nullptr;
+  if (g_used + n > g_capacity) return hipErrorOutOfMemory;
+  *p = std::malloc(16);
+  g_live[*p] = n;
+  g_used += n;
+  ++g_mallocs;
+  return hipSuccess;
+}
+hipError_t hipFreeAsync(void* p, hipStream_t) {  // the pool keeps it until it is trimmed
+  CHECK(g_live.count(p) == 1);
+  g_pooled += g_live[p];
+  g_live.erase(p);
+  std::free(p);
+  ++g_frees;
+  return hipSuccess;
+}
+hipError_t hipMemPoolTrimTo(hipMemPool_t, size_t) {
+  g_used -= g_pooled;
+  g_pooled = 0;
+  return hipSuccess;
+}
+hipError_t hipGetDevice(int* d) {
+  *d = 0;
+  return hipSuccess;
+}
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipDeviceSynchronize(void) { return hipSuccess; }
+hipError_t hipStreamQuery(hipStream_t) { return hipSuccess; }
+hipError_t hipGetLastError(void) { return hipSuccess; }
+const char* hipGetErrorString(hipError_t) { return "error"; }
+hipError_t hipDeviceGetDefaultMemPool(hipMemPool_t* p, int) {
+  *p = nullptr;
+  return hipSuccess;
+}
+hipError_t hipMemPoolSetAttribute(hipMemPool_t, hipMemPoolAttr, void*) { return hipSuccess; }
+}
+
+namespace {
+
+constexpr size_t MiB = (size_t)1 << 20;
+const hipStream_t kStream = reinterpret_cast<hipStream_t>((uintptr_t)64);
+
+// What earlier calls left idle, however small, is back on the device before a call is refused.
+int refusal() {
+  CHECK(guarded([] {
+          WsLease ws;
+          for (int i = 0; i < 8; ++i) (void)ws->get_bytes(i, 20 * MiB, kStream);  // slabs below 32 MiB
+        }) == GB_OK);
+  const size_t slabs = g_used;
+  CHECK(slabs >= 160 * MiB);
+  g_capacity = 300 * MiB;
+  CHECK(guarded([] {
+          { DBuf<char> freed(30 * MiB, kStream); }  // put aside by this very call
+          DBuf<char> large(280 * MiB, kStream);
+          CHECK(large.get() != nullptr);
+        }) == GB_OK);
+  CHECK(guarded([] { DBuf<char> too_large(301 * MiB, kStream); }) == GB_ENOMEM);
+  return 0;
+}
+
+// The same through a registered allocator.
+size_t g_hook_used = 0;
+std::map<void*, size_t> g_hook_live;
+void* hook_alloc(size_t n, void*, void*) {
+  if (g_hook_used + n > 300 * MiB) return nullptr;
+  void* p = std::malloc(16);
+  g_hook_live[p] = n;
+  g_hook_used += n;
+  return p;
+}
+void hook_free(void* p, void*, void*) {
+  g_hook_used -= g_hook_live[p];
+  g_hook_live.erase(p);
+  std::free(p);
+}
+int hook_refusal() {
+  CHECK(gb_set_allocator(hook_alloc, hook_free, nullptr) == GB_OK);
+  CHECK(guarded([] {
+          WsLease ws;
+          for (int i = 0; i < 4; ++i) (void)ws->get_bytes(i, 50 * MiB, kStream);
+        }) == GB_OK);
+  CHECK(g_hook_used >= 200 * MiB);
+  CHECK(guarded([] {
+          DBuf<char> large(280 * MiB, kStream);
+          CHECK(large.get() != nullptr);
+        }) == GB_OK);
+  CHECK(guarded([] { DBuf<char> too_large(301 * MiB, kStream); }) == GB_ENOMEM);
+  CHECK(g_hook_used == 0);
+  return 0;
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+  const std::string what = argc > 1 ? argv[1] : "";
+  int rc = 2;
+  if (what == "refusal") rc = refusal();
+  if (what == "hook_refusal") rc = hook_refusal();
+  if (rc == 0) std::printf("ok\n");
+  return rc;
+}

@@ -1,0 +1,31 @@
+"""The library's device-memory code on the CPU: api.hip as host C++ with a counted heap in place of
+the device (tests/memory/driver.cpp), under the address sanitizer."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("memory") / "driver")
+    cmd = ["g++", "-std=c++17", "-g", "-O1", "-fsanitize=address", "-no-pie", "-w",
+           "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+           os.path.join(ROOT, "tests", "memory", "driver.cpp"), "-o", exe,
+           "-Wl,--unresolved-symbols=ignore-all", "-lpthread"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    return exe
+
+
+def _run(driver, what):
+    r = subprocess.run([driver, what], capture_output=True, text=True, timeout=60,
+                       env=dict(os.environ, ASAN_OPTIONS="detect_leaks=0"))
+    assert r.returncode == 0 and r.stdout == "ok\n", (r.stdout + r.stderr)[-3000:]
+
+
+@pytest.mark.parametrize("what", ["refusal", "hook_refusal"])
+def test_idle_memory_goes_back_before_a_refusal(driver, what):
+    _run(driver, what)
