@@ -269,23 +269,39 @@ void Workspace::release_all() {
   }
 }
 
-std::mutex g_cached_mu;
-std::vector<CachedBuf> g_cached;  // idle
-size_t g_cached_bytes = 0;
+// Idle checkpoint buffers.  The entries own nothing and the list is never destroyed: an entry that
+// finds no host memory leaves its buffer with the caller, and a process may end with idle ones.
+namespace {
+struct IdleCached {
+  struct Entry {
+    void* p;
+    size_t bytes;
+    int device;
+    Allocator a;
+  };
+  std::mutex m;
+  std::vector<Entry> list;
+  size_t bytes = 0;
+};
+IdleCached& idle_cached() {
+  static auto* p = new IdleCached;
+  return *p;
+}
+}  // namespace
 
 CachedBuf::CachedBuf(size_t need, hipStream_t s) {
   GB_HIP(hipGetDevice(&device));
+  IdleCached& idle = idle_cached();
   {
-    std::lock_guard<std::mutex> lk(g_cached_mu);
-    for (size_t i = 0; i < g_cached.size(); ++i) {
-      CachedBuf& c = g_cached[i];
+    std::lock_guard<std::mutex> lk(idle.m);
+    for (size_t i = 0; i < idle.list.size(); ++i) {
+      const IdleCached::Entry c = idle.list[i];
       if (c.device != device || c.bytes < need || c.bytes > 2 * need) continue;
       p = c.p;
       bytes = c.bytes;
       a = c.a;
-      c.p = nullptr;  // its destructor has nothing to give back
-      g_cached_bytes -= bytes;
-      g_cached.erase(g_cached.begin() + i);
+      idle.bytes -= bytes;
+      idle.list.erase(idle.list.begin() + i);
       return;
     }
   }
@@ -295,16 +311,12 @@ CachedBuf::CachedBuf(size_t need, hipStream_t s) {
 
 CachedBuf::~CachedBuf() {
   if (!p) return;
+  IdleCached& idle = idle_cached();
   try {
-    std::lock_guard<std::mutex> lk(g_cached_mu);
-    if (g_cached_bytes + bytes <= kCachedMost) {
-      CachedBuf idle;
-      idle.p = p;
-      idle.bytes = bytes;
-      idle.device = device;
-      idle.a = a;
-      g_cached.push_back(std::move(idle));
-      g_cached_bytes += bytes;
+    std::lock_guard<std::mutex> lk(idle.m);
+    if (idle.bytes + bytes <= kCachedMost) {
+      idle.list.push_back({p, bytes, device, a});
+      idle.bytes += bytes;
       return;
     }
   } catch (...) {  // no room in the list: freed below
@@ -313,18 +325,18 @@ CachedBuf::~CachedBuf() {
 }
 
 void cached_trim() {
-  std::vector<CachedBuf> idle;
+  IdleCached& idle = idle_cached();
+  std::vector<IdleCached::Entry> list;
   {
-    std::lock_guard<std::mutex> lk(g_cached_mu);
-    idle.swap(g_cached);
-    g_cached_bytes = 0;
+    std::lock_guard<std::mutex> lk(idle.m);
+    list.swap(idle.list);
+    idle.bytes = 0;
   }
   int cur = 0;
   (void)hipGetDevice(&cur);
-  for (CachedBuf& c : idle) {
+  for (const IdleCached::Entry& c : list) {
     (void)hipSetDevice(c.device);
     dfree(c.p, nullptr, c.a);
-    c.p = nullptr;
   }
   (void)hipSetDevice(cur);
 }

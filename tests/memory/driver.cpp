@@ -127,6 +127,38 @@ int hook_refusal() {
   return 0;
 }
 
+// A checkpoint whose list has no memory for its entry is freed, once, and the list stays usable.
+int no_host_memory() {
+  {
+    std::vector<CachedBuf> held;
+    for (int i = 0; i < 40; ++i) held.emplace_back(40 * MiB, kStream);
+    g_no_host_memory = true;
+    held.clear();
+    g_no_host_memory = false;
+  }
+  CHECK(g_frees > 0);  // the list had no room for all of them
+  const int kept = 40 - g_frees, mallocs = g_mallocs;
+  {
+    std::vector<CachedBuf> again;
+    for (int i = 0; i < 40; ++i) again.emplace_back(40 * MiB, kStream);
+    CHECK(g_mallocs == mallocs + 40 - kept);
+  }
+  cached_trim();
+  CHECK(g_live.empty());
+  return 0;
+}
+
+// The process may end with idle checkpoints (nothing is freed then: the runtime may be gone).
+int idle_at_exit() {
+  const int frees = g_frees;
+  {
+    std::vector<CachedBuf> held;
+    for (int i = 0; i < 5; ++i) held.emplace_back(40 * MiB, kStream);
+  }
+  CHECK(g_frees == frees);
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -134,6 +166,8 @@ int main(int argc, char** argv) {
   int rc = 2;
   if (what == "refusal") rc = refusal();
   if (what == "hook_refusal") rc = hook_refusal();
+  if (what == "no_host_memory") rc = no_host_memory();
+  if (what == "idle_at_exit") rc = idle_at_exit();
   if (rc == 0) std::printf("ok\n");
   return rc;
 }

@@ -21,11 +21,16 @@ def driver(tmp_path_factory):
 
 
 def _run(driver, what):
-    r = subprocess.run([driver, what], capture_output=True, text=True, timeout=60,
+    r = subprocess.run([driver, what], capture_output=True, text=True, timeout=20,
                        env=dict(os.environ, ASAN_OPTIONS="detect_leaks=0"))
     assert r.returncode == 0 and r.stdout == "ok\n", (r.stdout + r.stderr)[-3000:]
 
 
 @pytest.mark.parametrize("what", ["refusal", "hook_refusal"])
 def test_idle_memory_goes_back_before_a_refusal(driver, what):
+    _run(driver, what)
+
+
+@pytest.mark.parametrize("what", ["no_host_memory", "idle_at_exit"])
+def test_idle_checkpoints(driver, what):
     _run(driver, what)
