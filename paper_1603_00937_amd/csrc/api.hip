@@ -37,24 +37,54 @@ Allocator g_alloc;  // the registered hook (all null: the device pool)
 // of a step at 256 orbitals.  Buffers of up to 32 MiB that a call frees are put aside
 // until it ends, and where the work of their streams is then known to be done (every call waits
 // for it; the query below makes sure) they go to a process-wide list of idle ones, from which any
-// later call of the device, on any thread and stream, takes one of its power of two.  What a failed
-// call freed, what is freed outside of a call and what the list has no room for goes back to the
-// device pool as before.
+// later call of the device, on any thread and stream, takes one of its power of two.  Where the list
+// is full, the buffers idle for longest make room, so that it follows the sizes in use.  They, what
+// a failed call freed and what is freed outside of a call go back to the device pool.
 namespace {
+// f() with `dev` as the current device
+template <typename F>
+void on_device(int dev, F&& f) {
+  int cur = dev;
+  (void)hipGetDevice(&cur);
+  if (cur != dev) (void)hipSetDevice(dev);
+  f();
+  if (cur != dev) (void)hipSetDevice(cur);
+}
 constexpr int kMinClass = 8, kMaxClass = 25;
 constexpr size_t kIdleMost = (size_t)256 << 20;
 struct IdleBuffers {
+  struct Entry {
+    void* p;
+    uint64_t since;
+  };
   std::mutex m;
-  std::map<std::pair<int, int>, std::vector<void*>> list;  // by device and class
+  // by device and class, each list in the order the buffers came in (the last is taken first)
+  std::map<std::pair<int, int>, std::vector<Entry>> list;
   size_t bytes = 0;
-  bool add(int dev, int cls, void* p) noexcept {  // false: full, or no memory for the entry
+  uint64_t clock = 0;
+  bool add(int dev, int cls, void* p) noexcept {  // false: no memory for the entry
     const size_t n = (size_t)1 << cls;
     try {
-      std::lock_guard<std::mutex> lk(m);
-      if (bytes + n > kIdleMost) return false;
-      list[{dev, cls}].push_back(p);
-      bytes += n;
-      return true;
+      for (;;) {
+        std::unique_lock<std::mutex> lk(m);
+        if (bytes + n <= kIdleMost) {
+          list[{dev, cls}].push_back({p, clock++});
+          bytes += n;
+          return true;
+        }
+        auto oldest = list.end();
+        for (auto it = list.begin(); it != list.end(); ++it)
+          if (!it->second.empty() && (oldest == list.end() || it->second[0].since <
+                                                                  oldest->second[0].since))
+            oldest = it;
+        if (oldest == list.end()) return false;
+        void* out = oldest->second[0].p;
+        const int on = oldest->first.first;
+        bytes -= (size_t)1 << oldest->first.second;
+        oldest->second.erase(oldest->second.begin());
+        lk.unlock();
+        on_device(on, [&] { (void)hipFreeAsync(out, nullptr); });
+      }
     } catch (...) {
       return false;
     }
@@ -98,7 +128,7 @@ struct CallScope {
     std::lock_guard<std::mutex> lk(b.m);
     auto it = b.list.find({dev, cls});
     if (it == b.list.end() || it->second.empty()) return nullptr;
-    void* p = it->second.back();
+    void* p = it->second.back().p;
     it->second.pop_back();
     b.bytes -= (size_t)1 << cls;
     return p;
@@ -135,19 +165,16 @@ thread_local CallScope* CallScope::top = nullptr;
 
 void small_trim() {
   IdleBuffers& b = idle_buffers();
-  std::map<std::pair<int, int>, std::vector<void*>> idle;
+  decltype(b.list) idle;
   {
     std::lock_guard<std::mutex> lk(b.m);
     idle.swap(b.list);
     b.bytes = 0;
   }
-  int cur = 0;
-  (void)hipGetDevice(&cur);
-  for (auto& kv : idle) {
-    (void)hipSetDevice(kv.first.first);
-    for (void* p : kv.second) (void)hipFreeAsync(p, nullptr);
-  }
-  (void)hipSetDevice(cur);
+  for (auto& kv : idle)
+    on_device(kv.first.first, [&] {
+      for (const auto& e : kv.second) (void)hipFreeAsync(e.p, nullptr);
+    });
 }
 
 // What no call holds goes back to the device (or to the allocator that made it): the idle lists, and
@@ -269,8 +296,9 @@ void Workspace::release_all() {
   }
 }
 
-// Idle checkpoint buffers.  The entries own nothing and the list is never destroyed: an entry that
-// finds no host memory leaves its buffer with the caller, and a process may end with idle ones.
+// Idle checkpoint buffers, those idle for longest first; they make room where the list is full.  The
+// entries own nothing and the list is never destroyed: an entry that finds no host memory leaves its
+// buffer with the caller, and a process may end with idle ones.
 namespace {
 struct IdleCached {
   struct Entry {
@@ -313,13 +341,20 @@ CachedBuf::~CachedBuf() {
   if (!p) return;
   IdleCached& idle = idle_cached();
   try {
-    std::lock_guard<std::mutex> lk(idle.m);
-    if (idle.bytes + bytes <= kCachedMost) {
-      idle.list.push_back({p, bytes, device, a});
-      idle.bytes += bytes;
-      return;
+    while (bytes <= kCachedMost) {
+      std::unique_lock<std::mutex> lk(idle.m);
+      if (idle.bytes + bytes <= kCachedMost) {
+        idle.list.push_back({p, bytes, device, a});
+        idle.bytes += bytes;
+        return;
+      }
+      const IdleCached::Entry out = idle.list[0];
+      idle.list.erase(idle.list.begin());
+      idle.bytes -= out.bytes;
+      lk.unlock();
+      on_device(out.device, [&] { dfree(out.p, nullptr, out.a); });
     }
-  } catch (...) {  // no room in the list: freed below
+  } catch (...) {  // no memory for the entry: freed below
   }
   dfree(p, nullptr, a);
 }
@@ -332,13 +367,8 @@ void cached_trim() {
     list.swap(idle.list);
     idle.bytes = 0;
   }
-  int cur = 0;
-  (void)hipGetDevice(&cur);
-  for (const IdleCached::Entry& c : list) {
-    (void)hipSetDevice(c.device);
-    dfree(c.p, nullptr, c.a);
-  }
-  (void)hipSetDevice(cur);
+  for (const IdleCached::Entry& c : list)
+    on_device(c.device, [&] { dfree(c.p, nullptr, c.a); });
 }
 
 std::mutex g_ws_mu;

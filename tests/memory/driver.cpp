@@ -159,6 +159,38 @@ int idle_at_exit() {
   return 0;
 }
 
+// Full lists follow the sizes in use.
+int full_lists() {
+  auto call = [](int count, size_t each) {
+    const int before = g_mallocs;
+    CHECK(guarded([&] {
+            std::vector<DBuf<char>> b;
+            for (int i = 0; i < count; ++i) b.emplace_back(each, kStream);
+          }) == GB_OK);
+    return g_mallocs - before;
+  };
+  CHECK(call(8, 32 * MiB) == 8);  // all that the list holds
+  CHECK(call(8, 32 * MiB) == 0);
+  CHECK(call(20, MiB) == 20);
+  CHECK(call(20, MiB) == 0);  // twenty of these and seven of the others
+  CHECK(call(8, 32 * MiB) == 1);
+  auto checkpoints = [](int count, size_t each) {
+    const int before = g_mallocs;
+    std::vector<CachedBuf> b;
+    for (int i = 0; i < count; ++i) b.emplace_back(each, kStream);
+    return g_mallocs - before;
+  };
+  CHECK(checkpoints(22, 2048 * MiB) == 22);
+  CHECK(checkpoints(22, 2048 * MiB) == 0);
+  CHECK(checkpoints(30, 200 * MiB) == 30);
+  CHECK(checkpoints(30, 200 * MiB) == 0);
+  const size_t idle = g_used - g_pooled;
+  CHECK(idle <= (48 << 10) * MiB + 256 * MiB);
+  CHECK(checkpoints(1, (60 << 10) * MiB) == 1);  // larger than the list: freed, and nothing else is
+  CHECK(g_used - g_pooled == idle);
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -168,6 +200,7 @@ int main(int argc, char** argv) {
   if (what == "hook_refusal") rc = hook_refusal();
   if (what == "no_host_memory") rc = no_host_memory();
   if (what == "idle_at_exit") rc = idle_at_exit();
+  if (what == "full_lists") rc = full_lists();
   if (rc == 0) std::printf("ok\n");
   return rc;
 }

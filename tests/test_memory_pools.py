@@ -34,3 +34,7 @@ def test_idle_memory_goes_back_before_a_refusal(driver, what):
 @pytest.mark.parametrize("what", ["no_host_memory", "idle_at_exit"])
 def test_idle_checkpoints(driver, what):
     _run(driver, what)
+
+
+def test_full_lists_follow_the_sizes_in_use(driver):
+    _run(driver, "full_lists")
