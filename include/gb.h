@@ -43,8 +43,11 @@ typedef int32_t gb_status;
 /* The dense batch buffers of gb_density / gb_foe_density are cached between calls (per device
  * and per concurrent call, grown when a call needs more), so a loop of calls does not
  * reallocate them; so are the host buffers of the multilevel partitioner (its coarse graphs
- * and the pinned copy of the graph it reads), and up to 256 MiB of the smaller device buffers that
- * calls have freed.  gb_trim frees the cached buffers of every call that has returned. */
+ * and the pinned copy of the graph it reads), up to 256 MiB of the smaller device buffers that
+ * calls have freed, and up to 48 GiB of checkpoints of destroyed tapes and of the terms that
+ * gb_foe_density keeps between its two passes.  Other users of the device do not see that memory as
+ * free until gb_trim, which frees the cached buffers of every call that has returned; a call that
+ * finds no memory does so by itself before it fails. */
 gb_status gb_trim(void);
 
 /* Kernel-variant table of the autotuner (the split squares' kernel, chosen per size class of batches,
@@ -285,7 +288,9 @@ typedef struct {
   double emin, emax;         /* spectral bounds; both 0 = Gershgorin                          */
   int32_t keep_tape;         /* 1: keep SP2 checkpoints for gb_density_vjp (GB_FP64 only)    */
   int32_t tape_stride;       /* checkpoint every tape_stride-th iterate; 0 = every iterate    *
-                              * where 32 of them take at most 32 GiB, else every fourth       */
+                              * where 32 of them take at most 32 GiB, else every fourth; an   *
+                              * expansion that goes past 32 GiB, or finds no memory for one,  *
+                              * keeps every fourth of those it has and goes on like that      */
   int32_t launch_mode;       /* 0 (default): device-driven loop -- one batched squaring     *
                               *    launch per step over every subgraph; the stop flag, step   *
                               *    counter, branch and step records stay on the device, every *

@@ -1748,7 +1748,19 @@ struct TapeData {
   DBuf<int4> tiles;
   DBuf<int32_t> core_ptr, sub_ptr, sub_idx, sub_pos;
   std::vector<CachedBuf> ckpt;  // X_0, X_stride, X_2stride, ...
+  bool thins = false;           // stride 1 by the library's choice: fewer where they find no room
+  void thin() {                 // to every fourth (nothing may read the others any more)
+    std::vector<CachedBuf> kept;
+    for (size_t i = 0; i < ckpt.size(); i += kThinned) kept.push_back(std::move(ckpt[i]));
+    ckpt.swap(kept);
+    stride = kThinned;
+    thins = false;
+  }
+  static constexpr int kThinned = 4;
 };
+// Most memory of a tape that keeps every iterate because nobody asked for another stride: some
+// thirty steps of 1 GiB.
+constexpr size_t kTapeMost = (size_t)32 << 30;
 
 namespace {
 
@@ -2258,16 +2270,38 @@ int sp2_loop(T*& X, T*& S, const Plan& pl, const DBuf<int4>& tiles, const int64_
       return it;
     }
     prev_b = r.b;
-    T* to = S;
+    T* to = nullptr;
     if constexpr (std::is_same<T, double>::value) {
       if (tape) {
         tape->branch.push_back((uint8_t)r.b);
-        if ((it + 1) % tape->stride == 0) {
-          tape->ckpt.emplace_back(pl.total * sizeof(double), s);
-          to = static_cast<double*>(tape->ckpt.back().p);
+        const size_t need = pl.total * sizeof(double);
+        bool room = !tape->thins || (tape->ckpt.size() + 1) * need <= kTapeMost;
+        if (room && (it + 1) % tape->stride == 0) {
+          try {
+            tape->ckpt.emplace_back(need, s);
+            to = static_cast<double*>(tape->ckpt.back().p);
+          } catch (const Error& e) {
+            if (e.code != GB_ENOMEM || !tape->thins) throw;
+            room = false;
+          }
+        }
+        if (!room) {
+          // X is a checkpoint, perhaps one of those that go
+          if (X != scratch[0] && X != scratch[1]) {
+            GB_HIP(hipMemcpyAsync(scratch[0], X, need, hipMemcpyDeviceToDevice, s));
+            X = scratch[0];
+            S = scratch[1];
+          }
+          GB_HIP(hipStreamSynchronize(s));
+          tape->thin();
+          if ((it + 1) % tape->stride == 0) {
+            tape->ckpt.emplace_back(need, s);
+            to = static_cast<double*>(tape->ckpt.back().p);
+          }
         }
       }
     }
+    if (!to) to = S;
     GB_HIP(hipEventRecord(tm.a, s));
     launch_step<T>(X, to, pl, tiles.get(), offs, s, planes, r.b == 1 ? 1 : 0, per_subgraph);
     GB_HIP(hipEventRecord(tm.b, s));
@@ -2771,8 +2805,10 @@ void density(const gb_ell& H, int32_t n_occ, const gb_sp2_opts& o, const Part& P
       t->emin = emin;
       t->emax = emax;
       // every iterate where some thirty of them are small change in HBM (the reverse sweep then
-      // recomputes nothing), else every fourth
-      t->stride = o.tape_stride > 0 ? o.tape_stride : 32 * pl.total * 8 <= (int64_t)32 << 30 ? 1 : 4;
+      // recomputes nothing), else, and from where they find no room on, every fourth
+      t->stride = o.tape_stride > 0 ? o.tape_stride
+                  : 32 * (size_t)pl.total * 8 <= kTapeMost ? 1 : TapeData::kThinned;
+      t->thins = o.tape_stride <= 0 && t->stride == 1;
       t->max_sub = P.max_sub;
       for (int q = 0; q < P.n_sub; ++q)
         t->max_core = std::max(t->max_core, P.h_core_ptr[q + 1] - P.h_core_ptr[q]);
