@@ -339,6 +339,7 @@ CachedBuf::CachedBuf(size_t need, hipStream_t s) {
 
 CachedBuf::~CachedBuf() {
   if (!p) return;
+  wait_if_failing();
   IdleCached& idle = idle_cached();
   try {
     while (bytes <= kCachedMost) {

@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <cstdint>
 #include <cstdio>
+#include <exception>
 #include <string>
 #include <vector>
 
@@ -69,12 +70,19 @@ struct DBuf {
   void detach_stream() { s = nullptr; }
 };
 
+// A call that fails may leave work behind on its stream.  What it gives back to a list, from which
+// another thread's call may take it at once, waits for the device first; a call that succeeds has
+// waited for its stream.  (The small buffers of a failed call are freed in stream order instead.)
+inline void wait_if_failing() {
+  if (std::uncaught_exceptions() > 0) (void)hipDeviceSynchronize();
+}
+
 // ---- cached batch buffers -------------------------------------------------------------------
 // The dense batch buffers (tens of GB at N = 100000) are kept between calls instead of being
 // returned to the pool: a call leases a workspace (one per concurrent call and device), takes
 // its buffers from numbered slots that grow when a call needs more, and gives it back at the
-// end.  Every call synchronises its stream before returning, so the next lease may use the
-// memory on any stream.  gb_trim frees the idle workspaces.
+// end.  Every call that succeeds synchronises its stream before returning, so the next lease may use
+// the memory on any stream.  gb_trim frees the idle workspaces.
 struct Workspace {
   int device = 0;
   struct Slab {
@@ -104,7 +112,9 @@ struct WsLease {
   // ext: a caller-owned workspace (not leased, not returned); nullptr leases a cached one
   explicit WsLease(Workspace* ext = nullptr) : w(ext ? ext : ws_acquire()), own(ext == nullptr) {}
   ~WsLease() {
-    if (own) ws_release(w);
+    if (!own) return;
+    wait_if_failing();
+    ws_release(w);
   }
   WsLease(const WsLease&) = delete;
   WsLease& operator=(const WsLease&) = delete;

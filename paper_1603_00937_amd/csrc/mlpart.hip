@@ -597,6 +597,7 @@ MlLease::MlLease() {
 }
 
 MlLease::~MlLease() {
+  wait_if_failing();  // copies into the pinned arrays
   std::lock_guard<std::mutex> lk(g_ml_mu);
   g_ml_free.push_back(p);
 }

@@ -2330,7 +2330,10 @@ struct ProgressLease {
   }
   ProgressLease(const ProgressLease&) = delete;
   ProgressLease& operator=(const ProgressLease&) = delete;
-  ~ProgressLease() { (void)pool().give(dev, p); }  // never freed: a failed loop's kernels may write it
+  ~ProgressLease() {
+    wait_if_failing();  // the loop's kernels write it
+    if (p && !pool().give(dev, p)) (void)hipHostFree(p);
+  }
 
  private:
   static IdlePool<LoopProgress*>& pool() {

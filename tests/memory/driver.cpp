@@ -12,7 +12,7 @@
 namespace {
 size_t g_capacity = (size_t)1 << 40, g_used = 0, g_pooled = 0;
 int g_mallocs = 0, g_frees = 0;
-bool g_no_host_memory = false;
+bool g_no_host_memory = false, g_running = false;  // running: work that nobody waited for
 std::map<void*, size_t> g_live;
 
 #define CHECK(c)                                                              \
@@ -62,7 +62,10 @@ hipError_t hipGetDevice(int* d) {
   return hipSuccess;
 }
 hipError_t hipSetDevice(int) { return hipSuccess; }
-hipError_t hipDeviceSynchronize(void) { return hipSuccess; }
+hipError_t hipDeviceSynchronize(void) {
+  g_running = false;
+  return hipSuccess;
+}
 hipError_t hipStreamQuery(hipStream_t) { return hipSuccess; }
 hipError_t hipGetLastError(void) { return hipSuccess; }
 const char* hipGetErrorString(hipError_t) { return "error"; }
@@ -191,6 +194,35 @@ int full_lists() {
   return 0;
 }
 
+// What a failed call leaves running is waited for before another call can take its buffers.
+int failed_call() {
+  void* held = nullptr;
+  CHECK(guarded([&] {
+          WsLease ws;
+          held = ws->get_bytes(0, 64 * MiB, kStream);
+        }) == GB_OK);
+  CHECK(guarded([&] {
+          WsLease ws;
+          CHECK(ws->get_bytes(0, 64 * MiB, kStream) == held);
+          g_running = true;
+          fail(GB_EHIP, "a call fails in between");
+        }) == GB_EHIP);
+  CHECK(!g_running);
+  CHECK(guarded([&] {
+          CachedBuf b(64 * MiB, kStream);
+          g_running = true;
+          fail(GB_EHIP, "a call fails in between");
+        }) == GB_EHIP);
+  CHECK(!g_running);
+  g_running = true;  // another stream's: no business of a call that succeeds
+  CHECK(guarded([&] {
+          WsLease ws;
+          CachedBuf b(64 * MiB, kStream);
+        }) == GB_OK);
+  CHECK(g_running);
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -201,6 +233,7 @@ int main(int argc, char** argv) {
   if (what == "no_host_memory") rc = no_host_memory();
   if (what == "idle_at_exit") rc = idle_at_exit();
   if (what == "full_lists") rc = full_lists();
+  if (what == "failed_call") rc = failed_call();
   if (rc == 0) std::printf("ok\n");
   return rc;
 }

@@ -38,3 +38,7 @@ def test_idle_checkpoints(driver, what):
 
 def test_full_lists_follow_the_sizes_in_use(driver):
     _run(driver, "full_lists")
+
+
+def test_failed_calls_give_nothing_back_that_is_in_use(driver):
+    _run(driver, "failed_call")
