@@ -526,9 +526,12 @@ __global__ __launch_bounds__(kT) void k_x2_rows_hash(const int32_t* __restrict__
 // The same rows in one pass over the pairs: the accumulators themselves sit in LDS pages of
 // 2^shift consecutive vertices, given out as row i's pairs first touch them (dir: page number ->
 // LDS slot).  Vertices close in space are close in number, so the ~1500 candidates of a row touch
-// few pages (about 160 of 32 vertices), and neither a candidate set nor ranks are needed: an
-// entry no pair reached is 0 and tau > 0 drops it.  Decisions, and the sums near tau, are those
-// of k_x2_rows, so the graph is the same bit for bit.  One wave takes a row k at a time, 64 slots
+// few pages (about 160 of 32 vertices), and neither a candidate set nor ranks are needed: the sums
+// start at -0, which the first product that is not -0 itself changes for good, so an entry that
+// still holds it was reached by no pair, or sums to 0 in any order, and tau > 0 drops it.  (Were it
+// +0, a tau below the rounding of the sums would have every such entry, half of the pages', summed
+// once more: 17 ms instead of 0.3 at N = 1024, tau = 1e-15.)  The other decisions, and the sums near
+// tau, are those of k_x2_rows, so the graph is the same bit for bit.  One wave takes a row k at a time, 64 slots
 // per step up to the row's last entry.  A row that needs more than pcap pages or keeps more than
 // cap entries reports it through `overflow` (pages, kept) and the launch is repeated with room or
 // left to the kernels below.
@@ -601,7 +604,7 @@ __global__ __launch_bounds__(kPT) void k_x2_rows_paged(
   }
   // a system of at most pcap pages gets them all, in order
   for (int q = threadIdx.x; q < ndir; q += kPT) dir[q] = ndir <= g.pcap ? q : -1;
-  for (int q = threadIdx.x; q < flat; q += kPT) acc[q] = 0.0;
+  for (int q = threadIdx.x; q < flat; q += kPT) acc[q] = -0.0;
   if (threadIdx.x == 0) {
     npages = 0;
     red[0] = w;
@@ -680,15 +683,15 @@ __global__ __launch_bounds__(kPT) void k_x2_rows_paged(
       const int f = ((qb + e * NW) << 6) | lane;
       const int pl = f < total ? plist[f >> g.shift] : 0;
       cols[e] = f < total ? (pl >> 10) << g.shift | (f & low) : n;
-      sums[e] = f < total ? fabs(acc[(pl & 1023) << g.shift | (f & low)]) : 0.0;
+      sums[e] = f < total ? acc[(pl & 1023) << g.shift | (f & low)] : -0.0;
     }
 #pragma unroll
     for (int e = 0; e < B; ++e) {
       const int q = qb + e * NW, j = cols[e];
       if (q >= groups) break;
-      const double a = sums[e];
+      const double a = fabs(sums[e]);
       bool keep = j == i, band = false;
-      if (j != i && j < n) {
+      if (j != i && j < n && !(sums[e] == 0.0 && signbit(sums[e]))) {
         band = all_ascending || fabs(a - tau) <= margin;
         keep = !band && a >= tau;
       }

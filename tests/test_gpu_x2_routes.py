@@ -77,3 +77,11 @@ def test_wide_rows_are_refused_on_every_route(n, width, sets, monkeypatch):
             gb.build_graph(col, val, tau)
     narrow = gb.build_graph(col[:, :1024].contiguous(), val[:, :1024].contiguous(), 1e-5)
     assert narrow.nnz == n
+
+
+@pytest.mark.parametrize("tau", [1e-300, 1e-16, 1e-15, 1e-14])
+def test_threshold_within_rounding(model_cache, tau, monkeypatch):
+    """Below the rounding of the sums every pair's sum is decided in ascending order; what no pair
+    reaches is not."""
+    m = model_cache("n1024")
+    _same_and_not_slower(m["H_col"], m["H_val"], tau, monkeypatch, 3.0)
