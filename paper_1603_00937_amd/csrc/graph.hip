@@ -1204,14 +1204,39 @@ void graph_x2_hash(const gb_ell& H, const double* x0, double tau, Csr& out, hipS
   GB_LAUNCH_CHECK();
 }
 
+// Does one pass with paged accumulators beat two passes over candidate sets?  It saves a visit of
+// every pair, and bitmaps whose handling grows with n, but gives pages out row by row and clears and
+// reads them whole, which takes rows of many pairs, the more so the further a row's partners are
+// apart in number.  Measured, one pass / two (ms), w the ELL width, on places in Morton order
+// (m) and lattices in row order (l), which spread a row over more pages:
+//   n = 4096      w  62  0.213 / 0.189 m    w 121  0.253 / 0.278 m    w 247  0.359 / 0.625 m
+//   n = 8192      w 123  0.475 / 0.386 m    w  54  0.364 / 0.229 l    w 241  0.817 / 1.03 m
+//   n = 18000     w 165  1.03 / 1.00 m      w  73  0.611 / 0.412 m    w 253  1.88 / 2.47 m
+//   n = 32768     w 131  1.67 / 1.53 m      w 125  2.11 / 1.68 l      w 255  3.22 / 4.45 m
+//   n = 64000     w  77  1.97 / 1.81 m      w 125  4.35 / 3.20 l      w 257  5.63 / 8.79 m
+//   n = 80000     w  77  2.20 / 2.10 m      w  27  1.91 / 1.04 l      w 137  3.51 / 3.89 m
+//   n = 100000    w  41  1.74 / 1.82 m      w  81  2.94 / 3.46 m      w 263  8.28 / 15.8 m
+//   n = 125000    w   7  1.92 / 3.22 l      w  27  2.67 / 3.47 l      w 255  10.6 / 21.8 m
+// Above 2^17 two passes use hash sets, whose cost does not grow with n: narrow rows stay with them
+// (n = 166375, w 7: 2.64 / 1.32 l; n = 512000, w 27: 22.5 / 11.4 l), the others do not (n = 150000,
+// w 41: 2.87 / 10.7 m; n = 262144, w 125: 18.8 / 57.8 l).
+bool x2_paged_pays(int n, int w) {
+  const int least = n <= 4096 ? 96 : n <= 65536 ? 192 : n <= 98304 ? 128 : n <= 114688 ? 64
+                  : n <= (1 << 17) ? 1 : 32;
+  return w >= least;
+}
+
 void graph_x2(const gb_ell& H, const double* x0, double tau, Csr& out, hipStream_t s) {
   const int n = H.n, w = H.width;
   // what the two-pass kernels' rows hold, whichever kernels would take these
   if (w > kX2Q * kT) fail(GB_EUNSUPPORTED, "X2 graph: ELL width %d above %d", w, kX2Q * kT);
   // tau = 0 keeps candidates whose sum is 0, which only the candidate sets know
-  if (tau > 0.0 && !vertex_sets_forced() && graph_x2_paged(H, x0, tau, out, s)) return;
-  // two passes: bitmaps 37 against 67 ms at n = 160002, 125 against 112 at n = 262000
-  if (use_hash_sets(n, 3 << 16)) {
+  if (tau > 0.0 && !vertex_sets_forced() && x2_paged_pays(n, w) &&
+      graph_x2_paged(H, x0, tau, out, s))
+    return;
+  // two passes, bitmaps against hash sets: 37 / 67 ms at n = 160002 (w 255), 125 / 112 at n = 262000;
+  // rows below 32 slots 3.2 / 1.3 (w 7) and 3.9 / 3.9 (w 27) at n = 166375
+  if (use_hash_sets(n, w < 32 ? 1 << 17 : 3 << 16)) {
     graph_x2_hash(H, x0, tau, out, s);
     return;
   }

@@ -85,3 +85,56 @@ def test_threshold_within_rounding(model_cache, tau, monkeypatch):
     reaches is not."""
     m = model_cache("n1024")
     _same_and_not_slower(m["H_col"], m["H_val"], tau, monkeypatch, 3.0)
+
+
+@pytest.mark.parametrize("L,reach,sets", [(10, 1, "bitmap"), (24, 1, "bitmap"), (32, 2, "bitmap"),
+                                          (44, 1, "bitmap"), (55, 1, "hash"), (80, 1, "hash")])
+def test_narrow_matrices(L, reach, sets, monkeypatch):
+    """A few pairs per row do not pay for the pages; sets: what such a matrix takes instead."""
+    col, val = _lattice(L, reach)
+    _same_and_not_slower(col, val, 1e-9, monkeypatch, 1.35, sets)
+
+
+def _ring(N, reach, seed):
+    """Symmetric H coupling every vertex to the `reach` next ones on a ring."""
+    rng = np.random.default_rng(seed)
+    up = rng.uniform(-0.3, 0.3, (reach + 1, N))
+    off = np.arange(-reach, reach + 1)
+    col = (np.arange(N)[:, None] + off) % N
+    val = np.stack([up[o] if o >= 0 else np.roll(up[-o], -o) for o in off], axis=1)
+    s = np.argsort(col, axis=1, kind="stable")
+    return (np.take_along_axis(col, s, 1).astype(np.int32),
+            np.ascontiguousarray(np.take_along_axis(val, s, 1)))
+
+
+def _same(col, val, tau, monkeypatch):
+    import torch
+    import paper_1603_00937_amd as gb
+    Hc, Hv = torch.from_numpy(col).cuda(), torch.from_numpy(val).cuda()
+    want, _ = _build(gb, Hc, Hv, tau, monkeypatch, "hash" if len(col) > 1 << 18 else "bitmap", 1)
+    got, _ = _build(gb, Hc, Hv, tau, monkeypatch, None, 1)
+    assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+
+
+@pytest.mark.parametrize("N,reach", [(97, 48), (200, 95), (1000, 50), (4096, 48), (4097, 96),
+                                     (6143, 96), (6144, 96), (6177, 100), (65536, 96), (65537, 64),
+                                     (98305, 32), (114689, 1), (131100, 16), (262200, 17),
+                                     (1048700, 16)])
+def test_one_pass_at_the_edges_of_its_page_tables(N, reach, monkeypatch):
+    """Rows just wide enough for one pass at every size where the choice or the pages change."""
+    _same(*_ring(N, reach, N), 1e-3, monkeypatch)
+
+
+def test_one_pass_with_padding_inside_rows(monkeypatch):
+    col, val = _ring(3000, 60, 8)
+    gap = np.random.default_rng(9).random(col.shape) < 0.2
+    gap[np.arange(3000)[:, None] == col] = False
+    col[gap], val[gap] = -1, 0.0
+    _same(col, val, 1e-4, monkeypatch)
+
+
+@pytest.mark.parametrize("N,reach", [(5000, 100), (9000, 100), (40000, 100), (140000, 20),
+                                     (140000, 60), (140000, 160)])
+def test_one_pass_with_random_numbers(N, reach, monkeypatch):
+    """All pages given out in order, too many of them, as many as room can be made for, and more."""
+    _same(*_renumbered(*_ring(N, reach, 5), 6), 1e-4, monkeypatch)
