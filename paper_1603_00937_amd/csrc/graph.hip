@@ -534,7 +534,9 @@ __global__ __launch_bounds__(kT) void k_x2_rows_hash(const int32_t* __restrict__
 // tau, are those of k_x2_rows, so the graph is the same bit for bit.  One wave takes a row k at a time, 64 slots
 // per step up to the row's last entry.  A row that needs more than pcap pages or keeps more than
 // cap entries reports it through `overflow` (pages, kept) and the launch is repeated with room or
-// left to the kernels below.
+// left to the kernels below; workgroups that start after a report of more than `most` pages, which
+// ends the attempt for good, return at once (vertices numbered at random, N = 18000: 4.4 ms spent on
+// two attempts before the two passes' 2.1, now 0.1).
 // The two-pass kernels visit every pair twice with an LDS atomic and two LDS look-ups; here a
 // pair costs one look-up and one ds_add_f64, and LDS no longer grows with n.  Bound by LDS and the
 // vector work of a pair at two workgroups per CU (the pages take ~50 KB), and, 40 % of it, by the chains
@@ -546,7 +548,7 @@ __global__ __launch_bounds__(kT) void k_x2_rows_hash(const int32_t* __restrict__
 // which share the rows they read, on one XCD: another 5 %.  512 threads: 256 take 23.9
 // and 1024 19.1 ms at 160002.
 struct X2Paged {
-  int shift, pcap, cap;
+  int shift, pcap, cap, most;
 };
 constexpr int kPT = 512;
 
@@ -583,7 +585,7 @@ __global__ __launch_bounds__(kPT) void k_x2_rows_paged(
     int all_ascending, X2Paged g, int32_t* __restrict__ cnt, int32_t* __restrict__ rows,
     int32_t* __restrict__ overflow) {
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ int32_t npages;
+  __shared__ int32_t npages, seen;
   const int i = xcd_run(blockIdx.x, n);
   if (i >= n) return;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -606,10 +608,15 @@ __global__ __launch_bounds__(kPT) void k_x2_rows_paged(
   for (int q = threadIdx.x; q < ndir; q += kPT) dir[q] = ndir <= g.pcap ? q : -1;
   for (int q = threadIdx.x; q < flat; q += kPT) acc[q] = -0.0;
   if (threadIdx.x == 0) {
+    seen = __hip_atomic_load(&overflow[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     npages = 0;
     red[0] = w;
   }
   __syncthreads();
+  if (seen > g.most) {  // the same for the whole workgroup
+    if (threadIdx.x == 0) cnt[i] = 0;
+    return;
+  }
   // the rows k of row i are its slots before the first padding entry
   for (int t = threadIdx.x; t < w; t += kPT)
     if ((unsigned)ci[t] >= (unsigned)n) atomicMin(&red[0], t);
@@ -1131,6 +1138,17 @@ bool graph_x2_paged(const gb_ell& H, const double* x0, double tau, Csr& out, hip
   g.cap = std::min(n, 2048);
   const size_t most = 158 * 1024;
   if (x2_paged_lds_bytes(n, w, g) > most) return false;
+  // Rows that ask for more pages: a second attempt costs as much as the first and has fewer
+  // workgroups per CU.  Bitmaps take less (randomly numbered, N = 8000, 239 slots: 1.8 ms for both
+  // attempts, 0.9 for bitmaps; N = 150000, 61 slots: 18.3 and 6.3); hash sets, which take their place
+  // above 3 << 16, do not (21.4).
+  const bool again = n > 3 << 16;
+  g.most = g.pcap;
+  if (again) {
+    X2Paged full = g;
+    while (g.most < ndir && (full.pcap = g.most + 1, x2_paged_lds_bytes(n, w, full) <= most))
+      ++g.most;
+  }
   DBuf<int32_t> cnt(n, s), ovf(2, s), rows, rlen;
   DBuf<double> rb;
   x2_row_bounds(H, x0, rb, rlen, s);
@@ -1151,8 +1169,8 @@ bool graph_x2_paged(const gb_ell& H, const double* x0, double tau, Csr& out, hip
     GB_HIP(hipStreamSynchronize(s));
     if (h[1] == 0 && h[2] == 0) break;
     // more pages (a row whose pages ran out has not counted what it keeps), more kept entries
-    if (attempt == 3) return false;
-    if (h[1] > 0) g.pcap = std::min(ndir, h[1] + h[1] / 8);
+    if (attempt == 3 || h[1] > g.most) return false;
+    if (h[1] > 0) g.pcap = std::min(g.most, h[1] + h[1] / 8);
     if (h[2] > 0) g.cap = std::min(n, (h[2] + 255) / 256 * 256);
     if (x2_paged_lds_bytes(n, w, g) > most) return false;
   }

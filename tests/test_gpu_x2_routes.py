@@ -134,7 +134,16 @@ def test_one_pass_with_padding_inside_rows(monkeypatch):
 
 
 @pytest.mark.parametrize("N,reach", [(5000, 100), (9000, 100), (40000, 100), (140000, 20),
-                                     (140000, 60), (140000, 160)])
+                                     (140000, 60), (140000, 160), (200000, 60), (200000, 160)])
 def test_one_pass_with_random_numbers(N, reach, monkeypatch):
     """All pages given out in order, too many of them, as many as room can be made for, and more."""
     _same(*_renumbered(*_ring(N, reach, 5), 6), 1e-4, monkeypatch)
+
+
+@pytest.mark.parametrize("N", [6400, 18000])
+def test_random_numbers_cost_little(N, monkeypatch):
+    """The pages of a randomly numbered system do not fit: that is found out early."""
+    from synth.model import ModelSpec, make_model
+    m = make_model(ModelSpec(n_sites=N // 2, seed=2))
+    col, val = _renumbered(m["H_col"], m["H_val"], 3)
+    _same_and_not_slower(col, val, 1e-5, monkeypatch, 1.5)
