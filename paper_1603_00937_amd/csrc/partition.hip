@@ -316,13 +316,19 @@ __global__ __launch_bounds__(kT) void k_row_words(int n, const int32_t* __restri
 
 // Common closed neighbours of the ends of every edge: w[e] = |row u and row col[e]| for the rows
 // of a symmetric CSR graph that holds its self loops (so each row is the closed neighbourhood).
-// One workgroup per vertex u, neighbours in number on one XCD: row u as a bitmap in LDS, then 16 lanes per neighbour
-// v >= u count row v's words against it; the count is symmetric, so they also write it at the
-// entry of u in row v, whose place they meet among the words (each entry has one writer).  *missing receives the smallest u whose row lacks u
-// (it is left as it was when every row holds its self loop).
+// One workgroup per vertex u, neighbours in number on one XCD: row u as a bitmap in LDS, then 16
+// lanes per neighbour v >= u count row v's words against it; the count is symmetric, so they also
+// write it at the entry of u in row v, whose place they meet among the words (each entry has one
+// writer).  *missing receives the smallest u whose row lacks u (it is left as it was when every row
+// holds its self loop).
 // Row v entry by entry against the bitmap, a wave per neighbour, took 1.84 ms at N = 18000 (535
-// entries a row) and 6.8 ms at N = 100000; words take 0.17 + 0.30 and 0.69 + 1.02 ms.
+// entries a row) and 6.8 ms at N = 100000; words take 0.17 + 0.30 and 0.69 + 1.02 ms.  Where a word
+// holds fewer than two entries (vertices numbered at random, lattices of few neighbours) it only
+// makes three words of one, 3.7 ms at N = 18000 numbered at random: such a row is left to
+// k_common_nb_entries, 1.75.  (In this kernel, whose registers leave six waves per SIMD, entries
+// took 2.2.)
 constexpr int kNbBatch = 512;
+__device__ __forceinline__ bool nb_by_entry(int words, int entries) { return 2 * words > entries; }
 template <bool BIG>
 __global__ __launch_bounds__(kT) void k_common_nb(int n, const int32_t* __restrict__ rp,
                                                   const int32_t* __restrict__ col,
@@ -337,9 +343,10 @@ __global__ __launch_bounds__(kT) void k_common_nb(int n, const int32_t* __restri
   int32_t* listed = reinterpret_cast<int32_t*>(nb + kNbBatch);
   const int u = xcd_run(blockIdx.x, n);
   if (u >= n) return;
+  const int b = rp[u], e_end = rp[u + 1];
+  if (nb_by_entry(wcnt[u], e_end - b)) return;  // the whole workgroup
   for (int i = threadIdx.x; i < nw; i += kT) bits[i] = 0u;
   __syncthreads();
-  const int b = rp[u], e_end = rp[u + 1];
   for (int i = threadIdx.x; i < wcnt[u]; i += kT) bits[words[b + i].idx] = words[b + i].mask;
   __syncthreads();
   if (threadIdx.x == 0 && !((bits[u >> 5] >> (u & 31)) & 1u)) atomicMin(missing, u);
@@ -401,6 +408,53 @@ __global__ __launch_bounds__(kT) void k_common_nb(int n, const int32_t* __restri
           if (q[h].x != u && pos[h] >= 0) w[pos[h]] = c[h];  // pos >= 0 in a symmetric graph
         }
       }
+    }
+  }
+}
+
+// The same for the rows left out there: one wave per neighbour v >= u counts row v's entries.
+__global__ __launch_bounds__(kT) void k_common_nb_entries(int n, const int32_t* __restrict__ rp,
+                                                          const int32_t* __restrict__ col,
+                                                          const int32_t* __restrict__ wcnt,
+                                                          int32_t* __restrict__ w,
+                                                          int32_t* __restrict__ missing) {
+  extern __shared__ uint32_t bits[];
+  const int u = blockIdx.x;
+  const int nw = (n + 31) >> 5;
+  const int b = rp[u], e_end = rp[u + 1];
+  if (!nb_by_entry(wcnt[u], e_end - b)) return;  // the whole workgroup
+  for (int i = threadIdx.x; i < nw; i += kT) bits[i] = 0u;
+  __syncthreads();
+  for (int e = b + threadIdx.x; e < e_end; e += kT) {
+    const int x = col[e];
+    atomicOr(&bits[x >> 5], 1u << (x & 31));
+  }
+  __syncthreads();
+  if (threadIdx.x == 0 && !((bits[u >> 5] >> (u & 31)) & 1u)) atomicMin(missing, u);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int e = b + wave; e < e_end; e += kT / 64) {
+    const int v = col[e];
+    if (v < u) continue;  // the same for the whole wave: workgroup v writes this entry
+    int c = 0, pos = -1;
+    const int f1 = rp[v + 1];
+    for (int f = rp[v] + lane; f < f1; f += 4 * 64) {  // four loads in flight per lane
+      int x[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[i] = f + 64 * i < f1 ? col[f + 64 * i] : -1;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (x[i] >= 0) {
+          c += (bits[x[i] >> 5] >> (x[i] & 31)) & 1u;
+          if (x[i] == u) pos = f + 64 * i;
+        }
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+      c += __shfl_down(c, off, 64);
+      pos = max(pos, __shfl_down(pos, off, 64));
+    }
+    if (lane == 0) {
+      w[e] = c;
+      if (v != u && pos >= 0) w[pos] = c;  // pos >= 0 in a symmetric graph
     }
   }
 }
@@ -790,6 +844,9 @@ void partition_multilevel_dev(const Csr& g, int32_t core_size, Part& P, hipStrea
   };
   if (lds_list <= 160 * 1024) count(k_common_nb<false>, lds_list);
   else count(k_common_nb<true>, lds);
+  GB_LAUNCH_CHECK();
+  hipLaunchKernelGGL(k_common_nb_entries, dim3(n), dim3(kT), lds, s, n, g.row_ptr.get(),
+                     g.col.get(), dwc.get(), dw.get(), dmiss.get());
   GB_LAUNCH_CHECK();
   DBuf<int32_t> dtop((size_t)n * kMlTop, s);
   hipLaunchKernelGGL(k_top_nb, dim3((n + kT / 64 - 1) / (kT / 64)), dim3(kT), 0, s, n,

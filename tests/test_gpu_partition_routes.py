@@ -89,3 +89,37 @@ def test_rows_are_not_fetched_one_by_one(kind):
     base = _time(lambda: gb.partition(g, 32, "block"))
     print(f"{kind}: {own * 1e3:.2f} ms, block {base * 1e3:.2f}, copies {small * 1e3:.2f}")
     assert own - base <= 0.6 * small + 0.002, (own, base, small)
+
+
+def _renumbered(n_sites, seed):
+    import torch
+    import paper_1603_00937_amd as gb
+    from synth.model import ModelSpec, make_model
+    m = make_model(ModelSpec(n_sites=n_sites, seed=2))
+    n = m["N"]
+    p = np.random.default_rng(seed).permutation(n)
+    out = []
+    for name in (np.arange(n), p):
+        c = np.where(m["H_col"] >= 0, name[np.maximum(m["H_col"], 0)], n)
+        s = np.argsort(c, axis=1, kind="stable")
+        c, v = np.take_along_axis(c, s, 1), np.take_along_axis(m["H_val"], s, 1)
+        col, val = np.empty_like(m["H_col"]), np.empty_like(m["H_val"])
+        col[name], val[name] = np.where(c == n, -1, c), v
+        out.append(gb.build_graph(torch.from_numpy(col).cuda(), torch.from_numpy(val).cuda(), 1e-5))
+    return out
+
+
+def test_cores_with_random_numbers():
+    import paper_1603_00937_amd as gb
+    for g in _renumbered(700, 5):
+        _check(gb, g, 32)
+
+
+def test_random_numbers_cost_little():
+    """The weights of 18000 randomly numbered vertices against the same graph in place order (with
+    core size 1 the weights and the growth are all there is)."""
+    import paper_1603_00937_amd as gb
+    ordered, shuffled = _renumbered(9000, 5)
+    a = _time(lambda: gb.partition(ordered, 1, "multilevel"))
+    b = _time(lambda: gb.partition(shuffled, 1, "multilevel"))
+    assert b <= 1.5 * a, (a, b)
