@@ -34,7 +34,7 @@ __device__ __forceinline__ double x0_entry(double h, bool diag, double emax, dou
 // by one workgroup: min and max are exact, so the order does not matter.  A NaN or Inf anywhere in
 // a row makes its ends so; fmin / fmax alone would skip a NaN.  Padding at the end of rows is read
 // 64 slots past the longest row of the group, no further (N = 4096, 247 of 2247 slots used: 0.17 ->
-// PADFIG ms).
+// 0.05 ms).
 // One thread per row straight from memory took 185 us at N = 18000 (255 slots) and 45 us at 256;
 // this takes 30 and 17 (128 us at N = 100000 x 335, 3.1 TB/s).
 constexpr int kDiscRows = 16;

@@ -3661,7 +3661,7 @@ void foe(const gb_ell& H, int32_t n_occ, const gb_foe_opts& o, const Part& P, do
   if ((size_t)max_np * 8 + (size_t)P.max_sub * 4 + 64 > 160 * 1024)
     fail(GB_EUNSUPPORTED, "subgraph of %d vertices too large", P.max_sub);
   // rows per workgroup: as many as the LDS of one CU holds (see k_foe_rows), at most four; past
-  // ~9900 vertices not even one row's two arrays fit, and V_{n-1} goes to global memory.  Fewer
+  // 10112 vertices not even one row's two arrays fit, and V_{n-1} goes to global memory.  Fewer
   // rows while that leaves at most a workgroup per compute unit (N = 512, 128 groups of four rows:
   // 2.99 -> 2.53 ms with two; N = 1024, 256 groups of four: 4.75 ms, with two 7.1)
   const size_t lds_max = 158 * 1024;
