@@ -41,15 +41,6 @@ Allocator g_alloc;  // the registered hook (all null: the device pool)
 // is full, the buffers idle for longest make room, so that it follows the sizes in use.  They, what
 // a failed call freed and what is freed outside of a call go back to the device pool.
 namespace {
-// f() with `dev` as the current device
-template <typename F>
-void on_device(int dev, F&& f) {
-  int cur = dev;
-  (void)hipGetDevice(&cur);
-  if (cur != dev) (void)hipSetDevice(dev);
-  f();
-  if (cur != dev) (void)hipSetDevice(cur);
-}
 constexpr int kMinClass = 8, kMaxClass = 25;
 constexpr size_t kIdleMost = (size_t)256 << 20;
 struct IdleBuffers {
@@ -560,6 +551,8 @@ gb_status gb_trim(void) {
     cached_trim();
     ml_trim();
     small_trim();
+    Timer::trim();
+    progress_trim();
   });
 }
 

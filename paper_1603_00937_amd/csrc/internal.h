@@ -7,6 +7,8 @@
 #include <cstdint>
 #include <cstdio>
 #include <exception>
+#include <map>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -76,6 +78,84 @@ struct DBuf {
 inline void wait_if_failing() {
   if (std::uncaught_exceptions() > 0) (void)hipDeviceSynchronize();
 }
+
+// ---- idle objects of a device ----
+// f() with `dev` as the current device
+template <typename F>
+void on_device(int dev, F&& f) {
+  int cur = dev;
+  (void)hipGetDevice(&cur);
+  if (cur != dev) (void)hipSetDevice(dev);
+  f();
+  if (cur != dev) (void)hipSetDevice(cur);
+}
+
+// Shared by the process's threads: no more than were ever in use at once, until gb_trim.  (Creating
+// and destroying the events of a call cost 20 us.)
+template <typename H>
+class IdlePool {
+ public:
+  bool take(int dev, H* h) {
+    std::lock_guard<std::mutex> g(m_);
+    auto& v = idle_[dev];
+    if (v.empty()) return false;
+    *h = v.back();
+    v.pop_back();
+    return true;
+  }
+  bool give(int dev, H h) noexcept {  // false: no room to keep it
+    try {
+      std::lock_guard<std::mutex> g(m_);
+      idle_[dev].push_back(h);
+      return true;
+    } catch (...) {
+      return false;
+    }
+  }
+  template <typename F>
+  void drain(F&& destroy) {
+    std::map<int, std::vector<H>> idle;
+    {
+      std::lock_guard<std::mutex> g(m_);
+      idle.swap(idle_);
+    }
+    for (auto& kv : idle)
+      on_device(kv.first, [&] {
+        for (H h : kv.second) destroy(h);
+      });
+  }
+
+ private:
+  std::mutex m_;
+  std::map<int, std::vector<H>> idle_;
+};
+
+struct Timer {
+  hipEvent_t a = nullptr, b = nullptr;
+  int dev = 0;
+  Timer() {
+    GB_HIP(hipGetDevice(&dev));
+    for (hipEvent_t* e : {&a, &b})
+      if (!pool().take(dev, e)) GB_HIP(hipEventCreate(e));
+  }
+  Timer(const Timer&) = delete;
+  Timer& operator=(const Timer&) = delete;
+  ~Timer() {
+    for (hipEvent_t e : {a, b})
+      if (e && !pool().give(dev, e)) (void)hipEventDestroy(e);
+  }
+  static void trim() {
+    pool().drain([](hipEvent_t e) { (void)hipEventDestroy(e); });
+  }
+
+ private:
+  static IdlePool<hipEvent_t>& pool() {
+    static auto* p = new IdlePool<hipEvent_t>;  // outlives the runtime's own teardown
+    return *p;
+  }
+};
+void progress_trim();  // the idle progress words of the device-driven loops (sp2.hip)
+
 
 // ---- cached batch buffers -------------------------------------------------------------------
 // The dense batch buffers (tens of GB at N = 100000) are kept between calls instead of being

@@ -1872,56 +1872,6 @@ void launch_plan_square_f64(const double* X, double* S, const Plan& pl, const in
   launch_square<double>(X, S, tiles, pl.lg, offs, s, lin);
 }
 
-// Idle objects of a device, shared by the process's threads: no more than were ever in use at
-// once.  (Creating and destroying the events of a call cost 20 us.)
-template <typename H>
-class IdlePool {
- public:
-  bool take(int dev, H* h) {
-    std::lock_guard<std::mutex> g(m_);
-    auto& v = idle_[dev];
-    if (v.empty()) return false;
-    *h = v.back();
-    v.pop_back();
-    return true;
-  }
-  bool give(int dev, H h) noexcept {  // false: no room to keep it
-    try {
-      std::lock_guard<std::mutex> g(m_);
-      idle_[dev].push_back(h);
-      return true;
-    } catch (...) {
-      return false;
-    }
-  }
-
- private:
-  std::mutex m_;
-  std::map<int, std::vector<H>> idle_;
-};
-
-struct Timer {
-  hipEvent_t a = nullptr, b = nullptr;
-  int dev = 0;
-  Timer() {
-    GB_HIP(hipGetDevice(&dev));
-    for (hipEvent_t* e : {&a, &b})
-      if (!pool().take(dev, e)) GB_HIP(hipEventCreate(e));
-  }
-  Timer(const Timer&) = delete;
-  Timer& operator=(const Timer&) = delete;
-  ~Timer() {
-    for (hipEvent_t e : {a, b})
-      if (e && !pool().give(dev, e)) (void)hipEventDestroy(e);
-  }
-
- private:
-  static IdlePool<hipEvent_t>& pool() {
-    static auto* p = new IdlePool<hipEvent_t>;  // outlives the runtime's own teardown
-    return *p;
-  }
-};
-
 float elapsed(hipEvent_t a, hipEvent_t b) {
   float ms = 0.f;
   GB_HIP(hipEventElapsedTime(&ms, a, b));
@@ -2335,12 +2285,19 @@ struct ProgressLease {
     if (p && !pool().give(dev, p)) (void)hipHostFree(p);
   }
 
- private:
   static IdlePool<LoopProgress*>& pool() {
     static auto* q = new IdlePool<LoopProgress*>;
     return *q;
   }
 };
+
+}  // namespace
+
+void progress_trim() {
+  ProgressLease::pool().drain([](LoopProgress* p) { (void)hipHostFree(p); });
+}
+
+namespace {
 
 double wall_clock_khz() {
   thread_local std::map<int, int> rate;

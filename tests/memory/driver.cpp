@@ -11,7 +11,7 @@
 
 namespace {
 size_t g_capacity = (size_t)1 << 40, g_used = 0, g_pooled = 0;
-int g_mallocs = 0, g_frees = 0;
+int g_mallocs = 0, g_frees = 0, g_events = 0, g_progress_trims = 0;
 bool g_no_host_memory = false, g_running = false;  // running: work that nobody waited for
 std::map<void*, size_t> g_live;
 
@@ -74,7 +74,21 @@ hipError_t hipDeviceGetDefaultMemPool(hipMemPool_t* p, int) {
   return hipSuccess;
 }
 hipError_t hipMemPoolSetAttribute(hipMemPool_t, hipMemPoolAttr, void*) { return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t* e) {
+  *e = reinterpret_cast<hipEvent_t>(std::malloc(16));
+  ++g_events;
+  return hipSuccess;
 }
+hipError_t hipEventDestroy(hipEvent_t e) {
+  std::free(e);
+  --g_events;
+  return hipSuccess;
+}
+}
+namespace gbi {  // what gb_trim asks of the rest of the library
+void ml_trim() {}
+void progress_trim() { ++g_progress_trims; }
+}  // namespace gbi
 
 namespace {
 
@@ -223,6 +237,27 @@ int failed_call() {
   return 0;
 }
 
+// gb_trim gives everything back that calls have kept, the events of their timings among it.
+int trim() {
+  {
+    Timer a, b;
+    WsLease ws;
+    (void)ws->get_bytes(0, 64 * MiB, kStream);
+    CachedBuf c(64 * MiB, kStream);
+  }
+  CHECK(guarded([] { DBuf<char> small(MiB, kStream); }) == GB_OK);
+  CHECK(g_events == 4 && g_live.size() == 3);
+  {
+    Timer again;
+    CHECK(g_events == 4);
+  }
+  CHECK(gb_trim() == GB_OK);
+  CHECK(g_events == 0 && g_progress_trims == 1 && g_live.empty());
+  Timer after;
+  CHECK(g_events == 2);
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -234,6 +269,7 @@ int main(int argc, char** argv) {
   if (what == "idle_at_exit") rc = idle_at_exit();
   if (what == "full_lists") rc = full_lists();
   if (what == "failed_call") rc = failed_call();
+  if (what == "trim") rc = trim();
   if (rc == 0) std::printf("ok\n");
   return rc;
 }

@@ -42,3 +42,7 @@ def test_full_lists_follow_the_sizes_in_use(driver):
 
 def test_failed_calls_give_nothing_back_that_is_in_use(driver):
     _run(driver, "failed_call")
+
+
+def test_trim_gives_everything_back(driver):
+    _run(driver, "trim")
