@@ -50,8 +50,8 @@ typedef int32_t gb_status;
  * finds no memory does so by itself before it fails. */
 gb_status gb_trim(void);
 
-/* Kernel-variant table of the autotuner (the split squares' kernel, chosen per size class of batches,
- * powers of two of their tiles, by timing each variant once on the whole batch; see
+/* Kernel-variant table of the autotuner (the split squares' kernel, chosen per size class of
+ * batches, powers of two of their tiles, by timing each variant once on the whole batch; see
  * gb_sp2_opts.tile_policy).  gb_tune_save writes the table of this process as JSON to `path`
  * (tagged with the library's source hash and the device: "libgb-tune-1" format); gb_tune_load
  * merges such a file into it, so a later process skips the timing runs.  A file written by

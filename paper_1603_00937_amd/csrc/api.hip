@@ -37,9 +37,9 @@ Allocator g_alloc;  // the registered hook (all null: the device pool)
 // of a step at 256 orbitals.  Buffers of up to 32 MiB that a call frees are put aside
 // until it ends, and where the work of their streams is then known to be done (every call waits
 // for it; the query below makes sure) they go to a process-wide list of idle ones, from which any
-// later call of the device, on any thread and stream, takes one of its power of two.  Where the list
-// is full, the buffers idle for longest make room, so that it follows the sizes in use.  They, what
-// a failed call freed and what is freed outside of a call go back to the device pool.
+// later call of the device, on any thread and stream, takes one of its power of two.  Where the
+// list is full, the buffers idle for longest make room, so that it follows the sizes in use.  They,
+// what a failed call freed and what is freed outside of a call go back to the device pool.
 namespace {
 constexpr int kMinClass = 8, kMaxClass = 25;
 constexpr size_t kIdleMost = (size_t)256 << 20;
@@ -168,8 +168,9 @@ void small_trim() {
     });
 }
 
-// What no call holds goes back to the device (or to the allocator that made it): the idle lists, and
-// what the running call has put aside, which takes the small buffers of the former on their way.
+// What no call holds goes back to the device (or to the allocator that made it): the idle lists,
+// and what the running call has put aside, which takes the small buffers of the former on their
+// way.
 static void give_back_idle() {
   ws_trim();
   cached_trim();
@@ -287,9 +288,9 @@ void Workspace::release_all() {
   }
 }
 
-// Idle checkpoint buffers, those idle for longest first; they make room where the list is full.  The
-// entries own nothing and the list is never destroyed: an entry that finds no host memory leaves its
-// buffer with the caller, and a process may end with idle ones.
+// Idle checkpoint buffers, those idle for longest first; they make room where the list is full.
+// The entries own nothing and the list is never destroyed: an entry that finds no host memory
+// leaves its buffer with the caller, and a process may end with idle ones.
 namespace {
 struct IdleCached {
   struct Entry {

@@ -533,23 +533,22 @@ __global__ __launch_bounds__(kT) void k_x2_rows_hash(const int32_t* __restrict__
 // start at -0, which the first product that is not -0 itself changes for good, so an entry that
 // still holds it was reached by no pair, or sums to 0 in any order, and tau > 0 drops it.  (Were it
 // +0, a tau below the rounding of the sums would have every such entry, half of the pages', summed
-// once more: 17 ms instead of 0.3 at N = 1024, tau = 1e-15.)  The other decisions, and the sums near
-// tau, are those of k_x2_rows, so the graph is the same bit for bit.  One wave takes a row k at a time, 64 slots
-// per step up to the row's last entry.  A row that needs more than pcap pages or keeps more than
-// cap entries reports it through `overflow` (pages, kept) and the launch is repeated with room or
-// left to the kernels below; workgroups that start after a report of more than `most` pages, which
-// ends the attempt for good, return at once (vertices numbered at random, N = 18000: 4.4 ms spent on
-// two attempts before the two passes' 2.1, now 0.1).
+// once more: 17 ms instead of 0.3 at N = 1024, tau = 1e-15.)  The other decisions, and the sums
+// near tau, are those of k_x2_rows, so the graph is the same bit for bit.  One wave takes a row k
+// at a time, 64 slots per step up to the row's last entry.  A row that needs more than pcap pages
+// or keeps more than cap entries reports it through `overflow` (pages, kept) and the launch is
+// repeated with room or left to the kernels below; workgroups that start after a report of more
+// than `most` pages, which ends the attempt for good, return at once (vertices numbered at random,
+// N = 18000: 4.4 ms spent on two attempts before the two passes' 2.1, now 0.1).
 // The two-pass kernels visit every pair twice with an LDS atomic and two LDS look-ups; here a
 // pair costs one look-up and one ds_add_f64, and LDS no longer grows with n.  Bound by LDS and the
-// vector work of a pair at two workgroups per CU (the pages take ~50 KB), and, 40 % of it, by the chains
-// of waits around the pairs: so eight look-ups go out at once, the scans shift lanes instead of
-// taking 18 barriers, and a wave reads four groups of sums before it decides (13.8 -> 12.6 ms at
-// 160002; the atomics alone cost 0.4).  Whole graph call, two-
-// pass bitmap -> paged: N = 1024 0.56 -> 0.48 ms, 18000 3.1 -> 2.7, 100000 (clustered) 18.5 ->
-// 10.1, 160002 36.8 -> 15.8 (67 with hash sets, which it took there); rows of consecutive numbers,
-// which share the rows they read, on one XCD: another 5 %.  512 threads: 256 take 23.9
-// and 1024 19.1 ms at 160002.
+// vector work of a pair at two workgroups per CU (the pages take ~50 KB), and, 40 % of it, by the
+// chains of waits around the pairs: so eight look-ups go out at once, the scans shift lanes instead
+// of taking 18 barriers, and a wave reads four groups of sums before it decides (13.8 -> 12.6 ms at
+// 160002; the atomics alone cost 0.4).  Whole graph call, two-pass bitmaps -> paged: N = 1000 0.31
+// -> 0.23 ms, 18000 2.17 -> 1.60, 100000 (clustered) 17.3 -> 8.1, 160002 35.0 -> 12.7 (67 with hash
+// sets, which it took there); rows of consecutive numbers, which share the rows they read, on one
+// XCD: 5 % of it.  512 threads: 256 take 1.5 times, 1024 1.2 times as long at 160002.
 struct X2Paged {
   int shift, pcap, cap, most;
 };
@@ -676,7 +675,8 @@ __global__ __launch_bounds__(kPT) void k_x2_rows_paged(
   for (int q = d0; q < d1; ++q) mine += dir[q] >= 0;
   int32_t used;
   int at = block_inclusive_scan<kPT>(mine, red, &used) - mine;
-  // page and slot in a word: LDS holds neither 2^10 slots of 256 bytes nor a directory of 2^16 pages
+  // page and slot in a word: LDS holds neither 2^10 slots of 256 bytes nor a directory of 2^16
+  // pages
   for (int q = d0; q < d1; ++q)
     if (dir[q] >= 0) plist[at++] = q << 10 | dir[q];
   __syncthreads();
@@ -1009,16 +1009,16 @@ void ell_threshold(const gb_ell& A, double tau, DBuf<int32_t>& rp, DBuf<int32_t>
   const int n = A.n;
   DBuf<int32_t> cnt(n, s);
   rp = DBuf<int32_t>(n + 1, s);
-  hipLaunchKernelGGL(k_ell_threshold<0>, dim3(blocks_for(n, kT / 64)), dim3(kT), 0, s, A.col, A.val, n,
-                     A.width, tau, cnt.get(), nullptr, nullptr);
+  hipLaunchKernelGGL(k_ell_threshold<0>, dim3(blocks_for(n, kT / 64)), dim3(kT), 0, s, A.col, A.val,
+                     n, A.width, tau, cnt.get(), nullptr, nullptr);
   GB_LAUNCH_CHECK();
   exclusive_scan_i32(cnt.get(), rp.get(), n, s);
   nnz = 0;
   GB_HIP(hipMemcpyAsync(&nnz, rp.get() + n, 4, hipMemcpyDeviceToHost, s));
   GB_HIP(hipStreamSynchronize(s));
   c = DBuf<int32_t>(nnz > 0 ? nnz : 1, s);
-  hipLaunchKernelGGL(k_ell_threshold<1>, dim3(blocks_for(n, kT / 64)), dim3(kT), 0, s, A.col, A.val, n,
-                     A.width, tau, nullptr, rp.get(), c.get());
+  hipLaunchKernelGGL(k_ell_threshold<1>, dim3(blocks_for(n, kT / 64)), dim3(kT), 0, s, A.col, A.val,
+                     n, A.width, tau, nullptr, rp.get(), c.get());
   GB_LAUNCH_CHECK();
 }
 
@@ -1143,8 +1143,8 @@ bool graph_x2_paged(const gb_ell& H, const double* x0, double tau, Csr& out, hip
   if (x2_paged_lds_bytes(n, w, g) > most) return false;
   // Rows that ask for more pages: a second attempt costs as much as the first and has fewer
   // workgroups per CU.  Bitmaps take less (randomly numbered, N = 8000, 239 slots: 1.8 ms for both
-  // attempts, 0.9 for bitmaps; N = 150000, 61 slots: 18.3 and 6.3); hash sets, which take their place
-  // above 3 << 16, do not (21.4).
+  // attempts, 0.9 for bitmaps; N = 150000, 61 slots: 18.3 and 6.3); hash sets, which take their
+  // place above 3 << 16, do not (21.4).
   const bool again = n > 3 << 16;
   g.most = g.pcap;
   if (again) {
@@ -1162,8 +1162,8 @@ bool graph_x2_paged(const gb_ell& H, const double* x0, double tau, Csr& out, hip
   for (int attempt = 0;; ++attempt) {
     rows = DBuf<int32_t>((size_t)n * g.cap, s);
     hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, s, ovf.get(), (int64_t)2);
-    hipLaunchKernelGGL(k_x2_rows_paged, dim3(xcd_grid(n)), dim3(kPT), x2_paged_lds_bytes(n, w, g), s, H.col,
-                       x0, rb.get(), rlen.get(), n, w, tau, all_asc, g, cnt.get(), rows.get(),
+    hipLaunchKernelGGL(k_x2_rows_paged, dim3(xcd_grid(n)), dim3(kPT),
+                       x2_paged_lds_bytes(n, w, g), s, H.col, x0, rb.get(), rlen.get(), n, w, tau, all_asc, g, cnt.get(), rows.get(),
                        ovf.get());
     GB_LAUNCH_CHECK();
     exclusive_scan_i32(cnt.get(), out.row_ptr.get(), n, s);
@@ -1226,9 +1226,9 @@ void graph_x2_hash(const gb_ell& H, const double* x0, double tau, Csr& out, hipS
 }
 
 // Does one pass with paged accumulators beat two passes over candidate sets?  It saves a visit of
-// every pair, and bitmaps whose handling grows with n, but gives pages out row by row and clears and
-// reads them whole, which takes rows of many pairs, the more so the further a row's partners are
-// apart in number.  Measured, one pass / two (ms), w the ELL width, on places in Morton order
+// every pair, and bitmaps whose handling grows with n, but gives pages out row by row and clears
+// and reads them whole, which takes rows of many pairs, the more so the further a row's partners
+// are apart in number.  Measured, one pass / two (ms), w the ELL width, on places in Morton order
 // (m) and lattices in row order (l), which spread a row over more pages:
 //   n = 4096      w  62  0.213 / 0.189 m    w 121  0.253 / 0.278 m    w 247  0.359 / 0.625 m
 //   n = 8192      w 123  0.475 / 0.386 m    w  54  0.364 / 0.229 l    w 241  0.817 / 1.03 m
@@ -1255,8 +1255,8 @@ void graph_x2(const gb_ell& H, const double* x0, double tau, Csr& out, hipStream
   if (tau > 0.0 && !vertex_sets_forced() && x2_paged_pays(n, w) &&
       graph_x2_paged(H, x0, tau, out, s))
     return;
-  // two passes, bitmaps against hash sets: 37 / 67 ms at n = 160002 (w 255), 125 / 112 at n = 262000;
-  // rows below 32 slots 3.2 / 1.3 (w 7) and 3.9 / 3.9 (w 27) at n = 166375
+  // two passes, bitmaps against hash sets: 37 / 67 ms at n = 160002 (w 255), 125 / 112 at n =
+  // 262000; rows below 32 slots 3.2 / 1.3 (w 7) and 3.9 / 3.9 (w 27) at n = 166375
   if (use_hash_sets(n, w < 32 ? 1 << 17 : 3 << 16)) {
     graph_x2_hash(H, x0, tau, out, s);
     return;

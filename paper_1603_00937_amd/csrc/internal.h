@@ -161,8 +161,8 @@ void progress_trim();  // the idle progress words of the device-driven loops (sp
 // The dense batch buffers (tens of GB at N = 100000) are kept between calls instead of being
 // returned to the pool: a call leases a workspace (one per concurrent call and device), takes
 // its buffers from numbered slots that grow when a call needs more, and gives it back at the
-// end.  Every call that succeeds synchronises its stream before returning, so the next lease may use
-// the memory on any stream.  gb_trim frees the idle workspaces.
+// end.  Every call that succeeds synchronises its stream before returning, so the next lease may
+// use the memory on any stream.  gb_trim frees the idle workspaces.
 struct Workspace {
   int device = 0;
   struct Slab {

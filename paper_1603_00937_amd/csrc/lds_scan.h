@@ -10,7 +10,8 @@ namespace gbi {
 
 // Inclusive prefix sum of x over the block's NT threads (whole waves), and the total.  Each wave
 // scans by lane shifts, the waves' sums go through red (NT / 64 entries, free once every thread has
-// passed the caller's next barrier): two barriers, where a scan of NT entries in LDS takes 2 log2 NT.
+// passed the caller's next barrier): two barriers, where a scan of NT entries in LDS takes 2 log2
+// NT.
 template <int NT>
 __device__ __forceinline__ int32_t block_inclusive_scan(int32_t x, int32_t* red, int32_t* total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -33,9 +34,9 @@ __device__ __forceinline__ int32_t block_inclusive_scan(int32_t x, int32_t* red,
 }
 
 // v[0..m) <- exclusive prefix sums of v (in place); returns the total.  All NT threads of the
-// block call it; red is an LDS array of at least NT / 64 entries.  Thread t owns the contiguous segment
-// [t s, t s + s) of v, s = ceil(m / NT): segment sums, one scan of the NT sums, then each segment
-// rewritten from its offset (one scan however long v is).
+// block call it; red is an LDS array of at least NT / 64 entries.  Thread t owns the contiguous
+// segment [t s, t s + s) of v, s = ceil(m / NT): segment sums, one scan of the NT sums, then each
+// segment rewritten from its offset (one scan however long v is).
 template <int NT>
 __device__ __forceinline__ int32_t lds_exclusive_scan(int32_t* v, int m, int32_t* red) {
   const int seg = (m + NT - 1) / NT;

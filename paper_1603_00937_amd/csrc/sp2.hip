@@ -86,8 +86,8 @@ constexpr int kBT = 128;  // workgroup tile edge
 // tiles carry n: the sums over k end with the chunk that holds row n - 1, and a wave whose block
 // begins beyond it only writes its zeros, so the padding (3 % of the rows at 900, half a percent
 // at 5000) is stored but not multiplied; the sums are the same without its zeros.  Step at N =
-// 1024 (64 FP64 blocks of ~900 rows) 20.68 -> 20.38 ms, FP32 density at N = 3000 46.29 -> 45.77; the
-// 16-bit squares, which the power bounds and not the count of products, keep their times.
+// 1024 (64 FP64 blocks of ~900 rows) 20.68 -> 20.38 ms, FP32 density at N = 3000 46.29 -> 45.77;
+// the 16-bit squares, which the power bounds and not the count of products, keep their times.
 __host__ __device__ constexpr int padded(int n) { return (n + 63) / 64 * 64; }
 
 // LDS slots of the squaring kernels' operand rows.  A fragment read (ds_read_b128) takes lane
@@ -182,8 +182,8 @@ __global__ __launch_bounds__(kT) void k_gather(const int32_t* __restrict__ hcol,
 //           general product did, and an entry of a diagonal tile and its transpose get the same
 //           two sums.  klim > 0: A is zero outside its first klim rows and
 //           columns, so a half of the sum whose panel of A lies below them ends after klim.
-//           57 blocks of ~1330 rows: 4.80 ms a step against 5.09 (general product on 128-edge tiles)
-//           + 0.46 (transpose and combine).
+//           57 blocks of ~1330 rows: 4.80 ms a step against 5.09 (general product on 128-edge
+//           tiles) + 0.46 (transpose and combine).
 // In MODE 0 (A = B = X) the SP2 update is fused into the epilogue: with the branch
 // 2X - X^2 selected (lin, or *lin_flag on the device-driven loop) the kernel writes 2X - X^2,
 // else X^2.  X is symmetric, so the mirrored entry takes the same value.
@@ -451,8 +451,8 @@ __global__ __launch_bounds__(kT, 2) void k_symm_mm(const T* __restrict__ A, cons
 // barrier and 16 products per wave, on fewer compute units than there are.  Here a wave has four
 // products per chunk, and the loads of two chunks go out under the products of the two before
 // (one chunk: 3 % slower at 512 rows, four: 8 % at 704).  Every output is the same sum in the same
-// order.  FP64, against k_symm_mm on 64-edge tiles: one block of 704 rows 41.9 -> 20.3 us, 16 of
-// 256 20.7 -> 15.5, 32 of 512 118 -> 91; large batches lose the reuse: 64 of ~900 rows 568 -> 639.
+// order.  FP64, against k_symm_mm on 64-edge tiles: one block of 704 rows 41.9 -> 20.1 us, 16 of
+// 256 20.4 -> 15.3, 32 of 512 115 -> 91; large batches lose the reuse: 64 of 900 rows 924 -> 935.
 template <typename T>
 __global__ __launch_bounds__(kT) void k_square_small(const T* __restrict__ X, T* __restrict__ S,
                                                      const int4* __restrict__ tiles,
@@ -642,10 +642,10 @@ __device__ __forceinline__ void split_epilogue(const f4v (&big)[BT / 32][BT / 32
 
 // Split squaring: the FP32 iterate itself is read and each lane splits the 16 bytes it loads
 // into the NP planes (bf16, or fp16 of 2^14 x) while staging them into the swizzled LDS layout
-// (four 16-byte pieces per 64-byte plane row, piece p of row r at slot p ^ swz4(r)).  X^2 is the sum of the
-// plane products that keep about 8 NP bits (bf16) or 22 bits (two fp16 planes) on the 16 x 16 x
-// 32 matrix cores, the leading product and the corrections in separate FP32 accumulators, added
-// once at the end; the epilogue applies the SP2 update and writes only the FP32 result.  The
+// (four 16-byte pieces per 64-byte plane row, piece p of row r at slot p ^ swz4(r)).  X^2 is the
+// sum of the plane products that keep about 8 NP bits (bf16) or 22 bits (two fp16 planes) on the 16
+// x 16 x 32 matrix cores, the leading product and the corrections in separate FP32 accumulators,
+// added once at the end; the epilogue applies the SP2 update and writes only the FP32 result.  The
 // next chunk is loaded into registers under the current chunk's products.  A workgroup of four
 // waves (2 x 2) computes a BT x BT tile (bi <= bj) of the symmetric product, BT = 128 or 64;
 // tiles and XCD order as in k_symm_mm.
@@ -1634,8 +1634,8 @@ struct Plan {
 // the eight XCD queues (greedy, costliest first, onto the least loaded queue) and the queues
 // are interleaved, so every tile of a subgraph runs on one XCD and its row panels stay in that
 // XCD's L2.  Too few subgraphs to fill the queues evenly are cut where a queue is full instead
-// (FP64 square of one block of 2048 rows 1171 -> 223 us, of two of 704 82 -> 43).  Queues are padded to equal length with empty
-// entries (subgraph -1).
+// (FP64 square of one block of 2048 rows 1171 -> 223 us, of two of 704 82 -> 43).  Queues are
+// padded to equal length with empty entries (subgraph -1).
 constexpr int kXcd = 8;
 
 void xcd_order(std::vector<int4>& out, const std::vector<int4>& tiles,
@@ -2018,11 +2018,11 @@ int tune_class(const Part& P) {
   return c;
 }
 
-// The split squares' kernel for a batch: each variant timed on the whole batch, once per process and
-// size class.  (One variant for all: a choice per size of block, each size timed by itself,
+// The split squares' kernel for a batch: each variant timed on the whole batch, once per process
+// and size class.  (One variant for all: a choice per size of block, each size timed by itself,
 // paid for every variant's own launch and for small groups that cannot fill the device, which
-// flattered small tiles: bf16 x 3 planes N = 2050 1.118 -> 1.032 ms a square, N = 6014 2.22 -> 2.11, fp16
-// N = 1400 0.341 -> 0.303, N = 2050 0.644 -> 0.633, N = 18000 3.88 -> 3.84.)
+// flattered small tiles: bf16 x 3 planes N = 2050 1.118 -> 1.032 ms a square, N = 6014 2.22 ->
+// 2.11, fp16 N = 1400 0.341 -> 0.303, N = 2050 0.644 -> 0.633, N = 18000 3.88 -> 3.84.)
 int tune_tiles(const Part& P, const float* X, float* S, const int64_t* offs, hipStream_t s, int kind,
                bool xcd, int planes) {
   const std::pair<int, int> key{kind, tune_class(P)};
@@ -2061,10 +2061,13 @@ int tune_tiles(const Part& P, const float* X, float* S, const int64_t* offs, hip
 
 // Squares on 32-edge tiles (k_square_small)?  FP64 while at most five 64-edge tiles fall to each of
 // the 256 compute units, which is what one holds at a time: the launch then lasts as long as a
-// tile does (1280 tiles, 128 blocks of 256 rows: 71.2 -> 54.6 us; 1088, 8 of 1024: 191 -> 166;
-// 3600, 32 of ~900: 568 -> 639).  FP32, whose products take half the time, up to one and a half
-// (325 tiles, one block of 1600: 72.0 -> 53.6; 396, 6 of 704: 35.3 -> 30.8; 448, 16 of 400:
-// 23.2 -> 23.7; 640, 64 of 256: 21.7 -> 22.9).
+// tile does.  us on 64-edge -> 32-edge tiles: 1056 64-edge ones (2 blocks of 2048 rows) 367 -> 329,
+// 1088 (8 of 1024) 191 -> 168, 1280 (128 of 256) 68.4 -> 53.6, but 1012 (4 of 1408) 202 -> 216.
+// Past the line the gain falls with the reuse that small tiles give up: 1440 (12 of 900) 230 -> 186,
+// 2024 (8 of 1408) 387 -> 407, 2400 (20 of 900) 371 -> 349, 3840 (32 of 900) 482 -> 468, 7680 (64 of
+// 900) 924 -> 935.  FP32, whose products take half the time, up to one and a half: 325 (one of 1600)
+// 72.5 -> 55.3, 396 (6 of 704) 35.3 -> 31.6, 400 (40 of 256) 17.7 -> 16.7; 448 (16 of 400) 23.7 ->
+// 24.2, 640 (64 of 256) 21.8 -> 22.7.
 template <typename T>
 bool small_batch(const Part& P) {
   int64_t t64 = 0;
@@ -2172,8 +2175,8 @@ void launch_step(const T* X, T* S, const Plan& pl, const int4* tiles, const int6
 // trip per step), then one squaring launch writes the next iterate.  Used for one launch per
 // subgraph, for the tape of the adjoint and for the alternating FP64 refinement.  Returns the
 // step index at which the stop rule fired, the replay ended, max_iter was reached, or (low
-// precision) the idempotency error stagnated or fell to e_hand; X then holds the result.  first: the
-// step at which a loop that goes on at it0 began (stagnation is judged over all of its steps).
+// precision) the idempotency error stagnated or fell to e_hand; X then holds the result.  first:
+// the step at which a loop that goes on at it0 began (stagnation is judged over all of its steps).
 template <typename T>
 int sp2_loop(T*& X, T*& S, const Plan& pl, const DBuf<int4>& tiles, const int64_t* offs,
              const int32_t* npad, const Part& P, double n_occ, double tol, int max_iter,
@@ -2484,9 +2487,9 @@ double smooth_coef(int m, int j) {
 }
 
 // The idempotency measure at which the low-precision loop hands over to S_6: one eigenvalue
-// carrying all of e ends C(11, 6) e^6 = 462 e^6 off, which is the tolerance here.  (Its own squares cost
-// 3.7 ms at N = 18000, two more slab products 2.3 ms, and a square at this stage gains at most one
-// order; beyond this point it also runs into its rounding floor.)
+// carrying all of e ends C(11, 6) e^6 = 462 e^6 off, which is the tolerance here.  (Its own squares
+// cost 3.7 ms at N = 18000, two more slab products 2.3 ms, and a square at this stage gains at most
+// one order; beyond this point it also runs into its rounding floor.)
 double handover_measure(double tol) { return std::pow(tol / 462.0, 1.0 / 6.0); }
 
 // Stop flag and last record of the refinement's checks (device-driven, as LoopState): done is 0,
@@ -3127,12 +3130,12 @@ namespace {
 // 16 takes slot 16 r + (c - g) mod 16, g being the pair's rank among the sixteen: slot q then reads
 // bank q + g.  Entries past the end fill the holes that short residues leave (conflicts down by
 // three quarters; N = 1024 4.51 -> 4.11 ms of recurrence for 0.13 ms of sorting).
-// A wave per pair, lanes side by side in a row of H (a thread per column took 0.39 ms; now 0.29 with
-// the order, 0.16 without).
+// A wave per pair, lanes side by side in a row of H (a thread per column took 0.39 ms; now 0.29
+// with the order, 0.16 without).
 constexpr int kFoePad = 8;
 __device__ inline int lane_value(int v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
-// Rank of a lane among the sixteen that a 16-byte LDS read serves together (lanes 0-3, 12-15, 20-23,
-// 24-27, then 4-7, 8-11, 16-19, 28-31, and the same of the upper half).
+// Rank of a lane among the sixteen that a 16-byte LDS read serves together (lanes 0-3, 12-15,
+// 20-23, 24-27, then 4-7, 8-11, 16-19, 28-31, and the same of the upper half).
 __device__ __forceinline__ int lds_rank(int lane) { return (lane & 31) / 8 * 4 + (lane & 3); }
 constexpr int kPairsPerBlock = 16;
 __global__ __launch_bounds__(kT) void k_foe_ell(const int32_t* __restrict__ hcol,
@@ -3280,16 +3283,16 @@ __global__ __launch_bounds__(kT) void k_foe_ell(const int32_t* __restrict__ hcol
 //         T_m T_n = (T_{m+n} + T_{|m-n|}) / 2 turns them into the core traces t_{2n+1} and
 //         t_{2n+2}, so the traces of M terms take M / 2 products.
 // An entry of Ht reads R doubles of V_n in LDS at a scattered column, which bounded the recurrence
-// with a thread per column (LDS active 72 % of the time, mostly bank conflicts).  So a thread takes two
-// columns that couple to the same others, which halves the reads, the lists are ordered by bank
+// with a thread per column (LDS active 72 % of the time, mostly bank conflicts).  So a thread takes
+// two columns that couple to the same others, which halves the reads, the lists are ordered by bank
 // (above), and R = 4 rows share an entry: eight products for two reads and 18 bytes of Ht.  What
 // bounds it now is those bytes out of L2: with half the rows per workgroup, twice the bytes, the
 // recurrence takes 6.45 ms for 4.11.  Lists are whole groups of U slots, a slot's address the
-// wave's plus the lane's pair: a test per slot cost more instructions than the products (5.35 against
-// 4.77 ms).  Order 160 at N = 1024 (64 subgraphs of ~900; whole call) 8.1 -> 4.8 ms against a column
-// per thread, 26 us per term (as full products of whole blocks, each term 2 n^3 flops and five
-// passes over the batch, 2.2 ms); N = 18000 (565 subgraphs of ~1200) 140 -> 84 ms, 0.50 ms per term
-// (57.6).  U = 4 5.0, U = 16 4.9 ms; workgroups of at most 512 threads: N = 18000 105 ms.
+// wave's plus the lane's pair: a test per slot cost more instructions than the products (5.35
+// against 4.77 ms).  Order 160 at N = 1024 (64 subgraphs of ~900; whole call) 8.1 -> 4.8 ms against
+// a column per thread, 26 us per term (as full products of whole blocks, each term 2 n^3 flops and
+// five passes over the batch, 2.2 ms); N = 18000 (565 subgraphs of ~1200) 140 -> 84 ms, 0.50 ms per
+// term (57.6).  U = 4 5.0, U = 16 4.9 ms; workgroups of at most 512 threads: N = 18000 105 ms.
 template <int R, bool SPILL>
 __global__ __launch_bounds__(1024) void k_foe_rows(
     const int4* __restrict__ items, const uint16_t* __restrict__ idx,
@@ -3436,9 +3439,9 @@ __global__ __launch_bounds__(kT) void k_foe_sums(const double* __restrict__ part
 
 // ---- Fermi function coefficients and mu on the device ----------------------------------------
 // What chebyshev_fermi and foe_solve_mu below compute on the host, from the traces to the
-// coefficients, next to the recurrence: 2 (M + 1) K cosines and some 55 K exponentials (M = 160, K = 1024)
-// kept the host busy for 3 of the call's 15.0 ms while the device waited (now 12.0 ms).  The
-// arguments are rounded as the host's are, n times theta_k.
+// coefficients, next to the recurrence: 2 (M + 1) K cosines and some 55 K exponentials (M = 160, K
+// = 1024) kept the host busy for 3 of the call's 15.0 ms while the device waited (now 12.0 ms).
+// The arguments are rounded as the host's are, n times theta_k.
 __device__ double node_theta(int k, int K) { return M_PI * (k + 0.5) / K; }
 
 // energies and weights of the nodes: sum_n c_n(mu) t_n = sum_k f(e_k; mu) w_k (wave per node)
@@ -3461,9 +3464,9 @@ __device__ double fermi_dev(double e, double beta, double mu) {
   return 1.0 / (1.0 + exp(beta * (e - mu)));
 }
 
-// mu with sum_k f(e_k; mu) w_k = n_occ by halving [emin, emax], as on the host (the sum of a truncated
-// expansion may cross n_occ more than once): out = {mu, the sums at emin and emax}.  Fifteen waves
-// take the fifteen midpoints that four halvings can ask for, so 14 rounds do for 55.
+// mu with sum_k f(e_k; mu) w_k = n_occ by halving [emin, emax], as on the host (the sum of a
+// truncated expansion may cross n_occ more than once): out = {mu, the sums at emin and emax}.
+// Fifteen waves take the fifteen midpoints that four halvings can ask for, so 14 rounds do for 55.
 __global__ __launch_bounds__(960) void k_foe_mu(const double* __restrict__ e,
                                                 const double* __restrict__ w, int K, double emin,
                                                 double emax, double beta, double n_occ,
@@ -3586,8 +3589,8 @@ double foe_solve_mu(const double* traces, int order, double emin, double emax, d
   return 0.5 * (lo + hi);
 }
 
-// Most memory for the terms that the pass for mu leaves to the pass for D (13 GiB at N = 18000, order
-// 160): what a card of 288 GB spares beside a batch.
+// Most memory for the terms that the pass for mu leaves to the pass for D (13 GiB at N = 18000,
+// order 160): what a card of 288 GB spares beside a batch.
 constexpr size_t kHistMost = (size_t)32 << 30;
 
 void foe(const gb_ell& H, int32_t n_occ, const gb_foe_opts& o, const Part& P, double emin,
