@@ -116,10 +116,10 @@ def test_cores_with_random_numbers():
 
 
 def test_random_numbers_cost_little():
-    """The weights of 18000 randomly numbered vertices against the same graph in place order (with
-    core size 1 the weights and the growth are all there is)."""
+    """18000 randomly numbered vertices against the same graph in place order: the host's part takes
+    longer (its look-ups jump), the weights must not take twice what entries cost on top."""
     import paper_1603_00937_amd as gb
     ordered, shuffled = _renumbered(9000, 5)
-    a = _time(lambda: gb.partition(ordered, 1, "multilevel"))
-    b = _time(lambda: gb.partition(shuffled, 1, "multilevel"))
-    assert b <= 1.5 * a, (a, b)
+    a = _time(lambda: gb.partition(ordered, 32, "multilevel"), 10)
+    b = _time(lambda: gb.partition(shuffled, 32, "multilevel"), 10)
+    assert b <= 1.75 * a, (a, b)
